@@ -5,7 +5,10 @@
 // The paper does not name the activation; ReLU, GELU (erf form) and tanh are
 // offered.  2 N d d_hid flop: a dense contraction, so it runs on the matrix cores.
 //
-// MFMA kernel (bf16, d % 64 == 0, d_hid % 256 == 0): a workgroup of 8 wavefronts
+// Up to 64 tokens (bf16, d % 64 == 0, d_hid % 256 == 0): a kernel that streams W1
+// once over all compute units (score_mlp_few_kernel).
+//
+// MFMA kernel (the same shapes, more tokens): a workgroup of 8 wavefronts
 // owns 256 tokens and walks over 256-wide tiles of hidden units; for each it
 // accumulates H^T = W1_tile X^T over d in steps of 64 channels with
 // v_mfma_f32_32x32x16_bf16 (A = W1 rows, B = token rows, so that a token is a lane
@@ -33,6 +36,7 @@ namespace dodo {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -232,6 +236,140 @@ __global__ void score_mlp_combine_kernel(const float* __restrict__ partial, int 
   scores[t] = (s == 0.f) ? 0.f : s;
 }
 
+// ---- few tokens (the streaming mode scores one token per sequence and step) ----
+// Bound by reading W1 once (33.5 MB at d = d_hid = 4096: 5 us at the read rate), so the work is spread by bytes of W1:
+// every compute unit gets a workgroup with an equal number of hidden units (16 of 4096, 20 of 5120; an incomplete
+// block of 16 costs idle lanes of the matrix cores, which have time to spare, and no traffic).  Its 8 wavefronts share
+// the channels in runs of 64 (a cache line of a row each), and a wavefront requests up to 16 runs before its first
+// matrix instruction; nothing is staged in LDS because no W1 row is used twice.
+// v_mfma_f32_16x16x32_bf16 with A = W1 rows, B = token rows (from L2): lane (n, q) holds token n and hidden units
+// 4 q .. 4 q + 3.  The wavefronts' sums meet in LDS and are added in wavefront order.
+// Measured, d = d_hid = 4096: 13 us for 16 tokens, 24 us for 64 (there the token rows, read from L2 by every workgroup,
+// cost more than W1), against 84 us in the tile kernel, whose 16 workgroups walk over the channels one 64-wide step
+// after the other; d = d_hid = 5120: 17 and 31 against 190 us.
+constexpr int kFewTokens = 64;    // most tokens: four blocks of 16 (beyond, a workgroup re-reads too much of X from L2)
+constexpr int kFewWaves = 8;
+constexpr int kFewRun = 64;       // channels per run
+
+int few_hid(int32_t d_hid) {  // hidden units per workgroup: at most two blocks of 16
+  const int even = (d_hid + compute_units() - 1) / compute_units();
+  return even < 32 ? even : 32;
+}
+int few_splits(int32_t d_hid) { return (d_hid + few_hid(d_hid) - 1) / few_hid(d_hid); }
+
+template <int NB, int RT>  // token blocks of 16, hidden blocks of 16
+__global__ __launch_bounds__(kFewWaves * kWave, 2) void score_mlp_few_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W1, const float* __restrict__ b1,
+    const uint16_t* __restrict__ w2, int act, int N, int d, int d_hid, int hid_per_wg, uint32_t x_stride, uint32_t x_bytes,
+    float* __restrict__ partial) {
+  // runs of W1 (8 registers each per hidden block) and of X (8 per token block) in flight; 256 registers in all
+  constexpr int kXDepth = NB == 1 ? 8 : NB == 2 ? 4 : 3;
+  constexpr int kDepth = (RT == 1 ? (NB == 4 ? 12 : 16) : (NB == 4 ? 6 : 8));
+  static_assert(kDepth % kXDepth == 0, "one unrolled pass over both rings");
+  __shared__ __attribute__((aligned(16))) float red[kFewWaves][NB * 16][RT * 16];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid % kWave, n = lane & 15, q = lane >> 4;
+  const int h0 = blockIdx.x * hid_per_wg;
+  const int n_hid = min(hid_per_wg, d_hid - h0);
+  const int runs = d / kFewRun;
+  // All loads are unconditional, so that a wait leaves the younger ones in flight; what lies past the last run, hidden
+  // unit or token falls outside of the buffers' ranges: it fetches nothing and reads as zeros.
+  constexpr uint32_t kOutside = 0x7ffffff0u;
+  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W1 + static_cast<int64_t>(h0) * d), 0, n_hid * d * 2, 0x00027000);
+  const auto xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, x_bytes, 0x00027000);
+  uint32_t w_off[RT], x_off[NB];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) w_off[i] = (static_cast<uint32_t>(16 * i + n) * d + 8 * q) * 2;
+#pragma unroll
+  for (int t = 0; t < NB; ++t) x_off[t] = 16 * t + n < N ? (static_cast<uint32_t>(16 * t + n) * x_stride + 8 * q) * 2 : kOutside;
+  floatx4 acc[NB][RT];
+#pragma unroll
+  for (int t = 0; t < NB; ++t)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[t][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  u32x4_t wv[kDepth][RT][2], xf[kXDepth][NB][2];
+  auto load_w = [&](u32x4_t (&v)[RT][2], int r) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const uint32_t off = r < runs ? w_off[i] + static_cast<uint32_t>(r) * (kFewRun * 2) : kOutside;
+      v[i][0] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, off, 0, 0);
+      v[i][1] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, off, 64, 0);
+    }
+  };
+  auto load_x = [&](u32x4_t (&v)[NB][2], int r) {  // (the halves of a cache line next to each other: the second hits)
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const uint32_t off = r < runs ? x_off[t] + static_cast<uint32_t>(r) * (kFewRun * 2) : kOutside;
+      v[t][0] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, off, 0, 0);
+      v[t][1] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, off, 64, 0);
+    }
+  };
+  // this wavefront's runs: wave, wave + 8, ...
+#pragma unroll
+  for (int u = 0; u < kDepth; ++u) {
+    load_w(wv[u], wave + u * kFewWaves);
+    if (u < kXDepth) load_x(xf[u], wave + u * kFewWaves);
+  }
+  for (int r0 = wave; r0 < runs; r0 += kFewWaves * kDepth) {
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u) {
+      const int r = r0 + u * kFewWaves;
+      if (r >= runs) break;  // uniform over the wavefront
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+            acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[u][i][half]),
+                                                                __builtin_bit_cast(bf16x8, xf[u % kXDepth][t][half]), acc[t][i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(wv[u], r + kDepth * kFewWaves);
+      load_x(xf[u % kXDepth], r + kXDepth * kFewWaves);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NB; ++t)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) *reinterpret_cast<floatx4*>(&red[wave][16 * t + n][16 * i + 4 * q]) = acc[t][i];
+  __syncthreads();
+  // 16 lanes per token, one hidden unit of each block per lane
+  const int hid = tid & 15;
+  float bias[RT], wt[RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const bool ok = 16 * i + hid < n_hid;
+    const int h = h0 + (ok ? 16 * i + hid : 0);
+    bias[i] = b1[h];
+    wt[i] = ok ? load_elem<DODO_DTYPE_BF16>(w2, h) : 0.f;
+  }
+  for (int tok = tid >> 4; tok < NB * 16; tok += kFewWaves * kWave / 16) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      float h = 0.f;
+#pragma unroll
+      for (int w = 0; w < kFewWaves; ++w) h += red[w][tok][16 * i + hid];
+      s = fmaf(wt[i], activation(h + bias[i], act), s);
+    }
+    s = lanes_sum<16>(s);
+    if (hid == 0 && tok < N) partial[static_cast<int64_t>(blockIdx.x) * N + tok] = s;
+  }
+}
+
+// partial scores of many splits for few tokens: a wavefront per token, every lane adds the splits of its own in order
+__global__ __launch_bounds__(kWave) void score_mlp_combine_few_kernel(const float* __restrict__ partial, int splits, int N,
+                                                                      float b2, float* __restrict__ scores) {
+  const int t = blockIdx.x;
+  float s = 0.f;
+#pragma unroll 4
+  for (int p = lane_id(); p < splits; p += kWave) s += partial[static_cast<int64_t>(p) * N + t];
+  s = wave_sum64(s) + b2;
+  if (threadIdx.x == 0) scores[t] = (s == 0.f) ? 0.f : s;
+}
+
 // ---- plain kernel: `kTok` token rows in LDS, one hidden unit per wavefront at a time
 constexpr int kPlainThreads = 256;
 template <int DTYPE>
@@ -291,6 +429,7 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   using namespace dodo;
   if (N <= 0 || d <= 0 || d_hid <= 0) return 0;
   if (dtype != DODO_DTYPE_BF16 || d % kBK != 0 || d_hid % kHidTile != 0) return 0;
+  if (N <= kFewTokens) return static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float);
   const int hs = hidden_splits(N, d_hid);
   return hs > 1 ? static_cast<size_t>(hs) * N * sizeof(float) : 0;
 }
@@ -306,6 +445,26 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
   if (!dtype_ok(dtype)) return DODO_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (mfma_path(dtype, N, d, d_hid, row_stride, hidden, W1, b1, w2)) {
+    if (N <= kFewTokens) {
+      const int splits = few_splits(d_hid), hid = few_hid(d_hid), n = static_cast<int>(N);
+      if (!ws || ws_bytes < static_cast<size_t>(splits) * n * sizeof(float)) return DODO_ERR_WORKSPACE_TOO_SMALL;
+      float* partial = static_cast<float*>(ws);
+      const uint32_t x_bytes = static_cast<uint32_t>(((N - 1) * row_stride + d) * 2);
+#define DODO_LAUNCH_FEW(NB, RT)                                                                                          \
+  hipLaunchKernelGGL((score_mlp_few_kernel<NB, RT>), dim3(splits), dim3(kFewWaves* kWave), 0, s,                         \
+                     static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(W1), b1,                        \
+                     static_cast<const uint16_t*>(w2), act, n, d, d_hid, hid, static_cast<uint32_t>(row_stride), x_bytes, partial)
+      if (hid <= 16) {
+        if (n <= 16) DODO_LAUNCH_FEW(1, 1); else if (n <= 32) DODO_LAUNCH_FEW(2, 1); else DODO_LAUNCH_FEW(4, 1);
+      } else {
+        if (n <= 16) DODO_LAUNCH_FEW(1, 2); else if (n <= 32) DODO_LAUNCH_FEW(2, 2); else DODO_LAUNCH_FEW(4, 2);
+      }
+#undef DODO_LAUNCH_FEW
+      const int rc = launch_status();
+      if (rc != DODO_OK) return rc;
+      hipLaunchKernelGGL(score_mlp_combine_few_kernel, dim3(n), dim3(kWave), 0, s, partial, splits, n, b2, scores);
+      return launch_status();
+    }
     const int hs = hidden_splits(N, d_hid);
     const size_t need = hs > 1 ? static_cast<size_t>(hs) * N * sizeof(float) : 0;
     if (need > 0 && (!ws || ws_bytes < need)) return DODO_ERR_WORKSPACE_TOO_SMALL;

@@ -45,6 +45,19 @@ def test_mfma_path_small_shapes(D, N, d, dh, act):
     _check(got, want)
 
 
+# few tokens: blocks of 16 tokens, runs of 64 channels over 8 wavefronts (1, 9 and 130 of them), equal shares of the
+# hidden units per compute unit (a single one, an incomplete second block of 16, two full blocks with a short last share)
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("d,dh", [(64, 256), (576, 5376), (128, 8448), (8320, 256)])
+def test_few_tokens(D, N, d, dh):
+    x, W1, b1, w2 = _case(970 + N, N, d, dh, torch.bfloat16)
+    want = oracle.score_mlp(W.to_numpy(x), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, 1)
+    padded = torch.full((N, d + 8), float("nan"), dtype=torch.bfloat16)  # rows further apart than d: nothing between them is read
+    padded[:, :d] = x
+    got = D.dodo_score_mlp(padded.to(dev())[:, :d], W1.to(dev()), b1.to(dev()), w2.to(dev()), 0.25, 1).cpu().numpy()
+    _check(got, want)
+
+
 @pytest.mark.parametrize("dtype,N,d,dh", [(torch.float32, 512, 256, 256), (torch.bfloat16, 37, 40, 100),
                                           (torch.float32, 9, 24, 7)])
 def test_plain_path_any_shape(D, dtype, N, d, dh):
