@@ -194,6 +194,11 @@ def dodo_score_layers(hidden: torch.Tensor, w: torch.Tensor, biases: Optional[to
     return scores
 
 
+# Longest sequence that one workgroup holds on chip: without a workspace it takes at most as long as several workgroups
+# take to exchange their counts through one, which would have to be filled with zeros first.
+_ONE_WORKGROUP_TOKENS = 33 * 1024
+
+
 def dodo_select_topk_workspace_bytes(B: int, max_n: int) -> int:
     return int(lib.dodo_select_topk_workspace_bytes(B, max_n))
 
@@ -210,7 +215,7 @@ def dodo_select_topk(scores: torch.Tensor, cu_seqlens: torch.Tensor, cu_nuggets:
         nugget_idx = torch.empty(total_nuggets, dtype=torch.int32, device=scores.device)
     assert nugget_idx.dtype == torch.int32 and nugget_idx.numel() >= total_nuggets
     need = dodo_select_topk_workspace_bytes(B, max_n)
-    if need and ws is None:
+    if need and ws is None and max_n > _ONE_WORKGROUP_TOKENS:
         # zero-filled, as the library requires before the first use (a call leaves it zero-filled)
         ws = torch.zeros(need, dtype=torch.uint8, device=scores.device)
     _check(lib.dodo_select_topk(_ptr(scores), _ptr(cu_seqlens), _ptr(cu_nuggets), B, max_n, max_k, flags,
@@ -477,7 +482,7 @@ def dodo_threshold_from_sample(sample: torch.Tensor, num: int, den: int, out: Op
     if out is None:
         out = torch.empty(1, dtype=torch.float32, device=sample.device)
     need = dodo_threshold_from_sample_workspace_bytes(sample.numel())
-    if need and ws is None:
+    if need and ws is None and sample.numel() > _ONE_WORKGROUP_TOKENS:
         ws = torch.empty(need, dtype=torch.uint8, device=sample.device)
     _check(lib.dodo_threshold_from_sample(_ptr(sample), sample.numel(), num, den, _ptr(out), _ptr(ws),
                                           0 if ws is None else ws.numel(), _stream()), "dodo_threshold_from_sample")

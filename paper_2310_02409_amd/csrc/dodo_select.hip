@@ -1,29 +1,27 @@
 // dodo_select_topk: per-sequence TopK of the scorer output (Eq. 14 of the Dodo
 // paper) plus the ordered, segmented compaction that writes the nugget index
-// lists.  Integer work only, so the result is unique and bit-exact:
-//   1. every fp32 score becomes an order-preserving uint32 key (NaN lowest,
-//      -0 == +0), staged in LDS when the sequence fits (<= 36864 tokens);
-//   2. a 4-pass, 8-bit MSB radix select finds the key T of the k-th best token
-//      and how many tokens equal to T are still needed; after the first pass
-//      the tokens that share the chosen top byte are collected in a list (if
-//      they are few enough), so that the other three passes touch only those;
-//   3. a stable compaction emits, in ascending position order, every token
-//      with key > T and the first `need` tokens with key == T (lowest index
-//      wins ties).
-// One workgroup per sequence; histograms use LDS integer atomics with a
-// wavefront-level pre-aggregation so that heavy ties do not serialise.
-// Long sequences (given a workspace) are cut into chunks with a workgroup
-// each: the chunks' histograms of a pass are added up in the workspace, every
-// workgroup waits until all have contributed (bounded) and then picks the
-// digit from the same totals; the compaction hands out output offsets and the
-// tie budget in chunk (= position) order in the same way.  The result is the
-// same bit for bit; one compute unit's instruction issue no longer bounds it.
-#include "dodo_common.h"
+// lists.  Integer comparisons decide (an order-preserving uint32 key per score: NaN
+// lowest, -0 == +0), so the result is unique and bit-exact.
+// One workgroup per sequence: it finds the key T of the k-th best token and how many
+// tokens equal to T are still needed (dodo_kth.h), then a stable compaction emits, in
+// ascending position order, every token with key > T and the first `need` tokens with
+// key == T (lowest index wins ties).  Three forms by the longest sequence:
+//   <= 8192 tokens   the scores sit in registers            (select_topk_regs_kernel)
+//   <= 33792 tokens  the scores sit in LDS                  (select_topk_lds_kernel)
+//   longer           re-read from memory by a 4-pass, 8-bit MSB radix select (select_topk_kernel)
+// Sequences beyond 8192 tokens, given a workspace, are cut into chunks with a workgroup
+// each (select_topk_kernel<.., true>): the chunks' histograms of a radix pass are added
+// up in the workspace, every workgroup waits until all have contributed (bounded) and
+// then picks the digit from the same totals; the compaction hands out output offsets
+// and the tie budget in chunk (= position) order in the same way.  Same result bit for
+// bit.  Its six exchanges take 20-24 us whatever the length: more than one workgroup
+// takes up to 33792 tokens (11 us for 16384, 16-21 us for 32768), less beyond.
+#include "dodo_kth.h"
 
 namespace dodo {
 namespace {
 
-constexpr int kStagedMaxKeys = 34 * 1024;  // 136 KiB of the 160 KiB LDS
+constexpr int kStagedMaxKeys = 34 * 1024;  // longest chunk: 136 KiB of the 160 KiB LDS
 constexpr int kCandCap = 8192;             // candidate list after the first pass: 16-bit positions, 16 KiB
 constexpr int kMultiMinKeys = 8192;        // sequences longer than this are worth several workgroups
 constexpr int kMultiChunkKeys = 4096;      // aimed-at keys per workgroup
@@ -36,14 +34,14 @@ constexpr uint32_t kStatusWaitFailed = 1u;
 constexpr int kMaxPolls = 1 << 17;         // bound of a wait for the other chunks (~0.1 s, never reached in a healthy run)
 
 // MULTI: G consecutive workgroups share a sequence (chunk c = blockIdx % G); lds_keys = keys that fit in LDS.
-template <int THREADS, bool STAGED, bool MULTI>
+template <int THREADS, bool MULTI>
 __global__ __launch_bounds__(THREADS) void select_topk_kernel(const float* __restrict__ scores,
                                                               const int32_t* __restrict__ cu_seqlens,
                                                               const int32_t* __restrict__ cu_nuggets, uint32_t flags,
                                                               int max_n, int lds_keys, int G, uint32_t* __restrict__ ws,
                                                               int32_t* __restrict__ nugget_idx) {
   constexpr int kWaves = THREADS / kWave;
-  extern __shared__ uint32_t keys_lds[];  // lds_keys keys, then kCandCap 16-bit positions (STAGED only)
+  extern __shared__ uint32_t keys_lds[];  // lds_keys keys, then kCandCap 16-bit positions (MULTI only)
   __shared__ uint32_t hist[256], hist_own[256];
   __shared__ uint32_t s_prefix, s_remaining, s_cand;
   __shared__ int wave_gt[kWaves], wave_eq[kWaves];
@@ -98,7 +96,7 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const float* __res
   };
 
   if (k_free > 0) {
-    if (STAGED) {
+    if (MULTI) {
       // batches of 8 loads in flight per thread: one global-memory latency per batch, not per key
       constexpr int kBatch = 8;
       const int n_free = n_own;
@@ -117,7 +115,7 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const float* __res
       }
       __syncthreads();
     }
-    auto key_at = [&](int i) -> uint32_t { return STAGED ? keys_lds[i] : order_key(s[i]); };
+    auto key_at = [&](int i) -> uint32_t { return MULTI ? keys_lds[i] : order_key(s[i]); };
     const int n_free = n_own;  // below, "the tokens" are this workgroup's; positions are relative to lo
     int pass_no = 0;
 
@@ -220,7 +218,7 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const float* __res
     };
     radix_pass(24, n_free, key_at);
     const int n_cand = static_cast<int>(s_cand);
-    if (STAGED && n_cand <= kCandCap) {
+    if (MULTI && n_cand <= kCandCap) {
       // positions of the tokens that share the chosen top byte, in any order
       uint16_t* cand = reinterpret_cast<uint16_t*>(keys_lds + lds_keys);
       __syncthreads();  // everyone has read s_cand
@@ -336,6 +334,163 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const float* __res
   }
 }
 
+// ---- sequences whose scores fit the registers of one workgroup ----
+// Wavefront w holds `rows` x 64 neighbouring tokens, one row of 64 per register, so positions ascend with (wavefront,
+// register, lane) and the compaction needs one exchange between wavefronts: their counts.  Scores are compared as
+// floats there (NaN compares false with everything: it ranks lowest; -0 == +0 as in the keys).
+// Latency-bound: per sequence two dependent rounds of loads, then five barriers (kth_largest) and one here.  Measured, per
+// launch, against a 4-pass radix select on keys in LDS: 8 x 4096 tokens 6.2 us (14.1), 16 x 2048 5.0 us (11.6),
+// 8 x 8192 9.2 us (15.6); masses of ties cost 1 to 2 us more.
+template <int THREADS, int KPT>
+__global__ __launch_bounds__(THREADS) void select_topk_regs_kernel(const float* __restrict__ scores,
+                                                                   const int32_t* __restrict__ cu_seqlens,
+                                                                   const int32_t* __restrict__ cu_nuggets, uint32_t flags,
+                                                                   int max_n, int32_t* __restrict__ nugget_idx) {
+  constexpr int kWaves = THREADS / kWave;
+  __shared__ KthShared<THREADS> sh;
+  __shared__ int wave_gt[kWaves], wave_eq[kWaves];
+  asm volatile("" ::"s"(scores), "s"(cu_seqlens), "s"(cu_nuggets), "s"(flags), "s"(max_n), "s"(nugget_idx));
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int seq0 = cu_seqlens[b], seq1 = cu_seqlens[b + 1];
+  const int nug0 = cu_nuggets[b], nug1 = cu_nuggets[b + 1];
+  asm volatile("" ::"s"(seq0), "s"(seq1), "s"(nug0), "s"(nug1));
+  const int n = seq1 - seq0;
+  int k = nug1 - nug0;
+  if (k <= 0 || n <= 0 || n > max_n) return;  // uniform over the workgroup
+  if (k > n) k = n;
+  const bool force = (flags & DODO_TOPK_FORCE_LAST) != 0;
+  const int n_free = force ? n - 1 : n;  // tokens that compete on score
+  const int k_free = force ? k - 1 : k;
+  int32_t* out = nugget_idx + nug0;
+  if (force && tid == 0) out[k - 1] = n - 1;
+  if (k_free <= 0) return;
+  const int rows = (n_free + THREADS - 1) / THREADS;  // <= KPT
+  const int start = wave * rows * kWave;
+  int lim = max(0, min(rows * kWave, n_free - start));  // this wavefront's tokens
+  const float* s = scores + seq0;
+  float v[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) v[j] = s[min(start + j * kWave + lane, n_free - 1)];  // all in flight together
+#pragma unroll
+  for (int j = 0; j < KPT; ++j)
+    if (j * kWave + lane >= lim) v[j] = __builtin_nanf("");
+  uint32_t T, need;
+  kth_largest<THREADS, KPT>(sh, v, lim, static_cast<uint32_t>(k_free), T, need);
+
+  forget_comparisons(v, lim);
+  const bool t_nan = T == 0u;  // the k-th best is a NaN: every number is better, NaN ties with NaN
+  const float t = __uint_as_float((T & 0x80000000u) ? T ^ 0x80000000u : ~T);
+  auto better = [&](int j) { return t_nan ? v[j] == v[j] : v[j] > t; };
+  auto equal = [&](int j) { return t_nan ? (v[j] != v[j] && j * kWave + lane < lim) : v[j] == t; };
+  int cnt_gt = 0, cnt_eq = 0;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    cnt_gt += __popcll(__ballot(better(j)));
+    cnt_eq += __popcll(__ballot(equal(j)));
+  }
+  if (lane == 0) {
+    wave_gt[wave] = cnt_gt;
+    wave_eq[wave] = cnt_eq;
+  }
+  __syncthreads();
+  forget_comparisons(v, lim);
+  const int need_eq = static_cast<int>(need);
+  int gt_before = 0, eq_base = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    gt_before += w < wave ? wave_gt[w] : 0;
+    eq_base += w < wave ? wave_eq[w] : 0;
+  }
+  int out_base = gt_before + min(eq_base, need_eq);
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    if (j >= rows) break;
+    const bool is_eq = equal(j);
+    const uint64_t eq_mask = __ballot(is_eq);
+    const bool sel = better(j) || (is_eq && eq_base + popc_below_lane(eq_mask) < need_eq);
+    const uint64_t sel_mask = __ballot(sel);
+    const int pos = out_base + popc_below_lane(sel_mask);
+    if (sel && pos < k_free) out[pos] = start + j * kWave + lane;  // pos < k_free always holds; the test keeps a logic slip in bounds
+    eq_base += __popcll(eq_mask);
+    out_base += __popcll(sel_mask);
+  }
+}
+
+// ---- sequences whose scores fit the LDS of one compute unit ----
+// Bound by instruction issue of the one compute unit that a sequence gets: about 3 us per pass over 32768 scores, of which
+// there are four (staging, counting against the bounds, output, and one more for ties).
+__global__ __launch_bounds__(kWideThreads) void select_topk_lds_kernel(const float* __restrict__ scores,
+                                                                       const int32_t* __restrict__ cu_seqlens,
+                                                                       const int32_t* __restrict__ cu_nuggets, uint32_t flags,
+                                                                       int max_n, int32_t* __restrict__ nugget_idx) {
+  constexpr int kWaves = kWideThreads / kWave;
+  extern __shared__ float staged[];  // max_n scores
+  __shared__ KthShared<kWideThreads> sh;
+  __shared__ float list[kWaves * kKthListPerWave];
+  __shared__ int wave_gt[kWaves], wave_eq[kWaves];
+  asm volatile("" ::"s"(scores), "s"(cu_seqlens), "s"(cu_nuggets), "s"(flags), "s"(max_n), "s"(nugget_idx));
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int seq0 = cu_seqlens[b], seq1 = cu_seqlens[b + 1];
+  const int nug0 = cu_nuggets[b], nug1 = cu_nuggets[b + 1];
+  asm volatile("" ::"s"(seq0), "s"(seq1), "s"(nug0), "s"(nug1));
+  const int n = seq1 - seq0;
+  int k = nug1 - nug0;
+  if (k <= 0 || n <= 0 || n > max_n) return;  // uniform over the workgroup
+  if (k > n) k = n;
+  const bool force = (flags & DODO_TOPK_FORCE_LAST) != 0;
+  const int n_free = force ? n - 1 : n;  // tokens that compete on score
+  const int k_free = force ? k - 1 : k;
+  int32_t* out = nugget_idx + nug0;
+  if (force && tid == 0) out[k - 1] = n - 1;
+  if (k_free <= 0) return;
+  const int rows = (n_free + kWideThreads - 1) / kWideThreads;
+  const int start = wave * rows * kWave;
+  const int lim = max(0, min(rows * kWave, n_free - start));  // this wavefront's tokens
+  stage_share(staged + start, scores + seq0 + start, lim);
+  const LdsShare share{staged + start, lim};
+  uint32_t T, need;
+  int cnt_gt, cnt_eq;
+  kth_largest_lds<kWideThreads>(sh, list, share, n_free, static_cast<uint32_t>(k_free), T, need, cnt_gt, cnt_eq);
+  if (lane == 0) {
+    wave_gt[wave] = cnt_gt;
+    wave_eq[wave] = cnt_eq;
+  }
+  __syncthreads();
+  const int need_eq = static_cast<int>(need);
+  int gt_before = 0, eq_base = 0, eq_all = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    gt_before += w < wave ? wave_gt[w] : 0;
+    eq_base += w < wave ? wave_eq[w] : 0;
+    eq_all += wave_eq[w];
+  }
+  int out_base = gt_before + min(eq_base, need_eq);
+  const float t = __uint_as_float((T & 0x80000000u) ? T ^ 0x80000000u : ~T);
+  if (eq_all == need_eq && T != 0u) {  // every score equal to the k-th best is taken (no tie to break): one comparison
+    for_share<4>(share, [&](float x, int i, bool exists) {
+      const bool sel = exists && x >= t;
+      const uint64_t sel_mask = __ballot(sel);
+      const int pos = out_base + popc_below_lane(sel_mask);
+      if (sel && pos < k_free) out[pos] = start + i;  // pos < k_free always holds; the test keeps a logic slip in bounds
+      out_base += __popcll(sel_mask);
+    });
+    return;
+  }
+  const bool t_nan = T == 0u;  // the k-th best is a NaN: every number is better, NaN ties with NaN
+  for_share<4>(share, [&](float x, int i, bool exists) {
+    const bool is_eq = exists && (t_nan ? x != x : x == t);
+    const uint64_t eq_mask = __ballot(is_eq);
+    const bool sel = (exists && (t_nan ? x == x : x > t)) || (is_eq && eq_base + popc_below_lane(eq_mask) < need_eq);
+    const uint64_t sel_mask = __ballot(sel);
+    const int pos = out_base + popc_below_lane(sel_mask);
+    if (sel && pos < k_free) out[pos] = start + i;
+    eq_base += __popcll(eq_mask);
+    out_base += __popcll(sel_mask);
+  });
+}
+
 // Chunks per sequence of the chunked form, or 0 when it does not apply (short sequences, or more workgroups than
 // compute units: all chunks of a sequence must be resident at the same time, since they wait for each other).
 int chunk_count(int32_t B, int32_t max_n) {
@@ -349,24 +504,11 @@ int chunk_count(int32_t B, int32_t max_n) {
   return chunk_len <= kStagedMaxKeys ? G : 0;
 }
 
-template <int THREADS>
-int launch_select(const float* scores, const int32_t* cu_seqlens, const int32_t* cu_nuggets, int32_t B, int32_t max_n,
-                  uint32_t flags, int32_t* nugget_idx, hipStream_t stream) {
-  if (max_n <= kStagedMaxKeys) {
-    const size_t lds = static_cast<size_t>(max_n) * sizeof(uint32_t) + kCandCap * sizeof(uint16_t);
-    auto kern = select_topk_kernel<THREADS, true, false>;
-    if (lds > 48 * 1024) {
-      {
-      const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(kern), static_cast<int>(lds));
-      if (rc_lds != DODO_OK) return rc_lds;
-    }
-    }
-    hipLaunchKernelGGL(kern, dim3(B), dim3(THREADS), lds, stream, scores, cu_seqlens, cu_nuggets, flags, max_n, max_n, 1,
-                       static_cast<uint32_t*>(nullptr), nugget_idx);
-  } else {
-    hipLaunchKernelGGL((select_topk_kernel<THREADS, false, false>), dim3(B), dim3(THREADS), 0, stream, scores, cu_seqlens,
-                       cu_nuggets, flags, max_n, 0, 1, static_cast<uint32_t*>(nullptr), nugget_idx);
-  }
+template <int THREADS, int KPT>
+int launch_select_regs(const float* scores, const int32_t* cu_seqlens, const int32_t* cu_nuggets, int32_t B, int32_t max_n,
+                       uint32_t flags, int32_t* nugget_idx, hipStream_t stream) {
+  hipLaunchKernelGGL((select_topk_regs_kernel<THREADS, KPT>), dim3(B), dim3(THREADS), 0, stream, scores, cu_seqlens, cu_nuggets,
+                     flags, max_n, nugget_idx);
   return launch_status();
 }
 
@@ -374,7 +516,7 @@ int launch_select_chunked(const float* scores, const int32_t* cu_seqlens, const 
                           int32_t max_n, int G, uint32_t flags, int32_t* nugget_idx, uint32_t* ws, hipStream_t stream) {
   const int chunk_len = ((max_n + G - 1) / G + kWave - 1) / kWave * kWave;
   const size_t lds = static_cast<size_t>(chunk_len) * sizeof(uint32_t) + kCandCap * sizeof(uint16_t);
-  auto kern = select_topk_kernel<1024, true, true>;
+  auto kern = select_topk_kernel<1024, true>;
   if (lds > 48 * 1024) {
     {
       const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(kern), static_cast<int>(lds));
@@ -410,8 +552,24 @@ extern "C" int dodo_select_topk(const float* scores, const int32_t* cu_seqlens, 
   if (G > 0 && ws != nullptr && ws_bytes >= (kWsHeader + static_cast<size_t>(B) * kWsPerSeq) * sizeof(uint32_t) &&
       (reinterpret_cast<uintptr_t>(ws) & 3u) == 0)
     return launch_select_chunked(scores, cu_seqlens, cu_nuggets, B, max_n, G, flags, nugget_idx, static_cast<uint32_t*>(ws), s);
-  // about four keys per thread: the kernel is latency-bound (few barriers matter more than lanes)
-  if (max_n <= 1024) return launch_select<256>(scores, cu_seqlens, cu_nuggets, B, max_n, flags, nugget_idx, s);
-  if (max_n <= 2048) return launch_select<512>(scores, cu_seqlens, cu_nuggets, B, max_n, flags, nugget_idx, s);
-  return launch_select<1024>(scores, cu_seqlens, cu_nuggets, B, max_n, flags, nugget_idx, s);
+  // one workgroup per sequence, as many threads as leave each a few scores (up to 34 where 1024 are not enough)
+#define DODO_SELECT_REGS(THREADS, KPT) \
+  if (max_n <= THREADS * KPT)          \
+  return launch_select_regs<THREADS, KPT>(scores, cu_seqlens, cu_nuggets, B, max_n, flags, nugget_idx, s)
+  DODO_SELECT_REGS(256, 4);
+  DODO_SELECT_REGS(512, 4);
+  DODO_SELECT_REGS(1024, 4);
+  DODO_SELECT_REGS(1024, 8);
+#undef DODO_SELECT_REGS
+  if (max_n <= kWideMaxKeys) {
+    const int lds = max_n * static_cast<int>(sizeof(float));
+    auto kern = select_topk_lds_kernel;
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (rc != DODO_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3(B), dim3(kWideThreads), lds, s, scores, cu_seqlens, cu_nuggets, flags, max_n, nugget_idx);
+    return launch_status();
+  }
+  hipLaunchKernelGGL((select_topk_kernel<1024, false>), dim3(B), dim3(1024), 0, s, scores, cu_seqlens, cu_nuggets, flags, max_n,
+                     0, 1, static_cast<uint32_t*>(nullptr), nugget_idx);
+  return launch_status();
 }

@@ -165,6 +165,46 @@ def test_select_is_deterministic(D):
         assert torch.equal(D.dodo_select_topk(s, cu_s, cu_kd, max(n_lens), max(k_lens), int(cu_k[-1])), first)
 
 
+def _hard_scores(kind, n, seed):
+    """Scores that take the different ways through the search for the k-th best."""
+    g = np.random.default_rng(seed)
+    s = g.standard_normal(n).astype(np.float32)
+    if kind == "ties":
+        s = W.quantise16(torch.from_numpy(s)).numpy()
+    elif kind == "three values":
+        s = g.choice(np.array([0.0, 1.0, 1.0000001], np.float32), n, p=[0.9, 0.05, 0.05])
+    elif kind == "exponents":  # no useful steps in value: nearly everything falls into one of them
+        s = (s * np.exp(20 * g.standard_normal(n))).astype(np.float32)
+    elif kind == "overflow":   # the range of the scores is not a finite number
+        s[::2] *= np.float32(3e38)
+    elif kind == "rising":     # positions and scores go together: a sample of positions misleads
+        s = np.arange(n, dtype=np.float32)
+    elif kind == "specials":
+        s[::3] = np.nan
+        s[1::11] = np.inf
+        s[2::13] = -np.inf
+        s[4::17] = -0.0
+    elif kind == "constant":
+        s[:] = -2.5
+    return s
+
+
+# sizes at the edges of the forms of the kernel (scores in registers of 256, 512 or 1024 threads, in LDS, in memory)
+@pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20001, 33792, 33793])
+@pytest.mark.parametrize("kind", ["gauss", "ties", "three values", "exponents", "overflow", "rising", "specials", "constant"])
+def test_select_one_workgroup_per_sequence(D, n, kind):
+    n_lens = [n, max(1, n // 3)]
+    scores = np.concatenate([_hard_scores(kind, m, 7 * n + i) for i, m in enumerate(n_lens)])
+    cu_s = oracle.cu_from_lengths(n_lens)
+    for k_lens in ([1, 1], [-(-m // 10) for m in n_lens], [max(1, m - 1) for m in n_lens], n_lens):
+        cu_k = oracle.cu_from_lengths(k_lens)
+        for flags in (0, 1):
+            got = D.dodo_select_topk(torch.from_numpy(scores).to(dev()), torch.from_numpy(cu_s).to(dev()),
+                                     torch.from_numpy(cu_k).to(dev()), n, max(k_lens), int(cu_k[-1]), flags,
+                                     ws=torch.zeros(16, dtype=torch.uint8, device=dev()))
+            assert np.array_equal(got.cpu().numpy(), oracle.select_topk(scores, cu_s, cu_k, flags)), (k_lens, flags)
+
+
 def test_select_long_sequences_over_several_workgroups(D):
     # with the workspace, sequences beyond 8192 tokens are cut into chunks that exchange histograms and counts
     n_lens = [20000, 9000, 33000, 70, 0]

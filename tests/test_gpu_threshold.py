@@ -62,6 +62,28 @@ def test_threshold_from_large_samples_over_many_workgroups(D, n, num, den, kind)
     assert one.tobytes() == want.tobytes()
 
 
+# sizes at the edges of the forms of the kernel (scores in registers, in LDS, in memory)
+@pytest.mark.parametrize("n", [2, 64, 4096, 4097, 15000, 33792, 33793])
+@pytest.mark.parametrize("kind", ["gauss", "ties", "exponents", "rising", "specials", "constant"])
+def test_threshold_from_sample_in_one_workgroup(D, n, kind):
+    g = np.random.default_rng(n)
+    s = g.standard_normal(n).astype(np.float32)
+    if kind == "ties":
+        s = W.quantise16(torch.from_numpy(s)).numpy()
+    elif kind == "exponents":
+        s = (s * np.exp(20 * g.standard_normal(n))).astype(np.float32)
+    elif kind == "rising":
+        s = np.arange(n, dtype=np.float32)
+    elif kind == "specials":
+        s[::3], s[1::11], s[2::13], s[4::17] = np.nan, np.inf, -np.inf, -0.0
+    elif kind == "constant":
+        s[:] = -2.5
+    for num, den in ((1, 10), (9, 10), (1, n)):
+        want = np.float32(oracle.threshold_from_sample(s, num, den))
+        got = D.dodo_threshold_from_sample(torch.from_numpy(s).to(dev()), num, den).cpu().numpy()[0]
+        assert got.tobytes() == want.tobytes(), (num, den, got, want)
+
+
 def test_threshold_from_sample_when_the_rank_falls_on_nan(D):
     s = torch.tensor([float("nan"), 5.0, float("nan"), 1.0, -0.0, 7.0], dtype=torch.float32)
     for num, den in [(1, 3), (1, 2), (4, 6)]:
