@@ -99,6 +99,7 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
 
 
 lib = _load()
+_current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -114,7 +115,8 @@ def _ptr(t: Optional[torch.Tensor]) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle alone: building the Python stream object costs 2.7 us, a quarter of a small call's host time
+    return _current_raw_stream(_current_device())
 
 
 def _check(rc: int, where: str) -> None:
@@ -131,6 +133,8 @@ def _dev(*ts: Optional[torch.Tensor]) -> None:
 def _dev_rows(*ts: torch.Tensor) -> None:
     """Device tensors whose rows (all dimensions but the first) are contiguous; the first dimension may be strided."""
     for t in ts:
+        if t.is_cuda and t.is_contiguous():
+            continue
         inner = 1
         for size, stride in zip(reversed(t.shape[1:]), reversed(t.stride()[1:])):
             if size != 1 and stride != inner:
