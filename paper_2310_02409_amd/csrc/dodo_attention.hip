@@ -22,7 +22,7 @@ extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, in
   using namespace dodo;
   if (B <= 0 || H <= 0 || d_h <= 0 || max_q <= 0 || max_k < 0 || max_local < 0) return 0;
   if (use_block_kernel(dtype, d_h, max_q)) return 0;
-  return splitk_workspace_bytes(B, H, d_h, max_q, splitk_count(B, H, max_q, max_k, max_local));
+  return splitk_workspace_bytes(B, H, d_h, max_q, splitk_count(B, H, d_h, max_q, max_k, max_local, dtype));
 }
 
 extern "C" size_t dodo_nugget_attention_workspace_bytes_grouped(int32_t B, int32_t H, int32_t H_kv, int32_t d_h,

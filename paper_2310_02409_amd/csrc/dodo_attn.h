@@ -36,7 +36,7 @@ constexpr int kMaxPolls = 1 << 17;               // bound of the combiner's wait
 
 // Split count of the bandwidth-bound kernels for these bounds (>= 1), shared by
 // the launches and the workspace query.
-int splitk_count(int32_t B, int32_t H, int32_t max_q, int32_t max_k, int32_t max_local);
+int splitk_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype);
 size_t splitk_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int nsplit);
 
 // fp32 or bf16, d_h in {64,128}, any max_q: one workgroup per (query row, head, split).

@@ -71,7 +71,8 @@ __device__ __forceinline__ float exp2_guard(float x) { return __builtin_amdgcn_e
 // sequence b is token cu_ctx[b] + nug_idx[cu_nuggets[b] + j] of it (no packed cache has been made).
 // GROUPED: the workgroup serves GH query heads of one KV head times QR query rows, more than one query vector in all
 // (else both are 1 and everything about them folds away).
-template <int DTYPE, int DH, int kThreads, bool INDEXED, bool GROUPED>
+constexpr int kThreads = 256;  // (1024-thread workgroups were never faster: two more rounds of the merge, and a split less)
+template <int DTYPE, int DH, bool INDEXED, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void splitk_attention_kernel(
     const void* __restrict__ Q, const void* __restrict__ Kn, const void* __restrict__ Vn,
     const void* __restrict__ Kl, const void* __restrict__ Vl, const int32_t* __restrict__ cu_q,
@@ -456,32 +457,31 @@ int launch_t(const AttnParams& p, int nsplit) {
                         ? static_cast<uint32_t*>(p.ws_flags)
                         : reinterpret_cast<uint32_t*>(static_cast<float*>(p.ws) +
                                                       static_cast<int64_t>(p.B) * p.max_q * p.H * nsplit * partial_floats<DH>());
-  // few workgroups (about one per CU) with many rows each: 16 wavefronts per workgroup keep enough
-  // loads in flight; otherwise 4 wavefronts and several workgroups per CU
-  const bool wide = rows * nsplit <= 512 && static_cast<int64_t>(p.max_k) + p.max_local >= 512;
   const dim3 grid(static_cast<unsigned>(p.H / gh), static_cast<unsigned>(row_groups), static_cast<unsigned>(nsplit));
-#define DODO_LAUNCH_SPLITK(THREADS, GROUPED)                                                                               \
-  hipLaunchKernelGGL((splitk_attention_kernel<DTYPE, DH, THREADS, INDEXED, GROUPED>), grid, dim3(THREADS), 0, p.stream, p.Q,  \
+#define DODO_LAUNCH_SPLITK(GROUPED)                                                                                        \
+  hipLaunchKernelGGL((splitk_attention_kernel<DTYPE, DH, INDEXED, GROUPED>), grid, dim3(kThreads), 0, p.stream, p.Q,          \
                      p.Kn, p.Vn, p.Kl, p.Vl, p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, p.H, \
                      p.H_kv, p.H / p.H_kv, gh_log2, qr_log2, p.max_q, nsplit, p.nug_tok_stride, p.nug_head_stride, p.scale_log2e, p.O, p.lse,         \
                      static_cast<float*>(p.ws), flags)
-  if (wide) {
-    if (gh * qr > 1) DODO_LAUNCH_SPLITK(1024, true); else DODO_LAUNCH_SPLITK(1024, false);
-  } else {
-    if (gh * qr > 1) DODO_LAUNCH_SPLITK(256, true); else DODO_LAUNCH_SPLITK(256, false);
-  }
+  if (gh * qr > 1) DODO_LAUNCH_SPLITK(true); else DODO_LAUNCH_SPLITK(false);
 #undef DODO_LAUNCH_SPLITK
   return launch_status();
 }
 
 }  // namespace
 
-int splitk_count(int32_t B, int32_t H, int32_t max_q, int32_t max_k, int32_t max_local) {
+// Splits of a (query row, head): as many as give each compute unit a workgroup, rounded down -- a split more than
+// that leaves some units with two (5 sequences x 40 heads, 2100 rows: 37.6 us unsplit, 40.9 in two; 3 x 40 heads, 1157
+// rows: 16.7 us in two, 18.7 in three).  The combining costs about 2 us, so nothing is split below 96 KiB of K rows
+// (350 rows of 32 heads, one sequence: 7.2 us unsplit, 7.4 in eight; 450 rows: 8.6 against 7.6; 667 rows: 10.5
+// against 8.0; 64-wide heads: level at twice as many rows), and a split keeps at least the rows that its
+// wavefronts request in one go.
+int splitk_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype) {
   const int64_t base = static_cast<int64_t>(B) * H * max_q;  // workgroups without splitting
-  const int64_t rows = static_cast<int64_t>(max_k) + max_local;
-  const int64_t want = (256 + base - 1) / base;            // aim at >= one (wide) workgroup per CU
-  const int64_t room = rows / 256 > 0 ? rows / 256 : 1;    // keep >= 256 rows per split
-  int64_t n = want < room ? want : room;
+  const int64_t k_bytes = (static_cast<int64_t>(max_k) + max_local) * d_h * elem_bytes(dtype);
+  if (k_bytes < 96 * 1024) return 1;
+  int64_t n = compute_units() / base;
+  if (n > k_bytes / (12 * 1024)) n = k_bytes / (12 * 1024);
   if (n < 1) n = 1;
   if (n > 64) n = 64;
   return static_cast<int>(n);
@@ -493,7 +493,7 @@ size_t splitk_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, 
 }
 
 int launch_splitk_attention(const AttnParams& p) {
-  const int nsplit = splitk_count(p.B, p.H, p.max_q, p.max_k, p.max_local);
+  const int nsplit = splitk_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.dtype);
   if (static_cast<int64_t>(p.B) * p.max_q * p.H * nsplit > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   // the kernel multiplies a row number by a stride in bytes kept in 32 bits
   if (p.nug_tok_stride * 4 > 0xffffffffLL || static_cast<int64_t>(p.H_kv) * p.d_h * 4 > 0xffffffffLL)

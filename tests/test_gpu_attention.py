@@ -94,6 +94,17 @@ def test_decode_split_k_paths(D):
     _full_check(D, 402, [1], [2000], [300], 2, 1, 64, torch.float32)
 
 
+@pytest.mark.parametrize("dtype,d_h,first", [(torch.bfloat16, 128, 384), (torch.bfloat16, 64, 768), (torch.float32, 64, 384)])
+def test_decode_around_the_first_split(D, dtype, d_h, first):
+    # `first` rows are 96 KiB of K, from where on a few (sequence, head) pairs are split: one row less, exactly, one more,
+    # and far beyond, next to sequences whose splits are empty or hold a single row
+    code = D.F32 if dtype == torch.float32 else D.BF16
+    for rows, splits in ((first - 1, 1), (first, 8), (first + 1, 8), (16 * first, 64)):
+        need = D.dodo_nugget_attention_workspace_bytes(2, 2, d_h, 1, rows - 100, 100, code)
+        assert (need // (4 * (d_h + 3) * 4) if need else 1) == splits
+        _full_check(D, 440 + rows % 7, [1, 1], [rows - 100, 7], [100, 3], 2, 2, d_h, dtype)
+
+
 def test_split_k_workspace_is_reusable_and_needs_no_initialisation(D):
     # the last split of a row waits for the flags of the others and clears them: the same workspace
     # serves call after call, and bytes that are not the "ready" value are as good as zeros
