@@ -160,14 +160,18 @@ template <bool MASK, int NCB>
 __device__ __forceinline__ void softmax_tile(floatx16 (&acc)[2], int limit, int g, float scale_log2e, float& m_run,
                                              float& l_run, floatx16 (&acc_o)[NCB], bf16x8 (&pf)[4]) {
   float tmax = kNegInf;
+  // The lane's part of the key index, 4 g, is taken off the limit, so that the comparisons are with constants: as 32 lane
+  // values the compiler kept the indices in registers across the loop (230 instead of 250 registers in the 8-wavefront
+  // kernel, 194 instead of 225 in the other; 64-row blocks 11.5 -> 10.2 us).
+  const int limit_g = limit - 4 * g;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       float s = acc[kb][v] * scale_log2e;
       if (MASK) {
-        const int key = 32 * kb + 8 * (v >> 2) + 4 * g + (v & 3);
-        s = (key < limit) ? s : kNegInf;
+        const int key = 32 * kb + 8 * (v >> 2) + (v & 3);
+        s = (key < limit_g) ? s : kNegInf;
       }
       acc[kb][v] = s;
       tmax = fmaxf(tmax, s);
@@ -209,12 +213,13 @@ template <bool MASK, bool SUMS>
 __device__ __forceinline__ void softmax_fixed(floatx16 (&acc)[2], int limit, int g, float scale_log2e, float& m_off,
                                               float& l_run, bf16x8 (&pf)[4]) {
   if (MASK) {
+    const int limit_g = limit - 4 * g;  // (see softmax_tile)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int key = 32 * kb + 8 * (v >> 2) + 4 * g + (v & 3);
-        acc[kb][v] = (key < limit) ? acc[kb][v] : kNegInf;
+        const int key = 32 * kb + 8 * (v >> 2) + (v & 3);
+        acc[kb][v] = (key < limit_g) ? acc[kb][v] : kNegInf;
       }
   }
   if (__any(m_off == kNegInf)) {  // some row of this wavefront has no offset yet (first visible tile)
