@@ -30,6 +30,21 @@ def test_score_matches_oracle(D, dtype, N, d):
     assert np.all(np.abs(got - ref) <= 1e-5 * (1 + np.abs(ref))), np.max(np.abs(got - ref))
 
 
+# every number of wave-wide loads that has a kernel of its own, and some that have none; rows: one, less than a
+# wavefront each, more than two for every wavefront that is resident
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 14, 16, 20, 24, 28, 32])
+def test_score_widths_of_whole_loads(D, dtype, chunks):
+    d = chunks * (512 if dtype == torch.bfloat16 else 256)
+    for N in (1, 3, 130) + ((20001,) if chunks <= 2 else ()):
+        x, w = W.normal(101, 2 * chunks, (N, d), 1.0, dtype), W.normal(101, 2 * chunks + 1, (d,), d ** -0.5, dtype)
+        padded = torch.full((N, d + 8), float("nan"), dtype=dtype)  # nothing between the rows is read
+        padded[:, :d] = x
+        ref = oracle.score(W.to_numpy(x), W.to_numpy(w), -0.25)
+        got = D.dodo_score(padded.to(dev())[:, :d], w.to(dev()), -0.25).cpu().numpy()
+        assert np.all(np.abs(got - ref) <= 1e-5 * (1 + np.abs(ref))), (N, np.max(np.abs(got - ref)))  # (as above)
+
+
 def test_score_exact_arithmetic_inputs_are_bit_exact(D):
     for dtype in (torch.float32, torch.bfloat16):
         x, w = W.exact_arithmetic_inputs(7, 2048, 4096, dtype)
@@ -176,7 +191,8 @@ def _hard_scores(kind, n, seed):
     elif kind == "exponents":  # no useful steps in value: nearly everything falls into one of them
         s = (s * np.exp(20 * g.standard_normal(n))).astype(np.float32)
     elif kind == "overflow":   # the range of the scores is not a finite number
-        s[::2] *= np.float32(3e38)
+        with np.errstate(over="ignore"):
+            s[::2] *= np.float32(3e38)
     elif kind == "rising":     # positions and scores go together: a sample of positions misleads
         s = np.arange(n, dtype=np.float32)
     elif kind == "specials":
