@@ -97,7 +97,8 @@ int dodo_score_layers(const void* hidden, const void* w, const float* biases, in
 #define DODO_ACT_GELU 1 /* x * Phi(x), erf form */
 #define DODO_ACT_TANH 2
 
-/* Bytes of device workspace dodo_score_mlp needs (may be 0). */
+/* Bytes of device workspace dodo_score_mlp would like for this N (may be 0).  It does not grow evenly with N; a smaller
+ * buffer, sized for another N, is accepted as long as the split that needs the least fits, and is slower. */
 size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d, int32_t d_hid);
 
 /*

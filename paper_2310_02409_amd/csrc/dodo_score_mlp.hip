@@ -9,20 +9,21 @@
 // once over all compute units (score_mlp_few_kernel).
 //
 // MFMA kernel (the same shapes, more tokens): a workgroup of 8 wavefronts
-// owns 256 tokens and walks over 256-wide tiles of hidden units; for each it
-// accumulates H^T = W1_tile X^T over d in steps of 64 channels with
+// owns 256 tokens and walks over 256-wide tiles of hidden units (or 4 wavefronts
+// 128 of each, for the tokens that do not fill the chip that way: plan_mlp);
+// for each it accumulates H^T = W1_tile X^T over d in steps of 64 channels with
 // v_mfma_f32_32x32x16_bf16 (A = W1 rows, B = token rows, so that a token is a lane
 // of the accumulators and the reduction over hidden units stays inside a lane),
 // then applies bias, activation and w2 to the accumulators and adds them to the
 // tokens' partial scores.  The N x d_hid intermediate never leaves the registers.
 // X and W1 tiles stream global -> LDS with 16-byte direct loads of whole 128-byte
-// rows into two 64 KiB stages; the 16-byte pieces of a row are XOR-swizzled so
+// rows into two stages of 64 (32) KiB; the 16-byte pieces of a row are XOR-swizzled so
 // that the fragment reads are conflict-free (measured: no bank-conflict cycles).
 // One barrier per step, after the third of its four 16-channel parts: by then a
 // wavefront holds the last part's fragments in registers, so the stage can be
 // refilled (for the step after next) right after the barrier, and the next
 // step's first fragments are fetched under the last part's matrix instructions.
-// The hidden tiles are split over (at least four) workgroups, and the workgroups
+// The hidden tiles are split over workgroups, and the workgroups
 // resident on one XCD form a patch of token tiles x splits that share their
 // panels through that XCD's L2; a second kernel adds the partial scores in split
 // order.  All sums have a fixed order (no atomics): run-to-run deterministic.
@@ -40,14 +41,25 @@ typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int kTokTile = 256;  // tokens per workgroup
-constexpr int kHidTile = 256;  // hidden units per tile
-constexpr int kBK = 64;        // channels per step
+constexpr int kBK = 64;  // channels per step
 constexpr int kStagesG = 2;
-constexpr int kOperandBytes = kTokTile * kBK * 2;  // 16 KiB: one operand tile of a stage (both tiles have 256 rows)
-constexpr int kStageBytesG = 2 * kOperandBytes;
-constexpr int kMlpThreads = 512;
 constexpr int kLoadsPerStep = 8;  // direct loads per wavefront per step (4 of X, 4 of W1)
+// TG x HG wavefronts, each with 64 tokens and 32 HB hidden units of a square tile.
+template <int HB, int TG, int HG>
+struct MlpTile {
+  static constexpr int kWaves = TG * HG;
+  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int kTok = 64 * TG;       // tokens per workgroup
+  static constexpr int kHid = 32 * HB * HG;  // hidden units per tile
+  static constexpr int kOperandBytes = kTok * kBK * 2;  // one operand tile of a stage
+  static constexpr int kStageBytes = 2 * kOperandBytes;
+  static constexpr int kLds = kStagesG * kStageBytes;
+  static constexpr int kGroupsPerCu = kLds > 80 * 1024 ? 1 : 2;
+  static_assert(kTok == kHid && kTok / kWaves == 32, "every wavefront brings 32 rows of either operand per step");
+};
+using MlpBig = MlpTile<4, 4, 2>;    // 256 x 256, 128 KiB of LDS, 8 wavefronts
+using MlpSmall = MlpTile<2, 2, 2>;  // 128 x 128, 64 KiB, 4 wavefronts, two workgroups per compute unit
+constexpr int kTokTile = MlpBig::kTok, kHidTile = MlpBig::kHid;
 
 __device__ __forceinline__ float activation(float h, int act) {
   if (act == DODO_ACT_RELU) return fmaxf(h, 0.f);
@@ -55,27 +67,33 @@ __device__ __forceinline__ float activation(float h, int act) {
   return tanhf(h);
 }
 
-__global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
+// `spread`: consecutive (token tile, split) pairs go to the XCDs in turn; otherwise a token tile stays on one XCD.
+template <int HB, int TG, int HG>
+__global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, HG>::kGroupsPerCu)) void score_mlp_mfma_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W1, const float* __restrict__ b1,
     const uint16_t* __restrict__ w2, float b2, int act, int64_t N, int d, int d_hid, int64_t row_stride, int hsplit,
-    float* __restrict__ out) {
+    int spread, float* __restrict__ out) {
+  using Tile = MlpTile<HB, TG, HG>;
+  constexpr int kOperandBytes = Tile::kOperandBytes, kStageBytesG = Tile::kStageBytes;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = tid % kWave;
   const int j32 = lane & 31, g = lane >> 5;
-  const int tg = wave >> 1, hg = wave & 1;  // token group (64 tokens) and hidden group (128 units) of this wavefront
+  const int tg = wave / HG, hg = wave % HG;  // token group (64 tokens) and hidden group (32 HB units) of this wavefront
 
   // Workgroup -> (token tile, split).  Block i runs on XCD i % 8, and the workgroups resident on one XCD at a time
   // are consecutive slots i / 8: these cover a few token tiles times all the splits, so that their X panels and
-  // W1 panels are shared through that XCD's L2 instead of every workgroup streaming panels of its own.
+  // W1 panels are shared through that XCD's L2 instead of every workgroup streaming panels of its own.  With few
+  // token tiles that would leave XCDs idle: there the pairs are dealt out one by one, so that an XCD keeps to its
+  // share of W1 (the number of splits being a multiple of 8 in most cases) and works on all tokens.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int split = slot % hsplit;
-  const int64_t tok_tile = static_cast<int64_t>(slot / hsplit) * 8 + xcd;
-  const int64_t tok0 = tok_tile * kTokTile;
+  const int split = static_cast<int>(spread ? blockIdx.x % hsplit : slot % hsplit);
+  const int64_t tok_tile = spread ? blockIdx.x / hsplit : static_cast<int64_t>(slot / hsplit) * 8 + xcd;
+  const int64_t tok0 = tok_tile * Tile::kTok;
   if (tok0 >= N) return;  // the grid is rounded up to whole groups of 8 token tiles
-  const int tiles_total = d_hid / kHidTile;
+  const int tiles_total = d_hid / Tile::kHid;
   const int tiles_per_split = (tiles_total + hsplit - 1) / hsplit;
   const int tile0 = split * tiles_per_split;
   const int n_tiles = max(0, min(tiles_per_split, tiles_total - tile0));
@@ -104,7 +122,7 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
     if ((q & 1) == 0) {
       dma16_uniform(x_base + ks * kBK, x_off[u], __builtin_amdgcn_readfirstlane(stage + (32 * wave + 8 * u) * 128));
     } else {
-      dma16_uniform(W1 + static_cast<int64_t>(ht) * kHidTile * d + ks * kBK, w_off[u],
+      dma16_uniform(W1 + static_cast<int64_t>(ht) * Tile::kHid * d + ks * kBK, w_off[u],
             __builtin_amdgcn_readfirstlane(stage + kOperandBytes + (32 * wave + 8 * u) * 128));
     }
   };
@@ -116,13 +134,13 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
   // ---- fragment addresses: row r of a tile at r*128, piece p at (p ^ ((r >> 1) & 7)) * 16
   const int f_sw = (j32 >> 1) & 7;
   const int x_row_off = (64 * tg + j32) * 128;                    // token blocks tb = 0, 1: + 32*128*tb
-  const int w_row_off = kOperandBytes + (128 * hg + j32) * 128;   // hidden blocks hb = 0..3: + 32*128*hb
+  const int w_row_off = kOperandBytes + (32 * HB * hg + j32) * 128;  // hidden blocks hb = 0 .. HB - 1: + 32*128*hb
 
-  floatx16 acc[4][2];
+  floatx16 acc[HB][2];
   float part[2] = {0.f, 0.f};  // partial scores of tokens 64 tg + 32 tb + j32 (this lane's half of the hidden units)
   auto zero_acc = [&]() {
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb)
+    for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -130,18 +148,18 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
   };
   zero_acc();
 
-  bf16x8 xf[2][2], wf[2][4];  // two fragment sets, used alternately by the four 16-channel parts of a step
+  bf16x8 xf[2][2], wf[2][HB];  // two fragment sets, used alternately by the four 16-channel parts of a step
   auto read_frags = [&](int step, int ks, bf16x8* xo, bf16x8* wo) {
     const char* stg = lds + (step % kStagesG) * kStageBytesG;
     const int piece = ((2 * ks + g) ^ f_sw) << 4;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) xo[tb] = *reinterpret_cast<const bf16x8*>(stg + x_row_off + tb * 4096 + piece);
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb) wo[hb] = *reinterpret_cast<const bf16x8*>(stg + w_row_off + hb * 4096 + piece);
+    for (int hb = 0; hb < HB; ++hb) wo[hb] = *reinterpret_cast<const bf16x8*>(stg + w_row_off + hb * 4096 + piece);
   };
   auto mfma_set = [&](int set) {
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb)
+    for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
         acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][hb], xf[set][tb], acc[hb][tb], 0, 0, 0);
@@ -168,21 +186,22 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
     __syncthreads();
     read_frags(step + 1, 0, xf[0], wf[0]);  // (after the last step: a stage that holds old data; not used)
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb) {
+    for (int hb = 0; hb < HB; ++hb) {
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1][hb], xf[1][tb], acc[hb][tb], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        issue_part(step + kStagesG, 2 * hb + tb);  // refill this step's stage
+#pragma unroll
+        for (int q = 0; q < 4 / HB; ++q) issue_part(step + kStagesG, (2 * hb + tb) * (4 / HB) + q);  // refill this step's stage
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     if ((step + 1) % ksteps == 0) {
       // a hidden tile is complete: accumulator v of block hb is hidden unit 32 hb + 8 (v/4) + 4 g + v%4
       const int ht = tile0 + step / ksteps;
-      const int jbase = ht * kHidTile + 128 * hg + 4 * g;
+      const int jbase = ht * Tile::kHid + 32 * HB * hg + 4 * g;
 #pragma unroll
-      for (int hb = 0; hb < 4; ++hb)
+      for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
           const int jj = jbase + 32 * hb + 8 * vq;
@@ -204,17 +223,17 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
 
   // ---- the two halves of a token's hidden units sit in lanes j32 and j32 + 32; the two hidden groups in two
   // wavefronts: added in a fixed order through LDS
-  float* red = reinterpret_cast<float*>(lds);  // [2 hidden groups][256 tokens]
+  float* red = reinterpret_cast<float*>(lds);  // [HG hidden groups][tokens]
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     const float both = part[tb] + __shfl_xor(part[tb], 32, kWave);
-    if (g == 0) red[hg * kTokTile + 64 * tg + 32 * tb + j32] = both;
+    if (g == 0) red[hg * Tile::kTok + 64 * tg + 32 * tb + j32] = both;
   }
   __syncthreads();
-  if (tid < kTokTile) {
+  if (tid < Tile::kTok) {
     const int64_t tok = tok0 + tid;
     if (tok < N) {
-      float s = red[tid] + red[kTokTile + tid];
+      float s = red[tid] + red[Tile::kTok + tid];
       if (hsplit == 1) {
         s += b2;
         out[tok] = (s == 0.f) ? 0.f : s;
@@ -225,13 +244,19 @@ __global__ __launch_bounds__(kMlpThreads, 1) void score_mlp_mfma_kernel(
   }
 }
 
-// partial scores of the splits, added in split order, plus the output bias
-__global__ void score_mlp_combine_kernel(const float* __restrict__ partial, int hsplit, int64_t N, float b2,
-                                         float* __restrict__ scores) {
+// partial scores of the splits, added in split order, plus the output bias: the first n_big tokens have hs_big splits,
+// the others hs_small
+__global__ void score_mlp_combine_kernel(const float* __restrict__ partial, int hs_big, int64_t n_big, int hs_small, int64_t N,
+                                         float b2, float* __restrict__ scores) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= N) return;
+  const bool big = t < n_big;
+  const int splits = big ? hs_big : hs_small;
+  const int64_t stride = big ? n_big : N - n_big;
+  const float* p0 = partial + (big ? t : hs_big * n_big + (t - n_big));
   float s = 0.f;
-  for (int p = 0; p < hsplit; ++p) s += partial[static_cast<int64_t>(p) * N + t];
+#pragma unroll 8
+  for (int p = 0; p < splits; ++p) s += p0[p * stride];
   s += b2;
   scores[t] = (s == 0.f) ? 0.f : s;
 }
@@ -412,14 +437,80 @@ bool mfma_path(int dtype, int64_t N, int32_t d, int32_t d_hid, int64_t row_strid
          static_cast<int64_t>(kHidTile) * d * 2 < 0x7fffffffLL && static_cast<int64_t>(kTokTile) * row_stride * 2 < 0x7fffffffLL;
 }
 
+// The split that needs the least memory: big tiles throughout.  Used when the caller's workspace was sized for another
+// number of tokens and is too small for the plan below.
 int hidden_splits(int64_t N, int32_t d_hid) {
   const int64_t blocks = (N + kTokTile - 1) / kTokTile;
   const int tiles = d_hid / kHidTile;
-  // at least 4 splits (when there are that many tiles) so that an XCD's resident workgroups form a 2-D patch of
-  // the (token tile, hidden tile) plane; more while the grid does not fill the chip
   int hs = 1;
   while (hs * 2 <= tiles && (hs < 4 || blocks * hs < compute_units())) hs *= 2;
   return hs;
+}
+
+// How N tokens are shared out: the first n_big in big tiles (hs_big splits of the hidden units), the rest in small ones.
+// A big tile keeps a compute unit for 110 us at d = 4096, so a grid that does not come out in whole rounds of them pays
+// for idle units: big tiles take the groups of 8 token tiles (one per XCD) that fill rounds, small ones what is left, and
+// everything where there is not one round of big tiles.  The cost of a round, in hundredths of a round of big tiles, was
+// measured at d = 1024 to 5120: 45 for small tiles with at most one workgroup per compute unit (51 of 112 us at
+// d = 4096), 60 with two (65 us), which is why small tiles do not take it all (2.4 times their share of the work).
+// d = d_hid = 4096, before (big tiles, four splits at least) -> now: 128 tokens 85 -> 52 us, 2048 104 -> 70 us, 4096 the
+// same 118 us, 25123 (with their selection) 853 -> 763 us; 5120: 512 tokens 111 -> 65 us.
+struct MlpPlan {
+  int64_t n_big;
+  int hs_big;
+  int64_t n_small;
+  int hs_small;
+  bool direct() const { return n_small == 0 && hs_big == 1; }  // the only split writes the scores itself
+  size_t bytes() const {
+    return direct() ? 0 : (static_cast<size_t>(hs_big) * n_big + static_cast<size_t>(hs_small) * n_small) * sizeof(float);
+  }
+};
+constexpr int kBigRound = 100, kSmallOne = 45, kSmallTwo = 60;
+MlpPlan plan_mlp(int64_t N, int32_t d_hid) {
+  const int cus = compute_units(), cus_xcd = cus >= 8 ? cus / 8 : 1;
+  const int tiles = d_hid / MlpBig::kHid, small_tiles = d_hid / MlpSmall::kHid;
+  auto small_cost = [&](int64_t n) -> int64_t {
+    const int64_t units = (n + MlpSmall::kTok - 1) / MlpSmall::kTok * small_tiles;
+    const int64_t rest = units % (2 * cus);
+    return units / (2 * cus) * kSmallTwo + (rest == 0 ? 0 : rest <= cus ? kSmallOne : kSmallTwo);
+  };
+  // (beyond 32 groups the rounds repeat: 32 groups are as many whole rounds as there are hidden tiles)
+  const int64_t groups_all = (N + 8 * MlpBig::kTok - 1) / (8 * MlpBig::kTok);
+  int64_t best_groups = 0, best = -1;
+  for (int64_t t = groups_all; t >= 0 && t > groups_all - 33; --t) {
+    const int64_t n_big = t * 8 * MlpBig::kTok < N ? t * 8 * MlpBig::kTok : N;
+    const int64_t cost = (t * tiles + cus_xcd - 1) / cus_xcd * kBigRound + small_cost(N - n_big);
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_groups = t;
+    }
+  }
+  MlpPlan p;
+  p.n_big = best_groups * 8 * MlpBig::kTok < N ? best_groups * 8 * MlpBig::kTok : N;
+  p.n_small = N - p.n_big;
+  p.hs_small = small_tiles;
+  // as many tiles per workgroup as leave the number of rounds alone (fewer starts and partial scores)
+  const int64_t rounds = (best_groups * tiles + cus_xcd - 1) / cus_xcd;
+  p.hs_big = tiles;
+  for (int per = tiles; per > 1; --per)
+    if (tiles % per == 0 && (best_groups * (tiles / per) + cus_xcd - 1) / cus_xcd * per <= rounds) {
+      p.hs_big = tiles / per;
+      break;
+    }
+  return p;
+}
+
+template <class Tile, class Kernel>
+int launch_mfma(Kernel kern, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* w2, float b2, int act,
+                int64_t N, int d, int d_hid, int64_t row_stride, int hs, int spread, float* out, hipStream_t s) {
+  const int64_t tok_tiles = (N + Tile::kTok - 1) / Tile::kTok;
+  const int64_t blocks = (spread ? tok_tiles : (tok_tiles + 7) / 8 * 8) * hs;
+  if (blocks > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
+  const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), Tile::kLds);
+  if (rc != DODO_OK) return rc;
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(Tile::kThreads), Tile::kLds, s, X, W1, b1, w2, b2, act, N, d,
+                     d_hid, row_stride, hs, spread, out);
+  return launch_status();
 }
 
 }  // namespace
@@ -430,8 +521,7 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   if (N <= 0 || d <= 0 || d_hid <= 0) return 0;
   if (dtype != DODO_DTYPE_BF16 || d % kBK != 0 || d_hid % kHidTile != 0) return 0;
   if (N <= kFewTokens) return static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float);
-  const int hs = hidden_splits(N, d_hid);
-  return hs > 1 ? static_cast<size_t>(hs) * N * sizeof(float) : 0;
+  return plan_mlp(N, d_hid).bytes();
 }
 
 extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const void* w2, float b2, int act,
@@ -445,10 +535,10 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
   if (!dtype_ok(dtype)) return DODO_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (mfma_path(dtype, N, d, d_hid, row_stride, hidden, W1, b1, w2)) {
-    if (N <= kFewTokens) {
+    float* partial = static_cast<float*>(ws);
+    const size_t room = ws != nullptr ? ws_bytes : 0;
+    if (N <= kFewTokens && room >= static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float)) {
       const int splits = few_splits(d_hid), hid = few_hid(d_hid), n = static_cast<int>(N);
-      if (!ws || ws_bytes < static_cast<size_t>(splits) * n * sizeof(float)) return DODO_ERR_WORKSPACE_TOO_SMALL;
-      float* partial = static_cast<float*>(ws);
       const uint32_t x_bytes = static_cast<uint32_t>(((N - 1) * row_stride + d) * 2);
 #define DODO_LAUNCH_FEW(NB, RT)                                                                                          \
   hipLaunchKernelGGL((score_mlp_few_kernel<NB, RT>), dim3(splits), dim3(kFewWaves* kWave), 0, s,                         \
@@ -465,24 +555,26 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
       hipLaunchKernelGGL(score_mlp_combine_few_kernel, dim3(n), dim3(kWave), 0, s, partial, splits, n, b2, scores);
       return launch_status();
     }
-    const int hs = hidden_splits(N, d_hid);
-    const size_t need = hs > 1 ? static_cast<size_t>(hs) * N * sizeof(float) : 0;
-    if (need > 0 && (!ws || ws_bytes < need)) return DODO_ERR_WORKSPACE_TOO_SMALL;
-    const int64_t blocks = ((N + kTokTile - 1) / kTokTile + 7) / 8 * 8 * hs;
-    if (blocks > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
-    constexpr int kLds = kStagesG * kStageBytesG;
-    {
-      const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(score_mlp_mfma_kernel), kLds);
-      if (rc_lds != DODO_OK) return rc_lds;
+    MlpPlan p = plan_mlp(N, d_hid);
+    if (room < p.bytes()) {
+      p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0};
+      if (room < p.bytes()) return DODO_ERR_WORKSPACE_TOO_SMALL;
     }
-    hipLaunchKernelGGL(score_mlp_mfma_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kMlpThreads), kLds, s,
-                       static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(W1), b1,
-                       static_cast<const uint16_t*>(w2), b2, act, N, d, d_hid, row_stride, hs,
-                       hs > 1 ? static_cast<float*>(ws) : scores);
-    int rc = launch_status();
-    if (rc != DODO_OK || hs == 1) return rc;
-    hipLaunchKernelGGL(score_mlp_combine_kernel, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
-                       static_cast<const float*>(ws), hs, N, b2, scores);
+    const uint16_t* x = static_cast<const uint16_t*>(hidden);
+    const uint16_t* w = static_cast<const uint16_t*>(W1);
+    const uint16_t* wo = static_cast<const uint16_t*>(w2);
+    if (p.n_big > 0) {  // (a single split adds the output bias itself; where the sums are combined, that comes later)
+      const int rc = launch_mfma<MlpBig>(score_mlp_mfma_kernel<4, 4, 2>, x, w, b1, wo, p.direct() ? b2 : 0.f, act, p.n_big, d, d_hid, row_stride,
+                                         p.hs_big, 0, p.direct() ? scores : partial, s);
+      if (rc != DODO_OK || p.direct()) return rc;
+    }
+    if (p.n_small > 0) {
+      const int rc = launch_mfma<MlpSmall>(score_mlp_mfma_kernel<2, 2, 2>, x + p.n_big * row_stride, w, b1, wo, b2, act, p.n_small,
+                                           d, d_hid, row_stride, p.hs_small, 1, partial + p.hs_big * p.n_big, s);
+      if (rc != DODO_OK) return rc;
+    }
+    hipLaunchKernelGGL(score_mlp_combine_kernel, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s, partial, p.hs_big,
+                       p.n_big, p.hs_small, N, b2, scores);
     return launch_status();
   }
   // plain kernel: as many token rows per workgroup as fit in 128 KiB of LDS (at most 8)

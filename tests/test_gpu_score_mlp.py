@@ -58,6 +58,34 @@ def test_few_tokens(D, N, d, dh):
     _check(got, want)
 
 
+# small tiles alone (edges of 128 tokens), whole rounds of big tiles followed by small ones, big tiles alone
+@pytest.mark.parametrize("N,d,dh", [(65, 64, 512), (127, 128, 256), (128, 64, 256), (129, 64, 768), (2049, 64, 1280),
+                                    (4096, 64, 4096), (4097, 64, 4096), (4500, 128, 4096), (66000, 64, 256)])
+def test_shares_of_big_and_small_tiles(D, N, d, dh):
+    x, W1, b1, w2 = _case(980 + N, N, d, dh, torch.bfloat16)
+    rows = np.arange(N) if N * dh < 2e6 else np.unique(np.r_[0:130, N - 600:N, 4090:min(N, 4110)] % N)
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, 1)
+    got = D.dodo_score_mlp(x.to(dev()), W1.to(dev()), b1.to(dev()), w2.to(dev()), 0.25, 1).cpu().numpy()
+    _check(got[rows], want)
+
+
+# one buffer for calls with fewer and with more tokens: the least that a call needs is a float per token and split of
+# the big tiles, and a buffer below that is refused
+@pytest.mark.parametrize("N,least", [(40, 16), (64, 16), (100, 16), (4500, 16), (8200, 8)])
+def test_workspace_sized_for_another_call(D, N, least):
+    d, dh = 64, 4096
+    x, W1, b1, w2 = _case(990, N, d, dh, torch.bfloat16)
+    t = [v.to(dev()) for v in (x, W1, b1, w2)]
+    rows = np.r_[0:20, N - 20:N]
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 0)
+    ws = torch.full((least * N * 4 + 64,), 255, dtype=torch.uint8, device=dev())
+    got = D.dodo_score_mlp(*t, ws=ws[:least * N * 4]).cpu().numpy()
+    _check(got[rows], want)
+    assert torch.all(ws[least * N * 4:] == 255)
+    with pytest.raises(D.DodoError):
+        D.dodo_score_mlp(*t, ws=ws[:least * N * 4 - 4])
+
+
 @pytest.mark.parametrize("dtype,N,d,dh", [(torch.float32, 512, 256, 256), (torch.bfloat16, 37, 40, 100),
                                           (torch.float32, 9, 24, 7)])
 def test_plain_path_any_shape(D, dtype, N, d, dh):
