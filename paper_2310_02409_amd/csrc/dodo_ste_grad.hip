@@ -10,15 +10,22 @@
 // local keys as well, so only nugget columns are touched here).
 //
 // Two contractions (Q K^T and dO V^T) restricted to the nugget columns:
-// 4 k q d_h flop per (sequence, head).  bf16 with d_h = 128 runs on the matrix
-// cores: each of a workgroup's 4 wavefronts owns 64 nuggets of one (sequence,
-// head), whose K and V fragments stay in its registers; the workgroup walks over
-// the sequence's query rows in tiles of 32 (Q and dO rows stream into a 3-stage
-// LDS ring by 16-byte direct loads, two tiles ahead, shared by the 4 wavefronts),
-// and a wavefront computes S and dP with v_mfma_f32_32x32x16_bf16 so that a nugget
-// is a lane and a query row an accumulator register, and adds P (dP - D) into a
-// per-lane sum.  No atomics: per-head sums go to the workspace and a last kernel
-// adds them in head order.  Other types and head sizes take a plain kernel.
+// 4 k q d_h flop per (sequence, head).  bf16 with d_h = 128 or 64 runs on the
+// matrix cores: each of a workgroup's 4 wavefronts owns 64 nuggets of one
+// (sequence, head), whose K and V fragments stay in its registers; the workgroup
+// walks over the sequence's query rows in tiles of 32 (Q, dO and O rows stream into
+// a 3-stage LDS ring by 16-byte direct loads, two tiles ahead, shared by the 4
+// wavefronts), and a wavefront computes S and dP with v_mfma_f32_32x32x16_bf16 so
+// that a nugget is a lane and a query row an accumulator register, and adds
+// P (dP - D) into a per-lane sum.  D of the next tile's rows comes from its dO and O
+// tiles, 8 rows per wavefront, while the matrix cores run.  No atomics: per-head sums go to
+// the workspace and a last kernel adds them in head order.  Other types and head
+// sizes take a plain kernel, with D from a kernel of its own.
+// Bound by the vector pipe (an exp2 per element of S) as much as by the matrix
+// pipe.  8 x 410 nuggets, 512 rows, 32 heads of 128: 48 us and no launch before
+// it (was 41.5 us after a 14 us kernel that made D and lse: forward and gradient
+// 135 -> 126 us); heads of 64 in the plain kernel: 2249 -> 33 us (4 x 250 nuggets,
+// 300 rows, 16 heads).  Error against 64 bits (2-norm): 2.6e-7 (was 3.8e-7).
 #include "dodo_common.h"
 
 namespace dodo {
@@ -28,17 +35,24 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int kDH = 128;
-constexpr int kRowBytes = kDH * 2;
 constexpr int kGradWaves = 4;
 constexpr int kGradThreads = kGradWaves * kWave;
 constexpr int kWaveNug = 64;                       // nuggets per wavefront
 constexpr int kNugTile = kGradWaves * kWaveNug;    // nuggets per workgroup
 constexpr int kQTile = 32;                         // query rows per step
 constexpr int kStagesSte = 3;
-constexpr int kStageBytesSte = 2 * kQTile * kRowBytes;  // Q tile, dO tile
-constexpr int kLoadsPerTileSte = 4;                // direct loads per wavefront per tile
-constexpr int kMaxQLds = 12288;                    // query rows of a sequence whose lse and D fit in LDS next to the stages
+constexpr int kLseChunk = 1024;                    // query rows whose lse sits in LDS at a time
+template <int DH>
+struct SteDims {
+  static constexpr int kRowBytes = DH * 2;
+  static constexpr int kPieces = kRowBytes / 16;            // 16-byte pieces of a row
+  static constexpr int kRowsPerInstr = 64 / kPieces;        // rows that one direct load instruction brings
+  static constexpr int kRowShift = DH == 128 ? 0 : 1;       // rows of 128 bytes cover half of the banks: swizzle by pairs
+  static constexpr int kTileBytes = kQTile * kRowBytes;
+  static constexpr int kStageBytes = 3 * kTileBytes;        // Q tile, dO tile, O tile
+  static constexpr int kInstr = 8 / kRowsPerInstr;          // instructions per wavefront, tile and tensor
+  static constexpr int kLds = kStagesSte * kStageBytes + (kLseChunk + 2 * kQTile) * 4;
+};
 constexpr float kLog2e = 1.4426950408889634f;
 
 // D[h][row] = dO[row,h] . O[row,h] and lse2[h][row] = lse[row,h] * log2(e), head-major so that the rows of a head are
@@ -46,12 +60,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 template <int DTYPE>
 __global__ __launch_bounds__(256) void ste_rowdot_kernel(const void* __restrict__ dO, const void* __restrict__ O,
                                                          const float* __restrict__ lse, int64_t Sq, int H, int d_h,
-                                                         float* __restrict__ aux_lse2, float* __restrict__ aux_D,
-                                                         float* __restrict__ partial, int64_t n_partial) {
-  // per-head sums that no workgroup writes later must read as zero: cleared here, by the first threads
-  const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int64_t i = gid; i < n_partial; i += static_cast<int64_t>(gridDim.x) * blockDim.x) partial[i] = 0.f;
-  const int64_t t = gid / 16;
+                                                         float* __restrict__ aux_lse2, float* __restrict__ aux_D) {
+  const int64_t t = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / 16;
   const int sub = threadIdx.x % 16;
   const bool live = t < Sq * H;
   float acc = 0.f;
@@ -88,15 +98,17 @@ __global__ __launch_bounds__(256) void ste_rowdot_kernel(const void* __restrict_
   }
 }
 
+template <int DH>
 __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
-    const uint16_t* __restrict__ dO, const float* __restrict__ aux_lse2, const float* __restrict__ aux_D,
+    const uint16_t* __restrict__ dO, const uint16_t* __restrict__ O, const float* __restrict__ lse,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_nuggets, int B, int H, int H_kv, int n_nug_tiles,
-    int max_q_pad, int64_t Sq, int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e,
-    float* __restrict__ partial) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // kStages stages of (Q tile | dO tile), then lse2, D
+    int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, float* __restrict__ partial) {
+  using SD = SteDims<DH>;
+  constexpr int kRowBytes = SD::kRowBytes, kP = SD::kPieces, kRowShift = SD::kRowShift, kTileBytes = SD::kTileBytes;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, -D of two tiles
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
-  // block i runs on XCD i % 8: the nugget tiles of one (sequence, head) sit on one XCD and share Q / dO in its L2
+  // block i runs on XCD i % 8: the nugget tiles of one (sequence, head) sit on one XCD and share Q / dO / O in its L2
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int bh = (slot / n_nug_tiles) * 8 + xcd;
   const int tile = slot % n_nug_tiles;
@@ -112,103 +124,149 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   const int lane = tid % kWave;
   const int n = lane & 31, g = lane >> 5;
   const int nug0 = tile * kNugTile + wave * kWaveNug;  // this wavefront's 64 nuggets
-  const bool active = nug0 < k_b;                      // (the others only help to load)
+  const bool active = nug0 < k_b;                      // (the others only help to load and with D)
 
-  // lse (base 2) and D of all query rows of this (sequence, head); rows past the end get +inf, which makes their
-  // weights 0
-  float* lse2_l = reinterpret_cast<float*>(lds + kStagesSte * kStageBytesSte);
-  float* dd_l = lse2_l + max_q_pad;
-  for (int r = tid; r < max_q_pad; r += kGradThreads) {
-    const bool ok = r < q_b;
-    lse2_l[r] = ok ? aux_lse2[static_cast<int64_t>(h) * Sq + q0 + r] : __builtin_inff();
-    dd_l[r] = ok ? aux_D[static_cast<int64_t>(h) * Sq + q0 + r] : 0.f;
+  // loader: a stage is 32 query rows of Q, dO and O; wavefront w brings rows 8w .. 8w+7 of each, whole rows; the 16-byte
+  // piece at position pos of LDS row r is piece pos ^ ((r >> kRowShift) & (kP - 1)) of the row, which keeps the fragment
+  // reads below conflict-free
+  const int l_row = lane / kP, l_pos = lane % kP;
+  const int64_t row_stride = static_cast<int64_t>(H) * DH;  // elements between query rows
+  const int64_t row0 = (static_cast<int64_t>(q0) * H + h) * DH;
+  const int n_qtiles = (q_b + kQTile - 1) / kQTile;
+  constexpr int kLoads = 3 * SD::kInstr;  // direct loads per wavefront per tile
+  auto issue_tile = [&](int t) {
+    const int tl = min(t, n_qtiles - 1);  // past the end: re-read the last tile into a stage nobody reads any more
+    const uint32_t stage = lds_base + (t % kStagesSte) * SD::kStageBytes;
+#pragma unroll
+    for (int u = 0; u < SD::kInstr; ++u) {
+      const int r8 = 8 * wave + SD::kRowsPerInstr * u;
+      const int row = r8 + l_row;
+      const uint32_t voff = static_cast<uint32_t>(min(tl * kQTile + row, q_b - 1)) * static_cast<uint32_t>(row_stride * 2) +
+                            ((l_pos ^ ((row >> kRowShift) & (kP - 1))) << 4);
+      const uint32_t dst = stage + r8 * kRowBytes;
+      dma16_uniform(Q + row0, voff, __builtin_amdgcn_readfirstlane(dst));
+      dma16_uniform(dO + row0, voff, __builtin_amdgcn_readfirstlane(dst + kTileBytes));
+      dma16_uniform(O + row0, voff, __builtin_amdgcn_readfirstlane(dst + 2 * kTileBytes));
+    }
+  };
+  if (n_qtiles > 0) {
+    issue_tile(0);
+    issue_tile(1);
   }
+
+  // lse (base 2) of a chunk of this (sequence, head)'s query rows; rows past the end get +inf, which makes their weights 0
+  float* lse2_l = reinterpret_cast<float*>(lds + kStagesSte * SD::kStageBytes);
+  float* dd_l = lse2_l + kLseChunk;
+  auto load_lse = [&](int r0) {
+    for (int r = tid; r < min(kLseChunk, n_qtiles * kQTile - r0); r += kGradThreads)
+      lse2_l[r] = r0 + r < q_b ? lse[static_cast<int64_t>(q0 + r0 + r) * H + h] * kLog2e : __builtin_inff();
+  };
+  load_lse(0);
 
   // K and V fragments of the two 32-nugget blocks (B operands: lane (n, g) holds channels 16 ks + 8 g .. + 8 of
   // nugget row n); rows past the sequence's last nugget re-read it, their sums are not stored
-  bf16x8 kf[2][kDH / 16], vf[2][kDH / 16];
+  bf16x8 kf[2][DH / 16], vf[2][DH / 16];
 #pragma unroll
   for (int blk = 0; blk < 2; ++blk) {
     const int r = min(nug0 + 32 * blk + n, k_b - 1);
     const int64_t off = static_cast<int64_t>(k0 + r) * nug_tok_stride + static_cast<int64_t>(kvh) * nug_head_stride + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < kDH / 16; ++ks) {
+    for (int ks = 0; ks < DH / 16; ++ks) {
       kf[blk][ks] = *reinterpret_cast<const bf16x8*>(Kn + off + 16 * ks);
       vf[blk][ks] = *reinterpret_cast<const bf16x8*>(Vn + off + 16 * ks);
     }
   }
-  // (the loads above are complete before the first direct load below is counted: the fragments are read there)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-  // loader: a stage is 32 query rows of Q and of dO; wavefront w brings rows 8w .. 8w+7 of both, 4 rows (16 lanes
-  // per 256-byte row) per instruction; the 16-byte piece at position pos of LDS row r is piece pos ^ (r & 15) of
-  // the row, which keeps the fragment reads below conflict-free
-  const int l_row = lane >> 4, l_pos = lane & 15;
-  const int64_t row_stride = static_cast<int64_t>(H) * kDH;  // elements between query rows
-  const uint16_t* q_base = Q + (static_cast<int64_t>(q0) * H + h) * kDH;
-  const uint16_t* do_base = dO + (static_cast<int64_t>(q0) * H + h) * kDH;
-  const int n_qtiles = (q_b + kQTile - 1) / kQTile;
-  auto issue_tile = [&](int t) {
-    const int tl = min(t, n_qtiles - 1);  // past the end: re-read the last tile into a stage nobody reads any more
-    const uint32_t stage = lds_base + (t % kStagesSte) * kStageBytesSte;
+  // The fragments are used here for the compiler's eyes: its waits for them then stand here.  (It does not take notice of
+  // a wait written in assembly: with only that, it waited for them inside the loop, down to vmcnt(0) at the last matrix
+  // instruction of every tile, that is for the tile that had just been requested.)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = 8 * wave + 4 * u + l_row;
-      const uint32_t voff = static_cast<uint32_t>(min(tl * kQTile + row, q_b - 1)) * static_cast<uint32_t>(row_stride * 2) +
-                            ((l_pos ^ (row & 15)) << 4);
-      const uint32_t dst = stage + (8 * wave + 4 * u) * kRowBytes;
-      dma16_uniform(q_base, voff, __builtin_amdgcn_readfirstlane(dst));
-      dma16_uniform(do_base, voff, __builtin_amdgcn_readfirstlane(dst + kQTile * kRowBytes));
+  for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+    for (int ks = 0; ks < DH / 16; ++ks) asm volatile("" : "+v"(kf[blk][ks]), "+v"(vf[blk][ks]));
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): tiles 0 and 1 too
+
+  // -D of tile t's rows, 8 lanes per row with DH / 8 channels each.  A wavefront takes the rows that it loaded itself, so
+  // only its own loads have to have landed; the next tile's barrier hands the sums to the others.
+  const int d_row = 8 * wave + (lane >> 3), d_sub = lane & 7;
+  auto row_dots = [&](int t) {
+    const char* rows = lds + (t % kStagesSte) * SD::kStageBytes + kTileBytes + d_row * kRowBytes;
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < kP / 8; ++i) {
+      const int off = ((kP / 8 * d_sub + i) ^ ((d_row >> kRowShift) & (kP - 1))) << 4;
+      const uint4 av = *reinterpret_cast<const uint4*>(rows + off);
+      const uint4 ov = *reinterpret_cast<const uint4*>(rows + kTileBytes + off);
+      const uint32_t aw[4] = {av.x, av.y, av.z, av.w}, ow[4] = {ov.x, ov.y, ov.z, ov.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc = fmaf(bf16_lo(aw[e]), bf16_lo(ow[e]), acc);
+        acc = fmaf(bf16_hi(aw[e]), bf16_hi(ow[e]), acc);
+      }
     }
+    acc = lanes_sum<8>(acc);
+    if (d_sub == 0) dd_l[(t & 1) * kQTile + d_row] = -acc;
   };
+  if (n_qtiles > 0) row_dots(0);
 
   float ds[2] = {0.f, 0.f};
-  if (n_qtiles > 0) {
-    issue_tile(0);
-    issue_tile(1);
-  }
   for (int t = 0; t < n_qtiles; ++t) {
-    __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerTileSte);  // this wavefront's part of tile t has landed, t+1 may be in flight
-    __syncthreads();  // everyone's part has landed (first pass: lse2 / D too); tile t-1 has been read by everyone
+    __syncthreads();  // everyone's part of tile t has landed, its D is there; tile t-1 has been read by everyone
+    const int c0 = t * kQTile % kLseChunk;
+    if (c0 == 0 && t > 0) {
+      load_lse(t * kQTile);
+      __syncthreads();
+    }
     issue_tile(t + 2);
-    if (!active) continue;
-    const char* stg = lds + (t % kStagesSte) * kStageBytesSte;
+    const char* stg = lds + (t % kStagesSte) * SD::kStageBytes;
     floatx16 acc_s[2], acc_p[2];
+    if (active) {
+      // S starts from 0, dP from -D
+      floatx16 neg_d;
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        acc_s[blk][v] = 0.f;
-        acc_p[blk][v] = 0.f;
+      for (int vq = 0; vq < 4; ++vq) {
+        const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
+        neg_d[4 * vq] = dd.x; neg_d[4 * vq + 1] = dd.y; neg_d[4 * vq + 2] = dd.z; neg_d[4 * vq + 3] = dd.w;
       }
-    const char* qrow = stg + n * kRowBytes;
-    const char* drow = stg + kQTile * kRowBytes + n * kRowBytes;
-#pragma unroll
-    for (int ks = 0; ks < kDH / 16; ++ks) {
-      const int piece = ((2 * ks + g) ^ (n & 15)) << 4;
-      const bf16x8 qa = *reinterpret_cast<const bf16x8*>(qrow + piece);
-      const bf16x8 da = *reinterpret_cast<const bf16x8*>(drow + piece);
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
-        acc_s[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[blk][ks], acc_s[blk], 0, 0, 0);
-        acc_p[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, vf[blk][ks], acc_p[blk], 0, 0, 0);
+        acc_p[blk] = neg_d;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc_s[blk][v] = 0.f;
+      }
+      const char* qrow = stg + n * kRowBytes;
+      const char* drow = stg + kTileBytes + n * kRowBytes;
+#pragma unroll
+      for (int ks = 0; ks < DH / 16; ++ks) {
+        const int piece = ((2 * ks + g) ^ ((n >> kRowShift) & (kP - 1))) << 4;
+        const bf16x8 qa = *reinterpret_cast<const bf16x8*>(qrow + piece);
+        const bf16x8 da = *reinterpret_cast<const bf16x8*>(drow + piece);
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+          acc_s[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[blk][ks], acc_s[blk], 0, 0, 0);
+          acc_p[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, vf[blk][ks], acc_p[blk], 0, 0, 0);
+        }
       }
     }
-    // accumulator v of a block is query row 8 (v / 4) + 4 g + v % 4 of the tile, for this lane's nugget
+    __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t+1 has landed, t+2 may be in flight
+    row_dots(t + 1);  // (past the end: of the last tile again, not used)
+    if (!active) continue;
+    // accumulator v of a block is query row 8 (v / 4) + 4 g + v % 4 of the tile, for this lane's nugget; a tile's rows are
+    // summed before they join the others (shorter chains of rounded additions)
+    float part[2] = {0.f, 0.f};
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) {
-      const float4 l2 = *reinterpret_cast<const float4*>(lse2_l + t * kQTile + 8 * vq + 4 * g);
-      const float4 dd = *reinterpret_cast<const float4*>(dd_l + t * kQTile + 8 * vq + 4 * g);
+      const float4 l2 = *reinterpret_cast<const float4*>(lse2_l + c0 + 8 * vq + 4 * g);
       const float l2v[4] = {l2.x, l2.y, l2.z, l2.w};
-      const float ddv[4] = {dd.x, dd.y, dd.z, dd.w};
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float p = __builtin_amdgcn_exp2f(acc_s[blk][4 * vq + e] * scale_log2e - l2v[e]);
-          ds[blk] = fmaf(p, acc_p[blk][4 * vq + e] - ddv[e], ds[blk]);
+          part[blk] = fmaf(p, acc_p[blk][4 * vq + e], part[blk]);
         }
     }
+    ds[0] += part[0];
+    ds[1] += part[1];
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // drain the look-ahead loads before the wavefront ends
 
@@ -329,36 +387,39 @@ extern "C" int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn
     head_stride = Kt * d_h;
   }
   const float scale_log2e = softmax_scale * kLog2e;
-  const unsigned rd_blocks = static_cast<unsigned>((Sq * H * 16 + 255) / 256);
-  if (dtype == DODO_DTYPE_BF16) {
-    hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_BF16>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
-                       aux_lse2, aux_D, partial, static_cast<int64_t>(H) * Kt);
-  } else {
-    hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_F32>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
-                       aux_lse2, aux_D, partial, static_cast<int64_t>(H) * Kt);
-  }
-  int rc = launch_status();
-  if (rc != DODO_OK) return rc;
-  const bool mfma = dtype == DODO_DTYPE_BF16 && d_h == kDH && max_q <= kMaxQLds &&
-                    static_cast<int64_t>(max_q) * H * kDH * 2 < 0x7fffffffLL;  // row offsets of a sequence in 32 bits
+  const bool mfma = dtype == DODO_DTYPE_BF16 && (d_h == 128 || d_h == 64) &&
+                    static_cast<int64_t>(max_q) * H * d_h * 2 < 0x7fffffffLL;  // row offsets of a sequence in 32 bits
+  int rc;
   if (mfma) {
     const int n_nug_tiles = (max_k + kNugTile - 1) / kNugTile;
     const int64_t bh8 = (static_cast<int64_t>(B) * H + 7) / 8 * 8;
     const int64_t grid = bh8 * n_nug_tiles;
     if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
-    const int max_q_pad = (max_q + kQTile - 1) / kQTile * kQTile;
-    const int kLds = kStagesSte * kStageBytesSte + 2 * max_q_pad * static_cast<int>(sizeof(float));
-    {
-      const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(ste_grad_mfma_kernel), kLds);
+    const auto launch = [&](auto kern, int lds_bytes) {
+      const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes);
       if (rc_lds != DODO_OK) return rc_lds;
-    }
-    hipLaunchKernelGGL(ste_grad_mfma_kernel, dim3(static_cast<unsigned>(grid)), dim3(kGradThreads), kLds, s,
-                       static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(Kn),
-                       static_cast<const uint16_t*>(Vn), static_cast<const uint16_t*>(dO), aux_lse2, aux_D, cu_q,
-                       cu_nuggets, B, H, H_kv, n_nug_tiles, max_q_pad, Sq, Kt, tok_stride, head_stride, scale_log2e, partial);
+      hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kGradThreads), lds_bytes, s,
+                         static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(Kn),
+                         static_cast<const uint16_t*>(Vn), static_cast<const uint16_t*>(dO),
+                         static_cast<const uint16_t*>(O), lse, cu_q, cu_nuggets, B, H, H_kv, n_nug_tiles, Kt, tok_stride,
+                         head_stride, scale_log2e, partial);
+      return DODO_OK;
+    };
+    rc = d_h == 128 ? launch(ste_grad_mfma_kernel<128>, SteDims<128>::kLds) : launch(ste_grad_mfma_kernel<64>, SteDims<64>::kLds);
+    if (rc != DODO_OK) return rc;
   } else {
     if (H > 65535) return DODO_ERR_UNSUPPORTED;
+    const unsigned rd_blocks = static_cast<unsigned>((Sq * H * 16 + 255) / 256);
     const dim3 grid(static_cast<unsigned>(Kt), static_cast<unsigned>(H));
+    if (dtype == DODO_DTYPE_BF16) {
+      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_BF16>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
+                         aux_lse2, aux_D);
+    } else {
+      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_F32>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
+                         aux_lse2, aux_D);
+    }
+    rc = launch_status();
+    if (rc != DODO_OK) return rc;
     if (dtype == DODO_DTYPE_BF16) {
       hipLaunchKernelGGL(ste_grad_plain_kernel<DODO_DTYPE_BF16>, grid, dim3(kWave), 0, s, Q, Kn, Vn, dO, aux_lse2, aux_D,
                          cu_q, cu_nuggets, B, H, H_kv, d_h, Sq, Kt, tok_stride, head_stride, scale_log2e, partial);

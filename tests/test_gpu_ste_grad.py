@@ -74,6 +74,22 @@ def test_mfma_kernel_bf16(D, q_lens, k_lens, m_lens, H, H_kv):
     assert torch.equal(got, got_hm)
 
 
+# heads of 64 channels; a sequence whose rows fill a chunk of 1024 log-sum-exps exactly, and one row more
+@pytest.mark.parametrize("q_lens,k_lens,m_lens,H,H_kv,d_h", [
+    ([100, 37, 256, 16, 0, 1], [13, 200, 0, 77, 9, 65], [150, 37, 300, 16, 3, 2], 4, 2, 64),
+    ([33, 200], [130, 257], [0, 100], 2, 2, 64),
+    ([1024, 1025], [70, 64], [1024, 1025], 1, 1, 64),
+    ([1025, 1024], [64, 70], [1025, 1024], 1, 1, 128),
+])
+def test_mfma_kernel_head_sizes_and_chunks(D, q_lens, k_lens, m_lens, H, H_kv, d_h):
+    t, cu = _case(702, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16)
+    scale = d_h ** -0.5
+    want = oracle.ste_score_grad(*(W.to_numpy(t[k]) for k in ("Q", "Kn", "Vn", "Kl", "Vl", "dO")), *cu, scale, 1.0)
+    got = _gpu(D, t, cu, q_lens, k_lens, m_lens, scale, 1.0)
+    _check(got, want, torch.bfloat16)
+    assert torch.equal(got, _gpu(D, t, cu, q_lens, k_lens, m_lens, scale, 1.0, layout=1))
+
+
 def test_accumulates_over_layers_and_is_deterministic(D):
     q_lens, k_lens, m_lens, H = [90, 64], [70, 20], [100, 64], 4
     scale = 128 ** -0.5
