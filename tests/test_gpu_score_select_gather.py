@@ -45,6 +45,24 @@ def test_score_widths_of_whole_loads(D, dtype, chunks):
         assert np.all(np.abs(got - ref) <= 1e-5 * (1 + np.abs(ref))), (N, np.max(np.abs(got - ref)))  # (as above)
 
 
+# many rows: one resident round that strides over the rows, or workgroups of four rows per wavefront (the last of them
+# incomplete); a score does not depend on how many rows there are, so calls over a few rows say what they are
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 512), (torch.bfloat16, 4096), (torch.float32, 256), (torch.bfloat16, 8192)])
+@pytest.mark.parametrize("N", [65535, 65536, 65537, 131089])
+def test_score_of_many_rows(D, dtype, d, N):
+    g = torch.Generator(device=dev()).manual_seed(d + N)
+    x = torch.randn((N, d), generator=g, dtype=dtype, device=dev())
+    w = torch.randn((d,), generator=g, dtype=dtype, device=dev())
+    out = torch.full((N + 64,), 7.0, device=dev())
+    got = D.dodo_score(x, w, 0.5, out[:N])
+    want = torch.cat([D.dodo_score(x[i:i + 8192], w, 0.5) for i in range(0, N, 8192)])
+    assert torch.equal(got, want) and bool((out[N:] == 7.0).all())
+    rows = [0, 1, 4095, 16383, 16384, N - 2, N - 1]
+    ref = oracle.score(W.to_numpy(x[rows].cpu()), W.to_numpy(w.cpu()), 0.5)
+    size = float(d) ** 0.5  # of a score: w has unit variance here
+    assert np.all(np.abs(got[rows].cpu().numpy() - ref) <= 1e-5 * size * (1 + np.abs(ref) / size))
+
+
 def test_score_exact_arithmetic_inputs_are_bit_exact(D):
     for dtype in (torch.float32, torch.bfloat16):
         x, w = W.exact_arithmetic_inputs(7, 2048, 4096, dtype)
