@@ -27,6 +27,7 @@ struct Elems;
 template <>
 struct Elems<DODO_DTYPE_BF16> {
   static constexpr int kPerLoad = 8;
+  typedef uint16_t Raw;
   // w points at 8 consecutive fp32 weights, 16-byte aligned
   __device__ static __forceinline__ float dot(const uint4& v, const float* w) {
     const float4 w0 = *reinterpret_cast<const float4*>(w), w1 = *reinterpret_cast<const float4*>(w + 4);
@@ -55,6 +56,7 @@ struct Elems<DODO_DTYPE_BF16> {
 template <>
 struct Elems<DODO_DTYPE_F32> {
   static constexpr int kPerLoad = 4;
+  typedef uint32_t Raw;
   // w points at 4 consecutive fp32 weights, 16-byte aligned
   __device__ static __forceinline__ float dot(const uint4& v, const float* w) {
     const float4 w0 = *reinterpret_cast<const float4*>(w);
@@ -108,6 +110,24 @@ __device__ __forceinline__ void stage_weights(const void* __restrict__ w, int d,
     }
   } else {
     for (int c = threadIdx.x; c < d; c += kScoreThreads) w_lds[c] = E::load_one(w, c);
+  }
+}
+
+// The weight vector as it is in memory, element by element (it need not be aligned to more than an element), by the whole
+// workgroup; d is a multiple of 64 loads, and as many as fit a batch are in flight per thread.
+template <int DTYPE>
+__device__ __forceinline__ void stage_raw_weights(const void* __restrict__ w, int d, uint4* __restrict__ w_raw) {
+  typedef typename Elems<DTYPE>::Raw Raw;
+  constexpr int kBatch = 8;
+  const Raw* src = static_cast<const Raw*>(w);
+  Raw* dst = reinterpret_cast<Raw*>(w_raw);
+  for (int c0 = threadIdx.x; c0 < d; c0 += kScoreThreads * kBatch) {
+    Raw x[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) x[u] = src[min(c0 + u * kScoreThreads, d - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (c0 + u * kScoreThreads < d) dst[c0 + u * kScoreThreads] = x[u];
   }
 }
 
@@ -172,7 +192,9 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const void* __rest
 // instruction per pair (two exact products and the fp32 sum), unpacking neither side.  Measured, 4096 channels in bf16,
 // against weights staged in LDS as fp32: 64 rows 3.1 -> 2.5 us, 3200 rows 9.3 -> 7.7 us, 15000 rows 21.9 -> 19.4 us
 // (6.3 TB/s), 32768 rows 41.9 -> 41.5 us (6.5 TB/s: bound by memory).
-template <int DTYPE, int PB, int NB>
+// A weight vector that does not start on a 16-byte boundary (STAGED) reaches the registers through LDS, as it is in
+// memory: the arithmetic, and so every score, is the same for any alignment.
+template <int DTYPE, int PB, int NB, bool STAGED>
 __global__ __launch_bounds__(kScoreThreads) void score_pipelined_kernel(const void* __restrict__ hidden_all,
                                                                         const void* __restrict__ w_all, float bias,
                                                                         int64_t N, int64_t row_stride,
@@ -207,8 +229,15 @@ __global__ __launch_bounds__(kScoreThreads) void score_pipelined_kernel(const vo
   uint4 buf[2][PB];  // used alternately, so that no copy has to wait for the loads in flight
   uint4 wv[NB * PB];
   load_batch(buf[0], wave, 0);
+  const uint4* w_src = reinterpret_cast<const uint4*>(w);
+  if (STAGED) {
+    extern __shared__ uint4 w_raw[];
+    stage_raw_weights<DTYPE>(w, NB * PB * kWave * E::kPerLoad, w_raw);
+    __syncthreads();
+    w_src = w_raw;
+  }
 #pragma unroll
-  for (int u = 0; u < NB * PB; ++u) wv[u] = reinterpret_cast<const uint4*>(w)[u * kWave + lane];
+  for (int u = 0; u < NB * PB; ++u) wv[u] = w_src[u * kWave + lane];
   for (int64_t row = wave; row < N; row += 2 * nwaves) {
     float acc = 0.f;
 #pragma unroll
@@ -240,10 +269,11 @@ int resident_blocks(K kernel, size_t lds) {
   return compute_units() * resident_blocks_per_cu(reinterpret_cast<const void*>(kernel), kScoreThreads, lds, 2);
 }
 
-template <int DTYPE, int PB, int NB>
+template <int DTYPE, int PB, int NB, bool STAGED>
 void launch_pipelined(const void* hidden, const void* w, float bias, int64_t N, int64_t row_stride, float* scores,
                       unsigned blocks, hipStream_t s, int L, const LayerDim& ld) {
-  const int cap = resident_blocks(score_pipelined_kernel<DTYPE, PB, NB>, 0);
+  const size_t lds = STAGED ? PB * NB * kWave * sizeof(uint4) : 0;
+  const int cap = resident_blocks(score_pipelined_kernel<DTYPE, PB, NB, STAGED>, lds);
   // What is resident at once, or, from two such rounds on, workgroups of kRowsPerWave rows per wavefront: wavefronts that
   // stride over hundreds of rows drift apart, and reads that are spread over the whole tensor are slower than a front that
   // moves through it.  bf16: 4096 channels, 400000 rows 525 -> 486 us (6.7 TB/s), 100000 rows 124 -> 119 us; 5120 channels,
@@ -256,8 +286,8 @@ void launch_pipelined(const void* hidden, const void* w, float bias, int64_t N, 
     blocks = static_cast<unsigned>(many);
   else if (blocks > static_cast<unsigned>(cap))
     blocks = cap;
-  hipLaunchKernelGGL((score_pipelined_kernel<DTYPE, PB, NB>), dim3(blocks, L), dim3(kScoreThreads), 0, s, hidden, w, bias, N,
-                     row_stride, scores, ld);
+  hipLaunchKernelGGL((score_pipelined_kernel<DTYPE, PB, NB, STAGED>), dim3(blocks, L), dim3(kScoreThreads), lds, s, hidden, w,
+                     bias, N, row_stride, scores, ld);
 }
 
 // (up to 4 batches of 8 loads: 128 registers of weights)
@@ -265,12 +295,17 @@ template <int DTYPE>
 bool try_pipelined(const void* hidden, const void* w, float bias, int64_t N, int d, int64_t row_stride, float* scores,
                    unsigned blocks, hipStream_t s, int L, const LayerDim& ld) {
   constexpr int kChunk = kWave * Elems<DTYPE>::kPerLoad;
-  if (d % kChunk != 0 || !aligned16(w) || (ld.w_ls * (DTYPE == DODO_DTYPE_F32 ? 4 : 2)) % 16 != 0) return false;
+  if (d % kChunk != 0) return false;
+  // (every layer's weights have to be aligned for the direct form; the scores do not depend on which of the two runs)
+  const bool aligned = aligned16(w) && (ld.w_ls * (DTYPE == DODO_DTYPE_F32 ? 4 : 2)) % 16 == 0;
   switch (d / kChunk) {
 #define DODO_SCORE_WIDTH(CHUNKS, PB, NB)                                                            \
   case CHUNKS:                                                                                      \
     static_assert(CHUNKS == PB * NB, "");                                                           \
-    launch_pipelined<DTYPE, PB, NB>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld);      \
+    if (aligned)                                                                                    \
+      launch_pipelined<DTYPE, PB, NB, false>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
+    else                                                                                            \
+      launch_pipelined<DTYPE, PB, NB, true>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
     return true
     DODO_SCORE_WIDTH(1, 1, 1);
     DODO_SCORE_WIDTH(2, 2, 1);

@@ -124,6 +124,29 @@ def test_score_layers_matches_oracle_and_the_single_layer_call(D, dtype, L, N, d
     assert np.all(np.abs(out[:, :N].cpu().numpy() - ref0) <= 1e-5 * (1 + np.abs(ref0))) and bool((out[:, N:] == 7.0).all())
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("chunks", [1, 3, 8, 10, 16, 32])
+def test_scores_do_not_depend_on_the_alignment_of_the_weights(D, dtype, chunks):
+    # weight vectors that start an odd number of elements past a 16-byte boundary, and layers an odd stride apart (so that
+    # some are aligned and some are not): bit for bit the scores of aligned weights
+    d, L, N = chunks * (512 if dtype == torch.bfloat16 else 256), 3, 130
+    x = W.normal(140, chunks, (L, N, d), 1.0, dtype).to(dev())
+    w = W.normal(141, chunks, (L, d), d ** -0.5, dtype).to(dev())
+    want = torch.stack([D.dodo_score(x[l], w[l], 0.5) for l in range(L)])
+    ref = oracle.score(W.to_numpy(x[1].cpu()), W.to_numpy(w[1].cpu()), 0.5)
+    assert np.all(np.abs(want[1].cpu().numpy() - ref) <= 1e-5 * (1 + np.abs(ref)))
+    biases = torch.full((L,), 0.5, device=dev())
+    for pad, off in ((8, 1), (8, 3), (1, 0), (3, 1)):
+        buf = torch.full((off + L * (d + pad),), float("nan"), dtype=dtype, device=dev())  # nothing around the weights is read
+        view = buf[off:].view(L, d + pad)[:, :d]
+        view.copy_(w)
+        assert torch.equal(torch.stack([D.dodo_score(x[l], view[l], 0.5) for l in range(L)]), want)
+        got = torch.full((L, N), float("nan"), device=dev())
+        rc = D.lib.dodo_score_layers(x.data_ptr(), view.data_ptr(), biases.data_ptr(), D.BF16 if dtype == torch.bfloat16 else D.F32,
+                                     L, N, d, d, N * d, d + pad, N, got.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0 and torch.equal(got, want)
+
+
 # ---------------------------------------------------------------- select
 def _select_both(D, scores_np, n_lens, k_lens, flags=0):
     cu_s, cu_k = oracle.cu_from_lengths(n_lens), oracle.cu_from_lengths(k_lens)
