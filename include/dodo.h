@@ -39,7 +39,7 @@ extern "C" {
 #define DODO_OK 0
 #define DODO_ERR_INVALID_ARG (-1)         /* null pointer, negative size, k > n, H % H_kv != 0, bad flag/layout */
 #define DODO_ERR_UNSUPPORTED (-2)         /* dtype / head_dim / alignment outside the supported set */
-#define DODO_ERR_WORKSPACE_TOO_SMALL (-3) /* ws_bytes below what the *_workspace_bytes query returns */
+#define DODO_ERR_WORKSPACE_TOO_SMALL (-3) /* ws_bytes below what the call needs: at most what the *_workspace_bytes query returns */
 #define DODO_ERR_HIP (-4)                 /* a HIP runtime call failed (launch error, no device) */
 #define DODO_ERR_SCRATCH_LIMIT (-5)       /* the problem needs more than the library's static scratch buffer holds */
 
@@ -97,8 +97,9 @@ int dodo_score_layers(const void* hidden, const void* w, const float* biases, in
 #define DODO_ACT_GELU 1 /* x * Phi(x), erf form */
 #define DODO_ACT_TANH 2
 
-/* Bytes of device workspace dodo_score_mlp would like for this N (may be 0).  It does not grow evenly with N; a smaller
- * buffer, sized for another N, is accepted as long as the split that needs the least fits, and is slower. */
+/* Bytes of device workspace dodo_score_mlp would like for this N (may be 0); a buffer of this size is accepted for every
+ * smaller N too.  A call whose workspace is below this, because it was sized for another N, may take a slower split of the
+ * work that needs less; below what that needs it returns DODO_ERR_WORKSPACE_TOO_SMALL. */
 size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d, int32_t d_hid);
 
 /*

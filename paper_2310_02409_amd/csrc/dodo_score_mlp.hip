@@ -31,6 +31,8 @@
 // Everything else (fp32 inputs, other shapes) takes a plain kernel that keeps a
 // few token rows in LDS and gives one wavefront a hidden unit at a time: correct
 // for any shape, slow for large ones (W1 is re-read for every group of tokens).
+#include <algorithm>
+
 #include "dodo_common.h"
 
 namespace dodo {
@@ -437,14 +439,27 @@ bool mfma_path(int dtype, int64_t N, int32_t d, int32_t d_hid, int64_t row_strid
          static_cast<int64_t>(kHidTile) * d * 2 < 0x7fffffffLL && static_cast<int64_t>(kTokTile) * row_stride * 2 < 0x7fffffffLL;
 }
 
-// The split that needs the least memory: big tiles throughout.  Used when the caller's workspace was sized for another
-// number of tokens and is too small for the plan below.
+// Splits of big tiles throughout, for a workspace that was sized for another number of tokens and is too small for the
+// plan below: what the chip needs to be filled, at least four.  A call without room for these is refused.
 int hidden_splits(int64_t N, int32_t d_hid) {
   const int64_t blocks = (N + kTokTile - 1) / kTokTile;
   const int tiles = d_hid / kHidTile;
   int hs = 1;
   while (hs * 2 <= tiles && (hs < 4 || blocks * hs < compute_units())) hs *= 2;
   return hs;
+}
+
+// The most that this form takes for any number of tokens up to N.  Its need is not even in N (twice the splits as soon as
+// half of them leave the chip idle), so a buffer that a caller keeps for falling N has to hold the largest: for every
+// number of splits, the need of the most tokens that get it.
+size_t hidden_splits_most_bytes(int64_t N, int32_t d_hid) {
+  int64_t most = 0;
+  for (int hs = 2; hs <= d_hid / kHidTile; hs *= 2) {
+    const int64_t last_block = hs <= 4 ? N : (compute_units() + hs / 2 - 1) / (hs / 2) - 1;  // of those with hs splits or more
+    const int64_t n = last_block <= N / kTokTile ? last_block * kTokTile : N;
+    if (n > 0) most = std::max(most, hidden_splits(n, d_hid) * n);
+  }
+  return static_cast<size_t>(most) * sizeof(float);
 }
 
 // How N tokens are shared out: the first n_big in big tiles (hs_big splits of the hidden units), the rest in small ones.
@@ -520,8 +535,11 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   using namespace dodo;
   if (N <= 0 || d <= 0 || d_hid <= 0) return 0;
   if (dtype != DODO_DTYPE_BF16 || d % kBK != 0 || d_hid % kHidTile != 0) return 0;
-  if (N <= kFewTokens) return static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float);
-  return plan_mlp(N, d_hid).bytes();
+  // room for this N, and for every smaller one as well: a caller may keep the buffer
+  const size_t few = static_cast<size_t>(few_splits(d_hid)) * (N < kFewTokens ? N : kFewTokens) * sizeof(float);
+  const size_t least = hidden_splits_most_bytes(N, d_hid);
+  const size_t plan = N <= kFewTokens ? 0 : plan_mlp(N, d_hid).bytes();
+  return std::max(plan, std::max(few, least));
 }
 
 extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const void* w2, float b2, int act,

@@ -152,6 +152,22 @@ def test_attention_argument_validation(lib):
     assert G(2, 64, 5, 128, 1, 3277, 1089, 1) == plain     # H_kv does not divide H: the plain size (the call refuses)
 
 
+@pytest.mark.parametrize("d_hid", [256, 512, 768, 2048, 4096, 5120, 8192])
+def test_score_mlp_workspace_serves_every_smaller_number_of_tokens(lib, d_hid):
+    # a call is refused below the need of big tiles with as many splits as fill 256 compute units, at least four
+    def refused_below(n):
+        hs = 1
+        while 2 * hs <= d_hid // 256 and (hs < 4 or -(-n // 256) * hs < 256):
+            hs *= 2
+        return 0 if hs == 1 else 4 * hs * n
+    edges = {256 * t + e for t in (1, 2, 4, 8, 16, 31, 32, 63, 64, 127, 128, 129, 200, 256, 300) for e in (-1, 0, 1)}
+    sizes = sorted(edges | {1, 40, 64, 65, 100, 4500, 61440, 140000})
+    most = 0
+    for n in sizes:
+        most = max(most, refused_below(n))
+        assert lib.dodo_score_mlp_workspace_bytes(1, n, 64, d_hid) >= most, n
+
+
 def test_threshold_path_argument_validation(lib):
     P = ctypes.c_void_p(16)  # never dereferenced: validation fails first
     i64 = ctypes.c_int64

@@ -86,6 +86,20 @@ def test_workspace_sized_for_another_call(D, N, least):
         D.dodo_score_mlp(*t, ws=ws[:least * N * 4 - 4])
 
 
+# one buffer, sized once for the most tokens, while their number falls
+@pytest.mark.parametrize("most", [65536, 32768, 300])
+def test_workspace_kept_for_fewer_tokens(D, most):
+    d, dh = 64, 4096
+    x, W1, b1, w2 = _case(991, most, d, dh, torch.bfloat16)
+    t = [v.to(dev()) for v in (x, W1, b1, w2)]
+    ws = torch.full((max(1, D.dodo_score_mlp_workspace_bytes(D.BF16, most, d, dh)),), 255, dtype=torch.uint8, device=dev())
+    for N in (most, 63488, 30720, 16128, 8200, 4097, 300, 65, 64, 1):
+        if N <= most:
+            rows = np.unique(np.r_[0:min(N, 20), max(0, N - 20):N])
+            got = D.dodo_score_mlp(t[0][:N], *t[1:], ws=ws).cpu().numpy()
+            _check(got[rows], oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 0))
+
+
 @pytest.mark.parametrize("dtype,N,d,dh", [(torch.float32, 512, 256, 256), (torch.bfloat16, 37, 40, 100),
                                           (torch.float32, 9, 24, 7)])
 def test_plain_path_any_shape(D, dtype, N, d, dh):
