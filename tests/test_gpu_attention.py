@@ -105,6 +105,23 @@ def test_decode_around_the_first_split(D, dtype, d_h, first):
         _full_check(D, 440 + rows % 7, [1, 1], [rows - 100, 7], [100, 3], 2, 2, d_h, dtype)
 
 
+@pytest.mark.parametrize("H,H_kv,k,d_h", [(130, 1, 3277, 128), (2, 2, 6554, 64), (512, 16, 3277, 64)])
+def test_fp32_decode_loses_nothing_over_long_caches(D, H, H_kv, k, d_h):
+    # one split of 16 row streams, 64 splits, several heads per workgroup.  Against 64 bits, in the 2-norm: logits, weights
+    # and merges cost about 1.6e-7 whatever the length (150 rows: 1.4e-7 to 1.7e-7); one running sum per stream would add
+    # as much again over 3534 rows (4.3e-7 in all), sums of 8 rows that join it add 1e-7 at most
+    g = torch.Generator(device=dev()).manual_seed(H)
+    m = 257
+    Q, Kn, Vn, Kl, Vl = (torch.randn((r, h, d_h), generator=g, device=dev())
+                         for r, h in ((1, H), (k, H_kv), (k, H_kv), (m, H_kv), (m, H_kv)))
+    cu = [torch.tensor([0, r], dtype=torch.int32, device=dev()) for r in (1, k, m)]
+    O, _ = D.dodo_nugget_attention(Q, Kn, Vn, Kl, Vl, *cu, 1, k, m, default_scale(d_h))
+    K, V = (torch.cat(t).double().repeat_interleave(H // H_kv, 1) for t in ((Kn, Kl), (Vn, Vl)))
+    P = torch.softmax((Q.double() * K).sum(-1) * default_scale(d_h), 0)
+    want = (P[..., None] * V).sum(0)
+    assert float((O[0].double() - want).norm() / want.norm()) <= 3e-7
+
+
 def test_split_k_workspace_is_reusable_and_needs_no_initialisation(D):
     # the last split of a row waits for the flags of the others and clears them: the same workspace
     # serves call after call, and bytes that are not the "ready" value are as good as zeros
