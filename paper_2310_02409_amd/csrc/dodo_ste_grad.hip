@@ -25,7 +25,8 @@
 // pipe.  8 x 410 nuggets, 512 rows, 32 heads of 128: 48 us and no launch before
 // it (was 41.5 us after a 14 us kernel that made D and lse: forward and gradient
 // 135 -> 126 us); heads of 64 in the plain kernel: 2249 -> 33 us (4 x 250 nuggets,
-// 300 rows, 16 heads).  Error against 64 bits (2-norm): 2.6e-7 (was 3.8e-7).
+// 300 rows, 16 heads; 35 us with the sums of SteDims::kExact).  Error against 64
+// bits (2-norm): 2.6e-7 (was 3.8e-7).
 #include "dodo_common.h"
 
 namespace dodo {
@@ -52,6 +53,12 @@ struct SteDims {
   static constexpr int kStageBytes = 3 * kTileBytes;        // Q tile, dO tile, O tile
   static constexpr int kInstr = 8 / kRowsPerInstr;          // instructions per wavefront, tile and tensor
   static constexpr int kLds = kStagesSte * kStageBytes + (kLseChunk + 2 * kQTile) * 4;
+  // dP can start from -D, which saves a subtraction per element, but then every accumulation rounds away bits of D, the same
+  // for all nuggets of a row; and a lane's sum over the tiles is a chain of rounded additions (4000 rows: 125 tiles).  Against
+  // 64 bits (2-norm), 4000 rows, 16 heads of 64: 5.6e-7 so, 2.9e-7 with the subtraction and a compensated sum, in 2 to 8%
+  // more time, 3.5e-7 in the plain kernel.  Heads of 128: 4.7e-7 as it is, 1.0e-6 with one chain over all rows; here the
+  // 2% that the compensated sum takes alone buy nothing that was there before.
+  static constexpr bool kExact = DH == 64;
 };
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -106,7 +113,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, float* __restrict__ partial) {
   using SD = SteDims<DH>;
   constexpr int kRowBytes = SD::kRowBytes, kP = SD::kPieces, kRowShift = SD::kRowShift, kTileBytes = SD::kTileBytes;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, -D of two tiles
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, D or -D of two tiles
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
   // block i runs on XCD i % 8: the nugget tiles of one (sequence, head) sit on one XCD and share Q / dO / O in its L2
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -185,7 +192,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     for (int ks = 0; ks < DH / 16; ++ks) asm volatile("" : "+v"(kf[blk][ks]), "+v"(vf[blk][ks]));
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): tiles 0 and 1 too
 
-  // -D of tile t's rows, 8 lanes per row with DH / 8 channels each.  A wavefront takes the rows that it loaded itself, so
+  // D (kExact) or -D of tile t's rows, 8 lanes per row with DH / 8 channels each.  A wavefront takes the rows that it loaded itself, so
   // only its own loads have to have landed; the next tile's barrier hands the sums to the others.
   const int d_row = 8 * wave + (lane >> 3), d_sub = lane & 7;
   auto row_dots = [&](int t) {
@@ -204,11 +211,11 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       }
     }
     acc = lanes_sum<8>(acc);
-    if (d_sub == 0) dd_l[(t & 1) * kQTile + d_row] = -acc;
+    if (d_sub == 0) dd_l[(t & 1) * kQTile + d_row] = SD::kExact ? acc : -acc;
   };
   if (n_qtiles > 0) row_dots(0);
 
-  float ds[2] = {0.f, 0.f};
+  float ds[2] = {0.f, 0.f}, lost[2] = {0.f, 0.f};  // sum, and what its additions rounded away
   for (int t = 0; t < n_qtiles; ++t) {
     __syncthreads();  // everyone's part of tile t has landed, its D is there; tile t-1 has been read by everyone
     const int c0 = t * kQTile % kLseChunk;
@@ -220,16 +227,20 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     const char* stg = lds + (t % kStagesSte) * SD::kStageBytes;
     floatx16 acc_s[2], acc_p[2];
     if (active) {
-      // S starts from 0, dP from -D
-      floatx16 neg_d;
+      // S starts from 0, dP from -D or from 0 (SteDims::kExact)
+      floatx16 first;
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
-        neg_d[4 * vq] = dd.x; neg_d[4 * vq + 1] = dd.y; neg_d[4 * vq + 2] = dd.z; neg_d[4 * vq + 3] = dd.w;
+      for (int v = 0; v < 16; ++v) first[v] = 0.f;
+      if (!SD::kExact) {
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
+          first[4 * vq] = dd.x; first[4 * vq + 1] = dd.y; first[4 * vq + 2] = dd.z; first[4 * vq + 3] = dd.w;
+        }
       }
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
-        acc_p[blk] = neg_d;
+        acc_p[blk] = first;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc_s[blk][v] = 0.f;
       }
@@ -257,16 +268,29 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     for (int vq = 0; vq < 4; ++vq) {
       const float4 l2 = *reinterpret_cast<const float4*>(lse2_l + c0 + 8 * vq + 4 * g);
       const float l2v[4] = {l2.x, l2.y, l2.z, l2.w};
+      float ddv[4] = {0.f, 0.f, 0.f, 0.f};
+      if (SD::kExact) {
+        const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
+        ddv[0] = dd.x; ddv[1] = dd.y; ddv[2] = dd.z; ddv[3] = dd.w;
+      }
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float p = __builtin_amdgcn_exp2f(acc_s[blk][4 * vq + e] * scale_log2e - l2v[e]);
-          part[blk] = fmaf(p, acc_p[blk][4 * vq + e], part[blk]);
+          part[blk] = fmaf(p, SD::kExact ? acc_p[blk][4 * vq + e] - ddv[e] : acc_p[blk][4 * vq + e], part[blk]);
         }
     }
-    ds[0] += part[0];
-    ds[1] += part[1];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      if (SD::kExact) {
+        const float add = part[blk] - lost[blk], sum = ds[blk] + add;
+        lost[blk] = (sum - ds[blk]) - add;
+        ds[blk] = sum;
+      } else {
+        ds[blk] += part[blk];
+      }
+    }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // drain the look-ahead loads before the wavefront ends
 

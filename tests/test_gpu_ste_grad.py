@@ -90,6 +90,22 @@ def test_mfma_kernel_head_sizes_and_chunks(D, q_lens, k_lens, m_lens, H, H_kv, d
     assert torch.equal(got, _gpu(D, t, cu, q_lens, k_lens, m_lens, scale, 1.0, layout=1))
 
 
+@pytest.mark.parametrize("d_h,bound", [(64, 2e-7), (128, 4e-7)])
+def test_sums_over_many_query_rows_keep_their_precision(D, d_h, bound):
+    # K = 0 and lse = 0 make every weight 1 exactly, so that the gradient is the sum of dO.v - D over rows and heads.
+    # Against 64 bits in the 2-norm: a lane of the plain kernel, 62 additions in a row, gives 1.6e-7 at 4000 rows; one sum
+    # over 125 tiles and D rounded at every accumulation gave 3.4e-7 with 64 channels.  (128: 7.4e-7 with one sum over all rows.)
+    g = torch.Generator(device=dev()).manual_seed(5)
+    q, k, H = 4000, 512, 4
+    Q, dO, O = (torch.randn(q, H, d_h, device=dev(), generator=g).bfloat16() for _ in range(3))
+    O *= 0.05
+    V = torch.randn(k, H, d_h, device=dev(), generator=g).bfloat16()
+    cu_q, cu_k = (torch.tensor([0, n], dtype=torch.int32, device=dev()) for n in (q, k))
+    got = D.dodo_ste_score_grad(Q, torch.zeros_like(V), V, dO, O, torch.zeros(q, H, device=dev()), cu_q, cu_k, q, k, d_h ** -0.5, 1.0)
+    want = ((dO.double().sum(0) * V.double()).sum((1, 2)) - (dO.double() * O.double()).sum())
+    assert float((got.double() - want).norm() / want.norm()) <= bound
+
+
 def test_accumulates_over_layers_and_is_deterministic(D):
     q_lens, k_lens, m_lens, H = [90, 64], [70, 20], [100, 64], 4
     scale = 128 ** -0.5
