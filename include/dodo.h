@@ -178,7 +178,9 @@ int dodo_gather_nuggets_layers(const void* K, const void* V, int dtype, const in
                                int32_t H_kv, int32_t d_h, int64_t token_stride, int64_t src_layer_stride,
                                int64_t dst_layer_stride, void* Kn, void* Vn, int layout, void* stream);
 
-/* Bytes of device workspace dodo_nugget_attention needs for these bounds (may be 0).  The workspace holds
+/* Bytes of device workspace with which dodo_nugget_attention runs for these bounds (may be 0); where it is not 0, it
+ * also serves every smaller B or max_q (which are split further).  Calls with max_k + max_local < 512 are accepted
+ * without a workspace and then not split.  The workspace holds
  * the partial results of the split-K kernel and one flag word per partial.  Its contents need not be
  * initialised, with one exception: no flag word may hold the library's "ready" value 0x600DD0D0 on
  * entry -- the call clears the flags it used, so zero-filled memory and memory that was a workspace in a
@@ -235,8 +237,8 @@ int dodo_nugget_attention(const void* Q, const void* Kn, const void* Vn, const v
  * to a buffer inside the library (a static device array of about 2.1 MB that every GPU the library runs
  * on holds until the process ends); the call itself allocates and frees nothing.  The buffer has room for
  * DODO_NOALLOC_MAX_PARTIALS partial results, i.e. (sequence, query row, head, split) combinations of a
- * call that splits (dodo_nugget_attention_workspace_bytes / ((d_h + 3) * 4) gives the number for given
- * bounds; 0 means the call needs no buffer at all and always fits); beyond that the call returns
+ * call that splits (dodo_nugget_attention_workspace_bytes / ((d_h + 3) * 4) is at least the number for
+ * given bounds; 0 means the call needs no buffer at all and always fits); beyond that the call returns
  * DODO_ERR_SCRATCH_LIMIT and launches nothing (the kernel for grouped heads and small query blocks never
  * does: it splits as far as the buffer has room).  All calls on one GPU share that GPU's buffer: calls that
  * may overlap in time on one GPU (different streams, different threads) race and must not be made; calls

@@ -22,7 +22,8 @@ extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, in
   using namespace dodo;
   if (B <= 0 || H <= 0 || d_h <= 0 || max_q <= 0 || max_k < 0 || max_local < 0) return 0;
   if (use_block_kernel(dtype, d_h, max_q)) return 0;
-  return splitk_workspace_bytes(B, H, d_h, max_q, splitk_count(B, H, d_h, max_q, max_k, max_local, dtype));
+  // room for this call, and for calls on fewer sequences or query rows: these split further
+  return splitk_most_records(B, H, d_h, max_q, max_k, max_local, dtype) * splitk_record_bytes(d_h);
 }
 
 extern "C" size_t dodo_nugget_attention_workspace_bytes_grouped(int32_t B, int32_t H, int32_t H_kv, int32_t d_h,
@@ -140,13 +141,16 @@ int attention_entry(const void* Q, const void* Kn, const void* Vn, const void* K
   }
   // (the grouped kernel splits only as far as the workspace it is given has room: it needs none)
   if (group_attention_applies(p)) return launch_group_attention(p);
-  const size_t need = dodo_nugget_attention_workspace_bytes(B, H, d_h, max_q, max_k, max_local, dtype);
-  if (v.library_scratch) {  // need = records * (d_h + 3) * 4 bytes: the limit is on the records
-    if (need / ((static_cast<size_t>(d_h) + 3) * sizeof(float)) > static_cast<size_t>(kScratchSlots)) return DODO_ERR_SCRATCH_LIMIT;
-  } else if (need > 0 && (!ws || ws_bytes < need)) {
-    return DODO_ERR_WORKSPACE_TOO_SMALL;
+  int nsplit = splitk_count(B, H, d_h, max_q, max_k, max_local, dtype);
+  const size_t records = nsplit > 1 ? static_cast<size_t>(B) * max_q * H * nsplit : 0;
+  if (v.library_scratch) {
+    if (records > static_cast<size_t>(kScratchSlots)) return DODO_ERR_SCRATCH_LIMIT;
+  } else if (records > 0 && (!ws || ws_bytes < records * splitk_record_bytes(d_h))) {
+    // fewer than 512 rows never need a workspace: without one they are not split
+    if (static_cast<int64_t>(max_k) + max_local >= 512) return DODO_ERR_WORKSPACE_TOO_SMALL;
+    nsplit = 1;
   }
-  return launch_splitk_attention(p);
+  return launch_splitk_attention(p, nsplit);
 }
 
 }  // namespace

@@ -34,13 +34,14 @@ __host__ __device__ constexpr int partial_floats() { return DH + 2; }
 constexpr uint32_t kPartialReady = 0x600DD0D0u;  // flag value of a record that has been written
 constexpr int kMaxPolls = 1 << 17;               // bound of the combiner's wait (~0.1 s, never reached in a healthy run)
 
-// Split count of the bandwidth-bound kernels for these bounds (>= 1), shared by
-// the launches and the workspace query.
+// Split count of the split-K kernel for these bounds (>= 1), and the most records that a call on at most as many
+// sequences and query rows writes.
 int splitk_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype);
-size_t splitk_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int nsplit);
+size_t splitk_most_records(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype);
+inline size_t splitk_record_bytes(int32_t d_h) { return (static_cast<size_t>(d_h) + 3) * sizeof(float); }  // and its flag
 
 // fp32 or bf16, d_h in {64,128}, any max_q: one workgroup per (query row, head, split).
-int launch_splitk_attention(const AttnParams& p);
+int launch_splitk_attention(const AttnParams& p, int nsplit);
 // bf16, d_h in {64,128}, at least 4 query vectors per KV head and sequence ((H / H_kv) * max_q): MFMA kernel that reads
 // every K/V row once for up to 32 of them (more: up to four passes).  group_attention_applies says whether it takes the call.
 // It splits the keys of a (sequence, KV head) pair as far as the caller's workspace has room for records;

@@ -499,30 +499,36 @@ int launch_t(const AttnParams& p, int nsplit) {
 
 }  // namespace
 
-// Splits of a (query row, head): as many as give each compute unit a workgroup, rounded down -- a split more than
-// that leaves some units with two (5 sequences x 40 heads, 2100 rows: 37.6 us unsplit, 40.9 in two; 3 x 40 heads, 1157
-// rows: 16.7 us in two, 18.7 in three).  The combining costs about 2 us, so nothing is split below 96 KiB of K rows
+namespace {
+// Most splits of a (query row, head).  The combining costs about 2 us, so nothing is split below 96 KiB of K rows
 // (350 rows of 32 heads, one sequence: 7.2 us unsplit, 7.4 in eight; 450 rows: 8.6 against 7.6; 667 rows: 10.5
-// against 8.0; 64-wide heads: level at twice as many rows), and a split keeps at least the rows that its
-// wavefronts request in one go.
-int splitk_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype) {
-  const int64_t base = static_cast<int64_t>(B) * H * max_q;  // workgroups without splitting
+// against 8.0; 64-wide heads: level at twice as many rows), and a split keeps at least 12 KiB of them (48 rows of 128
+// channels in bf16, three quarters of what its wavefronts request in one go).
+int64_t most_splits(int32_t d_h, int32_t max_k, int32_t max_local, int dtype) {
   const int64_t k_bytes = (static_cast<int64_t>(max_k) + max_local) * d_h * elem_bytes(dtype);
   if (k_bytes < 96 * 1024) return 1;
-  int64_t n = compute_units() / base;
-  if (n > k_bytes / (12 * 1024)) n = k_bytes / (12 * 1024);
-  if (n < 1) n = 1;
-  if (n > 64) n = 64;
-  return static_cast<int>(n);
+  const int64_t n = k_bytes / (12 * 1024);
+  return n < 64 ? n : 64;
+}
+}  // namespace
+
+// As many splits as give each compute unit a workgroup, rounded down -- a split more than that leaves some units with
+// two (5 sequences x 40 heads, 2100 rows: 37.6 us unsplit, 40.9 in two; 3 x 40 heads, 1157 rows: 16.7 us in two, 18.7
+// in three).
+int splitk_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype) {
+  const int64_t base = static_cast<int64_t>(B) * H * max_q;  // workgroups without splitting
+  const int64_t n = compute_units() / base, most = most_splits(d_h, max_k, max_local, dtype);
+  return static_cast<int>(n < 1 ? 1 : n < most ? n : most);
 }
 
-size_t splitk_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int nsplit) {
-  if (nsplit <= 1) return 0;
-  return static_cast<size_t>(B) * max_q * H * nsplit * (d_h + 3) * sizeof(float);  // records, then one flag each
+// For any smaller `base` the records are base * min(compute units / base, most_splits) at most.
+size_t splitk_most_records(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype) {
+  const int64_t base = static_cast<int64_t>(B) * H * max_q, most = most_splits(d_h, max_k, max_local, dtype);
+  if (most == 1 || base >= compute_units()) return 0;
+  return static_cast<size_t>(base * most < compute_units() ? base * most : compute_units());
 }
 
-int launch_splitk_attention(const AttnParams& p) {
-  const int nsplit = splitk_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.dtype);
+int launch_splitk_attention(const AttnParams& p, int nsplit) {
   if (static_cast<int64_t>(p.B) * p.max_q * p.H * nsplit > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   // the kernel multiplies a row number by a stride in bytes kept in 32 bits
   if (p.nug_tok_stride * 4 > 0xffffffffLL || static_cast<int64_t>(p.H_kv) * p.d_h * 4 > 0xffffffffLL)

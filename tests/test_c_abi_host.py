@@ -152,6 +152,21 @@ def test_attention_argument_validation(lib):
     assert G(2, 64, 5, 128, 1, 3277, 1089, 1) == plain     # H_kv does not divide H: the plain size (the call refuses)
 
 
+@pytest.mark.parametrize("dtype,H,d_h,rows", [(1, 32, 128, 4366), (1, 32, 128, 512), (1, 40, 128, 700), (1, 2, 64, 3000),
+                                              (0, 3, 64, 1000), (0, 130, 128, 600)])
+def test_attention_workspace_serves_every_smaller_batch(lib, dtype, H, d_h, rows):
+    # a call of b sequences is refused below a record per sequence, head and split, with a workgroup per compute unit
+    def refused_below(b):
+        splits = min(256 // (b * H), 64, rows * d_h * (2 if dtype else 4) // 12288)
+        return b * H * splits * (d_h + 3) * 4 if splits > 1 else 0
+    for B in range(1, 300):
+        have = lib.dodo_nugget_attention_workspace_bytes(B, H, d_h, 1, rows - 100, 100, dtype)
+        if B * H >= 256:
+            assert have == 0  # (enough workgroups without a split)
+        else:
+            assert have >= max(refused_below(b) for b in range(1, B + 1)), B
+
+
 @pytest.mark.parametrize("d_hid", [256, 512, 768, 2048, 4096, 5120, 8192])
 def test_score_mlp_workspace_serves_every_smaller_number_of_tokens(lib, d_hid):
     # a call is refused below the need of big tiles with as many splits as fill 256 compute units, at least four

@@ -141,6 +141,19 @@ def test_split_k_workspace_is_reusable_and_needs_no_initialisation(D):
         check_lse(lse, lse_ref, torch.bfloat16)
 
 
+def test_split_k_workspace_kept_while_sequences_finish(D):
+    # sized once for 7 sequences of 32 heads, which are not split themselves; short rows need none at all
+    H, d_h, k, m = 32, 128, 600, 50
+    ws = torch.empty(D.dodo_nugget_attention_workspace_bytes(7, H, d_h, 1, k, m, D.BF16), dtype=torch.uint8, device=dev())
+    for B, k_b, m_b, buf in ((7, k, m, ws), (4, k, m, ws), (3, k, m, ws), (1, k, m, ws), (1, 461, m, ws[:0])):
+        host, d = make_attention_case(470 + B, [1] * B, [k_b] * B, [m_b] * B, H, H, d_h, torch.bfloat16, dev())
+        O, _ = D.dodo_nugget_attention(d["Q"], d["Kn"], d["Vn"], d["Kl"], d["Vl"], d["cu_q"], d["cu_nuggets"], d["cu_local"],
+                                       1, k_b, m_b, default_scale(d_h), 0, ws=buf.zero_())
+        ref, _ = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                  host["cu_local"], default_scale(d_h))
+        check_attention(O, ref, torch.bfloat16)
+
+
 def test_split_k_grid_limit_is_reported(D):
     # more (sequence, query-row group) pairs than the second grid dimension takes: refused before any launch
     B = 66000
