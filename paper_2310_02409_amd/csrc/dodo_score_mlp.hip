@@ -367,10 +367,9 @@ __global__ __launch_bounds__(kFewWaves * kWave, 2) void score_mlp_few_kernel(
   float bias[RT], wt[RT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) {
-    const bool ok = 16 * i + hid < n_hid;
-    const int h = h0 + (ok ? 16 * i + hid : 0);
+    const int h = h0 + min(16 * i + hid, n_hid - 1);
     bias[i] = b1[h];
-    wt[i] = ok ? load_elem<DODO_DTYPE_BF16>(w2, h) : 0.f;
+    wt[i] = load_elem<DODO_DTYPE_BF16>(w2, h);
   }
   for (int tok = tid >> 4; tok < NB * 16; tok += kFewWaves * kWave / 16) {
     float s = 0.f;
@@ -379,7 +378,8 @@ __global__ __launch_bounds__(kFewWaves * kWave, 2) void score_mlp_few_kernel(
       float h = 0.f;
 #pragma unroll
       for (int w = 0; w < kFewWaves; ++w) h += red[w][tok][16 * i + hid];
-      s = fmaf(wt[i], activation(h + bias[i], act), s);
+      // (past the last hidden unit: zeros times a token, NaN where that holds an infinity)
+      s = 16 * i + hid < n_hid ? fmaf(wt[i], activation(h + bias[i], act), s) : s;
     }
     s = lanes_sum<16>(s);
     if (hid == 0 && tok < N) partial[static_cast<int64_t>(blockIdx.x) * N + tok] = s;

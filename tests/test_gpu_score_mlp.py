@@ -100,6 +100,17 @@ def test_workspace_kept_for_fewer_tokens(D, most):
             _check(got[rows], oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 0))
 
 
+@pytest.mark.parametrize("N,dh", [(1, 256), (16, 256), (40, 5120), (70, 256)])
+def test_infinite_channel_saturates(D, N, dh):
+    # tanh of an infinite hidden unit is 1 or -1: the score stays finite, also where a workgroup's share of the hidden units
+    # is no whole block
+    x, W1, b1, w2 = _case(996, N, 64, dh, torch.bfloat16)
+    x[N // 2, 9], x[0, 5] = float("-inf"), float("inf")
+    x[0, 9] = 0.0
+    got = D.dodo_score_mlp(*[v.to(dev()) for v in (x, W1, b1, w2)], act=D.TANH).cpu().numpy()
+    _check(got, oracle.score_mlp(W.to_numpy(x), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 2))
+
+
 @pytest.mark.parametrize("dtype,N,d,dh", [(torch.float32, 512, 256, 256), (torch.bfloat16, 37, 40, 100),
                                           (torch.float32, 9, 24, 7)])
 def test_plain_path_any_shape(D, dtype, N, d, dh):
