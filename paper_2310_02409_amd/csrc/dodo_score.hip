@@ -3,8 +3,8 @@
 // HBM-bound GEMV: every hidden row is read once, 16 bytes per lane per load,
 // one wavefront per row with several loads in flight and, for widths of whole
 // wave-wide loads, the next batch of loads in flight while the current one is
-// reduced, with the weight vector in registers; other widths stage it once per
-// workgroup in LDS as fp32.
+// reduced, with the weight vector in registers (in LDS beyond 32 loads); other
+// widths stage it once per workgroup in LDS as fp32.
 // Summation order is fixed, so the scores are run-to-run deterministic.
 #include "dodo_common.h"
 
@@ -192,9 +192,11 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const void* __rest
 // instruction per pair (two exact products and the fp32 sum), unpacking neither side.  Measured, 4096 channels in bf16,
 // against weights staged in LDS as fp32: 64 rows 3.1 -> 2.5 us, 3200 rows 9.3 -> 7.7 us, 15000 rows 21.9 -> 19.4 us
 // (6.3 TB/s), 32768 rows 41.9 -> 41.5 us (6.5 TB/s: bound by memory).
-// A weight vector that does not start on a 16-byte boundary (STAGED) reaches the registers through LDS, as it is in
-// memory: the arithmetic, and so every score, is the same for any alignment.
-template <int DTYPE, int PB, int NB, bool STAGED>
+// A weight vector that does not start on a 16-byte boundary (kStaged) reaches the registers through LDS, as it is in
+// memory: the arithmetic, and so every score, is the same for any alignment.  kInLds (fp32 beyond 8192 channels, where
+// registers would not do): it stays there.
+enum WeightsIn { kDirect, kStaged, kInLds };
+template <int DTYPE, int PB, int NB, WeightsIn WEIGHTS>
 __global__ __launch_bounds__(kScoreThreads) void score_pipelined_kernel(const void* __restrict__ hidden_all,
                                                                         const void* __restrict__ w_all, float bias,
                                                                         int64_t N, int64_t row_stride,
@@ -227,21 +229,32 @@ __global__ __launch_bounds__(kScoreThreads) void score_pipelined_kernel(const vo
     }
   };
   uint4 buf[2][PB];  // used alternately, so that no copy has to wait for the loads in flight
-  uint4 wv[NB * PB];
-  load_batch(buf[0], wave, 0);
+  constexpr int kInRegs = WEIGHTS == kInLds ? 1 : NB * PB;
+  uint4 wv[kInRegs];
+  if (WEIGHTS != kInLds) load_batch(buf[0], wave, 0);
   const uint4* w_src = reinterpret_cast<const uint4*>(w);
-  if (STAGED) {
+  if (WEIGHTS != kDirect) {
+    static_assert(WEIGHTS != kInLds || DTYPE == DODO_DTYPE_F32, "stage_weights converts to fp32");
     extern __shared__ uint4 w_raw[];
-    stage_raw_weights<DTYPE>(w, NB * PB * kWave * E::kPerLoad, w_raw);
+    if (WEIGHTS == kInLds)
+      stage_weights<DTYPE>(w, NB * PB * kWave * E::kPerLoad, reinterpret_cast<float*>(w_raw));
+    else
+      stage_raw_weights<DTYPE>(w, NB * PB * kWave * E::kPerLoad, w_raw);
     __syncthreads();
     w_src = w_raw;
   }
+  if (WEIGHTS != kInLds) {
 #pragma unroll
-  for (int u = 0; u < NB * PB; ++u) wv[u] = w_src[u * kWave + lane];
-  for (int64_t row = wave; row < N; row += 2 * nwaves) {
+    for (int u = 0; u < kInRegs; ++u) wv[u] = w_src[u * kWave + lane];
+  } else {
+    load_batch(buf[0], wave, 0);
+  }
+  constexpr int kRows = WEIGHTS == kInLds && NB % 2 == 0 ? 1 : 2;  // as many as leave which buffer is which known below
+  for (int64_t row = wave; row < N; row += kRows * nwaves) {
     float acc = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2 * NB; ++i) {  // two rows, so that which buffer is which is known here
+    for (int i = 0; i < kRows * NB; ++i) {
+      if (WEIGHTS == kInLds && i == NB && row + nwaves >= N) break;  // (many loads that would fetch nothing)
       load_batch(buf[(i + 1) & 1], row + (i + 1) / NB * nwaves, (i + 1) % NB);
       __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of the arithmetic
       const int64_t r = row + i / NB * nwaves;
@@ -249,9 +262,12 @@ __global__ __launch_bounds__(kScoreThreads) void score_pipelined_kernel(const vo
       if (i < NB || r < N) {
         float part[PB];
 #pragma unroll
-        for (int u = 0; u < PB; ++u) part[u] = E::dot(buf[i & 1][u], wv[bi * PB + u]);
+        for (int u = 0; u < PB; ++u)
+          part[u] = E::dot(buf[i & 1][u], WEIGHTS == kInLds ? w_src[(bi * PB + u) * kWave + lane] : wv[(bi * PB + u) % kInRegs]);
 #pragma unroll
         for (int u = 0; u < PB; ++u) acc += part[u];
+        // (or the compiler puts the arithmetic of the batches behind the loads of the whole row: 256 registers and spills)
+        if (WEIGHTS == kInLds) asm volatile("" : "+v"(acc));
         if (bi == NB - 1) {  // the row is complete
           const float s = wave_sum(acc) + bias;
           if (lane == 0) scores[r] = (s == 0.f) ? 0.f : s;  // -0 -> +0
@@ -269,28 +285,28 @@ int resident_blocks(K kernel, size_t lds) {
   return compute_units() * resident_blocks_per_cu(reinterpret_cast<const void*>(kernel), kScoreThreads, lds, 2);
 }
 
-template <int DTYPE, int PB, int NB, bool STAGED>
+template <int DTYPE, int PB, int NB, WeightsIn WEIGHTS>
 void launch_pipelined(const void* hidden, const void* w, float bias, int64_t N, int64_t row_stride, float* scores,
                       unsigned blocks, hipStream_t s, int L, const LayerDim& ld) {
-  const size_t lds = STAGED ? PB * NB * kWave * sizeof(uint4) : 0;
-  const int cap = resident_blocks(score_pipelined_kernel<DTYPE, PB, NB, STAGED>, lds);
+  const size_t lds = WEIGHTS != kDirect ? PB * NB * kWave * sizeof(uint4) : 0;
+  const int cap = resident_blocks(score_pipelined_kernel<DTYPE, PB, NB, WEIGHTS>, lds);
   // What is resident at once, or, from two such rounds on, workgroups of kRowsPerWave rows per wavefront: wavefronts that
   // stride over hundreds of rows drift apart, and reads that are spread over the whole tensor are slower than a front that
   // moves through it.  bf16: 4096 channels, 400000 rows 525 -> 486 us (6.7 TB/s), 100000 rows 124 -> 119 us; 5120 channels,
   // 200000 rows 327 -> 299 us, 32768 rows 50.7 -> 50.2 us; 1024 channels, 400000 rows 140 -> 124 us.  A workgroup that
   // starts has to be hidden by others on its compute unit: where fewer than four fit, the grid stays at one round (8192
-  // channels, 100000 rows: 248 us, 264 us with 2048 workgroups).
+  // channels, 100000 rows: 248 us, 264 us with 2048 workgroups), and where it fetches as much of the weights as of a row.
   const int64_t per_block = kRowsPerWave * (kScoreThreads / kWave);
   const int64_t many = (N + per_block - 1) / per_block;
-  if (cap >= 4 * compute_units() && many >= 2 * static_cast<int64_t>(cap) && many <= 0x7fffffff)
+  if (WEIGHTS != kInLds && cap >= 4 * compute_units() && many >= 2 * static_cast<int64_t>(cap) && many <= 0x7fffffff)
     blocks = static_cast<unsigned>(many);
   else if (blocks > static_cast<unsigned>(cap))
     blocks = cap;
-  hipLaunchKernelGGL((score_pipelined_kernel<DTYPE, PB, NB, STAGED>), dim3(blocks, L), dim3(kScoreThreads), lds, s, hidden, w,
+  hipLaunchKernelGGL((score_pipelined_kernel<DTYPE, PB, NB, WEIGHTS>), dim3(blocks, L), dim3(kScoreThreads), lds, s, hidden, w,
                      bias, N, row_stride, scores, ld);
 }
 
-// (up to 4 batches of 8 loads: 128 registers of weights)
+// (up to 4 batches of 8 loads: 128 registers of weights; fp32 has rows of up to twice that)
 template <int DTYPE>
 bool try_pipelined(const void* hidden, const void* w, float bias, int64_t N, int d, int64_t row_stride, float* scores,
                    unsigned blocks, hipStream_t s, int L, const LayerDim& ld) {
@@ -303,9 +319,9 @@ bool try_pipelined(const void* hidden, const void* w, float bias, int64_t N, int
   case CHUNKS:                                                                                      \
     static_assert(CHUNKS == PB * NB, "");                                                           \
     if (aligned)                                                                                    \
-      launch_pipelined<DTYPE, PB, NB, false>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
+      launch_pipelined<DTYPE, PB, NB, kDirect>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
     else                                                                                            \
-      launch_pipelined<DTYPE, PB, NB, true>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
+      launch_pipelined<DTYPE, PB, NB, kStaged>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
     return true
     DODO_SCORE_WIDTH(1, 1, 1);
     DODO_SCORE_WIDTH(2, 2, 1);
@@ -319,10 +335,28 @@ bool try_pipelined(const void* hidden, const void* w, float bias, int64_t N, int
     DODO_SCORE_WIDTH(12, 6, 2);
     DODO_SCORE_WIDTH(14, 7, 2);
     DODO_SCORE_WIDTH(16, 8, 2);
+    DODO_SCORE_WIDTH(18, 6, 3);
     DODO_SCORE_WIDTH(20, 5, 4);
+    DODO_SCORE_WIDTH(21, 7, 3);
     DODO_SCORE_WIDTH(24, 8, 3);
     DODO_SCORE_WIDTH(28, 7, 4);
     DODO_SCORE_WIDTH(32, 8, 4);
+#undef DODO_SCORE_WIDTH
+#define DODO_SCORE_WIDTH(CHUNKS, PB, NB)                                                            \
+  case CHUNKS:                                                                                      \
+    static_assert(CHUNKS == PB * NB, "");                                                           \
+    if constexpr (DTYPE == DODO_DTYPE_F32) {                                                        \
+      launch_pipelined<DTYPE, PB, NB, kInLds>(hidden, w, bias, N, row_stride, scores, blocks, s, L, ld); \
+      return true;                                                                                  \
+    }                                                                                               \
+    return false
+    DODO_SCORE_WIDTH(35, 7, 5);
+    DODO_SCORE_WIDTH(40, 8, 5);
+    DODO_SCORE_WIDTH(42, 7, 6);
+    DODO_SCORE_WIDTH(48, 8, 6);
+    DODO_SCORE_WIDTH(49, 7, 7);
+    DODO_SCORE_WIDTH(56, 8, 7);
+    DODO_SCORE_WIDTH(64, 8, 8);
 #undef DODO_SCORE_WIDTH
     default: return false;
   }
@@ -350,7 +384,8 @@ int score_entry(const void* hidden, const void* w, float bias, int dtype, int64_
   if (blocks > cap) blocks = cap;
   const size_t lds = static_cast<size_t>(d) * sizeof(float);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // widths that split evenly into batches of wave-wide loads (4096, 5120, 8192, ...) take the pipelined kernel
+  // widths that split evenly into batches of 5 to 8 (up to 8 loads: one batch) wave-wide loads (4096, 5120, 8192, ...) take
+  // the pipelined kernel
   const unsigned nblk = static_cast<unsigned>(blocks);
   if (dtype == DODO_DTYPE_BF16
           ? try_pipelined<DODO_DTYPE_BF16>(hidden, w, bias, N, d, row_stride, scores, nblk, s, L, ld)

@@ -33,7 +33,7 @@ def test_score_matches_oracle(D, dtype, N, d):
 # every number of wave-wide loads that has a kernel of its own, and some that have none; rows: one, less than a
 # wavefront each, more than two for every wavefront that is resident
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 14, 16, 20, 24, 28, 32])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 14, 16, 18, 20, 21, 24, 28, 32])
 def test_score_widths_of_whole_loads(D, dtype, chunks):
     d = chunks * (512 if dtype == torch.bfloat16 else 256)
     for N in (1, 3, 130) + ((20001,) if chunks <= 2 else ()):
@@ -43,6 +43,13 @@ def test_score_widths_of_whole_loads(D, dtype, chunks):
         ref = oracle.score(W.to_numpy(x), W.to_numpy(w), -0.25)
         got = D.dodo_score(padded.to(dev())[:, :d], w.to(dev()), -0.25).cpu().numpy()
         assert np.all(np.abs(got - ref) <= 1e-5 * (1 + np.abs(ref))), (N, np.max(np.abs(got - ref)))  # (as above)
+
+
+# widths whose weights stay in LDS, on and off a 16-byte boundary
+@pytest.mark.parametrize("chunks", [35, 40, 42, 48, 49, 56, 64])
+def test_score_widths_beyond_the_registers(D, chunks):
+    test_score_widths_of_whole_loads(D, torch.float32, chunks)
+    test_scores_do_not_depend_on_the_alignment_of_the_weights(D, torch.float32, chunks)
 
 
 # many rows: one resident round that strides over the rows, or workgroups of four rows per wavefront (the last of them
