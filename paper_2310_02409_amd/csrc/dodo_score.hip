@@ -295,10 +295,11 @@ void launch_pipelined(const void* hidden, const void* w, float bias, int64_t N, 
   // moves through it.  bf16: 4096 channels, 400000 rows 525 -> 486 us (6.7 TB/s), 100000 rows 124 -> 119 us; 5120 channels,
   // 200000 rows 327 -> 299 us, 32768 rows 50.7 -> 50.2 us; 1024 channels, 400000 rows 140 -> 124 us.  A workgroup that
   // starts has to be hidden by others on its compute unit: where fewer than four fit, the grid stays at one round (8192
-  // channels, 100000 rows: 248 us, 264 us with 2048 workgroups), and where it fetches as much of the weights as of a row.
+  // channels, 100000 rows: 248 us, 264 us with 2048 workgroups), and where it fetches as much of the weights as of a row,
+  // and beyond the 2^32 threads that a launch may have.
   const int64_t per_block = kRowsPerWave * (kScoreThreads / kWave);
   const int64_t many = (N + per_block - 1) / per_block;
-  if (WEIGHTS != kInLds && cap >= 4 * compute_units() && many >= 2 * static_cast<int64_t>(cap) && many <= 0x7fffffff)
+  if (WEIGHTS != kInLds && cap >= 4 * compute_units() && many >= 2 * static_cast<int64_t>(cap) && many <= 0xffffffffLL / kScoreThreads)
     blocks = static_cast<unsigned>(many);
   else if (blocks > static_cast<unsigned>(cap))
     blocks = cap;
