@@ -120,7 +120,7 @@ int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const vo
 /* Bytes of device workspace dodo_select_topk can use for B sequences of at most max_n tokens (0 for short
  * sequences).  With it, long sequences are split over several workgroups that exchange histograms and counts
  * through it; without it (NULL or too small) one workgroup per sequence does the same work: at least as fast up to
- * 33792 tokens, more slowly beyond.
+ * 34816 tokens, more slowly beyond.
  * The workspace must be zero-filled before its first use; a call leaves it zero-filled (apart from the status
  * word), so it can be reused by the next call as it is.  It must not be shared by calls that may overlap in time.
  * The workgroups of a sequence wait for each other (bounded: about 0.1 s), so they must be able to run at the
@@ -366,7 +366,7 @@ int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn, const voi
  * ties; NaN ranks lowest, -0 counts as +0.  If k >= n, or that score is NaN, the threshold is
  * -inf (keep everything).  Integer comparisons on the score bits only: bit-exact.  n >= 1.
  * ws is optional (dodo_threshold_from_sample_workspace_bytes(n) bytes, contents irrelevant; 0 for small samples):
- * with it a sample beyond 33792 scores is histogrammed by many workgroups, one launch per radix pass; without it
+ * with it a sample beyond 34816 scores is histogrammed by many workgroups, one launch per radix pass; without it
  * (NULL or too small) one workgroup does the same work, more slowly.  The result does not depend on it.
  */
 size_t dodo_threshold_from_sample_workspace_bytes(int64_t n);

@@ -200,7 +200,7 @@ def dodo_score_layers(hidden: torch.Tensor, w: torch.Tensor, biases: Optional[to
 
 # Longest sequence that one workgroup holds on chip: without a workspace it takes at most as long as several workgroups
 # take to exchange their counts through one, which would have to be filled with zeros first.
-_ONE_WORKGROUP_TOKENS = 33 * 1024
+_ONE_WORKGROUP_TOKENS = 34 * 1024  # (kWideMaxKeys in dodo_kth.h)
 
 
 def dodo_select_topk_workspace_bytes(B: int, max_n: int) -> int:

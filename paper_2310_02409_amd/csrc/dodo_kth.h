@@ -66,27 +66,30 @@ constexpr int kKthMaxCand = 64;  // a bin with at most this many scores is ranke
 // the scan gives a lane 32 neighbouring bins: four words of padding after each run of 32 keep its reads off each other's banks
 __device__ __forceinline__ uint32_t kth_slot(uint32_t bin) { return bin + ((bin >> 5) << 2); }
 
-template <int THREADS>
+constexpr int kKthHistWords = kKthBins / 32 * 36;
+
+// HIST_WORDS: more of them where the histogram's room serves as a list between its uses (kth_largest_lds).
+template <int THREADS, int HIST_WORDS = kKthHistWords>
 struct KthShared {
   static constexpr int kWaves = THREADS / kWave;
-  __attribute__((aligned(16))) uint32_t hist[kKthBins / 32 * 36];
+  __attribute__((aligned(16))) uint32_t hist[HIST_WORDS];
   __attribute__((aligned(16))) uint32_t lo[kWaves], hi[kWaves];
   uint32_t cand[kKthMaxCand];
   uint32_t n_cand, bin, rem, cnt;
 };
 
 // What the steps below share: v[j] is score 64 j + lane of the wavefront's share, NaN beyond the share's `lim` scores.
-template <int THREADS, int KPT>
+template <int THREADS, int KPT, class Shared = KthShared<THREADS>>
 struct Kth {
   static constexpr int kWaves = THREADS / kWave;
-  KthShared<THREADS>& sh;
+  Shared& sh;
   float (&v)[KPT];
   int& lim;
   uint32_t T = 0, need = 0;  // the result (see kth_largest)
 
   __device__ __forceinline__ bool valid(int j) const { return j * kWave + lane_id() < lim; }
   __device__ __forceinline__ void clear_hist() {
-    for (int i = threadIdx.x; i < kKthBins / 32 * 36; i += THREADS) sh.hist[i] = 0;
+    for (int i = threadIdx.x; i < kKthHistWords; i += THREADS) sh.hist[i] = 0;
   }
   // Called by the first wavefront: the bin that holds the rem-th largest of what was counted, what is left of rem inside
   // it, and how many it holds.
@@ -278,10 +281,10 @@ struct Kth {
 
 // 1 <= rank <= number of scores.  Returns the key of the rank-th largest in T, and in `need` how many of the scores
 // equal to it are among the rank largest.  Called by the whole workgroup; sh is not in use by others.
-template <int THREADS, int KPT>
-__device__ __forceinline__ void kth_largest(KthShared<THREADS>& sh, float (&v)[KPT], int& lim, uint32_t rank, uint32_t& T,
+template <int THREADS, int KPT, class Shared>
+__device__ __forceinline__ void kth_largest(Shared& sh, float (&v)[KPT], int& lim, uint32_t rank, uint32_t& T,
                                             uint32_t& need) {
-  Kth<THREADS, KPT> s{sh, v, lim};
+  Kth<THREADS, KPT, Shared> s{sh, v, lim};
   s.run(rank);
   T = s.T;
   need = s.need;
@@ -327,14 +330,14 @@ __device__ __forceinline__ void for_share(const LdsShare& sh, F f) {  // f(score
 }
 
 // The rem-th largest among the scores whose keys lie in [k_lo, k_hi], by 11-bit steps of the key range.
-template <int THREADS>
-__device__ __forceinline__ void kth_by_keys(KthShared<THREADS>& sh, const LdsShare& share, uint32_t rem, uint32_t k_lo,
+template <int THREADS, class Shared>
+__device__ __forceinline__ void kth_by_keys(Shared& sh, const LdsShare& share, uint32_t rem, uint32_t k_lo,
                                             uint32_t k_hi, uint32_t& T, uint32_t& need) {
   constexpr int kWaves = THREADS / kWave;
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   float none[1];
   int no_lim = 0;
-  Kth<THREADS, 1> s{sh, none, no_lim};
+  Kth<THREADS, 1, Shared> s{sh, none, no_lim};
   for (;;) {
     uint32_t kmin = 0xffffffffu, kmax = 0u;
     for_share<4>(share, [&](float x, int, bool exists) {
@@ -387,11 +390,16 @@ __device__ __forceinline__ void kth_by_keys(KthShared<THREADS>& sh, const LdsSha
 // bounds after all, everything is searched.
 // wave_gt and wave_eq: how many of the wavefront's scores are larger than and equal to the result.
 constexpr int kWideThreads = 1024;
-constexpr int kWideMaxKeys = 33 * 1024;  // next to 26 KiB of static LDS
+constexpr int kWideMaxKeys = 34 * 1024;  // next to 17 KiB of static LDS
 constexpr int kKthListPerWave = 256;  // on average 75 of a wavefront's 2048 scores lie between the bounds
+// The list takes the histogram's room: it is written after the sample's histogram has been read (a barrier between) and
+// read before the next one is cleared (another).
+using KthWideShared = KthShared<kWideThreads, kWideThreads / kWave * kKthListPerWave>;
 template <int THREADS>
-__device__ __forceinline__ void kth_largest_lds(KthShared<THREADS>& sh, float* list, const LdsShare& share, int n, uint32_t rank,
-                                                uint32_t& T, uint32_t& need, int& wave_gt, int& wave_eq) {
+__device__ __forceinline__ void kth_largest_lds(KthWideShared& sh, const LdsShare& share, int n, uint32_t rank, uint32_t& T,
+                                                uint32_t& need, int& wave_gt, int& wave_eq) {
+  static_assert(THREADS == kWideThreads && kWideThreads / kWave * kKthListPerWave >= kKthHistWords, "");
+  using Shared = KthWideShared;
   constexpr int kWaves = THREADS / kWave, kSamples = 4;
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   const float kInf = __builtin_inff();
@@ -405,7 +413,7 @@ __device__ __forceinline__ void kth_largest_lds(KthShared<THREADS>& sh, float* l
       const int at = (u * rows / kSamples) * kWave + lane;
       smp[u] = at < share.mine ? share.p[at] : __builtin_nanf("");
     }
-    Kth<THREADS, kSamples> s{sh, smp, lim};
+    Kth<THREADS, kSamples, Shared> s{sh, smp, lim};
     s.clear_hist();
     if (threadIdx.x == 0) sh.n_cand = 0;
     float mn, mx;
@@ -443,7 +451,7 @@ __device__ __forceinline__ void kth_largest_lds(KthShared<THREADS>& sh, float* l
       const float x_hi = b_hi < kKthBins ? mn + static_cast<float>(b_hi + 1) / steps : kInf;
       const float x_lo = b_lo > 0 ? mn + static_cast<float>(b_lo) / steps : -kInf;
       int n_gt = 0, n_in = 0;
-      float* mine = list + wave * kKthListPerWave;
+      float* mine = reinterpret_cast<float*>(sh.hist) + wave * kKthListPerWave;
       for_share<4>(share, [&](float x, int, bool exists) {
         const bool above = exists && x > x_hi, in = exists && x >= x_lo && x <= x_hi;
         const uint64_t mask = __ballot(in);

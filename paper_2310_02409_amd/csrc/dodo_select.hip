@@ -7,7 +7,7 @@
 // ascending position order, every token with key > T and the first `need` tokens with
 // key == T (lowest index wins ties).  Three forms by the longest sequence:
 //   <= 8192 tokens   the scores sit in registers            (select_topk_regs_kernel)
-//   <= 33792 tokens  the scores sit in LDS                  (select_topk_lds_kernel)
+//   <= 34816 tokens  the scores sit in LDS                  (select_topk_lds_kernel)
 //   longer           re-read from memory by a 4-pass, 8-bit MSB radix select (select_topk_kernel)
 // Sequences beyond 8192 tokens, given a workspace, are cut into chunks with a workgroup
 // each (select_topk_kernel<.., true>): the chunks' histograms of a radix pass are added
@@ -15,7 +15,7 @@
 // then picks the digit from the same totals; the compaction hands out output offsets
 // and the tie budget in chunk (= position) order in the same way.  Same result bit for
 // bit.  Its six exchanges take 20-24 us whatever the length: more than one workgroup
-// takes up to 33792 tokens (11 us for 16384, 16-21 us for 32768), less beyond.
+// takes up to 34816 tokens (11 us for 16384, 16-21 us for 32768), less beyond.
 #include "dodo_kth.h"
 
 namespace dodo {
@@ -426,8 +426,7 @@ __global__ __launch_bounds__(kWideThreads) void select_topk_lds_kernel(const flo
                                                                        int max_n, int32_t* __restrict__ nugget_idx) {
   constexpr int kWaves = kWideThreads / kWave;
   extern __shared__ float staged[];  // max_n scores
-  __shared__ KthShared<kWideThreads> sh;
-  __shared__ float list[kWaves * kKthListPerWave];
+  __shared__ KthWideShared sh;
   __shared__ int wave_gt[kWaves], wave_eq[kWaves];
   asm volatile("" ::"s"(scores), "s"(cu_seqlens), "s"(cu_nuggets), "s"(flags), "s"(max_n), "s"(nugget_idx));
   const int b = blockIdx.x;
@@ -452,7 +451,7 @@ __global__ __launch_bounds__(kWideThreads) void select_topk_lds_kernel(const flo
   const LdsShare share{staged + start, lim};
   uint32_t T, need;
   int cnt_gt, cnt_eq;
-  kth_largest_lds<kWideThreads>(sh, list, share, n_free, static_cast<uint32_t>(k_free), T, need, cnt_gt, cnt_eq);
+  kth_largest_lds<kWideThreads>(sh, share, n_free, static_cast<uint32_t>(k_free), T, need, cnt_gt, cnt_eq);
   if (lane == 0) {
     wave_gt[wave] = cnt_gt;
     wave_eq[wave] = cnt_eq;

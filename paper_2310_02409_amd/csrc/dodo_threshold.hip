@@ -48,17 +48,15 @@ __global__ __launch_bounds__(THREADS) void kth_regs_kernel(const float* __restri
 // against 29, 43 and (over several workgroups, in six launches) 40 us with the four radix passes over global memory below.
 __global__ __launch_bounds__(kWideThreads) void kth_lds_kernel(const float* __restrict__ sample, int n, int rank,
                                                                float* __restrict__ lambda_out) {
-  constexpr int kWaves = kWideThreads / kWave;
   extern __shared__ float staged[];  // n scores
-  __shared__ KthShared<kWideThreads> sh;
-  __shared__ float list[kWaves * kKthListPerWave];
+  __shared__ KthWideShared sh;
   const int rows = (n + kWideThreads - 1) / kWideThreads;
   const int start = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * rows * kWave;
   const int mine = max(0, min(rows * kWave, n - start));
   stage_share(staged + start, sample + start, mine);
   uint32_t T, need;
   int wave_gt, wave_eq;
-  kth_largest_lds<kWideThreads>(sh, list, LdsShare{staged + start, mine}, n, static_cast<uint32_t>(rank), T, need, wave_gt, wave_eq);
+  kth_largest_lds<kWideThreads>(sh, LdsShare{staged + start, mine}, n, static_cast<uint32_t>(rank), T, need, wave_gt, wave_eq);
   if (threadIdx.x == 0) *lambda_out = key_to_score(T);
 }
 

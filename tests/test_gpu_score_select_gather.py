@@ -254,7 +254,7 @@ def _hard_scores(kind, n, seed):
 
 
 # sizes at the edges of the forms of the kernel (scores in registers of 256, 512 or 1024 threads, in LDS, in memory)
-@pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20001, 33792, 33793])
+@pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20001, 33792, 33793, 34816, 34817])
 @pytest.mark.parametrize("kind", ["gauss", "ties", "three values", "exponents", "overflow", "rising", "specials", "constant"])
 def test_select_one_workgroup_per_sequence(D, n, kind):
     n_lens = [n, max(1, n // 3)]

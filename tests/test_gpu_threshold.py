@@ -63,7 +63,7 @@ def test_threshold_from_large_samples_over_many_workgroups(D, n, num, den, kind)
 
 
 # sizes at the edges of the forms of the kernel (scores in registers, in LDS, in memory)
-@pytest.mark.parametrize("n", [2, 64, 4096, 4097, 15000, 33792, 33793])
+@pytest.mark.parametrize("n", [2, 64, 4096, 4097, 15000, 33792, 33793, 34816, 34817])
 @pytest.mark.parametrize("kind", ["gauss", "ties", "exponents", "rising", "specials", "constant"])
 def test_threshold_from_sample_in_one_workgroup(D, n, kind):
     g = np.random.default_rng(n)
