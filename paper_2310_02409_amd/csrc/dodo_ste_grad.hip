@@ -18,15 +18,19 @@
 // wavefronts), and a wavefront computes S and dP with v_mfma_f32_32x32x16_bf16 so
 // that a nugget is a lane and a query row an accumulator register, and adds
 // P (dP - D) into a per-lane sum.  D of the next tile's rows comes from its dO and O
-// tiles, 8 rows per wavefront, while the matrix cores run.  No atomics: per-head sums go to
-// the workspace and a last kernel adds them in head order.  Other types and head
-// sizes take a plain kernel, with D from a kernel of its own.
+// tiles, 8 rows per wavefront, while the matrix cores run; with many nugget tiles, each
+// of which would read O and form D again, from a kernel of its own before it (the rule
+// is at the launch).  No atomics: per-head sums go to the workspace and a last kernel
+// adds them in head order.  Other types and head sizes take a plain kernel, with D from
+// the same kernel of its own.
 // Bound by the vector pipe (an exp2 per element of S) as much as by the matrix
 // pipe.  8 x 410 nuggets, 512 rows, 32 heads of 128: 48 us and no launch before
 // it (was 41.5 us after a 14 us kernel that made D and lse: forward and gradient
 // 135 -> 126 us); heads of 64 in the plain kernel: 2249 -> 33 us (4 x 250 nuggets,
-// 300 rows, 16 heads; 35 us with the sums of SteDims::kExact).  Error against 64
-// bits (2-norm): 2.6e-7 (was 3.8e-7).
+// 300 rows, 16 heads; 35 us with the sums of SteDims::kExact).  2 x 3277 nuggets,
+// 1024 rows, 32 heads of 128: 143 us with D in the kernel, 129 us with it before
+// (136 us before D moved into the kernel).  Error against 64 bits (2-norm), 512 rows,
+// 410 / 3277 nuggets: 2.9e-7 / 4.1e-7 (were 4.2e-7 / 4.7e-7).
 #include "dodo_common.h"
 
 namespace dodo {
@@ -43,16 +47,18 @@ constexpr int kNugTile = kGradWaves * kWaveNug;    // nuggets per workgroup
 constexpr int kQTile = 32;                         // query rows per step
 constexpr int kStagesSte = 3;
 constexpr int kLseChunk = 1024;                    // query rows whose lse sits in LDS at a time
-template <int DH>
+// PRE: D comes from ste_rowdot_kernel instead of the dO and O tiles.
+template <int DH, bool PRE>
 struct SteDims {
   static constexpr int kRowBytes = DH * 2;
   static constexpr int kPieces = kRowBytes / 16;            // 16-byte pieces of a row
   static constexpr int kRowsPerInstr = 64 / kPieces;        // rows that one direct load instruction brings
   static constexpr int kRowShift = DH == 128 ? 0 : 1;       // rows of 128 bytes cover half of the banks: swizzle by pairs
   static constexpr int kTileBytes = kQTile * kRowBytes;
-  static constexpr int kStageBytes = 3 * kTileBytes;        // Q tile, dO tile, O tile
+  static constexpr int kTensors = PRE ? 2 : 3;              // Q tile, dO tile, O tile
+  static constexpr int kStageBytes = kTensors * kTileBytes;
   static constexpr int kInstr = 8 / kRowsPerInstr;          // instructions per wavefront, tile and tensor
-  static constexpr int kLds = kStagesSte * kStageBytes + (kLseChunk + 2 * kQTile) * 4;
+  static constexpr int kLds = kStagesSte * kStageBytes + (kLseChunk + (PRE ? kLseChunk : 2 * kQTile)) * 4;
   // dP can start from -D, which saves a subtraction per element, but then every accumulation rounds away bits of D, the same
   // for all nuggets of a row; and a lane's sum over the tiles is a chain of rounded additions (4000 rows: 125 tiles).  Against
   // 64 bits (2-norm), 4000 rows, 16 heads of 64: 5.6e-7 so, 2.9e-7 with the subtraction and a compensated sum, in 2 to 8%
@@ -105,15 +111,15 @@ __global__ __launch_bounds__(256) void ste_rowdot_kernel(const void* __restrict_
   }
 }
 
-template <int DH>
+template <int DH, bool PRE>
 __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ dO, const uint16_t* __restrict__ O, const float* __restrict__ lse,
-    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_nuggets, int B, int H, int H_kv, int n_nug_tiles,
-    int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, float* __restrict__ partial) {
-  using SD = SteDims<DH>;
+    const float* __restrict__ aux_lse2, const float* __restrict__ aux_D, const int32_t* __restrict__ cu_q,
+    const int32_t* __restrict__ cu_nuggets, int B, int H, int H_kv, int n_nug_tiles, int64_t Sq, int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, float* __restrict__ partial) {
+  using SD = SteDims<DH, PRE>;
   constexpr int kRowBytes = SD::kRowBytes, kP = SD::kPieces, kRowShift = SD::kRowShift, kTileBytes = SD::kTileBytes;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, D or -D of two tiles
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, D or -D of two tiles or of the chunk
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
   // block i runs on XCD i % 8: the nugget tiles of one (sequence, head) sit on one XCD and share Q / dO / O in its L2
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   const int64_t row_stride = static_cast<int64_t>(H) * DH;  // elements between query rows
   const int64_t row0 = (static_cast<int64_t>(q0) * H + h) * DH;
   const int n_qtiles = (q_b + kQTile - 1) / kQTile;
-  constexpr int kLoads = 3 * SD::kInstr;  // direct loads per wavefront per tile
+  constexpr int kLoads = SD::kTensors * SD::kInstr;  // direct loads per wavefront per tile
   auto issue_tile = [&](int t) {
     const int tl = min(t, n_qtiles - 1);  // past the end: re-read the last tile into a stage nobody reads any more
     const uint32_t stage = lds_base + (t % kStagesSte) * SD::kStageBytes;
@@ -153,7 +159,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       const uint32_t dst = stage + r8 * kRowBytes;
       dma16_uniform(Q + row0, voff, __builtin_amdgcn_readfirstlane(dst));
       dma16_uniform(dO + row0, voff, __builtin_amdgcn_readfirstlane(dst + kTileBytes));
-      dma16_uniform(O + row0, voff, __builtin_amdgcn_readfirstlane(dst + 2 * kTileBytes));
+      if (!PRE) dma16_uniform(O + row0, voff, __builtin_amdgcn_readfirstlane(dst + 2 * kTileBytes));
     }
   };
   if (n_qtiles > 0) {
@@ -165,8 +171,17 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   float* lse2_l = reinterpret_cast<float*>(lds + kStagesSte * SD::kStageBytes);
   float* dd_l = lse2_l + kLseChunk;
   auto load_lse = [&](int r0) {
-    for (int r = tid; r < min(kLseChunk, n_qtiles * kQTile - r0); r += kGradThreads)
-      lse2_l[r] = r0 + r < q_b ? lse[static_cast<int64_t>(q0 + r0 + r) * H + h] * kLog2e : __builtin_inff();
+    for (int r = tid; r < min(kLseChunk, n_qtiles * kQTile - r0); r += kGradThreads) {
+      const bool ok = r0 + r < q_b;
+      if (PRE) {
+        const int64_t at = static_cast<int64_t>(h) * Sq + q0 + r0 + r;
+        const float D = ok ? aux_D[at] : 0.f;
+        lse2_l[r] = ok ? aux_lse2[at] : __builtin_inff();
+        dd_l[r] = SD::kExact ? D : -D;
+      } else {
+        lse2_l[r] = ok ? lse[static_cast<int64_t>(q0 + r0 + r) * H + h] * kLog2e : __builtin_inff();
+      }
+    }
   };
   load_lse(0);
 
@@ -213,10 +228,11 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     acc = lanes_sum<8>(acc);
     if (d_sub == 0) dd_l[(t & 1) * kQTile + d_row] = SD::kExact ? acc : -acc;
   };
-  if (n_qtiles > 0) row_dots(0);
+  if (!PRE && n_qtiles > 0) row_dots(0);
 
   float ds[2] = {0.f, 0.f}, lost[2] = {0.f, 0.f};  // sum, and what its additions rounded away
   for (int t = 0; t < n_qtiles; ++t) {
+    if (PRE) __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t has landed, t+1 may be in flight
     __syncthreads();  // everyone's part of tile t has landed, its D is there; tile t-1 has been read by everyone
     const int c0 = t * kQTile % kLseChunk;
     if (c0 == 0 && t > 0) {
@@ -224,6 +240,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       __syncthreads();
     }
     issue_tile(t + 2);
+    const float* dd_t = dd_l + (PRE ? c0 : (t & 1) * kQTile);
     const char* stg = lds + (t % kStagesSte) * SD::kStageBytes;
     floatx16 acc_s[2], acc_p[2];
     if (active) {
@@ -234,7 +251,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       if (!SD::kExact) {
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
-          const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
+          const float4 dd = *reinterpret_cast<const float4*>(dd_t + 8 * vq + 4 * g);
           first[4 * vq] = dd.x; first[4 * vq + 1] = dd.y; first[4 * vq + 2] = dd.z; first[4 * vq + 3] = dd.w;
         }
       }
@@ -258,8 +275,10 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
         }
       }
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t+1 has landed, t+2 may be in flight
-    row_dots(t + 1);  // (past the end: of the last tile again, not used)
+    if (!PRE) {
+      __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t+1 has landed, t+2 may be in flight
+      row_dots(t + 1);  // (past the end: of the last tile again, not used)
+    }
     if (!active) continue;
     // accumulator v of a block is query row 8 (v / 4) + 4 g + v % 4 of the tile, for this lane's nugget; a tile's rows are
     // summed before they join the others (shorter chains of rounded additions)
@@ -270,7 +289,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       const float l2v[4] = {l2.x, l2.y, l2.z, l2.w};
       float ddv[4] = {0.f, 0.f, 0.f, 0.f};
       if (SD::kExact) {
-        const float4 dd = *reinterpret_cast<const float4*>(dd_l + (t & 1) * kQTile + 8 * vq + 4 * g);
+        const float4 dd = *reinterpret_cast<const float4*>(dd_t + 8 * vq + 4 * g);
         ddv[0] = dd.x; ddv[1] = dd.y; ddv[2] = dd.z; ddv[3] = dd.w;
       }
 #pragma unroll
@@ -413,36 +432,50 @@ extern "C" int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn
   const float scale_log2e = softmax_scale * kLog2e;
   const bool mfma = dtype == DODO_DTYPE_BF16 && (d_h == 128 || d_h == 64) &&
                     static_cast<int64_t>(max_q) * H * d_h * 2 < 0x7fffffffLL;  // row offsets of a sequence in 32 bits
+  const auto row_dots = [&]() {
+    const unsigned blocks = static_cast<unsigned>((Sq * H * 16 + 255) / 256);
+    if (dtype == DODO_DTYPE_BF16)
+      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_BF16>, dim3(blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h, aux_lse2,
+                         aux_D);
+    else
+      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_F32>, dim3(blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h, aux_lse2,
+                         aux_D);
+    return launch_status();
+  };
   int rc;
   if (mfma) {
     const int n_nug_tiles = (max_k + kNugTile - 1) / kNugTile;
     const int64_t bh8 = (static_cast<int64_t>(B) * H + 7) / 8 * 8;
     const int64_t grid = bh8 * n_nug_tiles;
     if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
+    // D in the kernel costs about 0.3 us for every query tile that a compute unit's workgroups walk over, a kernel of
+    // its own 2 us and the reading of dO and O (5 TB/s; both in tenths of a us below).  Measured, 32 heads, in the kernel /
+    // before it: 8 x 512 rows, 410 nuggets 56.5 / 62.0 us, 1280 nuggets 123 / 119 us; 1 x 1024 rows, 1000 nuggets 50.4 / 46.7
+    // us; 2 x 1024 rows, 3277 nuggets 143 / 131 us; 1 x 128 rows, 1280 nuggets 15.0 / 16.2 us.  (Heads of 64: level.)
+    const int64_t steps = (grid + compute_units() - 1) / compute_units() * ((max_q + kQTile - 1) / kQTile);
+    const bool pre = d_h == 128 && 3 * steps > 20 + Sq * H / 1000;
+    if (pre) {
+      rc = row_dots();
+      if (rc != DODO_OK) return rc;
+    }
     const auto launch = [&](auto kern, int lds_bytes) {
       const int rc_lds = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes);
       if (rc_lds != DODO_OK) return rc_lds;
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kGradThreads), lds_bytes, s,
                          static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(Kn),
                          static_cast<const uint16_t*>(Vn), static_cast<const uint16_t*>(dO),
-                         static_cast<const uint16_t*>(O), lse, cu_q, cu_nuggets, B, H, H_kv, n_nug_tiles, Kt, tok_stride,
-                         head_stride, scale_log2e, partial);
+                         static_cast<const uint16_t*>(O), lse, aux_lse2, aux_D, cu_q, cu_nuggets, B, H, H_kv, n_nug_tiles,
+                         Sq, Kt, tok_stride, head_stride, scale_log2e, partial);
       return DODO_OK;
     };
-    rc = d_h == 128 ? launch(ste_grad_mfma_kernel<128>, SteDims<128>::kLds) : launch(ste_grad_mfma_kernel<64>, SteDims<64>::kLds);
+    rc = pre          ? launch(ste_grad_mfma_kernel<128, true>, SteDims<128, true>::kLds)
+         : d_h == 128 ? launch(ste_grad_mfma_kernel<128, false>, SteDims<128, false>::kLds)
+                      : launch(ste_grad_mfma_kernel<64, false>, SteDims<64, false>::kLds);
     if (rc != DODO_OK) return rc;
   } else {
     if (H > 65535) return DODO_ERR_UNSUPPORTED;
-    const unsigned rd_blocks = static_cast<unsigned>((Sq * H * 16 + 255) / 256);
     const dim3 grid(static_cast<unsigned>(Kt), static_cast<unsigned>(H));
-    if (dtype == DODO_DTYPE_BF16) {
-      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_BF16>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
-                         aux_lse2, aux_D);
-    } else {
-      hipLaunchKernelGGL(ste_rowdot_kernel<DODO_DTYPE_F32>, dim3(rd_blocks), dim3(256), 0, s, dO, O, lse, Sq, H, d_h,
-                         aux_lse2, aux_D);
-    }
-    rc = launch_status();
+    rc = row_dots();
     if (rc != DODO_OK) return rc;
     if (dtype == DODO_DTYPE_BF16) {
       hipLaunchKernelGGL(ste_grad_plain_kernel<DODO_DTYPE_BF16>, grid, dim3(kWave), 0, s, Q, Kn, Vn, dO, aux_lse2, aux_D,

@@ -80,6 +80,11 @@ def test_mfma_kernel_bf16(D, q_lens, k_lens, m_lens, H, H_kv):
     ([33, 200], [130, 257], [0, 100], 2, 2, 64),
     ([1024, 1025], [70, 64], [1024, 1025], 1, 1, 64),
     ([1025, 1024], [64, 70], [1025, 1024], 1, 1, 128),
+    # six nugget tiles: D in the kernel, and in a kernel of its own; the first of these over more than one chunk
+    ([192, 5], [1290, 1281], [40, 5], 2, 1, 128),
+    ([224, 5], [1290, 1281], [40, 5], 2, 1, 128),
+    ([224], [1290], [40], 2, 2, 64),
+    ([1030, 1024, 1033, 1030], [20, 64, 5, 33], [2, 2, 0, 2], 20, 20, 128),
 ])
 def test_mfma_kernel_head_sizes_and_chunks(D, q_lens, k_lens, m_lens, H, H_kv, d_h):
     t, cu = _case(702, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16)
