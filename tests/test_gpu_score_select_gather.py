@@ -248,6 +248,10 @@ def _hard_scores(kind, n, seed):
         s[1::11] = np.inf
         s[2::13] = -np.inf
         s[4::17] = -0.0
+    elif kind == "subnormals":
+        s = (s * np.float32(1e-39)).astype(np.float32)
+    elif kind == "some subnormals":  # as good as equal in steps of the range, and yet different
+        s[::2] = (s[::2] * np.float32(1e-41)).astype(np.float32)
     elif kind == "constant":
         s[:] = -2.5
     return s
@@ -255,7 +259,8 @@ def _hard_scores(kind, n, seed):
 
 # sizes at the edges of the forms of the kernel (scores in registers of 256, 512 or 1024 threads, in LDS, in memory)
 @pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20001, 33792, 33793, 34816, 34817])
-@pytest.mark.parametrize("kind", ["gauss", "ties", "three values", "exponents", "overflow", "rising", "specials", "constant"])
+@pytest.mark.parametrize("kind", ["gauss", "ties", "three values", "exponents", "overflow", "rising", "specials", "subnormals",
+                                  "some subnormals", "constant"])
 def test_select_one_workgroup_per_sequence(D, n, kind):
     n_lens = [n, max(1, n // 3)]
     scores = np.concatenate([_hard_scores(kind, m, 7 * n + i) for i, m in enumerate(n_lens)])
