@@ -645,13 +645,12 @@ def run_c5(torch, D, W, clock, dev, args):
     cu_s, cu_q, cu_l = sets[0]["cu_seqlens"], sets[0]["cu_q"], sets[0]["cu_local"]
     ws_bytes = D.dodo_nugget_attention_workspace_bytes(B, wl.H, wl.d_h, 1, max_k, m_dec + 64, D.BF16)
     ws = torch.zeros(max(ws_bytes, 16), dtype=torch.uint8, device=dev)
-    sel_ws = torch.zeros(max(D.dodo_select_topk_workspace_bytes(B, max_n), 16), dtype=torch.uint8, device=dev)
     for g in sets:
         D.dodo_score(g["hidden"], g["w"], 0.0, g["scores"])
         g["qscores"].copy_(W.quantise16(g["scores"]))  # the workload's 16-level tie stress (input preparation)
     fns = {
         "score": lambda g: D.dodo_score(g["hidden"], g["w"], 0.0, g["scores"]),
-        "select": lambda g: D.dodo_select_topk(g["qscores"], cu_s, cu_k, max_n, max_k, Kt, D.FORCE_LAST, g["idx"], ws=sel_ws),
+        "select": lambda g: D.dodo_select_topk(g["qscores"], cu_s, cu_k, max_n, max_k, Kt, D.FORCE_LAST, g["idx"]),
         "gather": lambda g: D.dodo_gather_nuggets(g["K"], g["V"], g["idx"], cu_s, cu_k, Kt, D.TOKEN_MAJOR, g["Kn"], g["Vn"]),
         "attn_block": lambda g: D.dodo_nugget_attention(g["Q"], g["Kn"], g["Vn"], g["Kl"], g["Vl"], cu_q, cu_k, cu_l, max_q,
                                                         max_k, max_m, scale, D.TOKEN_MAJOR, g["O"]),
@@ -673,7 +672,6 @@ def run_c5(torch, D, W, clock, dev, args):
     table["select"].pop("frac_of_hbm_peak")
     table["select"]["bound"] = "latency"
     add_pipeline_times(table, clock.pipeline(sets, fns), work)
-    assert int(sel_ws.view(torch.int32)[0]) == 0, "dodo_select_topk reported a failed wait"
     tg = table["select"]["avg_us"] + table["gather"]["avg_us"]
     table["topk_plus_gather_GBps"] = round((work["select"]["bytes"] + work["gather"]["bytes"]) / tg * 1e-3, 1)
     table["attn_block"]["query_tokens_per_s"] = round(sum(wl.q_lens) / table["attn_block"]["in_pipeline_us"] * 1e6)

@@ -119,8 +119,9 @@ int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const vo
 
 /* Bytes of device workspace dodo_select_topk can use for B sequences of at most max_n tokens (0 for short
  * sequences).  With it, long sequences are split over several workgroups that exchange histograms and counts
- * through it; without it (NULL or too small) one workgroup per sequence does the same work: at least as fast up to
- * 34816 tokens, more slowly beyond.
+ * through it; without it (NULL or too small) one workgroup per sequence does the same work: faster up to 34816 tokens
+ * (16384: 11 against 20-24 us; 32768: 16 to 22 against 20-24 us), more slowly beyond.  So a caller had better pass none
+ * up to there.
  * The workspace must be zero-filled before its first use; a call leaves it zero-filled (apart from the status
  * word), so it can be reused by the next call as it is.  It must not be shared by calls that may overlap in time.
  * The workgroups of a sequence wait for each other (bounded: about 0.1 s), so they must be able to run at the
@@ -142,7 +143,7 @@ size_t dodo_select_topk_workspace_bytes(int32_t B, int32_t max_n);
  * tokens with the highest score, in ascending order.  Equal scores: the lower
  * index wins.  NaN ranks below -inf; -0 equals +0.  With DODO_TOPK_FORCE_LAST
  * token n_b-1 is always selected and the other k_b-1 are the best of the rest.
- * Only integer comparisons on the score bits are used: the result is unique
+ * Scores are only compared, never rounded: the result is unique
  * and bit-exact.  max_n / max_k are host-side upper bounds on n_b / k_b
  * (0 < max_k <= max_n); a sequence longer than max_n is left unprocessed.
  * ws is optional (see dodo_select_topk_workspace_bytes); the result does not depend on it.  B == 0 is a no-op.
@@ -347,8 +348,9 @@ int dodo_nugget_attention_segments(const void* Q, const void* Kn, const void* Vn
  * adds to it (the sum over layers of Eq. 18: one call per layer), else it is overwritten.
  * grad_scale: softmax_scale if the score is added to the unscaled logit xi of Eq. 17, 1 if it is
  * added to the softmax input.  Sq = total query rows (host value); max_q / max_k bound q_b / k_b.
- * ws: dodo_ste_score_grad_workspace_bytes(Sq, H, Kt) bytes, contents irrelevant.
- * d_h % 8 == 0; bf16 with d_h = 128 runs on the matrix cores, everything else in a plain kernel.
+ * ws: dodo_ste_score_grad_workspace_bytes(Sq, H, Kt) bytes, contents irrelevant (2 Sq H floats of it only for calls that
+ * take dO.O of the rows from a kernel of its own, which depends on the sizes).
+ * d_h % 8 == 0; bf16 with d_h = 128 or 64 runs on the matrix cores, everything else in a plain kernel.
  * Deterministic (fixed summation order, no atomics).
  */
 size_t dodo_ste_score_grad_workspace_bytes(int64_t Sq, int32_t H, int64_t Kt);
@@ -364,7 +366,7 @@ int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn, const voi
  * k = dodo_nugget_count(n, num, den), writes to *lambda_out (device, fp32) the (k+1)-th highest
  * of the n sampled scores (device, fp32), so that exactly k of them exceed it when there are no
  * ties; NaN ranks lowest, -0 counts as +0.  If k >= n, or that score is NaN, the threshold is
- * -inf (keep everything).  Integer comparisons on the score bits only: bit-exact.  n >= 1.
+ * -inf (keep everything).  Scores are only compared: bit-exact.  n >= 1.
  * ws is optional (dodo_threshold_from_sample_workspace_bytes(n) bytes, contents irrelevant; 0 for small samples):
  * with it a sample beyond 34816 scores is histogrammed by many workgroups, one launch per radix pass; without it
  * (NULL or too small) one workgroup does the same work, more slowly.  The result does not depend on it.

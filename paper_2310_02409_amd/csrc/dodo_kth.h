@@ -1,5 +1,6 @@
 // The `rank`-th largest of the scores that one workgroup holds in its registers: shared by the TopK selection and the
-// threshold calibration.  Integer comparisons decide (order_key), so the result is unique.
+// threshold calibration.  Comparisons alone decide (of order_key, or of the scores to the same effect), so the result is
+// unique.
 //
 // Latency is all there is (a few thousand scores, microseconds), so the work is arranged for few barriers: one
 // histogram over 2048 equal steps of the scores' own range [min, max] leaves a handful of scores in the bin that holds

@@ -1,7 +1,8 @@
 // dodo_select_topk: per-sequence TopK of the scorer output (Eq. 14 of the Dodo
 // paper) plus the ordered, segmented compaction that writes the nugget index
-// lists.  Integer comparisons decide (an order-preserving uint32 key per score: NaN
-// lowest, -0 == +0), so the result is unique and bit-exact.
+// lists.  Comparisons alone decide (of an order-preserving uint32 key per score: NaN
+// lowest, -0 == +0; or of the scores themselves, to the same effect), so the result is
+// unique and bit-exact.
 // One workgroup per sequence: it finds the key T of the k-th best token and how many
 // tokens equal to T are still needed (dodo_kth.h), then a stable compaction emits, in
 // ascending position order, every token with key > T and the first `need` tokens with
@@ -23,7 +24,7 @@ namespace {
 
 constexpr int kStagedMaxKeys = 34 * 1024;  // longest chunk: 136 KiB of the 160 KiB LDS
 constexpr int kCandCap = 8192;             // candidate list after the first pass: 16-bit positions, 16 KiB
-constexpr int kMultiMinKeys = 8192;        // sequences longer than this are worth several workgroups
+constexpr int kMultiMinKeys = 8192;        // longer sequences are cut into chunks if the caller gives a workspace (up to kWideMaxKeys it had better not)
 constexpr int kMultiChunkKeys = 4096;      // aimed-at keys per workgroup
 constexpr int kMaxChunks = 16;
 // workspace of the chunked form: a header whose first word is the status word, then per sequence 4 histograms,
@@ -551,7 +552,7 @@ extern "C" int dodo_select_topk(const float* scores, const int32_t* cu_seqlens, 
   if (G > 0 && ws != nullptr && ws_bytes >= (kWsHeader + static_cast<size_t>(B) * kWsPerSeq) * sizeof(uint32_t) &&
       (reinterpret_cast<uintptr_t>(ws) & 3u) == 0)
     return launch_select_chunked(scores, cu_seqlens, cu_nuggets, B, max_n, G, flags, nugget_idx, static_cast<uint32_t*>(ws), s);
-  // one workgroup per sequence, as many threads as leave each a few scores (up to 34 where 1024 are not enough)
+  // one workgroup per sequence, as many threads as leave each a few scores (up to 8 where 1024 are not enough)
 #define DODO_SELECT_REGS(THREADS, KPT) \
   if (max_n <= THREADS * KPT)          \
   return launch_select_regs<THREADS, KPT>(scores, cu_seqlens, cu_nuggets, B, max_n, flags, nugget_idx, s)
