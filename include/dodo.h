@@ -120,7 +120,7 @@ int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const vo
 /* Bytes of device workspace dodo_select_topk can use for B sequences of at most max_n tokens (0 for short
  * sequences).  With it, long sequences are split over several workgroups that exchange histograms and counts
  * through it; without it (NULL or too small) one workgroup per sequence does the same work: faster up to 34816 tokens
- * (16384: 11 against 20-24 us; 32768: 16 to 22 against 20-24 us), more slowly beyond.  So a caller had better pass none
+ * (16384: 11 against 20-24 us; 32768: 16 to 23 against 20-25 us), more slowly beyond.  So a caller had better pass none
  * up to there.
  * The workspace must be zero-filled before its first use; a call leaves it zero-filled (apart from the status
  * word), so it can be reused by the next call as it is.  It must not be shared by calls that may overlap in time.
