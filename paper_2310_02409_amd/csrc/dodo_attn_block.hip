@@ -27,6 +27,15 @@
 // separated by workgroup barriers: while one group issues the 32 MFMAs of
 // "PV(t-1), then S(t)", the other does the softmax of its tile.  Small query
 // blocks (<= 128 rows) use a plain 4-wavefront kernel.
+//
+// What bounds the 8-wavefront kernel: the two phases are about equally long (cycle
+// counter, 3277 nuggets: 1200 cycles of matrix instructions, 1088 of them the pipe's
+// own; softmax 920 and tile requests 320 beside them; 75 for the barrier).  Row sums
+// from 16x16x32 products (a 33rd block of V^T took twice the matrix cycles), tile
+// requests whose limits are the buffer's range instead of clamps per lane, masks by
+// bit selects, the row maximum taken in the first tile only: 2048 rows, 103 nuggets,
+// 16 x 40 heads 812 -> 772 us (931 -> 981 TFLOP/s); 1024 rows, 3277 nuggets, 2 x 32
+// heads 119 -> 113 us; 512 rows, 410 nuggets, 8 x 32 heads 75.5 -> 72.6 us.
 #include <type_traits>
 
 #include "dodo_attn.h"
@@ -37,6 +46,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short shortx4;
 typedef __attribute__((ext_vector_type(8))) short shortx8;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(8))) float floatx8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 
@@ -92,66 +102,60 @@ struct TileLoader {
     v_piece_bytes = ((((pos >> 2) ^ ((row0 >> kRowShift) & kGranMask)) << 2) | (pos & 3)) * 16u;
     lds_chunk0 = wave * kPerWave * 1024;
   }
-  // Rows past the end of the region re-read its last row (finite data, masked later).
-  __device__ __forceinline__ void issue(const uint16_t* kbase, const uint16_t* vbase, uint32_t stride_bytes, int cnt,
-                                        uint32_t lds_k, uint32_t lds_v) const {
+  template <bool IS_V>
+  __device__ __forceinline__ uint32_t piece_bytes(int row) const {
+    return IS_V ? v_piece_bytes : (pos ^ ((row >> kRowShift) & (kP - 1))) * 16u;
+  }
+  // Byte offsets of this lane's loads from the tile's first row, `stride_bytes` apart
+  template <bool IS_V>
+  __device__ __forceinline__ void offsets(uint32_t stride_bytes, uint32_t (&off)[kPerWave]) const {
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
       const int row = row0 + kRowsPerInstr * u;
-      const uint32_t roff = static_cast<uint32_t>(min(row, cnt - 1)) * stride_bytes;
-      const uint32_t k_piece_bytes = (pos ^ ((row >> kRowShift) & (kP - 1))) * 16u;
-      dma16_uniform(kbase, roff + k_piece_bytes, __builtin_amdgcn_readfirstlane(lds_k + lds_chunk0 + u * 1024));
-      dma16_uniform(vbase, roff + v_piece_bytes, __builtin_amdgcn_readfirstlane(lds_v + lds_chunk0 + u * 1024));
+      off[u] = static_cast<uint32_t>(row) * stride_bytes + piece_bytes<IS_V>(row);
     }
   }
-  // 64 rows in the V arrangement only
-  __device__ __forceinline__ void issue_rows_v(const uint16_t* base, uint32_t stride_bytes, int cnt, uint32_t lds_dst) const {
-#pragma unroll
-    for (int u = 0; u < kPerWave; ++u) {
-      const uint32_t roff = static_cast<uint32_t>(min(row0 + kRowsPerInstr * u, cnt - 1)) * stride_bytes;
-      dma16_uniform(base, roff + v_piece_bytes, __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
-    }
-  }
-  // 64 rows in the K arrangement only (also used for the query rows)
-  __device__ __forceinline__ void issue_rows(const uint16_t* base, uint32_t stride_bytes, int cnt, uint32_t lds_dst) const {
+  // The same with the rows taken through an index list: row r of the tile is token idx[r] (idx points into LDS at the
+  // tile's first entry; rows past the last of `cnt` re-read that one)
+  template <bool IS_V>
+  __device__ __forceinline__ void offsets_idx(uint32_t stride_bytes, int cnt, const int32_t* idx, uint32_t (&off)[kPerWave]) const {
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
       const int row = row0 + kRowsPerInstr * u;
-      const uint32_t roff = static_cast<uint32_t>(min(row, cnt - 1)) * stride_bytes;
-      dma16_uniform(base, roff + (pos ^ ((row >> kRowShift) & (kP - 1))) * 16u, __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
+      off[u] = static_cast<uint32_t>(idx[min(row, cnt - 1)]) * stride_bytes + piece_bytes<IS_V>(row);
     }
   }
-  // The same three with the rows taken through an index list: row r of the tile is token idx[r] of `base`
-  // (idx points into LDS at the tile's first entry).
-  __device__ __forceinline__ void issue_idx(const uint16_t* kbase, const uint16_t* vbase, uint32_t stride_bytes, int cnt,
-                                            uint32_t lds_k, uint32_t lds_v, const int32_t* idx) const {
+  // V's offsets from K's of the same rows
+  __device__ __forceinline__ void k_to_v(const uint32_t (&k)[kPerWave], uint32_t (&v)[kPerWave]) const {
 #pragma unroll
-    for (int u = 0; u < kPerWave; ++u) {
-      const int row = row0 + kRowsPerInstr * u;
-      const uint32_t roff = static_cast<uint32_t>(idx[min(row, cnt - 1)]) * stride_bytes;
-      const uint32_t k_piece_bytes = (pos ^ ((row >> kRowShift) & (kP - 1))) * 16u;
-      dma16_uniform(kbase, roff + k_piece_bytes, __builtin_amdgcn_readfirstlane(lds_k + lds_chunk0 + u * 1024));
-      dma16_uniform(vbase, roff + v_piece_bytes, __builtin_amdgcn_readfirstlane(lds_v + lds_chunk0 + u * 1024));
-    }
+    for (int u = 0; u < kPerWave; ++u) v[u] = k[u] + (v_piece_bytes - piece_bytes<false>(row0 + kRowsPerInstr * u));
   }
-  __device__ __forceinline__ void issue_rows_v_idx(const uint16_t* base, uint32_t stride_bytes, int cnt, uint32_t lds_dst,
-                                                   const int32_t* idx) const {
+  // 64 rows at base + off, requested through a buffer that ends `range` bytes after base: what lies beyond fetches
+  // nothing and reads as zeros, so that neither the rows past a tile's last one nor a tile past the last need a test per
+  // lane.  Every call enqueues the same number of loads.
+  __device__ __forceinline__ void issue(const uint16_t* base, uint32_t range, const uint32_t (&off)[kPerWave], uint32_t lds_dst) const {
+    const uint64_t b = reinterpret_cast<uint64_t>(base);
+    u32x4_t buf;
+    buf.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b));
+    buf.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32) & 0xffffu);
+    buf.z = __builtin_amdgcn_readfirstlane(range);
+    buf.w = 0x00027000u;
 #pragma unroll
-    for (int u = 0; u < kPerWave; ++u) {
-      const uint32_t roff = static_cast<uint32_t>(idx[min(row0 + kRowsPerInstr * u, cnt - 1)]) * stride_bytes;
-      dma16_uniform(base, roff + v_piece_bytes, __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
-    }
-  }
-  __device__ __forceinline__ void issue_rows_idx(const uint16_t* base, uint32_t stride_bytes, int cnt, uint32_t lds_dst,
-                                                 const int32_t* idx) const {
-#pragma unroll
-    for (int u = 0; u < kPerWave; ++u) {
-      const int row = row0 + kRowsPerInstr * u;
-      const uint32_t roff = static_cast<uint32_t>(idx[min(row, cnt - 1)]) * stride_bytes;
-      dma16_uniform(base, roff + (pos ^ ((row >> kRowShift) & (kP - 1))) * 16u, __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
-    }
+    for (int u = 0; u < kPerWave; ++u) dma16_buffer(buf, off[u], __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
   }
 };
+
+// One bit per key of a 32-key block, set for the first `limit` of them (any limit).
+__device__ __forceinline__ uint32_t first_keys(int limit) {
+  const int n = min(32, max(0, limit));
+  return n == 32 ? 0xffffffffu : (1u << n) - 1u;
+}
+// x where bit `key` (a constant) is set, -inf elsewhere: a field extract and a bit select (a comparison would go through
+// the scalar registers, with two idle slots before each select)
+__device__ __forceinline__ float visible_or_neg_inf(float x, uint32_t bits, int key) {
+  const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(bits << (31 - key)) >> 31);
+  return __uint_as_float((__float_as_uint(x) & m) | (0xff800000u & ~m));
+}
 
 // Online-softmax update of one 32-row block for one 64-key tile.  acc holds the raw
 // S^T accumulators (two 32-key blocks); accumulator v of block kb <-> key 32kb + 8(v/4) + 4g + v%4.
@@ -160,19 +164,14 @@ template <bool MASK, int NCB>
 __device__ __forceinline__ void softmax_tile(floatx16 (&acc)[2], int limit, int g, float scale_log2e, float& m_run,
                                              float& l_run, floatx16 (&acc_o)[NCB], bf16x8 (&pf)[4]) {
   float tmax = kNegInf;
-  // The lane's part of the key index, 4 g, is taken off the limit, so that the comparisons are with constants: as 32 lane
-  // values the compiler kept the indices in registers across the loop (230 instead of 250 registers in the 8-wavefront
-  // kernel, 194 instead of 225 in the other; 64-row blocks 11.5 -> 10.2 us).
-  const int limit_g = limit - 4 * g;
+  // (the lane's part of the key index, 4 g, is taken off the limit, so that the bits' positions are constants)
+  const uint32_t bits[2] = {first_keys(limit - 4 * g), first_keys(limit - 4 * g - 32)};
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       float s = acc[kb][v] * scale_log2e;
-      if (MASK) {
-        const int key = 32 * kb + 8 * (v >> 2) + (v & 3);
-        s = (key < limit_g) ? s : kNegInf;
-      }
+      if (MASK) s = visible_or_neg_inf(s, bits[kb], 8 * (v >> 2) + (v & 3));
       acc[kb][v] = s;
       tmax = fmaxf(tmax, s);
     }
@@ -204,46 +203,36 @@ __device__ __forceinline__ void softmax_tile(floatx16 (&acc)[2], int limit, int 
   l_run += psum;
 }
 
-// Softmax update with a fixed exponent offset per row (used by the two-group kernel): the offset
-// m_off is the row maximum of the first tile the row sees and is never moved afterwards, so the
-// output accumulators are not rescaled -- O = sum(p v) / sum(p) does not depend on the offset.
-// An overflow of the fixed offset shows up as a non-finite row sum at the end, in which case the
-// caller redoes the rows with softmax_tile.  Needs scale_log2e > 0.
-template <bool MASK, bool SUMS>
-__device__ __forceinline__ void softmax_fixed(floatx16 (&acc)[2], int limit, int g, float scale_log2e, float& m_off,
-                                              float& l_run, bf16x8 (&pf)[4]) {
-  if (MASK) {
-    const int limit_g = limit - 4 * g;  // (see softmax_tile)
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int key = 32 * kb + 8 * (v >> 2) + (v & 3);
-        acc[kb][v] = (key < limit_g) ? acc[kb][v] : kNegInf;
-      }
-  }
-  if (__any(m_off == kNegInf)) {  // some row of this wavefront has no offset yet (first visible tile)
-    float tmax = kNegInf;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, acc[kb][v]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
-    m_off = (m_off == kNegInf) ? tmax * scale_log2e : m_off;  // such rows have all-zero accumulators
-  }
-  const float neg = (m_off == kNegInf) ? 0.f : -m_off;
-  float psum[2] = {0.f, 0.f};
+// Keys [0, limit) of the tile are visible to this lane's row.
+__device__ __forceinline__ void mask_tile(floatx16 (&acc)[2], int limit, int g) {
+  const uint32_t bits[2] = {first_keys(limit - 4 * g), first_keys(limit - 4 * g - 32)};
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      floatx8 p;
+    for (int v = 0; v < 16; ++v) acc[kb][v] = visible_or_neg_inf(acc[kb][v], bits[kb], 8 * (v >> 2) + (v & 3));
+}
+__device__ __forceinline__ float tile_max(const floatx16 (&acc)[2]) {
+  float tmax = kNegInf;
 #pragma unroll
-      for (int v = 0; v < 8; ++v) p[v] = exp2_hw(fmaf(acc[kb][8 * half + v], scale_log2e, neg));
-      if (SUMS) psum[kb] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-      pf[2 * kb + half] = __builtin_convertvector(p, bf16x8);  // hardware RNE pack
-    }
-  if (SUMS) l_run += psum[0] + psum[1];
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, acc[kb][v]);
+  return fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+}
+// Softmax with a fixed exponent offset per row (used by the two-group kernel): the offset m_off is the row maximum of
+// the first tile -- every row that sees anything sees keys of it -- and is never moved afterwards, so the output
+// accumulators are not rescaled: O = sum(p v) / sum(p) does not depend on the offset.  An overflow of the fixed offset
+// shows up as a non-finite row sum at the end, in which case the caller redoes the rows with softmax_tile.  Needs
+// scale_log2e > 0.
+__device__ __forceinline__ void softmax_fixed(const floatx16 (&acc)[2], float scale_log2e, float m_off, bf16x8 (&pf)[4]) {
+  const float neg = (m_off == kNegInf) ? 0.f : -m_off;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    floatx8 p;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) p[v] = exp2_hw(fmaf(acc[i >> 1][8 * (i & 1) + v], scale_log2e, neg));
+    pf[i] = __builtin_convertvector(p, bf16x8);  // hardware RNE pack
+  }
 }
 
 // NW = 4: plain loop, two workgroups per CU.  NW = 8: two groups of four wavefronts in
@@ -351,24 +340,56 @@ __device__ __forceinline__ void attend_query_block(
   const uint16_t* locK = Kl + (static_cast<int64_t>(l0) * H_kv + kvh) * kDH;
   const uint16_t* locV = Vl + (static_cast<int64_t>(l0) * H_kv + kvh) * kDH;
 
-  TileLoader<NW, DH> loader;
-  loader.init(wave, lane);
-  // Every call enqueues the same number of loads per lane (a tile past the end re-reads the last
-  // one into a stage nobody reads), so the vmcnt arithmetic of the loops is uniform.
-  auto issue_tile = [&](int tile) {
-    const int stage = tile % kStages;
-    const int tl = min(tile, n_tiles - 1);
-    const bool nug = tl < n_nug_tiles;
-    const int base = nug ? tl * kBN : (tl - n_nug_tiles) * kBN;
-    const int cnt = min(kBN, (nug ? k_b : wg_vis) - base);
+  // Who brings what of a tile: in the 4-wavefront kernel every wavefront a part of K and of V; in the 8-wavefront kernel
+  // the wavefronts of group 1 K and those of group 0 V.  Every request enqueues the same number of loads per lane (a tile
+  // past the end fetches nothing), so the vmcnt arithmetic of the loops is uniform.
+  TileLoader<4, DH> loader;
+  loader.init(wave & 3, lane);
+  constexpr int kPer = TileLoader<4, DH>::kPerWave;
+  constexpr int kLoadsPerTile = NW == 8 ? kPer : 2 * kPer;
+  uint32_t off[kPer];       // of the tensor that this wavefront's group brings (4 wavefronts: of K)
+  uint32_t off_stride = 0;  // the token stride that they were made for
+  auto request = [&](int tile, auto v_tag, auto both_tag) {
+    constexpr bool IS_V = decltype(v_tag)::value, BOTH = decltype(both_tag)::value;
+    const bool nug = tile < n_nug_tiles;
+    const int base = nug ? tile * kBN : (tile - n_nug_tiles) * kBN;
+    const int cnt = min(kBN, (nug ? k_b : wg_vis) - base);  // no more than 0 past the last tile
     const int64_t stride = nug ? nug_tok_stride : loc_stride;
+    const uint32_t stride_bytes = static_cast<uint32_t>(stride) * 2u;
+    const uint32_t dst = lds_base + (2 * (tile % kStages) + (IS_V ? 1 : 0)) * kTileBytes;
+    const uint16_t* ptr = nug ? (IS_V ? nugV : nugK) : (IS_V ? locV : locK);
+    const uint16_t* ptr_v = nug ? nugV : locV;
+    auto issue = [&](int64_t first, uint32_t range) {  // the region's row at element `first` is offset 0
+      loader.issue(ptr + first, range, off, dst);
+      if (BOTH) {
+        uint32_t off_v[kPer];
+        loader.k_to_v(off, off_v);
+        loader.issue(ptr_v + first, range, off_v, dst + kTileBytes);
+      }
+    };
     if (IDX && nug) {
-      loader.issue_idx(nugK, nugV, static_cast<uint32_t>(stride) * 2u, cnt, lds_base + (2 * stage) * kTileBytes,
-                       lds_base + (2 * stage + 1) * kTileBytes, idx_l + base);
+      loader.template offsets_idx<IS_V>(stride_bytes, cnt, idx_l + base, off);
+      off_stride = 0;
+      issue(0, 0x7fffffffu);  // (offsets from the sequence's first token, below 2^31: checked on the host)
     } else {
-      loader.issue((nug ? nugK : locK) + base * stride, (nug ? nugV : locV) + base * stride,
-                   static_cast<uint32_t>(stride) * 2u, cnt, lds_base + (2 * stage) * kTileBytes,
-                   lds_base + (2 * stage + 1) * kTileBytes);
+      if (off_stride != stride_bytes) {
+        loader.template offsets<IS_V>(stride_bytes, off);
+        off_stride = stride_bytes;
+      }
+      issue(base * stride, cnt > 0 ? static_cast<uint32_t>(cnt - 1) * stride_bytes + kRowBytes : 0u);
+    }
+  };
+  using K = std::false_type;
+  using V = std::true_type;
+  using Alone = std::false_type;
+  using WithV = std::true_type;
+  auto issue_tile = [&](int tile) {
+    if (NW == 4) {
+      request(tile, K{}, WithV{});
+    } else if (wave < 4) {
+      request(tile, V{}, Alone{});
+    } else {
+      request(tile, K{}, Alone{});
     }
   };
   // per-tile bookkeeping shared by the phases
@@ -391,18 +412,21 @@ __device__ __forceinline__ void attend_query_block(
   // through LDS like a K tile (whole rows per request; a lane fetching its own row from global
   // memory would touch 32 rows per instruction), into the stages that tiles 1.. (NW = 4) or 2..
   // (NW = 8) use later.  Q^T fragments: lane (j, g) holds Q[my_i][16*ds + 8*g .. +8) for ds = 0..7.
-  // Rows past the end of the sequence re-read its last row; nothing of them is stored.
-  constexpr int kLoadsPerTile = TileLoader<NW, DH>::kPerWave * 2;
+  // Rows past the end of the sequence read as zeros; nothing of them is stored.
   constexpr int kQSlot0 = NW == 8 ? 4 : 2;  // first 16 KiB slot of the query rows
   bf16x8 qf[kDH / 16];
   if (n_tiles > 0) {
     issue_tile(0);
+    TileLoader<NW, DH> q_loader;
+    q_loader.init(wave, lane);
+    uint32_t q_off[TileLoader<NW, DH>::kPerWave];
+    q_loader.template offsets<false>(static_cast<uint32_t>(H) * kRowBytes, q_off);
 #pragma unroll
     for (int c = 0; c < kBM / kBN; ++c) {
-      const int r0 = i0 + kBN * c;
-      const int64_t base_row = q0 + min(r0, q_b - 1);
-      loader.issue_rows(Q + (base_row * H + h) * kDH, static_cast<uint32_t>(H) * kRowBytes, max(1, min(kBN, q_b - r0)),
-                        lds_base + (kQSlot0 + c) * kTileBytes);
+      const int rows = min(kBN, q_b - i0 - kBN * c);
+      q_loader.issue(Q + (static_cast<int64_t>(q0 + i0 + kBN * c) * H + h) * kDH,
+                     rows > 0 ? static_cast<uint32_t>(rows - 1) * static_cast<uint32_t>(H) * kRowBytes + kRowBytes : 0u, q_off,
+                     lds_base + (kQSlot0 + c) * kTileBytes);
     }
     if (NW == 8) {
       issue_tile(1);
@@ -465,16 +489,15 @@ __device__ __forceinline__ void attend_query_block(
     }
   };
   // O^T += V^T P^T of one tile: V^T fragment s = 4*t + cb; slot 8g+4e+r of k-step t <-> key 16t + 8e + 4g + r.
-  // The two-group kernel takes the row sums of P from the matrix pipe as well, which has slack
-  // there while the softmax phase has none: P^T is also multiplied with a 33rd block of V^T whose
-  // only non-zero row is all ones, so accumulator row 0 of that block (lane j, g = 0, register 0)
-  // collects sum_k P[k][query] -- of the bf16-rounded P, exactly what O^T is accumulated from.
-  constexpr bool kOnesBlock = true;
-  floatx16 acc_l;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc_l[v] = 0.f;
-  const bf16x8 ones_frag = __builtin_bit_cast(
-      bf16x8, j == 0 ? make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u) : make_uint4(0, 0, 0, 0));
+  // The two-group kernel takes the row sums of P from the matrix pipe as well, of the bf16-rounded P, exactly what O^T is
+  // accumulated from: one 16x16x32 product per P^T fragment (half the cycles of a 33rd block of V^T).  Read as a 32 x 16
+  // operand, lane l of the fragment holds column l % 16 and keys of group l / 16: groups 0 and 2 are the keys of queries
+  // 0 .. 15, groups 1 and 3 those of queries 16 .. 31, so row 0 of the left operand has ones in groups 0 and 2, row 1 in
+  // groups 1 and 3, and accumulators 0 and 1 of lane n < 16 collect the sums of queries n and n + 16 over all keys.
+  floatx4 acc_l = {0.f, 0.f, 0.f, 0.f};
+  const bool sel_one = (lane & 15) == ((lane >> 4) & 1);
+  const bf16x8 sel_frag = __builtin_bit_cast(
+      bf16x8, sel_one ? make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u) : make_uint4(0, 0, 0, 0));
   auto read_vt = [&](int tile, int s) -> bf16x8 {
     const char* vbuf = lds + (2 * (tile % kStages) + 1) * kTileBytes + v_in;
     const int t = s / kNCB, cb = s % kNCB;
@@ -500,13 +523,6 @@ __device__ __forceinline__ void attend_query_block(
     }
   };
   bool bail = false;
-  auto softmax_fast = [&](const TileInfo& ti, floatx16 (&acc_s)[2], bf16x8 (&pf)[4]) {
-    if (ti.need_mask) {
-      softmax_fixed<true, !kOnesBlock>(acc_s, ti.limit, g, scale_log2e, m_run, l_run, pf);
-    } else {
-      softmax_fixed<false, !kOnesBlock>(acc_s, kBN, g, scale_log2e, m_run, l_run, pf);
-    }
-  };
   auto softmax = [&](const TileInfo& ti, floatx16 (&acc_s)[2], bf16x8 (&pf)[4]) {
     if (ti.need_mask) {
       softmax_tile<true, kNCB>(acc_s, ti.limit, g, scale_log2e, m_run, l_run, acc_o, pf);
@@ -560,8 +576,8 @@ __device__ __forceinline__ void attend_query_block(
           ring[s % kAhead] = read_k(t, s + kAhead - kSteps);
         }
         acc_o[s % kNCB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, pf[s / kNCB], acc_o[s % kNCB], 0, 0, 0);
-        if (kOnesBlock && (s % kNCB) == kNCB - 1)
-          acc_l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones_frag, pf[s / kNCB], acc_l, 0, 0, 0);
+        if ((s % kNCB) == kNCB - 1)
+          acc_l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel_frag, pf[s / kNCB], acc_l, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -579,40 +595,16 @@ __device__ __forceinline__ void attend_query_block(
       }
     };
     auto valu_work = [&](int t) {  // softmax of tile t, then the first V^T fragments for PV(t)
-      softmax_fast(tile_info(t), acc_s, pf);
+      const TileInfo ti = tile_info(t);
+      if (ti.need_mask) mask_tile(acc_s, ti.limit, g);
+      if (t == 0) m_run = tile_max(acc_s) * scale_log2e;  // (-inf: no key visible)
+      softmax_fixed(acc_s, scale_log2e, m_run, pf);
 #pragma unroll
       for (int s = 0; s < kAhead; ++s) ring[s] = read_vt(t, s);
     };
-    // In the loop a wavefront requests tiles where it would otherwise idle at a barrier, after its
-    // softmax: a request can take hundreds of cycles to issue when the memory pipeline is backed
-    // up.  The wavefronts of group 1 bring K of tile t+2 (during phase 2t), those of group 0 its V
-    // (during phase 2t+1), four requests per wavefront as in the prologue's split.
-    TileLoader<4, DH> half_loader;
-    half_loader.init(wave & 3, lane);
-    auto issue_half = [&](int tile, auto v_tag) {
-      constexpr bool IS_V = decltype(v_tag)::value;
-      const int stage = tile % kStages;
-      const int tl = min(tile, n_tiles - 1);
-      const bool nug = tl < n_nug_tiles;
-      const int base = nug ? tl * kBN : (tl - n_nug_tiles) * kBN;
-      const int cnt = min(kBN, (nug ? k_b : wg_vis) - base);
-      const int64_t stride = nug ? nug_tok_stride : loc_stride;
-      if (IDX && nug) {
-        if (IS_V) {
-          half_loader.issue_rows_v_idx(nugV, static_cast<uint32_t>(stride) * 2u, cnt,
-                                       lds_base + (2 * stage + 1) * kTileBytes, idx_l + base);
-        } else {
-          half_loader.issue_rows_idx(nugK, static_cast<uint32_t>(stride) * 2u, cnt, lds_base + (2 * stage) * kTileBytes,
-                                     idx_l + base);
-        }
-      } else if (IS_V) {
-        half_loader.issue_rows_v((nug ? nugV : locV) + base * stride, static_cast<uint32_t>(stride) * 2u, cnt,
-                                 lds_base + (2 * stage + 1) * kTileBytes);
-      } else {
-        half_loader.issue_rows((nug ? nugK : locK) + base * stride, static_cast<uint32_t>(stride) * 2u, cnt,
-                               lds_base + (2 * stage) * kTileBytes);
-      }
-    };
+    // In the loop a wavefront requests tiles in its softmax phase: a request can take hundreds of cycles to issue when the
+    // memory pipeline is backed up.  The wavefronts of group 1 bring K of
+    // tile t+2 (during phase 2t), those of group 0 its V (during phase 2t+1).
     auto end_odd_phase = [&](int t) {  // ends phase 2t+1: tile t+1 must have landed
       // younger requests of this wavefront in flight: two tiles' worth while the prologue's are pending, else one
       if (t == 0) {
@@ -630,7 +622,7 @@ __device__ __forceinline__ void attend_query_block(
       auto iteration = [&](int t, auto grp_tag, auto kind_tag) {
         constexpr int GRP = decltype(grp_tag)::value, KIND = decltype(kind_tag)::value;
         if (GRP == 1) {
-          if (t >= 2) issue_half(t + 2, std::false_type{});
+          if (t >= 2) request(t + 2, K{}, Alone{});
           if (KIND == 1 || KIND == 2) valu_work(t - 1);
           __syncthreads();
         }
@@ -648,7 +640,7 @@ __device__ __forceinline__ void attend_query_block(
         __builtin_amdgcn_s_setprio(0);
         if (GRP == 0) {
           __syncthreads();
-          if (t >= 2) issue_half(t + 2, std::true_type{});
+          if (t >= 2) request(t + 2, V{}, Alone{});
           if (KIND == 0 || KIND == 1) valu_work(t);
         }
         end_odd_phase(t);
@@ -672,8 +664,9 @@ __device__ __forceinline__ void attend_query_block(
       } else {
         run(std::integral_constant<int, 1>{});
       }
-      if (kOnesBlock) l_run = (g == 0) ? acc_l[0] : 0.f;
-      const float l_row = l_run + __shfl_xor(l_run, 32, kWave);
+      const float sum_lo = __shfl(acc_l[0], lane & 15, kWave), sum_hi = __shfl(acc_l[1], lane & 15, kWave);
+      const float l_row = (j & 16) ? sum_hi : sum_lo;
+      l_run = (g == 0) ? l_row : 0.f;
       bail = !(l_row - l_row == 0.f);  // +inf or NaN: some logit overflowed the row's fixed offset
     } else {
       bail = n_tiles > 0;
@@ -752,19 +745,26 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
     const int32_t* __restrict__ cu_nuggets, const int32_t* __restrict__ nug_len,
     const int32_t* __restrict__ cu_local, const int32_t* __restrict__ loc_len, const int32_t* __restrict__ nug_idx,
     const int32_t* __restrict__ cu_ctx,
-    int B, int H, int H_kv, int n_qblocks, int pair, int heavy_last, FastDiv div_groups, FastDiv div_H, FastDiv div_G,
+    int B, int H, int H_kv, int n_qblocks, int pair, int heavy_last, int heads_xcd, FastDiv div_heads_xcd, FastDiv div_groups, FastDiv div_H, FastDiv div_G,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse) {
   // all arguments in one round of scalar loads (the compiler would fetch them a few at a time, before each first use)
   asm volatile("" ::"s"(Q), "s"(Kn), "s"(Vn), "s"(Kl), "s"(Vl), "s"(cu_q), "s"(cu_nuggets), "s"(nug_len), "s"(cu_local),
                "s"(loc_len), "s"(nug_idx), "s"(cu_ctx), "s"(B), "s"(H), "s"(H_kv), "s"(n_qblocks), "s"(pair),
-               "s"(heavy_last), "s"(div_groups.mul), "s"(div_groups.shift), "s"(div_H.mul), "s"(div_H.shift),
+               "s"(heavy_last), "s"(heads_xcd), "s"(div_heads_xcd.mul), "s"(div_heads_xcd.shift), "s"(div_groups.mul), "s"(div_groups.shift), "s"(div_H.mul), "s"(div_H.shift),
                "s"(div_G.mul), "s"(div_G.shift), "s"(nug_tok_stride), "s"(nug_head_stride), "s"(scale_log2e), "s"(O),
                "s"(lse));
   const int n_groups = pair ? (n_qblocks + 1) >> 1 : n_qblocks;  // (div_groups divides by this)
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  // The i-th (sequence, head) pair of an XCD: heads_xcd consecutive heads of every sequence (ragged sequences weigh on all
+  // XCDs alike), starting at another head in each sequence, or every eighth pair (heads_xcd = 0).
+  auto pair_of = [&](int i, int x) -> int {
+    if (heads_xcd == 0) return i * 8 + x;
+    const int b = static_cast<int>(fast_div(static_cast<uint32_t>(i), div_heads_xcd));
+    return b * H + ((x + b) & 7) * heads_xcd + (i - b * heads_xcd);
+  };
   const int j = static_cast<int>(fast_div(static_cast<uint32_t>(slot), div_groups));
-  const int bh = j * 8 + xcd;
+  const int bh = pair_of(j, xcd);
   const int heavy = n_qblocks - 1 - (slot - j * n_groups), light = n_qblocks - 1 - heavy;
   if (bh >= B * H) return;
   // Two neighbouring workgroups of an XCD (j even and odd) share two (sequence, head) pairs
@@ -772,7 +772,7 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
   // the other the light block of the first and then the heavy block of the second.  Both carry the
   // same load, the two blocks that read the same K/V run at the same time and share it in L2, and
   // the bursts of first loads come from half of the compute units at a time.
-  const int bh_other = (j ^ 1) * 8 + xcd;
+  const int bh_other = pair_of(j ^ 1, xcd);
   const bool cross = pair && light != heavy && bh_other < B * H;
   int bh1 = bh, q1 = heavy, bh2 = bh, q2 = (pair && light != heavy) ? light : -1;
   if (cross) {
@@ -802,6 +802,17 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
   }
 }
 
+// Heads that an XCD gets of every sequence, next to each other (0: the pairs of sequence and head go to the XCDs in turn).
+// Heads are neighbours in a token's row of 256-byte pieces: with every eighth of them a tile's rows come from two of an
+// L2's sixteen channels, which the 8-wavefront kernel feels (8 sequences of 512 rows, 410 nuggets, 32 heads 72.7 -> 70.4 us;
+// 2048 rows, 103 nuggets, 40 heads the same), and the query heads of one K/V head are spread over all L2s (64 heads over 8:
+// 512 rows 66.7 -> 63.7 us, 128 rows 36.3 -> 33.1; 32 heads over 8, 64 rows 22.2 -> 19.3).  The 4-wavefront kernel, a few
+// tiles long, does better without where heads are not grouped (64 rows, 80 nuggets 11.05 against 11.2 us, 128 rows, 410
+// nuggets 26.45 against 26.8).
+int heads_per_xcd(const AttnParams& p, int waves) {
+  return p.H % 8 == 0 && (waves == 8 || p.H != p.H_kv) ? p.H / 8 : 0;
+}
+
 template <int NW, bool IDX, int DH>
 int launch_nw(const AttnParams& p) {
   using Cfg = BlockCfg<NW, DH>;
@@ -813,6 +824,7 @@ int launch_nw(const AttnParams& p) {
   const int pair = (n_qblocks >= 2 && bh8 * ((n_qblocks + 1) / 2) >= compute_units()) ? 1 : 0;
   const int64_t grid = bh8 * (pair ? (n_qblocks + 1) / 2 : n_qblocks);
   if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
+  const int heads_xcd = heads_per_xcd(p, NW);
   auto kern = block_attention_kernel<NW, IDX, DH>;
   if (kLds > 64 * 1024) {
     const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLds);
@@ -822,7 +834,7 @@ int launch_nw(const AttnParams& p) {
                      static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.Kn),
                      static_cast<const uint16_t*>(p.Vn), static_cast<const uint16_t*>(p.Kl),
                      static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, p.B, p.H, p.H_kv,
-                     n_qblocks, pair, p.heavy_last, make_fast_div(static_cast<uint32_t>(pair ? (n_qblocks + 1) / 2 : n_qblocks)),
+                     n_qblocks, pair, p.heavy_last, heads_xcd, make_fast_div(static_cast<uint32_t>(heads_xcd > 0 ? heads_xcd : 1)), make_fast_div(static_cast<uint32_t>(pair ? (n_qblocks + 1) / 2 : n_qblocks)),
                      make_fast_div(static_cast<uint32_t>(p.H)), make_fast_div(static_cast<uint32_t>(p.H / p.H_kv)),
                      p.nug_tok_stride, p.nug_head_stride, p.scale_log2e, static_cast<uint16_t*>(p.O), p.lse);
   return launch_status();

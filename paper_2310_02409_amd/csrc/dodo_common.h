@@ -92,6 +92,13 @@ __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, u
                : "memory", "m0");
 }
 
+// The same through a buffer descriptor (in scalar registers): lanes whose offset lies outside of its range fetch nothing and
+// put zeros into LDS.
+__device__ __forceinline__ void dma16_buffer(const u32x4_t& buf, uint32_t voff, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
+               : "memory", "m0");
+}
+
 // Sum over groups of NL consecutive lanes (NL = 8 or 16: inside one row of 16 lanes), every lane getting its
 // group's total: data-parallel-primitive adds with the partner lane of a pair, the partner pair of a quad, the
 // mirrored half and the mirrored row.  At every step the partner holds its own group's sum in all of its lanes and
