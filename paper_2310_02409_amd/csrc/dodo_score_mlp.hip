@@ -46,21 +46,24 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kBK = 64;  // channels per step
 constexpr int kStagesG = 2;
 constexpr int kLoadsPerStep = 8;  // direct loads per wavefront per step (4 of X, 4 of W1)
-// TG x HG wavefronts, each with 64 tokens and 32 HB hidden units of a square tile.
-template <int HB, int TG, int HG>
+// TG x HG wavefronts, each with 64 tokens and 32 HB hidden units of a square tile; KS such groups of wavefronts share the
+// channels.
+template <int HB, int TG, int HG, int KS>
 struct MlpTile {
   static constexpr int kWaves = TG * HG;
-  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int kThreads = KS * kWaves * kWave;
   static constexpr int kTok = 64 * TG;       // tokens per workgroup
   static constexpr int kHid = 32 * HB * HG;  // hidden units per tile
   static constexpr int kOperandBytes = kTok * kBK * 2;  // one operand tile of a stage
   static constexpr int kStageBytes = 2 * kOperandBytes;
-  static constexpr int kLds = kStagesG * kStageBytes;
+  static constexpr int kChannels = KS * kBK;  // per step
+  static constexpr int kLds = KS * kStagesG * kStageBytes;
   static constexpr int kGroupsPerCu = kLds > 80 * 1024 ? 1 : 2;
   static_assert(kTok == kHid && kTok / kWaves == 32, "every wavefront brings 32 rows of either operand per step");
 };
-using MlpBig = MlpTile<4, 4, 2>;    // 256 x 256, 128 KiB of LDS, 8 wavefronts
-using MlpSmall = MlpTile<2, 2, 2>;  // 128 x 128, 64 KiB, 4 wavefronts, two workgroups per compute unit
+using MlpBig = MlpTile<4, 4, 2, 1>;    // 256 x 256, 128 KiB of LDS, 8 wavefronts
+using MlpSmall = MlpTile<2, 2, 2, 1>;  // 128 x 128, 64 KiB, 4 wavefronts, two workgroups per compute unit
+using MlpHalves = MlpTile<2, 2, 2, 2>;  // the same tile, 8 wavefronts, 128 KiB
 constexpr int kTokTile = MlpBig::kTok, kHidTile = MlpBig::kHid;
 
 __device__ __forceinline__ float activation(float h, int act) {
@@ -69,18 +72,20 @@ __device__ __forceinline__ float activation(float h, int act) {
   return tanhf(h);
 }
 
+// KS = 2: one hidden tile per workgroup (hsplit = d_hid / kHid), d a multiple of 2 kBK.
 // `spread`: consecutive (token tile, split) pairs go to the XCDs in turn; otherwise a token tile stays on one XCD.
-template <int HB, int TG, int HG>
-__global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, HG>::kGroupsPerCu)) void score_mlp_mfma_kernel(
+template <int HB, int TG, int HG, int KS>
+__global__ __launch_bounds__((MlpTile<HB, TG, HG, KS>::kThreads), (MlpTile<HB, TG, HG, KS>::kGroupsPerCu)) void score_mlp_mfma_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W1, const float* __restrict__ b1,
     const uint16_t* __restrict__ w2, float b2, int act, int64_t N, int d, int d_hid, int64_t row_stride, int hsplit,
     int spread, float* __restrict__ out) {
-  using Tile = MlpTile<HB, TG, HG>;
+  using Tile = MlpTile<HB, TG, HG, KS>;
   constexpr int kOperandBytes = Tile::kOperandBytes, kStageBytesG = Tile::kStageBytes;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int kg = wave_all / Tile::kWaves, wave = wave_all % Tile::kWaves;  // share of the channels; wavefront of its group
   const int lane = tid % kWave;
   const int j32 = lane & 31, g = lane >> 5;
   const int tg = wave / HG, hg = wave % HG;  // token group (64 tokens) and hidden group (32 HB units) of this wavefront
@@ -99,7 +104,7 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, H
   const int tiles_per_split = (tiles_total + hsplit - 1) / hsplit;
   const int tile0 = split * tiles_per_split;
   const int n_tiles = max(0, min(tiles_per_split, tiles_total - tile0));
-  const int ksteps = d / kBK;
+  const int ksteps = d / (kBK * KS);
   const int n_steps = n_tiles * ksteps;
 
   // ---- loader: per step, wavefront w brings rows 32w .. 32w+31 of the X tile and of the W1 tile, 8 rows of 128
@@ -119,12 +124,13 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, H
   auto issue_part = [&](int step, int q) {  // eighth q of a step's loads: (u = q / 2, operand = q % 2)
     const int st = min(step, n_steps - 1);  // past the end: re-read the last step into a stage nobody reads any more
     const int ht = tile0 + st / ksteps, ks = st % ksteps;
-    const uint32_t stage = lds_base + (step % kStagesG) * kStageBytesG;
+    const uint32_t stage = lds_base + (kg * kStagesG + step % kStagesG) * kStageBytesG;
+    const int c0 = (kg * ksteps + ks) * kBK;
     const int u = q >> 1;
     if ((q & 1) == 0) {
-      dma16_uniform(x_base + ks * kBK, x_off[u], __builtin_amdgcn_readfirstlane(stage + (32 * wave + 8 * u) * 128));
+      dma16_uniform(x_base + c0, x_off[u], __builtin_amdgcn_readfirstlane(stage + (32 * wave + 8 * u) * 128));
     } else {
-      dma16_uniform(W1 + static_cast<int64_t>(ht) * Tile::kHid * d + ks * kBK, w_off[u],
+      dma16_uniform(W1 + static_cast<int64_t>(ht) * Tile::kHid * d + c0, w_off[u],
             __builtin_amdgcn_readfirstlane(stage + kOperandBytes + (32 * wave + 8 * u) * 128));
     }
   };
@@ -152,7 +158,7 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, H
 
   bf16x8 xf[2][2], wf[2][HB];  // two fragment sets, used alternately by the four 16-channel parts of a step
   auto read_frags = [&](int step, int ks, bf16x8* xo, bf16x8* wo) {
-    const char* stg = lds + (step % kStagesG) * kStageBytesG;
+    const char* stg = lds + (kg * kStagesG + step % kStagesG) * kStageBytesG;
     const int piece = ((2 * ks + g) ^ f_sw) << 4;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) xo[tb] = *reinterpret_cast<const bf16x8*>(stg + x_row_off + tb * 4096 + piece);
@@ -166,62 +172,124 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, H
       for (int tb = 0; tb < 2; ++tb)
         acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][hb], xf[set][tb], acc[hb][tb], 0, 0, 0);
   };
-  if (n_steps > 0) {
-    issue_step(0);
-    issue_step(1);
-    __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerStep);  // step 0 has landed
-    __syncthreads();
-    read_frags(0, 0, xf[0], wf[0]);
-  }
-  for (int step = 0; step < n_steps; ++step) {
-    // parts 0..2: the next part's fragments are requested, then the matrix cores work on the current part's
-    read_frags(step, 1, xf[1], wf[1]);
-    mfma_set(0);
-    read_frags(step, 2, xf[0], wf[0]);
-    mfma_set(1);
-    read_frags(step, 3, xf[1], wf[1]);
-    mfma_set(0);
-    // this wavefront has read everything it needs of this step's stage, and its part of the next step has landed;
-    // after the barrier that holds for every wavefront
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-    __syncthreads();
-    read_frags(step + 1, 0, xf[0], wf[0]);  // (after the last step: a stage that holds old data; not used)
+  // A hidden tile is complete: accumulator v of block hb is hidden unit 32 hb + 8 (v/4) + 4 g + v%4.  Token blocks
+  // tb0 .. tb1 - 1 of this wavefront.
+  auto second_layer = [&](int ht, int tb0, int tb1) {
+    const int jbase = ht * Tile::kHid + 32 * HB * hg + 4 * g;
 #pragma unroll
-    for (int hb = 0; hb < HB; ++hb) {
+    for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1][hb], xf[1][tb], acc[hb][tb], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int vq = 0; vq < 4; ++vq) {
+        const int jj = jbase + 32 * hb + 8 * vq;
+        const float4 bb = *reinterpret_cast<const float4*>(b1 + jj);
+        const uint2 ww = *reinterpret_cast<const uint2*>(w2 + jj);
+        const float wv[4] = {bf16_lo(ww.x), bf16_hi(ww.x), bf16_lo(ww.y), bf16_hi(ww.y)};
+        const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
-        for (int q = 0; q < 4 / HB; ++q) issue_part(step + kStagesG, (2 * hb + tb) * (4 / HB) + q);  // refill this step's stage
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    if ((step + 1) % ksteps == 0) {
-      // a hidden tile is complete: accumulator v of block hb is hidden unit 32 hb + 8 (v/4) + 4 g + v%4
-      const int ht = tile0 + step / ksteps;
-      const int jbase = ht * Tile::kHid + 32 * HB * hg + 4 * g;
-#pragma unroll
-      for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int jj = jbase + 32 * hb + 8 * vq;
-          const float4 bb = *reinterpret_cast<const float4*>(b1 + jj);
-          const uint2 ww = *reinterpret_cast<const uint2*>(w2 + jj);
-          const float wv[4] = {bf16_lo(ww.x), bf16_hi(ww.x), bf16_lo(ww.y), bf16_hi(ww.y)};
-          const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-#pragma unroll
-          for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < 2; ++tb)
+          if (tb >= tb0 && tb < tb1) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
               part[tb] = fmaf(wv[e], activation(acc[hb][tb][4 * vq + e] + bv[e], act), part[tb]);
+          }
+      }
+  };
+  if (n_steps > 0) {
+    issue_step(0);
+    issue_step(1);
+  }
+  if constexpr (KS == 2) {
+    // One workgroup per compute unit and 64 KiB per step: what limits it is the time from a stage's refill to its next use.
+    // All of a step's fragments go to registers at its start, so the stage is refilled after a quarter of its matrix
+    // instructions instead of three (39.3 -> 35.6 us for 128 to 547 tokens at d = d_hid = 4096; 51 us before there were
+    // two groups).  With two workgroups per compute unit, which fill each other's waits, that costs (68.5 -> 70.9 us for
+    // 2048 tokens).
+    bf16x8 xa[4][2], wa[4][HB];
+    for (int step = 0; step < n_steps; ++step) {
+      __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerStep);  // this step has landed, the next may be on its way
+      __syncthreads();
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) read_frags(step, ks, xa[ks], wa[ks]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        if (ks == 1) {
+          __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): every fragment of the step is in registers
+          __syncthreads();                      // in every wavefront: the stage is free
         }
-      zero_acc();
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+          for (int tb = 0; tb < 2; ++tb) {
+            acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[ks][hb], xa[ks][tb], acc[hb][tb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            const int q = (ks - 1) * 2 * HB + hb * 2 + tb;
+            if (q >= 0 && q < kLoadsPerStep) issue_part(step + kStagesG, q);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+      }
+    }
+  } else {
+    if (n_steps > 0) {
+      __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerStep);  // step 0 has landed
+      __syncthreads();
+      read_frags(0, 0, xf[0], wf[0]);
+    }
+    for (int step = 0; step < n_steps; ++step) {
+      // parts 0..2: the next part's fragments are requested, then the matrix cores work on the current part's
+      read_frags(step, 1, xf[1], wf[1]);
+      mfma_set(0);
+      read_frags(step, 2, xf[0], wf[0]);
+      mfma_set(1);
+      read_frags(step, 3, xf[1], wf[1]);
+      mfma_set(0);
+      // this wavefront has read everything it needs of this step's stage, and its part of the next step has landed;
+      // after the barrier that holds for every wavefront
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+      __syncthreads();
+      read_frags(step + 1, 0, xf[0], wf[0]);  // (after the last step: a stage that holds old data; not used)
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb) {
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+          acc[hb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1][hb], xf[1][tb], acc[hb][tb], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < 4 / HB; ++q) issue_part(step + kStagesG, (2 * hb + tb) * (4 / HB) + q);  // refill this step's stage
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if ((step + 1) % ksteps == 0) {
+        second_layer(tile0 + step / ksteps, 0, 2);
+        zero_acc();
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // drain the look-ahead loads
   __syncthreads();                     // (the stages are about to be reused as a reduction buffer)
+
+  if (KS == 2) {
+    // (one hidden tile per workgroup) each group hands the other its sums of the token block that the other finishes
+    float* mine = reinterpret_cast<float*>(lds) + (kg * Tile::kWaves + wave) * (HB * 16 * kWave) + lane;
+    const float* theirs = reinterpret_cast<const float*>(lds) + ((1 - kg) * Tile::kWaves + wave) * (HB * 16 * kWave) + lane;
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mine[(hb * 16 + v) * kWave] = kg == 0 ? acc[hb][1][v] : acc[hb][0][v];
+    __syncthreads();
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float other = theirs[(hb * 16 + v) * kWave];
+        if (kg == 0) acc[hb][0][v] += other; else acc[hb][1][v] += other;
+      }
+    if (n_steps > 0) {
+      if (kg == 0) second_layer(tile0, 0, 1); else second_layer(tile0, 1, 2);
+    }
+    __syncthreads();
+  }
 
   // ---- the two halves of a token's hidden units sit in lanes j32 and j32 + 32; the two hidden groups in two
   // wavefronts: added in a fixed order through LDS
@@ -229,7 +297,7 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG>::kThreads), (MlpTile<HB, TG, H
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     const float both = part[tb] + __shfl_xor(part[tb], 32, kWave);
-    if (g == 0) red[hg * Tile::kTok + 64 * tg + 32 * tb + j32] = both;
+    if (g == 0 && (KS == 1 || tb == kg)) red[hg * Tile::kTok + 64 * tg + 32 * tb + j32] = both;
   }
   __syncthreads();
   if (tid < Tile::kTok) {
@@ -466,26 +534,32 @@ size_t hidden_splits_most_bytes(int64_t N, int32_t d_hid) {
 // A big tile keeps a compute unit for 110 us at d = 4096, so a grid that does not come out in whole rounds of them pays
 // for idle units: big tiles take the groups of 8 token tiles (one per XCD) that fill rounds, small ones what is left, and
 // everything where there is not one round of big tiles.  The cost of a round, in hundredths of a round of big tiles, was
-// measured at d = 1024 to 5120: 45 for small tiles with at most one workgroup per compute unit (51 of 112 us at
-// d = 4096), 60 with two (65 us), which is why small tiles do not take it all (2.4 times their share of the work).
-// d = d_hid = 4096, before (big tiles, four splits at least) -> now: 128 tokens 85 -> 52 us, 2048 104 -> 70 us, 4096 the
-// same 118 us, 25123 (with their selection) 853 -> 763 us; 5120: 512 tokens 111 -> 65 us.
+// measured at d = 1024 to 5120: 60 for small tiles with two workgroups per compute unit (65 of 112 us at d = 4096), which is
+// why small tiles do not take it all (2.4 times their share of the work); 45 with at most one, or 32 (35.6 us) where these
+// are all there is and have two groups of wavefronts share the channels (which needs an even number of steps).  A second
+// round of those would take longer than two workgroups per unit (1500 tokens 69.6 against 58.5 us).
+// d = d_hid = 4096, big tiles with four splits at least -> now: 128 tokens 85 -> 36 us, 2048 104 -> 70 us, 4096 the
+// same 116 us, 25123 (with their selection) 853 -> 716 us; 5120: 512 tokens 111 -> 44 us.
 struct MlpPlan {
   int64_t n_big;
   int hs_big;
   int64_t n_small;
   int hs_small;
+  bool halves;  // small tiles: two groups of wavefronts share the channels
   bool direct() const { return n_small == 0 && hs_big == 1; }  // the only split writes the scores itself
   size_t bytes() const {
     return direct() ? 0 : (static_cast<size_t>(hs_big) * n_big + static_cast<size_t>(hs_small) * n_small) * sizeof(float);
   }
 };
-constexpr int kBigRound = 100, kSmallOne = 45, kSmallTwo = 60;
-MlpPlan plan_mlp(int64_t N, int32_t d_hid) {
+constexpr int kBigRound = 100, kSmallHalves = 32, kSmallOne = 45, kSmallTwo = 60;
+MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid) {
   const int cus = compute_units(), cus_xcd = cus >= 8 ? cus / 8 : 1;
   const int tiles = d_hid / MlpBig::kHid, small_tiles = d_hid / MlpSmall::kHid;
+  auto small_units = [&](int64_t n) -> int64_t { return (n + MlpSmall::kTok - 1) / MlpSmall::kTok * small_tiles; };
+  auto in_halves = [&](int64_t n) { return d % MlpHalves::kChannels == 0 && small_units(n) <= cus; };
   auto small_cost = [&](int64_t n) -> int64_t {
-    const int64_t units = (n + MlpSmall::kTok - 1) / MlpSmall::kTok * small_tiles;
+    const int64_t units = small_units(n);
+    if (units > 0 && in_halves(n)) return kSmallHalves;
     const int64_t rest = units % (2 * cus);
     return units / (2 * cus) * kSmallTwo + (rest == 0 ? 0 : rest <= cus ? kSmallOne : kSmallTwo);
   };
@@ -504,6 +578,7 @@ MlpPlan plan_mlp(int64_t N, int32_t d_hid) {
   p.n_big = best_groups * 8 * MlpBig::kTok < N ? best_groups * 8 * MlpBig::kTok : N;
   p.n_small = N - p.n_big;
   p.hs_small = small_tiles;
+  p.halves = in_halves(p.n_small);
   // as many tiles per workgroup as leave the number of rounds alone (fewer starts and partial scores)
   const int64_t rounds = (best_groups * tiles + cus_xcd - 1) / cus_xcd;
   p.hs_big = tiles;
@@ -538,7 +613,7 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   // room for this N, and for every smaller one as well: a caller may keep the buffer
   const size_t few = static_cast<size_t>(few_splits(d_hid)) * (N < kFewTokens ? N : kFewTokens) * sizeof(float);
   const size_t least = hidden_splits_most_bytes(N, d_hid);
-  const size_t plan = N <= kFewTokens ? 0 : plan_mlp(N, d_hid).bytes();
+  const size_t plan = N <= kFewTokens ? 0 : plan_mlp(N, d, d_hid).bytes();
   return std::max(plan, std::max(few, least));
 }
 
@@ -573,22 +648,25 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
       hipLaunchKernelGGL(score_mlp_combine_few_kernel, dim3(n), dim3(kWave), 0, s, partial, splits, n, b2, scores);
       return launch_status();
     }
-    MlpPlan p = plan_mlp(N, d_hid);
+    MlpPlan p = plan_mlp(N, d, d_hid);
     if (room < p.bytes()) {
-      p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0};
+      p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0, false};
       if (room < p.bytes()) return DODO_ERR_WORKSPACE_TOO_SMALL;
     }
     const uint16_t* x = static_cast<const uint16_t*>(hidden);
     const uint16_t* w = static_cast<const uint16_t*>(W1);
     const uint16_t* wo = static_cast<const uint16_t*>(w2);
     if (p.n_big > 0) {  // (a single split adds the output bias itself; where the sums are combined, that comes later)
-      const int rc = launch_mfma<MlpBig>(score_mlp_mfma_kernel<4, 4, 2>, x, w, b1, wo, p.direct() ? b2 : 0.f, act, p.n_big, d, d_hid, row_stride,
+      const int rc = launch_mfma<MlpBig>(score_mlp_mfma_kernel<4, 4, 2, 1>, x, w, b1, wo, p.direct() ? b2 : 0.f, act, p.n_big, d, d_hid, row_stride,
                                          p.hs_big, 0, p.direct() ? scores : partial, s);
       if (rc != DODO_OK || p.direct()) return rc;
     }
     if (p.n_small > 0) {
-      const int rc = launch_mfma<MlpSmall>(score_mlp_mfma_kernel<2, 2, 2>, x + p.n_big * row_stride, w, b1, wo, b2, act, p.n_small,
-                                           d, d_hid, row_stride, p.hs_small, 1, partial + p.hs_big * p.n_big, s);
+      const int rc = p.halves
+          ? launch_mfma<MlpHalves>(score_mlp_mfma_kernel<2, 2, 2, 2>, x + p.n_big * row_stride, w, b1, wo, b2, act, p.n_small,
+                                   d, d_hid, row_stride, p.hs_small, 1, partial + p.hs_big * p.n_big, s)
+          : launch_mfma<MlpSmall>(score_mlp_mfma_kernel<2, 2, 2, 1>, x + p.n_big * row_stride, w, b1, wo, b2, act, p.n_small,
+                                  d, d_hid, row_stride, p.hs_small, 1, partial + p.hs_big * p.n_big, s);
       if (rc != DODO_OK) return rc;
     }
     hipLaunchKernelGGL(score_mlp_combine_kernel, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s, partial, p.hs_big,

@@ -145,3 +145,16 @@ def test_llama7b_shape_sampled_tokens(D):
     rows = [0, 1, 255, 256, 4095, 4096, 17000, 32767] + [int(v) for v in np.random.default_rng(1).integers(0, N, 8)]
     want = oracle.score_mlp(W.to_numpy(x[rows].cpu()), W.to_numpy(W1.cpu()), b1.cpu().numpy(), W.to_numpy(w2.cpu()), 0.125, 1)
     _check(got[rows].cpu().numpy(), want)
+
+
+# small tiles whose channels two groups of wavefronts share: one, two and an odd number of steps each, the most tiles that
+# take this form and one more, and an odd number of steps in all, which does not
+@pytest.mark.parametrize("N,d,dh", [(65, 128, 256), (129, 256, 512), (128, 384, 256), (1024, 128, 4096), (1025, 128, 4096),
+                                    (130, 192, 512), (200, 1024, 512)])
+@pytest.mark.parametrize("act", [0, 2])
+def test_channels_shared_by_two_groups(D, N, d, dh, act):
+    x, W1, b1, w2 = _case(1000 + N, N, d, dh, torch.bfloat16)
+    rows = np.unique(np.r_[0:min(N, 140), N - 20:N])
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, act)
+    got = D.dodo_score_mlp(x.to(dev()), W1.to(dev()), b1.to(dev()), w2.to(dev()), 0.25, act).cpu().numpy()
+    _check(got[rows], want)
