@@ -1,7 +1,12 @@
-"""ctypes binding of libdodo.so: argument marshalling only."""
+"""Binding of libdodo.so: argument marshalling only.
+
+Every function checks its arguments and calls the library through ctypes.  The calls of a compress-and-attend pass and of a
+decode step first try the extension module (csrc/dodo_torch.cpp), which does the same in native code for arguments in the
+plain form -- contiguous GPU tensors of the expected types -- and declines everything else."""
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import math
 import os
 from typing import Optional, Sequence, Tuple
@@ -10,6 +15,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdodo.so")
+NATIVE_PATH = os.path.join(_HERE, "_dodo_torch.so")
 
 F32, BF16 = 0, 1
 RELU, GELU, TANH = 0, 1, 2
@@ -98,7 +104,27 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
     return L
 
 
+def _load_native(path: str = NATIVE_PATH):
+    if not os.path.exists(path):
+        raise ImportError(
+            f"{path} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()'). "
+            "There is no fallback path.")
+    spec = importlib.util.spec_from_file_location("_dodo_torch", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
+def _raise_status(rc: int, where: str) -> None:
+    raise DodoError(rc, where)
+
+
 lib = _load()
+_native = _load_native()
+_native.bind(_raise_status, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
+    lib.dodo_score, lib.dodo_select_topk, lib.dodo_gather_nuggets, lib.dodo_nugget_attention_workspace_bytes,
+    lib.dodo_nugget_attention_workspace_bytes_grouped, lib.dodo_nugget_attention, lib.dodo_nugget_attention_indexed,
+    lib.dodo_nugget_attention_cached, lib.dodo_stream_append, lib.dodo_score_mlp_workspace_bytes, lib.dodo_score_mlp)))
 _current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
@@ -168,6 +194,9 @@ def cu_nuggets_from_lengths(seq_lens: Sequence[int], num: int, den: int, device)
 def dodo_score(hidden: torch.Tensor, w: torch.Tensor, bias: float = 0.0,
                scores: Optional[torch.Tensor] = None) -> torch.Tensor:
     """scores[t] = hidden[t] . w + bias (fp32 [N]) for packed hidden [N, d]."""
+    done = _native.score(hidden, w, bias, scores)
+    if done is not None:
+        return done
     _dev(w, scores)
     _dev_rows(hidden)
     N, d = hidden.shape
@@ -211,6 +240,10 @@ def dodo_select_topk(scores: torch.Tensor, cu_seqlens: torch.Tensor, cu_nuggets:
                      total_nuggets: int, flags: int = 0, nugget_idx: Optional[torch.Tensor] = None,
                      ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Sequence-local, ascending indices of each sequence's top-k scores, packed by cu_nuggets (int32 [Kt])."""
+    done = _native.select_topk(scores, cu_seqlens, cu_nuggets, max_n, max_k, total_nuggets, flags, nugget_idx, ws,
+                               _ONE_WORKGROUP_TOKENS)
+    if done is not None:
+        return done
     _dev(scores, cu_seqlens, cu_nuggets, nugget_idx, ws)
     assert scores.dtype == torch.float32 and cu_seqlens.dtype == torch.int32 and cu_nuggets.dtype == torch.int32
     B = cu_seqlens.numel() - 1
@@ -232,6 +265,9 @@ def dodo_gather_nuggets(K: torch.Tensor, V: torch.Tensor, nugget_idx: torch.Tens
                         cu_nuggets: torch.Tensor, total_nuggets: int, layout: int = TOKEN_MAJOR,
                         Kn: Optional[torch.Tensor] = None, Vn: Optional[torch.Tensor] = None):
     """Packs the chosen rows of K, V [N, H_kv, d_h] into the nugget cache."""
+    done = _native.gather_nuggets(K, V, nugget_idx, cu_seqlens, cu_nuggets, total_nuggets, layout, Kn, Vn)
+    if done is not None:
+        return done
     _dev(nugget_idx, cu_seqlens, cu_nuggets, Kn, Vn)
     _dev_rows(K, V)
     _, H_kv, d_h = K.shape
@@ -302,6 +338,10 @@ def dodo_nugget_attention(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.Tensor, K
                           lse: Optional[torch.Tensor] = None, want_lse: bool = False,
                           ws: Optional[torch.Tensor] = None):
     """Attention of Q [Sq, H, d_h] over [nuggets ; causally visible local rows]; returns (O, lse or None)."""
+    done = _native.nugget_attention(Q, Kn, Vn, Kl, Vl, cu_q, cu_nuggets, cu_local, max_q, max_k, max_local, softmax_scale,
+                                    layout, O, lse, want_lse, ws)
+    if done is not None:
+        return done
     _dev(Q, Kn, Vn, Kl, Vl, cu_q, cu_nuggets, cu_local, O, lse, ws)
     Sq, H, d_h = Q.shape
     H_kv = Kl.shape[1]
@@ -347,6 +387,10 @@ def dodo_nugget_attention_indexed(Q: torch.Tensor, K: torch.Tensor, V: torch.Ten
                                   want_lse: bool = False, ws: Optional[torch.Tensor] = None):
     """dodo_nugget_attention with the nuggets read in place from the context's K, V [N, H_kv, d_h] through
     the index list (no packed cache); returns (O, lse or None)."""
+    done = _native.nugget_attention_indexed(Q, K, V, nugget_idx, cu_seqlens, Kl, Vl, cu_q, cu_nuggets, cu_local, max_q, max_k,
+                                            max_local, max_n, softmax_scale, O, lse, want_lse, ws)
+    if done is not None:
+        return done
     _dev(Q, nugget_idx, cu_seqlens, Kl, Vl, cu_q, cu_nuggets, cu_local, O, lse, ws)
     if not (K.is_cuda and V.is_cuda) or K.stride() != V.stride() or K.stride(2) != 1 or K.stride(1) != K.shape[2]:
         raise ValueError("K, V must be device tensors [N, H_kv, d_h] with contiguous rows and equal strides")
@@ -458,6 +502,10 @@ def dodo_nugget_attention_cached(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.Te
                                  want_lse: bool = False, ws: Optional[torch.Tensor] = None):
     """dodo_nugget_attention over caches with room to grow: nuggets of sequence b are the rows
     nugget_start[b] .. + nugget_len[b] of Kn / Vn [rows, H_kv, d_h]; returns (O, lse or None)."""
+    done = _native.nugget_attention_cached(Q, Kn, Vn, Kl, Vl, cu_q, nugget_start, nugget_len, cu_local, max_q, max_k, max_local,
+                                           softmax_scale, layout, O, lse, want_lse, ws)
+    if done is not None:
+        return done
     _dev(Q, Kn, Vn, Kl, Vl, cu_q, nugget_start, nugget_len, cu_local, O, lse, ws)
     Sq, H, d_h = Q.shape
     H_kv = Kl.shape[1]
@@ -518,6 +566,8 @@ def dodo_stream_append(scores: torch.Tensor, lam: torch.Tensor, K_rows: torch.Te
                        dropped: Optional[torch.Tensor] = None) -> None:
     """One decode step: rows [B, H_kv, d_h] whose score exceeds Lambda are appended to the caches
     [B, cap, H_kv, d_h] (in place), counts [B] int32 is updated in place."""
+    if _native.stream_append(scores, lam, K_rows, V_rows, counts, Kn, Vn, dropped):
+        return
     _dev(scores, lam, K_rows, V_rows, counts, Kn, Vn, dropped)
     B, H_kv, d_h = K_rows.shape
     cap = Kn.shape[1]
@@ -553,6 +603,9 @@ def dodo_score_mlp(hidden: torch.Tensor, W1: torch.Tensor, b1: torch.Tensor, w2:
                    act: int = RELU, out: Optional[torch.Tensor] = None,
                    ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """2-layer scorer (App. B): s = w2 . act(W1 x + b1) + b2 with W1 [d_hid, d]; returns fp32 scores [N]."""
+    done = _native.score_mlp(hidden, W1, b1, w2, b2, act, out, ws)
+    if done is not None:
+        return done
     _dev(W1, b1, w2, out, ws)
     if not hidden.is_cuda or hidden.stride(1) != 1:
         raise ValueError("hidden must be a device tensor with unit stride along d")
