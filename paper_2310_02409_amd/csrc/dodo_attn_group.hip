@@ -107,8 +107,8 @@ __device__ __forceinline__ void softmax_tile32(floatx16& acc, int limit, int g, 
   l_run += psum;
 }
 
-// NWV wavefronts per workgroup.  Grid: (KV head, sequence, split).
-template <int DH, int NWV>
+// NWV wavefronts per workgroup; STREAM: K/V rows with the non-temporal hint.  Grid: (KV head, sequence, split).
+template <int DH, int NWV, bool STREAM>
 __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
@@ -208,9 +208,9 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
       const uint32_t row_term = static_cast<uint32_t>(ld_row0) * stride_bytes;
 #pragma unroll
       for (int u = 0; u < GD::kInstrPerTensor; ++u) {
-        dma16_uniform(kbase + GD::kRowsPerInstr * u * stride, row_term + k_piece0[u],
+        dma16_uniform<STREAM>(kbase + GD::kRowsPerInstr * u * stride, row_term + k_piece0[u],
                       __builtin_amdgcn_readfirstlane(dst + u * 1024));
-        dma16_uniform(vbase + GD::kRowsPerInstr * u * stride, row_term + v_piece0,
+        dma16_uniform<STREAM>(vbase + GD::kRowsPerInstr * u * stride, row_term + v_piece0,
                       __builtin_amdgcn_readfirstlane(dst + kTensorBytes + u * 1024));
       }
       return;
@@ -219,8 +219,8 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
     for (int u = 0; u < GD::kInstrPerTensor; ++u) {
       const int row = ld_row0 + GD::kRowsPerInstr * u;
       const uint32_t roff = static_cast<uint32_t>(min(row, cnt - 1)) * stride_bytes;
-      dma16_uniform(kbase, roff + k_piece_of(row), __builtin_amdgcn_readfirstlane(dst + u * 1024));
-      dma16_uniform(vbase, roff + v_piece_of(row), __builtin_amdgcn_readfirstlane(dst + kTensorBytes + u * 1024));
+      dma16_uniform<STREAM>(kbase, roff + k_piece_of(row), __builtin_amdgcn_readfirstlane(dst + u * 1024));
+      dma16_uniform<STREAM>(vbase, roff + v_piece_of(row), __builtin_amdgcn_readfirstlane(dst + kTensorBytes + u * 1024));
     }
   };
 
@@ -497,15 +497,15 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
   }
 }
 
-template <int DH, int NWV>
+template <int DH, int NWV, bool STREAM>
 int launch_nwv(const AttnParams& p, int row0, int rows_per, int nsplit, uint32_t* flags) {
   constexpr int kLds = NWV * GroupDims<DH>::kWaveLds;
-  const void* kernel = reinterpret_cast<const void*>(&group_attention_kernel<DH, NWV>);
+  const void* kernel = reinterpret_cast<const void*>(&group_attention_kernel<DH, NWV, STREAM>);
   const int rc = allow_dynamic_lds(kernel, kLds);
   if (rc != DODO_OK) return rc;
   const int G = p.H / p.H_kv;
   const dim3 grid(static_cast<unsigned>(p.H_kv), static_cast<unsigned>(p.B), static_cast<unsigned>(nsplit));
-  hipLaunchKernelGGL((group_attention_kernel<DH, NWV>), grid, dim3(NWV * kWave), kLds, p.stream,
+  hipLaunchKernelGGL((group_attention_kernel<DH, NWV, STREAM>), grid, dim3(NWV * kWave), kLds, p.stream,
                      static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.Kn),
                      static_cast<const uint16_t*>(p.Vn), static_cast<const uint16_t*>(p.Kl),
                      static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.H,
@@ -513,6 +513,24 @@ int launch_nwv(const AttnParams& p, int row0, int rows_per, int nsplit, uint32_t
                      p.nug_head_stride, p.scale_log2e, static_cast<uint16_t*>(p.O), p.lse, static_cast<float*>(p.ws),
                      flags);
   return launch_status();
+}
+
+template <int DH>
+int launch_dh(const AttnParams& p, bool two, bool stream, int row0, int rows_per, int nsplit, uint32_t* flags) {
+  if (stream) {
+    return two ? launch_nwv<DH, 2, true>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, true>(p, row0, rows_per, nsplit, flags);
+  }
+  return two ? launch_nwv<DH, 2, false>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, false>(p, row0, rows_per, nsplit, flags);
+}
+
+// Whether the K/V rows are requested with the non-temporal hint: where the call reads them once and they are more than half
+// of the 256 MB last-level cache, so that little of them would be found there by the next call (another layer as a rule).
+// 64 sequences of 667 rows: 64 heads over 8 37.9 -> 34.3 us (177 MB, 5.1 TB/s), 4 query rows of 32 heads 110 -> 105 us.
+// Below that a cache that stays resident from call to call loses (66 MB, the same rows again: 27.4 -> 28.5 us), and so do
+// calls of several passes (64 sequences, 15 query rows 154.6 -> 156.8 us).
+bool streams_rows(const AttnParams& p, int rows_per) {
+  const int64_t bytes = static_cast<int64_t>(p.B) * (static_cast<int64_t>(p.max_k) + p.max_local) * p.H_kv * p.d_h * 4;
+  return p.max_q <= rows_per && bytes >= (128ll << 20);
 }
 
 constexpr int kWantedWorkgroups = 512;  // two per compute unit of the 256
@@ -585,13 +603,10 @@ int launch_group_attention(const AttnParams& p) {
   // two workgroups of two wavefronts per compute unit when there are that many; else one of four
   const bool two = static_cast<int64_t>(p.B) * p.H_kv * nsplit >= 2 * compute_units();
   const int rows_per = kMaxVectors / (p.H / p.H_kv);
+  const bool stream = streams_rows(p, rows_per);
   for (int row0 = 0; row0 < p.max_q; row0 += rows_per) {  // (records and flags of different rows are apart)
-    int rc;
-    if (p.d_h == 128) {
-      rc = two ? launch_nwv<128, 2>(p, row0, rows_per, nsplit, flags) : launch_nwv<128, 4>(p, row0, rows_per, nsplit, flags);
-    } else {
-      rc = two ? launch_nwv<64, 2>(p, row0, rows_per, nsplit, flags) : launch_nwv<64, 4>(p, row0, rows_per, nsplit, flags);
-    }
+    const int rc = p.d_h == 128 ? launch_dh<128>(p, two, stream, row0, rows_per, nsplit, flags)
+                                : launch_dh<64>(p, two, stream, row0, rows_per, nsplit, flags);
     if (rc != DODO_OK) return rc;
   }
   return DODO_OK;

@@ -83,13 +83,20 @@ __device__ __forceinline__ float load_elem(const void* p, int64_t i) {
 // One 16-byte-per-lane direct global->LDS load from base + voff: the lanes' data land at lds_dst + 16*lane; base
 // and lds_dst are wavefront-uniform (base is made so explicitly: the compiler may hold it in vector registers).
 // Inline assembly, so the compiler does not order later LDS reads behind it: callers keep the vmcnt bookkeeping.
+// STREAM: with the non-temporal hint, for data that no one reads again soon.
+template <bool STREAM = false>
 __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, uint32_t lds_dst) {
   const uint64_t b = reinterpret_cast<uint64_t>(base);
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(b))));
   const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(b >> 32))));
   const uint64_t ub = (static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo);
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(lds_dst)
-               : "memory", "m0");
+  if (STREAM) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(ub), "s"(lds_dst)
+                 : "memory", "m0");
+  } else {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(lds_dst)
+                 : "memory", "m0");
+  }
 }
 
 // The same through a buffer descriptor (in scalar registers): lanes whose offset lies outside of its range fetch nothing and

@@ -27,3 +27,23 @@ def test_edges_of_tiles_masks_and_head_blocks(q_lens, H, H_kv, d_h, k0):
                                      max(q_lens), max(k_lens), max(m_lens), scale, want_lse=True)
     check_attention(O, want, torch.bfloat16)
     check_lse(lse, lse_want, torch.bfloat16)
+
+
+# grouped heads and small query blocks, one split each: rows requested with the non-temporal hint (the host bounds promise
+# more than half of the last-level cache) and without, the same bits; the longest block of one pass, the next of two
+@pytest.mark.parametrize("q,H,H_kv,d_h", [(1, 64, 8, 128), (1, 32, 8, 64), (4, 32, 32, 128), (8, 32, 8, 64), (9, 32, 8, 128)])
+def test_streamed_rows_of_grouped_heads(q, H, H_kv, d_h):
+    import paper_2310_02409_amd as D
+    B = 70
+    k_lens, m_lens = [i % 67 for i in range(B)], [q + i % 35 for i in range(B)]
+    host, t = make_attention_case(470 + q, [q] * B, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"],
+                                      host["cu_nuggets"], host["cu_local"], scale)
+    got = [D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], q, max_k,
+                                   max(m_lens), scale, want_lse=True, ws=torch.zeros(16, dtype=torch.uint8, device=dev()))
+           for max_k in (max(k_lens), 20000)]
+    for O, lse in got:
+        check_attention(O, want, torch.bfloat16)
+        check_lse(lse, lse_want, torch.bfloat16)
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
