@@ -186,7 +186,9 @@ int dodo_gather_nuggets_layers(const void* K, const void* V, int dtype, const in
  * initialised, with one exception: no flag word may hold the library's "ready" value 0x600DD0D0 on
  * entry -- the call clears the flags it used, so zero-filled memory and memory that was a workspace in a
  * completed call with the same arguments both qualify; fill it with zeros after a call that was aborted or
- * before a call with other sizes.
+ * before a call with other sizes.  Calls that the query-block kernel takes (bf16, max_q >= 16) need none: with
+ * one, few query rows over many keys have their keys shared out over more workgroups, as far as it has room
+ * (16-byte aligned; contents irrelevant, and none of the words left there is the ready value).
  * A workspace must not be shared by calls that may overlap in time. */
 size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k,
                                              int32_t max_local, int dtype);
@@ -239,7 +241,8 @@ int dodo_nugget_attention(const void* Q, const void* Kn, const void* Vn, const v
  * on holds until the process ends); the call itself allocates and frees nothing.  The buffer has room for
  * DODO_NOALLOC_MAX_PARTIALS partial results, i.e. (sequence, query row, head, split) combinations of a
  * call that splits (dodo_nugget_attention_workspace_bytes / ((d_h + 3) * 4) is at least the number for
- * given bounds; 0 means the call needs no buffer at all and always fits); beyond that the call returns
+ * given bounds; 0 means the call needs no buffer at all and always fits, and so do calls that the query-block
+ * kernel takes, which does not share the keys out here); beyond that the call returns
  * DODO_ERR_SCRATCH_LIMIT and launches nothing (the kernel for grouped heads and small query blocks never
  * does: it splits as far as the buffer has room).  All calls on one GPU share that GPU's buffer: calls that
  * may overlap in time on one GPU (different streams, different threads) race and must not be made; calls

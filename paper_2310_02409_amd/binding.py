@@ -321,12 +321,15 @@ def dodo_nugget_attention_workspace_bytes_grouped(B: int, H: int, H_kv: int, d_h
 
 
 def _attention_workspace(need: int, ws: Optional[torch.Tensor], B: int, H: int, max_q: int, device: torch.device,
-                         grouped: bool) -> Optional[torch.Tensor]:
+                         code: int, grouped: bool) -> Optional[torch.Tensor]:
     """The caller's workspace, or a new one if this call uses any."""
+    block = code == BF16 and max_q >= 16  # the query-block kernel: partial results only, no flags
     # more (row, head) pairs than half of the 256 compute units are not split: what the library asks for is then for smaller
     # batches, which a buffer of this call alone does not serve (the kernel for grouped heads splits by other rules)
-    if need == 0 or ws is not None or (not grouped and 2 * B * H * max_q > 256):
+    if need == 0 or ws is not None or (not grouped and not block and 2 * B * H * max_q > 256):
         return ws
+    if block:
+        return torch.empty(need, dtype=torch.uint8, device=device)
     # zero-filled: the split-K flags must not hold the library's "ready" value on entry
     return torch.zeros(need, dtype=torch.uint8, device=device)
 
@@ -355,7 +358,7 @@ def dodo_nugget_attention(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.Tensor, K
         lse = torch.empty((Sq, H), dtype=torch.float32, device=Q.device)
     code = _dtype_code(Q)
     need = dodo_nugget_attention_workspace_bytes_grouped(B, H, H_kv, d_h, max_q, max_k, max_local, code)
-    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, code == BF16 and H * max_q >= 4 * H_kv)
+    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, code, code == BF16 and H * max_q >= 4 * H_kv)
     _check(lib.dodo_nugget_attention(_ptr(Q), _ptr(Kn), _ptr(Vn), _ptr(Kl), _ptr(Vl), _ptr(cu_q), _ptr(cu_nuggets),
                                      _ptr(cu_local), B, H, H_kv, d_h, max_q, max_k, max_local, Kt,
                                      float(softmax_scale), code, layout, _ptr(O), _ptr(lse), _ptr(ws),
@@ -405,7 +408,7 @@ def dodo_nugget_attention_indexed(Q: torch.Tensor, K: torch.Tensor, V: torch.Ten
         lse = torch.empty((Sq, H), dtype=torch.float32, device=Q.device)
     code = _dtype_code(Q)
     need = dodo_nugget_attention_workspace_bytes(B, H, d_h, max_q, max_k, max_local, code)
-    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, False)
+    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, code, False)
     _check(lib.dodo_nugget_attention_indexed(_ptr(Q), _ptr(K), _ptr(V), _ptr(nugget_idx), _ptr(cu_seqlens), _ptr(Kl),
                                              _ptr(Vl), _ptr(cu_q), _ptr(cu_nuggets), _ptr(cu_local), B, H, H_kv, d_h,
                                              max_q, max_k, max_local, max_n, K.stride(0), float(softmax_scale), code,
@@ -484,7 +487,7 @@ def dodo_nugget_attention_segments(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.
         lse = torch.empty((Sq, H), dtype=torch.float32, device=Q.device)
     code = _dtype_code(Q)
     need = dodo_nugget_attention_workspace_bytes_grouped(n_seg, H, H_kv, d_h, max_q, max_k, max_local, code)
-    ws = _attention_workspace(need, ws, n_seg, H, max_q, Q.device, code == BF16 and H * max_q >= 4 * H_kv)
+    ws = _attention_workspace(need, ws, n_seg, H, max_q, Q.device, code, code == BF16 and H * max_q >= 4 * H_kv)
     _check(lib.dodo_nugget_attention_segments(_ptr(Q), _ptr(Kn), _ptr(Vn), _ptr(K), _ptr(V), _ptr(seg_cu_q),
                                               _ptr(seg_nug_start), _ptr(seg_nug_len), _ptr(seg_loc_start),
                                               _ptr(seg_loc_len), n_seg, H, H_kv, d_h, max_q, max_k, max_local, Kt,
@@ -519,7 +522,7 @@ def dodo_nugget_attention_cached(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.Te
         lse = torch.empty((Sq, H), dtype=torch.float32, device=Q.device)
     code = _dtype_code(Q)
     need = dodo_nugget_attention_workspace_bytes_grouped(B, H, H_kv, d_h, max_q, max_k, max_local, code)
-    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, code == BF16 and H * max_q >= 4 * H_kv)
+    ws = _attention_workspace(need, ws, B, H, max_q, Q.device, code, code == BF16 and H * max_q >= 4 * H_kv)
     _check(lib.dodo_nugget_attention_cached(_ptr(Q), _ptr(Kn), _ptr(Vn), _ptr(Kl), _ptr(Vl), _ptr(cu_q),
                                             _ptr(nugget_start), _ptr(nugget_len), _ptr(cu_local), B, H, H_kv, d_h,
                                             max_q, max_k, max_local, Kt, float(softmax_scale), code, layout, _ptr(O),

@@ -21,7 +21,7 @@ extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, in
                                                         int32_t max_local, int dtype) {
   using namespace dodo;
   if (B <= 0 || H <= 0 || d_h <= 0 || max_q <= 0 || max_k < 0 || max_local < 0) return 0;
-  if (use_block_kernel(dtype, d_h, max_q)) return 0;
+  if (use_block_kernel(dtype, d_h, max_q)) return block_workspace_bytes(B, H, d_h, max_q, max_k, max_local);
   // room for this call, and for calls on fewer sequences or query rows: these split further
   return splitk_most_records(B, H, d_h, max_q, max_k, max_local, dtype) * splitk_record_bytes(d_h);
 }

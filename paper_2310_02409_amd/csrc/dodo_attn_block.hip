@@ -282,15 +282,27 @@ __device__ __forceinline__ SeqGeom load_seq_geom(int bh, FastDiv div_H, int H, F
   return g;
 }
 
+// What a workgroup knows of its share of a query block's keys, and where its partial results go (split form only).
+struct SplitArgs {
+  int split, nsplit;
+  float* o;        // [split][row slot][DH], not normalised
+  float2* ml;      // [split][row slot]: exponent offset (base 2) and sum
+  int64_t slots;   // row slots: (row of the call, head)
+  int64_t first_row;  // the call's first query row
+};
+
 // One query block (kBM rows) of one (sequence, head); called by the whole workgroup.
+// SPLIT (4 wavefronts): the workgroup takes an equal share of the key tiles and leaves its sums to
+// combine_splits_kernel.
 // IDX: Kn / Vn are the context's K / V and nugget j of sequence b is its token cu_ctx[b] + nug_idx[cu_nuggets[b] + j].
-template <int NW, bool IDX, int DH>
+template <int NW, bool IDX, int DH, bool SPLIT>
 __device__ __forceinline__ void attend_query_block(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ nug_idx,
     int H, int H_kv, const SeqGeom& geom, int qblk,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
-    float* __restrict__ lse) {
+    float* __restrict__ lse, const SplitArgs& sp) {
+  static_assert(NW == 4 || !SPLIT, "only the 4-wavefront kernel shares the keys out");
   using Cfg = BlockCfg<NW, DH>;
   using HD = HeadDims<DH>;
   constexpr int kDH = DH, kRowBytes = HD::kRowBytes, kTileBytes = HD::kTileBytes;
@@ -325,6 +337,10 @@ __device__ __forceinline__ void attend_query_block(
   const int n_nug_tiles = (k_b + kBN - 1) / kBN;
   const int n_loc_tiles = (wg_vis + kBN - 1) / kBN;
   const int n_tiles = n_nug_tiles + n_loc_tiles;
+  // the tiles of this workgroup: an even number per split, because a tile's stage follows from its index
+  const int per_split = SPLIT ? 2 * ((n_tiles + 2 * sp.nsplit - 1) / (2 * sp.nsplit)) : n_tiles;
+  const int t_begin = SPLIT ? min(n_tiles, sp.split * per_split) : 0;
+  const int t_end = SPLIT ? min(n_tiles, t_begin + per_split) : n_tiles;
 
   const int64_t nug_row0 = IDX ? geom.ctx0 : k0;  // IDX: the index list holds tokens of the sequence that starts here
   const uint16_t* nugK = Kn + nug_row0 * nug_tok_stride + static_cast<int64_t>(kvh) * nug_head_stride;
@@ -385,7 +401,7 @@ __device__ __forceinline__ void attend_query_block(
   using WithV = std::true_type;
   auto issue_tile = [&](int tile) {
     if (NW == 4) {
-      request(tile, K{}, WithV{});
+      if (!SPLIT || tile < t_end) request(tile, K{}, WithV{});
     } else if (wave < 4) {
       request(tile, V{}, Alone{});
     } else {
@@ -415,8 +431,8 @@ __device__ __forceinline__ void attend_query_block(
   // Rows past the end of the sequence read as zeros; nothing of them is stored.
   constexpr int kQSlot0 = NW == 8 ? 4 : 2;  // first 16 KiB slot of the query rows
   bf16x8 qf[kDH / 16];
-  if (n_tiles > 0) {
-    issue_tile(0);
+  if (t_begin < t_end) {
+    issue_tile(t_begin);
     TileLoader<NW, DH> q_loader;
     q_loader.init(wave, lane);
     uint32_t q_off[TileLoader<NW, DH>::kPerWave];
@@ -534,7 +550,7 @@ __device__ __forceinline__ void attend_query_block(
   if constexpr (NW == 4) {
     // ---- plain loop: one barrier per tile, next tile in flight ----
     // (the first barrier also tells that every wavefront has taken its Q fragments out of stage 1)
-    for (int tile = 0; tile < n_tiles; ++tile) {
+    for (int tile = t_begin; tile < t_end; ++tile) {
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wavefront's part of the tile has landed
       __syncthreads();                      // everyone's part has landed; the other stage is free
       issue_tile(tile + 1);
@@ -703,6 +719,24 @@ __device__ __forceinline__ void attend_query_block(
   // both the 8-byte writes and the 16-byte reads free of bank conflicts.
   if (NW == 4) __syncthreads();  // every wavefront is done with the K/V stages
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+  if constexpr (SPLIT) {
+    if (row_ok) {
+      // A workspace may serve a call with flags next, and no flag may hold the ready value: neither does a record.
+      auto word = [](float x) { return __float_as_uint(x) == kPartialReady ? __uint_as_float(kPartialReady + 1) : x; };
+      const int64_t slot = static_cast<int64_t>(sp.split) * sp.slots + (q0 - sp.first_row + my_i) * H + h;
+      if (g == 0) sp.ml[slot] = make_float2(word(m_run), word(l_tot));
+      if (l_tot > 0.f) {
+        float* o = sp.o + slot * DH + 4 * g;
+#pragma unroll
+        for (int cb = 0; cb < kNCB; ++cb)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq)
+            *reinterpret_cast<float4*>(o + 32 * cb + 8 * vq) =
+                make_float4(word(acc_o[cb][4 * vq]), word(acc_o[cb][4 * vq + 1]), word(acc_o[cb][4 * vq + 2]), word(acc_o[cb][4 * vq + 3]));
+      }
+    }
+    return;
+  }
   {
     const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
     char* obuf = lds + wave * (32 * kRowBytes);
@@ -738,7 +772,7 @@ __device__ __forceinline__ void attend_query_block(
 // after the other: a block i from the end and a block i from the start, so that under the causal
 // mask all workgroups carry the same load (new workgroups are handed out in order, and a compute
 // unit that finishes early is not refilled before the ones ahead of it in that order).
-template <int NW, bool IDX, int DH>
+template <int NW, bool IDX, int DH, bool SPLIT>
 __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kMinBlocks)) void block_attention_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
@@ -747,7 +781,7 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
     const int32_t* __restrict__ cu_ctx,
     int B, int H, int H_kv, int n_qblocks, int pair, int heavy_last, int heads_xcd, FastDiv div_heads_xcd, FastDiv div_groups, FastDiv div_H, FastDiv div_G,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
-    float* __restrict__ lse) {
+    float* __restrict__ lse, float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t slots) {
   // all arguments in one round of scalar loads (the compiler would fetch them a few at a time, before each first use)
   asm volatile("" ::"s"(Q), "s"(Kn), "s"(Vn), "s"(Kl), "s"(Vl), "s"(cu_q), "s"(cu_nuggets), "s"(nug_len), "s"(cu_local),
                "s"(loc_len), "s"(nug_idx), "s"(cu_ctx), "s"(B), "s"(H), "s"(H_kv), "s"(n_qblocks), "s"(pair),
@@ -793,13 +827,44 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
   // both blocks' sequence data are requested here, before the first block's work
   const SeqGeom g1 = load_seq_geom<IDX>(bh1, div_H, H, div_G, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
   const SeqGeom g2 = load_seq_geom<IDX>(q2 >= 0 ? bh2 : bh1, div_H, H, div_G, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
-  attend_query_block<NW, IDX, DH>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g1, q1, nug_tok_stride, nug_head_stride, scale_log2e, O,
-                                  lse);
-  if (q2 >= 0) {
+  SplitArgs sp{0, 1, nullptr, nullptr, 0, 0};
+  if (SPLIT) sp = SplitArgs{static_cast<int>(blockIdx.y), static_cast<int>(gridDim.y), part_o, part_ml, slots, cu_q[0]};
+  attend_query_block<NW, IDX, DH, SPLIT>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g1, q1, nug_tok_stride, nug_head_stride,
+                                         scale_log2e, O, lse, sp);
+  if (!SPLIT && q2 >= 0) {
     __syncthreads();  // the first block's use of LDS is over
-    attend_query_block<NW, IDX, DH>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g2, q2, nug_tok_stride, nug_head_stride, scale_log2e, O,
-                                    lse);
+    attend_query_block<NW, IDX, DH, SPLIT>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g2, q2, nug_tok_stride, nug_head_stride,
+                                           scale_log2e, O, lse, sp);
   }
+}
+
+// The splits' partial results of a row, merged in split order: DH / 4 lanes per row, four channels each.
+constexpr int kCombineThreads = 256;
+template <int DH>
+__global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(
+    const float* __restrict__ part_o, const float2* __restrict__ part_ml, int64_t slots, int nsplit, const int32_t* __restrict__ cu_q,
+    int B, int H, uint16_t* __restrict__ O, float* __restrict__ lse) {
+  constexpr int kLanes = DH / 4;
+  const int64_t slot = static_cast<int64_t>(blockIdx.x) * (kCombineThreads / kLanes) + threadIdx.x / kLanes;
+  const int c = threadIdx.x % kLanes;
+  const int64_t row0 = cu_q[0], rows = cu_q[B] - row0;
+  if (slot >= min(slots, rows * H)) return;
+  float M = kNegInf;
+  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part_ml[s * slots + slot].x);
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  float sum = 0.f;
+  for (int s = 0; s < nsplit; ++s) {
+    const float2 ml = part_ml[s * slots + slot];
+    if (!(ml.y > 0.f)) continue;  // (a split that saw nothing of the row has written no channels)
+    const float w = exp2_hw(ml.x - M);
+    const float4 p = *reinterpret_cast<const float4*>(part_o + (s * slots + slot) * DH + 4 * c);
+    sum = fmaf(ml.y, w, sum);
+    o.x = fmaf(p.x, w, o.x); o.y = fmaf(p.y, w, o.y); o.z = fmaf(p.z, w, o.z); o.w = fmaf(p.w, w, o.w);
+  }
+  const float inv = sum > 0.f ? 1.f / sum : 0.f;
+  const int64_t at = row0 * H + slot;
+  *reinterpret_cast<uint2*>(O + at * DH + 4 * c) = make_uint2(pack2_bf16(o.x * inv, o.y * inv), pack2_bf16(o.z * inv, o.w * inv));
+  if (lse != nullptr && c == 0) lse[at] = sum > 0.f ? (M + __log2f(sum)) * 0.6931471805599453f : kNegInf;
 }
 
 // Heads that an XCD gets of every sequence, next to each other (0: the pairs of sequence and head go to the XCDs in turn).
@@ -813,31 +878,71 @@ int heads_per_xcd(const AttnParams& p, int waves) {
   return p.H % 8 == 0 && (waves == 8 || p.H != p.H_kv) ? p.H / 8 : 0;
 }
 
-template <int NW, bool IDX, int DH>
-int launch_nw(const AttnParams& p) {
+// nsplit > 1: the keys are shared by that many workgroups per query block, whose partial results the workspace holds.
+template <int NW, bool IDX, int DH, bool SPLIT = false>
+int launch_nw(const AttnParams& p, int nsplit = 1) {
   using Cfg = BlockCfg<NW, DH>;
   if (IDX && p.max_k > Cfg::kIdxCap) return DODO_ERR_UNSUPPORTED;
   constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0);
   const int n_qblocks = (p.max_q + Cfg::kBM - 1) / Cfg::kBM;
   // pairs of query blocks per workgroup, if that still leaves a workgroup for every compute unit
   const int64_t bh8 = (static_cast<int64_t>(p.B) * p.H + 7) / 8 * 8;
-  const int pair = (n_qblocks >= 2 && bh8 * ((n_qblocks + 1) / 2) >= compute_units()) ? 1 : 0;
+  const int pair = (!SPLIT && n_qblocks >= 2 && bh8 * ((n_qblocks + 1) / 2) >= compute_units()) ? 1 : 0;
   const int64_t grid = bh8 * (pair ? (n_qblocks + 1) / 2 : n_qblocks);
   if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   const int heads_xcd = heads_per_xcd(p, NW);
-  auto kern = block_attention_kernel<NW, IDX, DH>;
+  auto kern = block_attention_kernel<NW, IDX, DH, SPLIT>;
+  const int64_t slots = SPLIT ? static_cast<int64_t>(p.B) * p.max_q * p.H : 0;
+  float* part_o = SPLIT ? static_cast<float*>(p.ws) : nullptr;
+  float2* part_ml = SPLIT ? reinterpret_cast<float2*>(part_o + slots * nsplit * DH) : nullptr;
   if (kLds > 64 * 1024) {
     const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLds);
     if (rc != DODO_OK) return rc;
   }
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(Cfg::kThreads), kLds, p.stream,
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid), SPLIT ? nsplit : 1), dim3(Cfg::kThreads), kLds, p.stream,
                      static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.Kn),
                      static_cast<const uint16_t*>(p.Vn), static_cast<const uint16_t*>(p.Kl),
                      static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, p.B, p.H, p.H_kv,
                      n_qblocks, pair, p.heavy_last, heads_xcd, make_fast_div(static_cast<uint32_t>(heads_xcd > 0 ? heads_xcd : 1)), make_fast_div(static_cast<uint32_t>(pair ? (n_qblocks + 1) / 2 : n_qblocks)),
                      make_fast_div(static_cast<uint32_t>(p.H)), make_fast_div(static_cast<uint32_t>(p.H / p.H_kv)),
-                     p.nug_tok_stride, p.nug_head_stride, p.scale_log2e, static_cast<uint16_t*>(p.O), p.lse);
+                     p.nug_tok_stride, p.nug_head_stride, p.scale_log2e, static_cast<uint16_t*>(p.O), p.lse, part_o, part_ml, slots);
+  const int rc = launch_status();
+  if (rc != DODO_OK || !SPLIT) return rc;
+  constexpr int kRows = kCombineThreads / (DH / 4);
+  hipLaunchKernelGGL(combine_splits_kernel<DH>, dim3(static_cast<unsigned>((slots + kRows - 1) / kRows)), dim3(kCombineThreads), 0,
+                     p.stream, part_o, part_ml, slots, nsplit, p.cu_q, p.B, p.H, static_cast<uint16_t*>(p.O), p.lse);
   return launch_status();
+}
+
+inline size_t split_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int64_t n) {
+  return static_cast<size_t>(B) * max_q * H * n * (static_cast<size_t>(d_h) + 2) * sizeof(float);
+}
+
+// How many workgroups share the keys of a query block of 128 rows (1: no sharing), where a workgroup per block would leave
+// most of the chip idle.  Sharing costs a launch and two passes over the partial results (one write, one read), so it is for
+// few rows and many keys; the count is the one with the least expected time.  Measured (ns): a 64-key tile 1350 in the
+// 4-wavefront kernel, 1.6 times that with two workgroups on a compute unit, 1200 in the 8-wavefront kernel (256 rows); heads
+// of 64 channels two thirds of that; 5000 for the second launch and the starts; the partial results at 2 TB/s, written and
+// read.  64 rows, 3000 nuggets, 32 heads 71 -> 26 us; 3 x 23 rows, 2700 nuggets, 40 heads 67.5 -> 43 us; 128 rows, 1500
+// nuggets, 64 heads over 8 42.5 -> 24 us; 2 x 21 rows, 332 nuggets, 32 heads 15.4 -> 13.6 us.  512 rows, 400 nuggets, 32 heads
+// (17 MB of partial results for two splits) stay as they are: 23.7 us against 25.5.
+int split_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local) {
+  const int64_t cus = compute_units(), bh = static_cast<int64_t>(B) * H;
+  const int64_t units = bh * ((max_q + 127) / 128);
+  if (units > cus) return 1;
+  const int64_t tiles = (static_cast<int64_t>(max_k) + kBN - 1) / kBN + (static_cast<int64_t>(max_local) + kBN - 1) / kBN;
+  const int64_t tile_ns = d_h == 128 ? 1350 : 900, tile8_ns = d_h == 128 ? 1200 : 800;
+  int64_t best = tiles * (max_q > 128 ? tile8_ns : tile_ns);
+  int count = 1;
+  for (int64_t n = 2; n <= 16 && n * units <= 2 * cus && 2 * n <= tiles; ++n) {
+    const int64_t busy = n * units > cus ? tile_ns * 8 / 5 : tile_ns;
+    const int64_t t = (tiles + n - 1) / n * busy + 5000 + static_cast<int64_t>(split_bytes(B, H, d_h, max_q, n) / 2000);
+    if (t < best) {
+      best = t;
+      count = static_cast<int>(n);
+    }
+  }
+  return count;
 }
 
 template <int DH>
@@ -846,16 +951,25 @@ int launch_dh(const AttnParams& p) {
   if (p.nug_tok_stride * 2 * kBN > 0x7fffffffLL || static_cast<int64_t>(p.H_kv) * DH * 2 * kBN > 0x7fffffffLL ||
       static_cast<int64_t>(p.H) * DH * 2 * kBN > 0x7fffffffLL)
     return DODO_ERR_UNSUPPORTED;
+  int nsplit = p.ws != nullptr && aligned16(p.ws) ? split_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local) : 1;
+  while (nsplit > 1 && split_bytes(p.B, p.H, p.d_h, p.max_q, nsplit) > p.ws_bytes) --nsplit;
   if (p.nug_idx != nullptr) {
     // a token's byte offset from its sequence's first row is kept in 32 bits as well
     if (static_cast<int64_t>(p.max_n) * p.nug_tok_stride * 2 > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
+    if (nsplit > 1 && p.max_k <= BlockCfg<4, DH>::kIdxCap) return launch_nw<4, true, DH, true>(p, nsplit);
     return p.max_q > 128 ? launch_nw<8, true, DH>(p) : launch_nw<4, true, DH>(p);
   }
+  if (nsplit > 1) return launch_nw<4, false, DH, true>(p, nsplit);
   if (p.max_q > 128) return launch_nw<8, false, DH>(p);
   return launch_nw<4, false, DH>(p);
 }
 
 }  // namespace
+
+size_t block_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local) {
+  const int n = split_count(B, H, d_h, max_q, max_k, max_local);
+  return n > 1 ? split_bytes(B, H, d_h, max_q, n) : 0;
+}
 
 int launch_block_attention(const AttnParams& p) {
   if (p.dtype != DODO_DTYPE_BF16) return DODO_ERR_UNSUPPORTED;

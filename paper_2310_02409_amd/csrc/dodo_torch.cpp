@@ -222,7 +222,12 @@ struct AttentionArgs {
   }
   // (the rule of _attention_workspace)
   void workspace(size_t need, bool grouped) {
-    if (need == 0 || ws.defined() || (!grouped && 2ll * B * H * max_q > 256)) return;
+    const bool block = code == DODO_DTYPE_BF16 && max_q >= 16;
+    if (need == 0 || ws.defined() || (!grouped && !block && 2ll * B * H * max_q > 256)) return;
+    if (block) {
+      ws = at::empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
+      return;
+    }
     ws = at::zeros({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
   }
   PyObject* result() const {

@@ -47,3 +47,61 @@ def test_streamed_rows_of_grouped_heads(q, H, H_kv, d_h):
         check_attention(O, want, torch.bfloat16)
         check_lse(lse, lse_want, torch.bfloat16)
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+def _split_case(q_lens, k_lens, m_lens, H, H_kv, d_h):
+    host, t = make_attention_case(520 + len(q_lens) + H, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                            host["cu_local"], scale)
+    return t, scale, want
+
+
+# few rows over many keys: the keys of a query block shared by several workgroups, with the workspace that this would like,
+# with one for two splits, and without; rows and blocks that see nothing, splits without a tile, blocks of 128 rows of what the
+# 8-wavefront kernel would take whole
+@pytest.mark.parametrize("q_lens,k_lens,m_lens,H,H_kv,d_h", [
+    ([20], [1500], [33], 4, 4, 128), ([16, 128, 31], [1100, 0, 64], [16, 700, 20], 8, 2, 128), ([130, 257], [1300, 900], [130, 300], 2, 2, 64),
+    ([64, 40], [1999, 1], [10, 40], 3, 1, 128), ([129], [2113], [0], 4, 4, 64),
+])
+def test_keys_shared_by_workgroups(q_lens, k_lens, m_lens, H, H_kv, d_h):
+    import paper_2310_02409_amd as D
+    t, scale, (want, lse_want) = _split_case(q_lens, k_lens, m_lens, H, H_kv, d_h)
+    B, mq, mk, mm = len(q_lens), max(q_lens), max(k_lens), max(m_lens)
+    need = D.dodo_nugget_attention_workspace_bytes(B, H, d_h, mq, mk, mm, D.BF16)
+    two = B * mq * H * 2 * (d_h + 2) * 4
+    assert need >= two
+    a = (t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], mq, mk, mm, scale)
+    results = []
+    for size in (need, two, 16, None):
+        ws = None if size is None else torch.full((size,), 255, dtype=torch.uint8, device=dev())
+        O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], *a, want_lse=True, ws=ws)
+        check_attention(O, want, torch.bfloat16)
+        check_lse(lse, lse_want, torch.bfloat16)
+        results.append((O, lse))
+    assert torch.equal(results[0][0], results[3][0]) and torch.equal(results[0][1], results[3][1])  # (None: the binding allocates)
+    O = torch.empty_like(t["Q"])
+    D.dodo_nugget_attention_noalloc(t["Q"], t["Kn"], t["Vn"], *a, 0, O)
+    assert torch.equal(O, results[2][0])
+    hm = D.dodo_nugget_attention(t["Q"], t["Kn"].transpose(0, 1).contiguous(), t["Vn"].transpose(0, 1).contiguous(), *a, D.HEAD_MAJOR)[0]
+    assert torch.equal(hm, results[0][0])
+
+
+def test_shared_keys_through_an_index_list_and_a_workspace_used_by_a_decode_call_next():
+    import paper_2310_02409_amd as D
+    import workloads as W
+    H, q, n, k = 4, 48, 3000, 1200
+    g = torch.Generator().manual_seed(9)
+    r = lambda *s: torch.randn(s, generator=g).to(torch.bfloat16).to(dev())
+    K, V, Q, Kl, Vl = r(n, H, 128), r(n, H, 128), r(q, H, 128), r(60, H, 128), r(60, H, 128)
+    idx = torch.randperm(n, generator=g)[:k].sort().values.int().to(dev())
+    cu = lambda v: W.cumulative([v], dev())
+    Kn, Vn = D.dodo_gather_nuggets(K, V, idx, cu(n), cu(k), k)
+    ws = torch.zeros(D.dodo_nugget_attention_workspace_bytes(1, H, 128, q, k, 60, D.BF16), dtype=torch.uint8, device=dev())
+    args = (Kl, Vl, cu(q), cu(k), cu(60), q, k, 60)
+    O, lse = D.dodo_nugget_attention(Q, Kn, Vn, *args, want_lse=True, ws=ws)
+    Oi, lse_i = D.dodo_nugget_attention_indexed(Q, K, V, idx, cu(n), *args, n, want_lse=True, ws=ws)
+    assert torch.equal(O, Oi) and torch.equal(lse, lse_i)
+    one = (Q[:1].contiguous(), Kn, Vn, Kl, Vl, cu(1), cu(k), cu(60), 1, k, 60)
+    fresh = D.dodo_nugget_attention(*one, ws=torch.zeros_like(ws))[0]
+    assert torch.equal(D.dodo_nugget_attention(*one, ws=ws)[0], fresh)
