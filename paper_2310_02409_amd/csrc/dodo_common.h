@@ -83,6 +83,11 @@ __device__ __forceinline__ float load_elem(const void* p, int64_t i) {
 // One 16-byte-per-lane direct global->LDS load from base + voff: the lanes' data land at lds_dst + 16*lane; base
 // and lds_dst are wavefront-uniform (base is made so explicitly: the compiler may hold it in vector registers).
 // Inline assembly, so the compiler does not order later LDS reads behind it: callers keep the vmcnt bookkeeping.
+// The compiler does not count wait states into it either: a scalar register that a vector instruction (v_readfirstlane)
+// wrote may be read by a memory instruction 5 wait states later, so m0's write and 4 idle ones stand before the load whatever
+// comes before.  (With the one that m0 needs, 55 loads of the build came 2 to 4 after the write.  The three more cost nothing
+// that can be measured, whether per load or once per descriptor: 2048 rows, 103 nuggets, 16 x 40 heads 843 against 844 us a
+// layer, 8 x 512 rows, 410 nuggets 134.0 against 134.3.)
 // STREAM: with the non-temporal hint, for data that no one reads again soon.
 template <bool STREAM = false>
 __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, uint32_t lds_dst) {
@@ -91,10 +96,10 @@ __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, u
   const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(b >> 32))));
   const uint64_t ub = (static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo);
   if (STREAM) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(ub), "s"(lds_dst)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(ub), "s"(lds_dst)
                  : "memory", "m0");
   } else {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(lds_dst)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(lds_dst)
                  : "memory", "m0");
   }
 }
@@ -102,7 +107,7 @@ __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, u
 // The same through a buffer descriptor (in scalar registers): lanes whose offset lies outside of its range fetch nothing and
 // put zeros into LDS.
 __device__ __forceinline__ void dma16_buffer(const u32x4_t& buf, uint32_t voff, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
                : "memory", "m0");
 }
 
