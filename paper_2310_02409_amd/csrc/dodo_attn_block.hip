@@ -282,11 +282,15 @@ __device__ __forceinline__ SeqGeom load_seq_geom(int bh, FastDiv div_H, int H, F
   return g;
 }
 
+// In the place of a sum: the share has no tile that the row's wavefront looked at.  (Of a sum that is 0 or NaN the channels count
+// all the same: a NaN or an infinity in K or V makes them NaN, and the row's result with them, as without sharing.)
+constexpr float kNoKeys = -1.f;
+
 // What a workgroup knows of its share of a query block's keys, and where its partial results go (split form only).
 struct SplitArgs {
   int split, nsplit;
-  float* o;        // [split][row slot][DH], not normalised
-  float2* ml;      // [split][row slot]: exponent offset (base 2) and sum
+  float* o;        // [split][row slot][DH], not normalised; nothing where ml holds kNoKeys
+  float2* ml;      // [split][row slot]: exponent offset (base 2) and sum, or kNoKeys
   int64_t slots;   // row slots: (row of the call, head)
   int64_t first_row;  // the call's first query row
 };
@@ -550,6 +554,7 @@ __device__ __forceinline__ void attend_query_block(
     }
   };
 
+  bool saw_keys = false;  // (split form)
   if constexpr (NW == 4) {
     // ---- plain loop: one barrier per tile, next tile in flight ----
     // (the first barrier also tells that every wavefront has taken its Q fragments out of stage 1)
@@ -559,6 +564,7 @@ __device__ __forceinline__ void attend_query_block(
       issue_tile(tile + 1);
       const TileInfo ti = tile_info(tile);
       if (!ti.visible) continue;
+      saw_keys = true;
       floatx16 acc_s[2];
       bf16x8 pf[4];
       compute_s(tile, acc_s);
@@ -727,8 +733,8 @@ __device__ __forceinline__ void attend_query_block(
       // A workspace may serve a call with flags next, and no flag may hold the ready value: neither does a record.
       auto word = [](float x) { return __float_as_uint(x) == kPartialReady ? __uint_as_float(kPartialReady + 1) : x; };
       const int64_t slot = static_cast<int64_t>(sp.split) * sp.slots + (q0 - sp.first_row + my_i) * H + h;
-      if (g == 0) sp.ml[slot] = make_float2(word(m_run), word(l_tot));
-      if (l_tot > 0.f) {
+      if (g == 0) sp.ml[slot] = make_float2(word(m_run), saw_keys ? word(l_tot) : kNoKeys);
+      if (saw_keys) {
         float* o = sp.o + slot * DH + 4 * g;
 #pragma unroll
         for (int cb = 0; cb < kNCB; ++cb)
@@ -854,12 +860,13 @@ __global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(
   if (slot >= min(slots, rows * H)) return;
   float M = kNegInf;
   for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part_ml[s * slots + slot].x);
+  const float M_use = M == kNegInf ? 0.f : M;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   float sum = 0.f;
   for (int s = 0; s < nsplit; ++s) {
     const float2 ml = part_ml[s * slots + slot];
-    if (!(ml.y > 0.f)) continue;  // (a split that saw nothing of the row has written no channels)
-    const float w = exp2_hw(ml.x - M);
+    if (ml.y == kNoKeys) continue;
+    const float w = exp2_hw(ml.x - M_use);
     const float4 p = *reinterpret_cast<const float4*>(part_o + (s * slots + slot) * DH + 4 * c);
     sum = fmaf(ml.y, w, sum);
     o.x = fmaf(p.x, w, o.x); o.y = fmaf(p.y, w, o.y); o.z = fmaf(p.z, w, o.z); o.w = fmaf(p.w, w, o.w);

@@ -105,3 +105,39 @@ def test_shared_keys_through_an_index_list_and_a_workspace_used_by_a_decode_call
     one = (Q[:1].contiguous(), Kn, Vn, Kl, Vl, cu(1), cu(k), cu(60), 1, k, 60)
     fresh = D.dodo_nugget_attention(*one, ws=torch.zeros_like(ws))[0]
     assert torch.equal(D.dodo_nugget_attention(*one, ws=ws)[0], fresh)
+
+
+def _finite(x):
+    return torch.isfinite(x.float())
+
+
+# A NaN or an infinity in K or V reaches the rows that see it, whether the keys are shared out or not: the same rows finite with
+# a workspace and without, and those as if the others were not there.  Nuggets of the middle of the keys; every query row of
+# their K/V head sees them.  (lse of a row without a sum is -inf.)
+@pytest.mark.parametrize("d_h", [64, 128])
+@pytest.mark.parametrize("tensor,value", [("Kn", float("nan")), ("Kn", float("inf")), ("Vn", float("nan")), ("Vn", float("-inf"))])
+def test_shared_keys_that_are_not_finite(tensor, value, d_h):
+    import paper_2310_02409_amd as D
+    q_lens, k_lens, m_lens, H, H_kv = [20, 40], [1500, 1100], [33, 64], 4, 2
+    host, t = make_attention_case(540, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    t["Q"][..., 3] = t["Q"][..., 3].abs() + 0.5  # an infinite channel of K makes an infinite logit, of one sign
+    t[tensor][700, 1, 3] = value                 # sequence 0, K/V head 1: query heads 2 and 3
+    scale = default_scale(d_h)
+    a = (t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 40, 1500, 64, scale)
+    need = D.dodo_nugget_attention_workspace_bytes(2, H, d_h, 40, 1500, 64, D.BF16)
+    two = 2 * 40 * H * 2 * (d_h + 2) * 4
+    assert need > two
+    got = []
+    for size in (16, two, need):
+        O, lse = (torch.full_like(t["Q"], float("nan")), torch.full((60, H), float("nan"), device=dev()))
+        D.dodo_nugget_attention(*a, O=O, lse=lse, ws=torch.full((size,), 255, dtype=torch.uint8, device=dev()))
+        got.append((O, lse))
+    hit = torch.zeros(60, H, dtype=torch.bool, device=dev())
+    hit[:20, 2:] = True
+    for O, lse in got:
+        assert torch.equal(_finite(O), _finite(got[0][0])) and torch.equal(_finite(lse), _finite(got[0][1]))
+        assert torch.equal(_finite(O).all(-1), ~hit) and not (torch.isnan(lse)).any()
+        fine = _finite(got[0][0])
+        assert (O[fine].float() - got[0][0][fine].float()).abs().max() <= 2e-2
+        ok = _finite(lse)
+        assert (lse[ok] - got[0][1][ok]).abs().max() <= 2e-2
