@@ -3,6 +3,7 @@ import pytest
 import torch
 
 import oracle
+import workloads as W
 from gpu_util import check_attention, check_lse, default_scale, dev, make_attention_case
 
 pytestmark = pytest.mark.gpu
@@ -141,3 +142,25 @@ def test_shared_keys_that_are_not_finite(tensor, value, d_h):
         assert (O[fine].float() - got[0][0][fine].float()).abs().max() <= 2e-2
         ok = _finite(lse)
         assert (lse[ok] - got[0][1][ok]).abs().max() <= 2e-2
+
+
+# The two-group kernel takes a row's exponent offset from its first tile: a first tile whose logits are all -inf (nuggets that a
+# caller rules out so) leaves it none.  The rest decides, also where it lies far from zero.
+@pytest.mark.parametrize("far", [0.0, -300.0, 300.0])
+def test_first_tile_without_a_finite_logit(far):
+    import paper_2310_02409_amd as D
+    q, k, m, H, d_h = 160, 100, 160, 2, 128
+    host, t = make_attention_case(550, [q], [k], [m], H, H, d_h, torch.bfloat16, "cpu")
+    scale = default_scale(d_h)
+    t["Q"][..., 0], t["Q"][..., 1] = 1.0, 16.0
+    for x in (t["Kn"], t["Kl"]):
+        x[..., 0], x[..., 1] = 0.0, far / (16.0 * scale)
+    t["Kn"][:64, :, 0] = float("-inf")
+    host = {n: W.to_numpy(v) for n, v in t.items()}
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], scale)
+    g = {n: v.to(dev()) for n, v in t.items()}
+    O, lse = D.dodo_nugget_attention(g["Q"], g["Kn"], g["Vn"], g["Kl"], g["Vl"], g["cu_q"], g["cu_nuggets"], g["cu_local"], q, k, m, scale,
+                                     want_lse=True, ws=torch.zeros(16, dtype=torch.uint8, device=dev()))
+    check_attention(O, want, torch.bfloat16)
+    check_lse(lse, lse_want, torch.bfloat16)
