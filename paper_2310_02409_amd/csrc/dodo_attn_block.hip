@@ -435,7 +435,8 @@ __device__ __forceinline__ void attend_query_block(
   // through LDS like a K tile (whole rows per request; a lane fetching its own row from global
   // memory would touch 32 rows per instruction), into the stages that tiles 1.. (NW = 4) or 2..
   // (NW = 8) use later.  Q^T fragments: lane (j, g) holds Q[my_i][16*ds + 8*g .. +8) for ds = 0..7.
-  // Rows past the end of the sequence read as zeros; nothing of them is stored.
+  // Rows past the end of the sequence read as zeros, and their lanes take the last row's fragments instead: zeros would make NaN of
+  // an infinite key, which spreads through the row sums below and has the block done twice.  Nothing of them is stored.
   constexpr int kQSlot0 = NW == 8 ? 4 : 2;  // first 16 KiB slot of the query rows
   bf16x8 qf[kDH / 16];
   if (t_begin < t_end) {
@@ -458,10 +459,11 @@ __device__ __forceinline__ void attend_query_block(
       __builtin_amdgcn_s_waitcnt(0x0f70);
     }
     __syncthreads();
-    const char* qbuf = lds + kQSlot0 * kTileBytes + (wave * 32 + j) * kRowBytes;
+    const int j_q = max(0, min(j, q_b - 1 - w_i0));
+    const char* qbuf = lds + kQSlot0 * kTileBytes + (wave * 32 + j_q) * kRowBytes;
 #pragma unroll
     for (int ds = 0; ds < kDH / 16; ++ds)
-      qf[ds] = *reinterpret_cast<const bf16x8*>(qbuf + (((2 * ds + g) ^ ((j >> kRowShift) & (kP - 1))) << 4));
+      qf[ds] = *reinterpret_cast<const bf16x8*>(qbuf + (((2 * ds + g) ^ ((j_q >> kRowShift) & (kP - 1))) << 4));
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the fragments are in registers
     if (NW == 8) {
       __syncthreads();  // everyone has its fragments: the stages are free again

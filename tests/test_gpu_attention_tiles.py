@@ -164,3 +164,20 @@ def test_first_tile_without_a_finite_logit(far):
                                      want_lse=True, ws=torch.zeros(16, dtype=torch.uint8, device=dev()))
     check_attention(O, want, torch.bfloat16)
     check_lse(lse, lse_want, torch.bfloat16)
+
+
+# Rows past the sequence's last one in a query block (they read as zeros, so that a ruled-out nugget's logits are NaN there) have
+# no say in the others' results: the same bits as in a block that is full.
+def test_rows_past_the_last_do_not_count():
+    import paper_2310_02409_amd as D
+    q, k, H, d_h = 160, 300, 2, 128
+    _, t = make_attention_case(560, [q], [k], [0], H, H, d_h, torch.bfloat16, dev())
+    t["Q"][..., 0] = 1.0
+    t["Kn"][7, :, 0] = float("-inf")
+    got = []
+    for rows in (160, 150):
+        cu = torch.tensor([0, rows], dtype=torch.int32, device=dev())
+        got.append(D.dodo_nugget_attention(t["Q"][:rows].contiguous(), t["Kn"], t["Vn"], t["Kl"], t["Vl"], cu, t["cu_nuggets"], t["cu_local"], rows, k,
+                                           0, want_lse=True, ws=torch.zeros(16, dtype=torch.uint8, device=dev())))
+    assert _finite(got[1][0]).all() and _finite(got[1][1]).all()
+    assert torch.equal(got[0][0][:150], got[1][0]) and torch.equal(got[0][1][:150], got[1][1])
