@@ -256,6 +256,19 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       load_lse(t * kQTile);
       __syncthreads();
     }
+    // Rows past the sequence's last one have weight 0, which takes away any finite logit; a zero row's logit of an infinite channel of
+    // K is NaN.  They get the last row's channels of Q (in LDS, once per sequence: level, where requests clamped in the loop cost 1 to 2.5% of every call).
+    if (t == n_qtiles - 1 && n_qtiles * kQTile > q_b) {
+      char* tile_q = lds + (t % kStagesSte) * SD::kStageBytes;
+      const int last = q_b - 1 - t * kQTile;
+      for (int i = tid; i < kQTile * kP; i += kGradThreads) {
+        const int row = i / kP, piece = i % kP;
+        if (row > last)
+          *reinterpret_cast<uint4*>(tile_q + row * kRowBytes + ((piece ^ ((row >> kRowShift) & (kP - 1))) << 4)) =
+              *reinterpret_cast<const uint4*>(tile_q + last * kRowBytes + ((piece ^ ((last >> kRowShift) & (kP - 1))) << 4));
+      }
+      __syncthreads();
+    }
     if (!active) issue_tile(t + 2);
     const float* dd_t = dd_l + (PRE ? c0 : (t & 1) * kQTile);
     const char* stg = lds + (t % kStagesSte) * SD::kStageBytes;
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     }
     if (!PRE) {
       __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t+1 has landed, t+2 may be in flight
-      row_dots(t + 1);  // (past the end: of the last tile again, not used)
+      row_dots(t + 1);  // (past the end: zeros, not used)
     }
     if (!active) continue;
     // accumulator v of a block is query row 8 (v / 4) + 4 g + v % 4 of the tile, for this lane's nugget; a tile's rows are

@@ -133,3 +133,22 @@ def test_prefill_shape_two_sequences(D):
     scale = 128 ** -0.5
     want = oracle.ste_score_grad(*(W.to_numpy(t[k]) for k in ("Q", "Kn", "Vn", "Kl", "Vl", "dO")), *cu, scale, scale)
     _check(_gpu(D, t, cu, q_lens, k_lens, m_lens, scale, scale), want, torch.bfloat16)
+
+
+# A nugget that the caller rules out (its logits are -inf in every row) has no gradient, and changes no other one's, whether or
+# not the sequence's rows fill whole tiles of 32.
+@pytest.mark.parametrize("q,H,d_h", [(64, 2, 128), (70, 2, 128), (230, 2, 128), (70, 4, 64)])
+def test_ruled_out_nugget(D, q, H, d_h):
+    k, m = 100, 80
+    t, cu = _case(760, [q], [k], [m], H, H, d_h, torch.bfloat16)
+    t["Q"][..., 0] = 1.0
+    t["Kn"][..., 0], t["Kl"][..., 0] = 0.0, 0.0
+    t["Kn"][41, :, 0] = float("-inf")
+    scale = d_h ** -0.5
+    got = _gpu(D, t, cu, [q], [k], [m], scale, scale).cpu()
+    rest = [i for i in range(k) if i != 41]
+    fewer = dict(t, Kn=t["Kn"][rest], Vn=t["Vn"][rest])
+    want = oracle.ste_score_grad(*(W.to_numpy(fewer[n]) for n in ("Q", "Kn", "Vn", "Kl", "Vl", "dO")), cu[0],
+                                 oracle.cu_from_lengths([k - 1]), cu[2], scale, scale)
+    assert got[41] == 0
+    _check(got[rest], want, torch.bfloat16)
