@@ -527,8 +527,14 @@ int launch_dh(const AttnParams& p, bool two, bool stream, int row0, int rows_per
 // of the 256 MB last-level cache, so that little of them would be found there by the next call (another layer as a rule).
 // 64 sequences of 667 rows: 64 heads over 8 37.9 -> 34.3 us (177 MB, 5.1 TB/s), 4 query rows of 32 heads 110 -> 105 us.
 // Below that a cache that stays resident from call to call loses (66 MB, the same rows again: 27.4 -> 28.5 us), and so do
-// calls of several passes (64 sequences, 15 query rows 154.6 -> 156.8 us).
+// calls of several passes (64 sequences, 15 query rows 154.6 -> 156.8 us).  The bounds count a sequence's rows as its own, which
+// those of segments are not: the segments of a text share its nuggets and overlap in its local rows (4 texts of 4096 tokens in
+// segments of 8, 295 MB of rows counted as 18 GB: 1599 -> 1686 us with the hint; 2 of 2048 117 -> 123).  In the cached form max_k
+// may be a capacity far above the fill.  Measured there, 64 heads over 8: 64 caches of 2048 rows full 116 -> 97 us, half full
+// 70 -> 60, a tenth full 30.2 -> 27.6 (4 layers in turn); 16 caches of 4096 a tenth full, 4 layers in turn 20.3 -> 21.0, 8 layers
+// 22.0 -> 21.1; 64 of 2048 with 20 rows each, 4 layers in turn 14.2 -> 15.9, one layer 13.3 -> 12.5.  The bound serves it too.
 bool streams_rows(const AttnParams& p, int rows_per) {
+  if (p.loc_len != nullptr) return false;  // the segment form
   const int64_t bytes = static_cast<int64_t>(p.B) * (static_cast<int64_t>(p.max_k) + p.max_local) * p.H_kv * p.d_h * 4;
   return p.max_q <= rows_per && bytes >= (128ll << 20);
 }

@@ -181,3 +181,30 @@ def test_rows_past_the_last_do_not_count():
                                            0, want_lse=True, ws=torch.zeros(16, dtype=torch.uint8, device=dev())))
     assert _finite(got[1][0]).all() and _finite(got[1][1]).all()
     assert torch.equal(got[0][0][:150], got[1][0]) and torch.equal(got[0][1][:150], got[1][1])
+
+
+def _kernels(call):
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "group_attention_kernel" in e.name]
+
+
+# Segments of a text share its nuggets and overlap in its local rows: they are asked for without the non-temporal hint however
+# large the bounds, where a plain call with the same bounds has it.
+def test_rows_of_segments_are_not_streamed():
+    import paper_2310_02409_amd as D
+    n, seg, H, d_h, k = 64, 8, 16, 128, 40
+    host, t = make_attention_case(570, [n], [k], [n], H, H, d_h, torch.bfloat16, dev())
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=dev())
+    starts = list(range(0, n, seg))
+    scale, big = default_scale(d_h), 1 << 20
+    kv = (t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"])
+    ws = torch.zeros(16, dtype=torch.uint8, device=dev())
+    seg_args = (i32(starts + [n]), i32([0] * len(starts)), i32([s * k // n for s in starts]), i32([max(0, s - 16) for s in starts]),
+                i32([s + seg - max(0, s - 16) for s in starts]))
+    names = _kernels(lambda: D.dodo_nugget_attention_segments(*kv, *seg_args, seg, big, seg + 16, scale, ws=ws))
+    assert len(names) == 1 and "false" in names[0] and "true" not in names[0]
+    cu = i32(starts + [n])
+    names = _kernels(lambda: D.dodo_nugget_attention(*kv, cu, i32([s * k // n for s in starts] + [k]), cu, seg, big, seg, scale, ws=ws))
+    assert len(names) == 1 and "true" in names[0]
