@@ -179,6 +179,10 @@ int dodo_gather_nuggets_layers(const void* K, const void* V, int dtype, const in
                                int32_t H_kv, int32_t d_h, int64_t token_stride, int64_t src_layer_stride,
                                int64_t dst_layer_stride, void* Kn, void* Vn, int layout, void* stream);
 
+/* Query rows (max_q) from which bf16 attention calls go to the query-block kernel, whose workspace holds no flag words and
+ * may be handed over uninitialised (below). */
+#define DODO_ATTENTION_BLOCK_MIN_Q 16
+
 /* Bytes of device workspace with which dodo_nugget_attention runs for these bounds (may be 0); where it is not 0, it
  * also serves every smaller B or max_q (which are split further).  Calls with max_k + max_local < 512 are accepted
  * without a workspace and then not split.  The workspace holds
@@ -186,7 +190,7 @@ int dodo_gather_nuggets_layers(const void* K, const void* V, int dtype, const in
  * initialised, with one exception: no flag word may hold the library's "ready" value 0x600DD0D0 on
  * entry -- the call clears the flags it used, so zero-filled memory and memory that was a workspace in a
  * completed call with the same arguments both qualify; fill it with zeros after a call that was aborted or
- * before a call with other sizes.  Calls that the query-block kernel takes (bf16, max_q >= 16) need none: with
+ * before a call with other sizes.  Calls that the query-block kernel takes (bf16, max_q >= DODO_ATTENTION_BLOCK_MIN_Q) need none: with
  * one, few query rows over many keys have their keys shared out over more workgroups, as far as it has room
  * (16-byte aligned; contents irrelevant, and none of the words left there is the ready value).
  * A workspace must not be shared by calls that may overlap in time. */
@@ -215,7 +219,7 @@ size_t dodo_nugget_attention_workspace_bytes_grouped(int32_t B, int32_t H, int32
  * Query head h reads KV head h / (H / H_kv).  max_q / max_k / max_local are
  * host-side upper bounds on q_b / k_b / m_b.  Arithmetic: bf16 inputs are
  * multiplied on the matrix cores with fp32 accumulation when max_q >= 16
- * (query-block kernel); smaller max_q and all fp32 inputs use the bandwidth-
+ * (DODO_ATTENTION_BLOCK_MIN_Q; query-block kernel); smaller max_q and all fp32 inputs use the bandwidth-
  * bound split-K kernel, whose last split combines the partials in split order.  Both are deterministic.
  * Supported: d_h in {64, 128}, fp32 or bf16.  When 4 or more query vectors read the same K/V rows -- (H / H_kv) *
  * max_q of them: grouped-query heads, a small query block, or both -- and the inputs are bf16, a

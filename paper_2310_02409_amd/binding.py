@@ -125,6 +125,7 @@ _native.bind(_raise_status, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
     lib.dodo_score, lib.dodo_select_topk, lib.dodo_gather_nuggets, lib.dodo_nugget_attention_workspace_bytes,
     lib.dodo_nugget_attention_workspace_bytes_grouped, lib.dodo_nugget_attention, lib.dodo_nugget_attention_indexed,
     lib.dodo_nugget_attention_cached, lib.dodo_stream_append, lib.dodo_score_mlp_workspace_bytes, lib.dodo_score_mlp)))
+_BLOCK_MIN_Q = _native.ATTENTION_BLOCK_MIN_Q  # the header's
 _current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
@@ -323,7 +324,7 @@ def dodo_nugget_attention_workspace_bytes_grouped(B: int, H: int, H_kv: int, d_h
 def _attention_workspace(need: int, ws: Optional[torch.Tensor], B: int, H: int, max_q: int, device: torch.device,
                          code: int, grouped: bool) -> Optional[torch.Tensor]:
     """The caller's workspace, or a new one if this call uses any."""
-    block = code == BF16 and max_q >= 16  # the query-block kernel: partial results only, no flags
+    block = code == BF16 and max_q >= _BLOCK_MIN_Q  # the query-block kernel: partial results only, no flags
     # more (row, head) pairs than half of the 256 compute units are not split: what the library asks for is then for smaller
     # batches, which a buffer of this call alone does not serve (the kernel for grouped heads splits by other rules)
     if need == 0 or ws is not None or (not grouped and not block and 2 * B * H * max_q > 256):

@@ -8,10 +8,8 @@
 namespace dodo {
 namespace {
 
-constexpr int kBlockKernelMinQ = 16;
-
 bool use_block_kernel(int dtype, int32_t d_h, int32_t max_q) {
-  return dtype == DODO_DTYPE_BF16 && (d_h == 128 || d_h == 64) && max_q >= kBlockKernelMinQ;
+  return dtype == DODO_DTYPE_BF16 && (d_h == 128 || d_h == 64) && max_q >= DODO_ATTENTION_BLOCK_MIN_Q;
 }
 
 }  // namespace

@@ -222,7 +222,7 @@ struct AttentionArgs {
   }
   // (the rule of _attention_workspace)
   void workspace(size_t need, bool grouped) {
-    const bool block = code == DODO_DTYPE_BF16 && max_q >= 16;
+    const bool block = code == DODO_DTYPE_BF16 && max_q >= DODO_ATTENTION_BLOCK_MIN_Q;
     if (need == 0 || ws.defined() || (!grouped && !block && 2ll * B * H * max_q > 256)) return;
     if (block) {
       ws = at::empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
@@ -396,4 +396,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dodo_torch", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__dodo_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__dodo_torch() {
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddIntConstant(m, "ATTENTION_BLOCK_MIN_Q", DODO_ATTENTION_BLOCK_MIN_Q) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -241,3 +241,22 @@ def test_ste_score_grad_argument_validation(lib):
     assert G(P, P, P, P, P, P, P, P, 2, 4, 4, 128, 8, 8, i64(16), i64(10), 0.1, 0.1, 0, 1, 0, P, P, 16, 0) == -3       # workspace
     assert G(P, P, P, P, P, 0, P, P, 2, 4, 4, 128, 8, 8, i64(16), i64(10), 0.1, 0.1, 0, 1, 0, P, P, 1 << 20, 0) == -1  # lse missing
     assert G(0, 0, 0, 0, 0, 0, 0, 0, 0, 4, 4, 128, 8, 8, i64(16), i64(10), 0.1, 0.1, 0, 1, 0, 0, 0, 0, 0) == 0         # B == 0
+
+
+def test_where_workspaces_without_flags_begin(lib, monkeypatch):
+    # the header's limit, the library's own and the binding's are one: below it a workspace holds flags, which have to be zeros
+    # (records of d_h + 2 floats and a flag each), from there on partial results alone (d_h + 2 floats each)
+    import paper_2310_02409_amd.binding as B
+    text = open(HEADER).read()
+    limit = int(re.search(r"#define DODO_ATTENTION_BLOCK_MIN_Q (\d+)", text).group(1))
+    assert limit == B._BLOCK_MIN_Q
+    need = lambda q: B.dodo_nugget_attention_workspace_bytes(1, 4, 128, q, 20000, 64, B.BF16)
+    assert need(limit - 1) > 0 and need(limit - 1) % (131 * 4) == 0 and need(limit - 1) % (130 * 4) != 0
+    assert need(limit) > 0 and need(limit) % (130 * 4) == 0 and need(limit) % (131 * 4) != 0
+    made = []
+    monkeypatch.setattr(B, "torch", type("T", (), {"uint8": None, "Tensor": B.torch.Tensor, "device": B.torch.device,
+                                                   "zeros": lambda *a, **k: made.append("zeros"),
+                                                   "empty": lambda *a, **k: made.append("empty")}))
+    for q, code in ((limit - 1, B.BF16), (limit, B.BF16), (limit, B.F32)):
+        B._attention_workspace(64, None, 1, 1, q, None, code, True)
+    assert made == ["zeros", "empty", "zeros"]
