@@ -732,10 +732,12 @@ __device__ __forceinline__ void attend_query_block(
   if (NW == 4) __syncthreads();  // every wavefront is done with the K/V stages
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
   if constexpr (SPLIT) {
-    if (row_ok) {
+    // (slots follow from max_q: rows of a sequence that is longer have none and are not written, rather than past the workspace)
+    const int64_t row_slot = static_cast<int64_t>(q0 - sp.first_row + my_i) * H + h;
+    if (row_ok && row_slot < sp.slots) {
       // A workspace may serve a call with flags next, and no flag may hold the ready value: neither does a record.
       auto word = [](float x) { return __float_as_uint(x) == kPartialReady ? __uint_as_float(kPartialReady + 1) : x; };
-      const int64_t slot = static_cast<int64_t>(sp.split) * sp.slots + (q0 - sp.first_row + my_i) * H + h;
+      const int64_t slot = static_cast<int64_t>(sp.split) * sp.slots + row_slot;
       if (g == 0) sp.ml[slot] = make_float2(word(m_run), saw_keys ? word(l_tot) : kNoKeys);
       if (saw_keys) {
         float* o = sp.o + slot * DH + 4 * g;

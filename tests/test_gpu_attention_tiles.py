@@ -208,3 +208,20 @@ def test_rows_of_segments_are_not_streamed():
     cu = i32(starts + [n])
     names = _kernels(lambda: D.dodo_nugget_attention(*kv, cu, i32([s * k // n for s in starts] + [k]), cu, seg, big, seg, scale, ws=ws))
     assert len(names) == 1 and "true" in names[0]
+
+
+# A bound on the query rows that is too small leaves rows without a place for their shares: nothing is written past the workspace,
+# and the rows within the bound are whole.
+@pytest.mark.parametrize("q,said", [(25, 20), (200, 130)])
+def test_more_rows_than_said_stay_inside_the_workspace(q, said):
+    import paper_2310_02409_amd as D
+    H, d_h, k, m = 2, 128, 2500, 300
+    t, scale, (want, lse_want) = _split_case([q], [k], [m], H, H, d_h)
+    need = D.dodo_nugget_attention_workspace_bytes(1, H, d_h, said, k, m, D.BF16)
+    assert need > 0
+    room = torch.full((need + (1 << 22),), 255, dtype=torch.uint8, device=dev())
+    O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], said, k, m, scale,
+                                     want_lse=True, ws=room[:need])
+    assert torch.all(room[need:] == 255)
+    check_attention(O[:said], want[:said], torch.bfloat16)
+    check_lse(lse[:said], lse_want[:said], torch.bfloat16)
