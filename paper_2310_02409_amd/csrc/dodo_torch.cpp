@@ -85,6 +85,25 @@ float* fptr(const at::Tensor& t) { return static_cast<float*>(ptr(t)); }
 size_t bytes_of(const at::Tensor& ws) { return ws.defined() ? static_cast<size_t>(ws.numel()) : 0; }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 PyObject* wrap(const at::Tensor& t) { return THPVariable_Wrap(t); }
+
+// New tensors, made without the interpreter lock as torch's own functions make them: an allocation may wait for the device, for
+// another thread's or for an allocator that needs the interpreter.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+at::Tensor new_empty(at::IntArrayRef sizes, const at::TensorOptions& options) {
+  Unlocked u;
+  return at::empty(sizes, options);
+}
+at::Tensor new_zeros(at::IntArrayRef sizes, const at::TensorOptions& options) {
+  Unlocked u;
+  return at::zeros(sizes, options);
+}
+at::Tensor new_like(const at::Tensor& t) {
+  Unlocked u;
+  return at::empty_like(t);
+}
 // an argument that is handed back is the caller's own object
 PyObject* same_or_new(PyObject* given, const at::Tensor& t) {
   if (given == Py_None) return wrap(t);
@@ -127,7 +146,7 @@ PyObject* score(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(hidden.dim() == 2 && w.dim() == 1 && w.size(0) == hidden.size(1) && w.scalar_type() == hidden.scalar_type());
     const int code = dtype_code(hidden);
     const int64_t N = hidden.size(0);
-    if (!scores.defined()) scores = at::empty({N}, hidden.options().dtype(at::kFloat));
+    if (!scores.defined()) scores = new_empty({N}, hidden.options().dtype(at::kFloat));
     require(scores.scalar_type() == at::kFloat && scores.numel() == N);
     const int32_t d = int32(hidden.size(1));
     void* s = stream();
@@ -147,7 +166,7 @@ PyObject* select_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(scores.scalar_type() == at::kFloat && cu_seqlens.numel() == cu_nuggets.numel() && flags >= 0 && flags <= 0x7fffffff);
     require(ws.defined() || max_n <= whole(a[9]));
     require(cu_seqlens.numel() >= 1 && total >= 0);
-    if (!idx.defined()) idx = at::empty({total}, cu_seqlens.options().device(scores.device()));
+    if (!idx.defined()) idx = new_empty({total}, cu_seqlens.options().device(scores.device()));
     require(idx.scalar_type() == at::kInt && idx.numel() >= total);
     const int32_t B = int32(cu_seqlens.numel() - 1);
     void* s = stream();
@@ -171,8 +190,8 @@ PyObject* gather_nuggets(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const int64_t h_kv = K.size(1), d_h = K.size(2);
     const bool token = layout == DODO_LAYOUT_TOKEN_MAJOR;
     const int64_t shape[3] = {token ? total : h_kv, token ? h_kv : total, d_h};
-    if (!Kn.defined()) Kn = at::empty(shape, K.options());
-    if (!Vn.defined()) Vn = at::empty(shape, K.options());
+    if (!Kn.defined()) Kn = new_empty(shape, K.options());
+    if (!Vn.defined()) Vn = new_empty(shape, K.options());
     require(Kn.sizes() == at::IntArrayRef(shape) && Vn.sizes() == at::IntArrayRef(shape));
     const int32_t B = int32(cu_seqlens.numel() - 1), h = int32(h_kv), dh = int32(d_h);
     void* s = stream();
@@ -217,18 +236,18 @@ struct AttentionArgs {
     code = dtype_code(Q);
     scale = static_cast<float>(softmax_scale == Py_None ? 1.0 / std::sqrt(static_cast<double>(d_h)) : real(softmax_scale));
     const bool want = truth(want_lse);
-    if (!O.defined()) O = at::empty_like(Q);
-    if (!lse.defined() && want) lse = at::empty({Q.size(0), Q.size(1)}, Q.options().dtype(at::kFloat));
+    if (!O.defined()) O = new_like(Q);
+    if (!lse.defined() && want) lse = new_empty({Q.size(0), Q.size(1)}, Q.options().dtype(at::kFloat));
   }
   // (the rule of _attention_workspace)
   void workspace(size_t need, bool grouped) {
     const bool block = code == DODO_DTYPE_BF16 && max_q >= DODO_ATTENTION_BLOCK_MIN_Q;
     if (need == 0 || ws.defined() || (!grouped && !block && 2ll * B * H * max_q > 256)) return;
     if (block) {
-      ws = at::empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
+      ws = new_empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
       return;
     }
-    ws = at::zeros({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
+    ws = new_zeros({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
   }
   PyObject* result() const {
     PyObject* o = same_or_new(O_given, O);
@@ -342,10 +361,10 @@ PyObject* score_mlp(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(W1.size(1) == d && b1.size(0) == d_hid && w2.size(0) == d_hid && b1.scalar_type() == at::kFloat);
     require(W1.scalar_type() == hidden.scalar_type() && w2.scalar_type() == hidden.scalar_type());
     const int code = dtype_code(hidden);
-    if (!out.defined()) out = at::empty({N}, hidden.options().dtype(at::kFloat));
+    if (!out.defined()) out = new_empty({N}, hidden.options().dtype(at::kFloat));
     if (!ws.defined()) {
       const size_t need = L.score_mlp_ws(code, N, d, d_hid);
-      if (need > 0) ws = at::empty({static_cast<int64_t>(need)}, hidden.options().dtype(at::kByte));
+      if (need > 0) ws = new_empty({static_cast<int64_t>(need)}, hidden.options().dtype(at::kByte));
     }
     void* s = stream();
     if (!run("dodo_score_mlp", [&] {

@@ -1,5 +1,6 @@
 """The binding's native calls (csrc/dodo_torch.cpp) against the same calls through ctypes: results, returned objects and
 refusals are the same, and what is not in the plain form is declined."""
+import threading
 import types
 
 import pytest
@@ -149,3 +150,25 @@ def test_host_tensors_are_declined(without_native):
     without_native()
     assert _errors(calls) == native
     assert all(kind is ValueError for kind, _ in native)
+
+
+# Threads with streams of their own, whose calls give up the interpreter lock where they allocate and where they launch
+@pytest.mark.gpu
+def test_calls_from_several_threads():
+    t = _inputs("cuda", torch.bfloat16)
+    want = _calls(t)
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                got = _calls(t)
+                torch.cuda.current_stream().synchronize()
+                wrong.extend(n for n in want for x, y in zip(_flat(got[n]), _flat(want[n])) if x is not None and not torch.equal(x, y))
+    threads = [threading.Thread(target=work) for _ in range(4)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong
