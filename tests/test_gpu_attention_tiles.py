@@ -50,6 +50,33 @@ def test_streamed_rows_of_grouped_heads(q, H, H_kv, d_h):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+# the same with the keys of a (sequence, K/V head) pair shared by several workgroups, whose records and flags the last one reads:
+# plain call, head-major cache and cached form, twice on one workspace
+@pytest.mark.parametrize("q,H,H_kv,d_h", [(1, 64, 8, 128), (2, 32, 8, 128), (1, 32, 4, 64), (4, 16, 16, 64)])
+def test_streamed_rows_in_several_splits(q, H, H_kv, d_h):
+    import paper_2310_02409_amd as D
+    k_lens, m_lens, big = [3001, 1500], [700, 513], 1 << 16
+    host, t = make_attention_case(480 + q, [q] * 2, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"],
+                                      host["cu_nuggets"], host["cu_local"], scale)
+    need = D.dodo_nugget_attention_workspace_bytes_grouped(2, H, H_kv, d_h, q, max(k_lens), max(m_lens), D.BF16)
+    assert need > 2 * (2 * q * H * (d_h + 3) * 4) and 2 * big * H_kv * d_h * 4 >= 128 << 20
+    ws = torch.zeros(need, dtype=torch.uint8, device=dev())
+    Kh, Vh = (t[n].transpose(0, 1).contiguous() for n in ("Kn", "Vn"))
+    start, length = t["cu_nuggets"][:2].contiguous(), torch.tensor(k_lens, dtype=torch.int32, device=dev())
+    loc = (t["Kl"], t["Vl"], t["cu_q"])
+    kw = dict(want_lse=True, ws=ws)
+    calls = [lambda mk: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], *loc, t["cu_nuggets"], t["cu_local"], q, mk, max(m_lens), scale, **kw),
+             lambda mk: D.dodo_nugget_attention(t["Q"], Kh, Vh, *loc, t["cu_nuggets"], t["cu_local"], q, mk, max(m_lens), scale, D.HEAD_MAJOR, **kw),
+             lambda mk: D.dodo_nugget_attention_cached(t["Q"], t["Kn"], t["Vn"], *loc, start, length, t["cu_local"], q, mk, max(m_lens), scale, **kw)]
+    for call in calls:
+        for _ in range(2):
+            O, lse = call(big)
+            check_attention(O, want, torch.bfloat16)
+            check_lse(lse, lse_want, torch.bfloat16)
+
+
 def _split_case(q_lens, k_lens, m_lens, H, H_kv, d_h):
     host, t = make_attention_case(520 + len(q_lens) + H, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
     scale = default_scale(d_h)
@@ -225,3 +252,23 @@ def test_more_rows_than_said_stay_inside_the_workspace(q, said):
     assert torch.all(room[need:] == 255)
     check_attention(O[:said], want[:said], torch.bfloat16)
     check_lse(lse[:said], lse_want[:said], torch.bfloat16)
+
+
+# A workspace that is anything but zero, though free of the ready value, serves calls that share keys out and decode calls in turn:
+# a ragged batch leaves words of it alone, and none that it writes is a flag to the next call.
+def test_workspace_of_shared_keys_serves_a_decode_call():
+    import paper_2310_02409_amd as D
+    q_lens, k_lens, m_lens, H, d_h = [48, 17, 33], [2900, 1, 2000], [60, 20, 33], 4, 128
+    t, scale, (want, _) = _split_case(q_lens, k_lens, m_lens, H, H, d_h)
+    mq, mk, mm = max(q_lens), max(k_lens), max(m_lens)
+    one = dict(cu_q=torch.arange(4, dtype=torch.int32, device=dev()), Q=t["Q"][:3].contiguous())
+    decode = lambda ws: D.dodo_nugget_attention(one["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], one["cu_q"], t["cu_nuggets"], t["cu_local"], 1, mk, mm,
+                                                scale, want_lse=True, ws=ws)
+    size = max(D.dodo_nugget_attention_workspace_bytes(3, H, d_h, n, mk, mm, D.BF16) for n in (1, mq))
+    fresh = decode(torch.zeros(size, dtype=torch.uint8, device=dev()))
+    ws = torch.full((size,), 0x5A, dtype=torch.uint8, device=dev())
+    for _ in range(2):
+        O = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], mq, mk, mm, scale, ws=ws)[0]
+        check_attention(O, want, torch.bfloat16)
+        got = decode(ws)
+        assert torch.equal(got[0], fresh[0]) and torch.equal(got[1], fresh[1])

@@ -158,3 +158,17 @@ def test_channels_shared_by_two_groups(D, N, d, dh, act):
     want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, act)
     got = D.dodo_score_mlp(x.to(dev()), W1.to(dev()), b1.to(dev()), w2.to(dev()), 0.25, act).cpu().numpy()
     _check(got[rows], want)
+
+
+# Infinite and NaN channels in either group's half: tanh of an infinite hidden unit is 1 or -1, a NaN channel makes its token's score
+# NaN and no other one's.
+@pytest.mark.parametrize("N,d,dh", [(65, 128, 256), (130, 128, 512), (200, 384, 256)])
+def test_channels_shared_by_two_groups_that_are_not_finite(D, N, d, dh):
+    x, W1, b1, w2 = _case(1010 + N, N, d, dh, torch.bfloat16)
+    x[N // 2, 9], x[3, d - 5], x[N - 1, d // 2] = float("-inf"), float("inf"), float("inf")
+    nan = [1, 40, N - 2]
+    x[1, 0], x[40, d // 2 - 1], x[N - 2, d - 1] = float("nan"), float("nan"), float("nan")
+    got = D.dodo_score_mlp(*[v.to(dev()) for v in (x, W1, b1, w2)], act=D.TANH).cpu().numpy()
+    assert np.isnan(got[nan]).all()
+    rest = np.setdiff1d(np.arange(N), nan)
+    _check(got[rest], oracle.score_mlp(W.to_numpy(x[rest]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 2))
