@@ -1,6 +1,7 @@
 // dodo_nugget_attention: argument checks and dispatch between the MFMA
 // query-block kernel and the two bandwidth-bound kernels (one query vector per K/V row read: split-K kernel on
 // the vector pipe; several: grouped kernel on the matrix cores).
+#include <algorithm>
 #include <mutex>
 
 #include "dodo_attn.h"
@@ -19,7 +20,15 @@ extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, in
                                                         int32_t max_local, int dtype) {
   using namespace dodo;
   if (B <= 0 || H <= 0 || d_h <= 0 || max_q <= 0 || max_k < 0 || max_local < 0) return 0;
-  if (use_block_kernel(dtype, d_h, max_q)) return block_workspace_bytes(B, H, d_h, max_q, max_k, max_local);
+  if (use_block_kernel(dtype, d_h, max_q)) {
+    const size_t block = block_workspace_bytes(B, H, d_h, max_q, max_k, max_local);
+    if (block == 0) return 0;
+    // it serves smaller calls too, and those of fewer rows than a query block split their keys over up to a record per
+    // compute unit (the most (row, head) pairs that still do)
+    const int64_t fewer = std::min<int64_t>(static_cast<int64_t>(B) * (DODO_ATTENTION_BLOCK_MIN_Q - 1), (compute_units() - 1) / H);
+    const size_t decode = fewer < 1 ? 0 : splitk_most_records(1, H, d_h, static_cast<int32_t>(fewer), max_k, max_local, dtype);
+    return std::max(block, decode * splitk_record_bytes(d_h));
+  }
   // room for this call, and for calls on fewer sequences or query rows: these split further
   return splitk_most_records(B, H, d_h, max_q, max_k, max_local, dtype) * splitk_record_bytes(d_h);
 }

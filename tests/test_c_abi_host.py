@@ -260,3 +260,16 @@ def test_where_workspaces_without_flags_begin(lib, monkeypatch):
     for q, code in ((limit - 1, B.BF16), (limit, B.BF16), (limit, B.F32)):
         B._attention_workspace(64, None, 1, 1, q, None, code, True)
     assert made == ["zeros", "empty", "zeros"]
+
+
+def test_attention_workspace_serves_every_smaller_call():
+    # where the query is not 0, no call with fewer sequences or query rows asks for more: also where the smaller one goes to another kernel
+    import paper_2310_02409_amd as D
+    seen = 0
+    for B, H, d_h, k in [(B, H, d_h, k) for B in (1, 2, 8) for H in (1, 2, 3, 8, 32) for d_h in (64, 128) for k in (512, 1000, 20000)]:
+        need = lambda b, q: D.dodo_nugget_attention_workspace_bytes(b, H, d_h, q, k, 64, D.BF16)
+        smaller = max(need(b, q) for b in range(1, B + 1) for q in (1, 2, 3, 5, 8, 15))
+        for q in (16, 17, 40, 129, 500):
+            seen += need(B, q) > 0
+            assert need(B, q) == 0 or need(B, q) >= smaller, (B, H, d_h, k, q)
+    assert seen > 100
