@@ -190,9 +190,11 @@ int dodo_gather_nuggets_layers(const void* K, const void* V, int dtype, const in
  * initialised, with one exception: no flag word may hold the library's "ready" value 0x600DD0D0 on
  * entry -- the call clears the flags it used, so zero-filled memory and memory that was a workspace in a
  * completed call with the same arguments both qualify; fill it with zeros after a call that was aborted or
- * before a call with other sizes.  Calls that the query-block kernel takes (bf16, max_q >= DODO_ATTENTION_BLOCK_MIN_Q) need none: with
- * one, few query rows over many keys have their keys shared out over more workgroups, as far as it has room
- * (16-byte aligned; contents irrelevant, and none of the words left there is the ready value).
+ * before a call with other sizes.  Calls that the query-block kernel takes (bf16, max_q >=
+ * DODO_ATTENTION_BLOCK_MIN_Q) need none: with one, few query rows over many keys have their keys shared out over
+ * more workgroups, as far as it has room (16-byte aligned; contents irrelevant).  Such a call writes no word that is
+ * the ready value and leaves some words as they were: memory that was free of that value before it still is; fill
+ * other memory with zeros before a call with flags.
  * A workspace must not be shared by calls that may overlap in time. */
 size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k,
                                              int32_t max_local, int dtype);

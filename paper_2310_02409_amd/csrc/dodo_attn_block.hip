@@ -630,8 +630,8 @@ __device__ __forceinline__ void attend_query_block(
       for (int s = 0; s < kAhead; ++s) ring[s] = read_vt(t, s);
     };
     // In the loop a wavefront requests tiles in its softmax phase: a request can take hundreds of cycles to issue when the
-    // memory pipeline is backed up.  The wavefronts of group 1 bring K of
-    // tile t+2 (during phase 2t), those of group 0 its V (during phase 2t+1).
+    // memory pipeline is backed up.  The wavefronts of group 1 bring K of tile t+2 (during phase 2t), those of group 0 its V
+    // (during phase 2t+1).
     auto end_odd_phase = [&](int t) {  // ends phase 2t+1: tile t+1 must have landed
       // younger requests of this wavefront in flight: two tiles' worth while the prologue's are pending, else one
       if (t == 0) {

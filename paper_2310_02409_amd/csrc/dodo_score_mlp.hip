@@ -23,6 +23,9 @@
 // wavefront holds the last part's fragments in registers, so the stage can be
 // refilled (for the step after next) right after the barrier, and the next
 // step's first fragments are fetched under the last part's matrix instructions.
+// Where there is at most one small tile per compute unit, two groups of 4 wavefronts
+// share its channels; all of a step's fragments go to registers then, and a step has
+// two barriers: it has landed, and it has been read.
 // The hidden tiles are split over workgroups, and the workgroups
 // resident on one XCD form a patch of token tiles x splits that share their
 // panels through that XCD's L2; a second kernel adds the partial scores in split

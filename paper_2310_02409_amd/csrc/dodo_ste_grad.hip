@@ -23,13 +23,14 @@
 // is at the launch).  No atomics: per-head sums go to the workspace and a last kernel
 // adds them in head order.  Other types and head sizes take a plain kernel, with D from
 // the same kernel of its own.
-// Bound by the vector pipe (an exp2 per element of S) as much as by the matrix
-// pipe.  8 x 410 nuggets, 512 rows, 32 heads of 128: 48 us and no launch before
-// it (was 41.5 us after a 14 us kernel that made D and lse: forward and gradient
-// 135 -> 126 us); heads of 64 in the plain kernel: 2249 -> 33 us (4 x 250 nuggets,
-// 300 rows, 16 heads; 35 us with the sums of SteDims::kExact).  2 x 3277 nuggets,
-// 1024 rows, 32 heads of 128: 143 us with D in the kernel, 129 us with it before
-// (136 us before D moved into the kernel).  Error against 64 bits (2-norm), 512 rows,
+// What bounds it (cycle counter, 8 x 410 nuggets, 512 rows, 32 heads of 128): 24 K of
+// a workgroup's 86 K cycles are the wait for K, V and the first tiles; a tile of
+// 32 rows takes some 3600 cycles, 2048 of them the matrix instructions of a SIMD's
+// two wavefronts, the sums for D 470 and the softmax 780 beside them.  That shape:
+// 44 us, 49 to 51 us with the sum over heads (56.5 us before its loop was reworked,
+// 41.5 us after a 14 us kernel that made D and lse before that).  2 x 3277 nuggets,
+// 1024 rows: 130 us (136 us).  Heads of 64, 4 x 250 nuggets, 300 rows, 16 heads:
+// 17.3 us, 2249 us in the plain kernel.  Error against 64 bits (2-norm), 512 rows,
 // 410 / 3277 nuggets: 2.9e-7 / 4.1e-7 (were 4.2e-7 / 4.7e-7).
 #include "dodo_common.h"
 
@@ -256,8 +257,9 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       load_lse(t * kQTile);
       __syncthreads();
     }
-    // Rows past the sequence's last one have weight 0, which takes away any finite logit; a zero row's logit of an infinite channel of
-    // K is NaN.  They get the last row's channels of Q (in LDS, once per sequence: level, where requests clamped in the loop cost 1 to 2.5% of every call).
+    // Rows past the sequence's last one have weight 0, which takes away any finite logit; a zero row's logit of an infinite
+    // channel of K is NaN.  They get the last row's channels of Q (in LDS, once per sequence: no call slower by more than its
+    // runs differ, where requests clamped in the loop cost 1 to 2.5%).
     if (t == n_qtiles - 1 && n_qtiles * kQTile > q_b) {
       char* tile_q = lds + (t % kStagesSte) * SD::kStageBytes;
       const int last = q_b - 1 - t * kQTile;
@@ -493,8 +495,9 @@ extern "C" int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn
     if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
     // D in the kernel costs about 0.3 us for every query tile that a compute unit's workgroups walk over, a kernel of
     // its own 2 us and the reading of dO and O (5 TB/s; both in tenths of a us below).  Measured, 32 heads, in the kernel /
-    // before it: 8 x 512 rows, 410 nuggets 56.5 / 62.0 us, 1280 nuggets 123 / 119 us; 1 x 1024 rows, 1000 nuggets 50.4 / 46.7
-    // us; 2 x 1024 rows, 3277 nuggets 143 / 131 us; 1 x 128 rows, 1280 nuggets 15.0 / 16.2 us.  (Heads of 64: level.)
+    // before it: 8 x 512 rows, 410 nuggets 48.9 / 58.5 us, 1280 nuggets 113 / 109 us, 1638 nuggets 148 / 139 us; 1 x 1024
+    // rows, 1000 nuggets 49.0 / 45.6 us; 2 x 1024 rows, 3277 nuggets 135 / 130 us; 1 x 128 rows, 1280 nuggets 14.3 / 15.8 us; 64
+    // heads over 8, 5 x 777 rows, 155 nuggets 54.9 / 71.6 us.  (Heads of 64: level.)
     const int64_t steps = (grid + compute_units() - 1) / compute_units() * ((max_q + kQTile - 1) / kQTile);
     const bool pre = d_h == 128 && 3 * steps > 20 + Sq * H / 1000;
     if (pre) {
