@@ -490,6 +490,12 @@ def next_rows_c2(torch, D, W, clock, dev, wl, g, cu_k, ks, ws, cu_qd, cu_ld, dec
     r.update(TFLOPs=round(mlp_flop / r["avg_us"] * 1e-6, 1),
              frac_of_bf16_peak=round(mlp_flop / r["avg_us"] * 1e-6 / MFMA_BF16_PEAK_TFLOPS, 3), note="ReLU, d_hid = d")
     out["scorer_2layer"] = r
+    # the same for few tokens: a decode batch (W1 read once), and what does not fill a round of big tiles
+    for n in (16, 512):
+        r = t(lambda: D.dodo_score_mlp(g["hidden"][:n], W1, b1, w2, 0.0, D.RELU, mlp_out[:n], mlp_ws))
+        r["GBps"] = round((d * d + n * d) * 2 / r["avg_us"] * 1e-3, 1)
+        r["TFLOPs"] = round(2.0 * n * d * d / r["avg_us"] * 1e-6, 1)
+        out[f"scorer_2layer_{n}_tokens"] = r
     # segment form of the autoregressive objective: the 8 x 4096 tokens as 64 segments of 512 with tau = 128
     seg_len, tau = 512, 128
     mk = lambda tid, n, h: W.normal(wl.seed, tid, (n, h, wl.d_h), 1.0, wl.dtype, dev)
@@ -551,6 +557,13 @@ def next_rows_c2(torch, D, W, clock, dev, wl, g, cu_k, ks, ws, cu_qd, cu_ld, dec
     r = shared_rows(64, 32, 32, 4, kg, mg, 3300)
     r["note"] = "batch 64, multi-head attention, query blocks of 4 rows (each row of a head reads the same K/V rows)"
     out["query_block_of_4_rows"] = r
+    # few query rows over many nuggets: the keys of a query block are shared by several workgroups
+    for Bs, Hs, Hkvs, qs, ks_, ms_, tid0 in ((1, 32, 32, 64, 3000, 128, 3400), (3, 40, 40, 23, 2700, 123, 3500),
+                                             (1, 64, 8, 128, 1500, 200, 3600)):
+        r = shared_rows(Bs, Hs, Hkvs, qs, ks_, ms_, tid0)
+        f = work_attention([qs] * Bs, [ks_] * Bs, [ms_] * Bs, Hs, Hkvs, wl.d_h)["flop"]
+        r.update(TFLOPs=round(f / r["avg_us"] * 1e-6, 1), note="kernel and the merge of the shares")
+        out[f"attn_block_{Bs}x{qs}_rows_{ks_}_nuggets_{Hs}_heads_over_{Hkvs}"] = r
     # query-block attention with 64-wide heads (64 heads x 64: the same flop count as the 32 x 128 workload)
     mk = lambda tid, n, h: W.normal(wl.seed, 3100 + tid, (n, h, 64), 1.0, wl.dtype, dev)
     Q6, Kn6, Vn6 = mk(0, sum(wl.q_lens), 64), mk(1, Kt, 64), mk(2, Kt, 64)
