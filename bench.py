@@ -562,7 +562,7 @@ def next_rows_c2(torch, D, W, clock, dev, wl, g, cu_k, ks, ws, cu_qd, cu_ld, dec
                                              (1, 64, 8, 128, 1500, 200, 3600)):
         r = shared_rows(Bs, Hs, Hkvs, qs, ks_, ms_, tid0)
         f = work_attention([qs] * Bs, [ks_] * Bs, [ms_] * Bs, Hs, Hkvs, wl.d_h)["flop"]
-        r.update(TFLOPs=round(f / r["avg_us"] * 1e-6, 1), note="kernel and the merge of the shares")
+        r.update(TFLOPs=round(f / r["avg_us"] * 1e-6, 1), bound="latency", note="kernel and the merge of the shares")
         out[f"attn_block_{Bs}x{qs}_rows_{ks_}_nuggets_{Hs}_heads_over_{Hkvs}"] = r
     # query-block attention with 64-wide heads (64 heads x 64: the same flop count as the 32 x 128 workload)
     mk = lambda tid, n, h: W.normal(wl.seed, 3100 + tid, (n, h, 64), 1.0, wl.dtype, dev)
