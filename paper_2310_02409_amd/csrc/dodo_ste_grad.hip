@@ -148,16 +148,21 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   const int64_t row0 = (static_cast<int64_t>(q0) * H + h) * DH;
   const int n_qtiles = (q_b + kQTile - 1) / kQTile;
   constexpr int kLoads = SD::kTensors * SD::kInstr;  // direct loads per wavefront per tile
-  // Requested through buffers that end with the tile's last row: the lanes' offsets are the same for every tile, what lies
-  // beyond the sequence's last row reads as zeros, and a tile past the end fetches nothing.
+  // Requested through buffers that end with the tile's last row: the lanes' offsets are the same for every tile, and a tile past
+  // the end fetches nothing.  Every row of a tile is one of the sequence: the last tile ends with the sequence and begins with
+  // rows of the one before, and a sequence of fewer rows than a tile repeats its last one; such rows have weight 0.  (Zeros in
+  // their place would make NaN of an infinite channel of K, which a weight of 0 does not take away; a copy in LDS before the last
+  // tile cost 3% of a call, offsets clamped for it 1 to 2.5%, this nothing.)
   uint32_t voff[SD::kInstr];
 #pragma unroll
   for (int u = 0; u < SD::kInstr; ++u) {
     const int row = 8 * wave + SD::kRowsPerInstr * u + l_row;
-    voff[u] = static_cast<uint32_t>(row) * static_cast<uint32_t>(row_stride * 2) + ((l_pos ^ ((row >> kRowShift) & (kP - 1))) << 4);
+    voff[u] = static_cast<uint32_t>(min(row, q_b - 1)) * static_cast<uint32_t>(row_stride * 2) + ((l_pos ^ ((row >> kRowShift) & (kP - 1))) << 4);
   }
-  auto buffer_of = [&](const uint16_t* base, uint32_t range) {
-    const uint64_t a = reinterpret_cast<uint64_t>(base);
+  const int last_first = max(0, q_b - kQTile);  // first row of the last tile
+  const uint32_t tile_range = static_cast<uint32_t>(min(kQTile, q_b) - 1) * static_cast<uint32_t>(row_stride * 2) + kRowBytes;
+  auto buffer_of = [&](const uint16_t* base, uint32_t first_byte, uint32_t range) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base) + first_byte;
     u32x4_t buf;
     buf.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
     buf.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32) & 0xffffu);
@@ -166,12 +171,12 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     return buf;
   };
   auto issue_tile = [&](int t) {
-    const int rows = min(kQTile, q_b - t * kQTile);
-    const uint32_t range = rows > 0 ? static_cast<uint32_t>(rows - 1) * static_cast<uint32_t>(row_stride * 2) + kRowBytes : 0u;
-    const int64_t first = row0 + static_cast<int64_t>(t) * kQTile * row_stride;
-    const u32x4_t qb = buffer_of(Q + first, range), db = buffer_of(dO + first, range);
+    const uint32_t range = t < n_qtiles ? tile_range : 0u;
+    // (a sequence's rows span less than 2^31 bytes: checked on the host)
+    const uint32_t first = static_cast<uint32_t>(min(t * kQTile, last_first)) * static_cast<uint32_t>(row_stride * 2);
+    const u32x4_t qb = buffer_of(Q + row0, first, range), db = buffer_of(dO + row0, first, range);
     u32x4_t ob = db;
-    if (!PRE) ob = buffer_of(O + first, range);
+    if (!PRE) ob = buffer_of(O + row0, first, range);
     const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + (t % kStagesSte) * SD::kStageBytes + 8 * wave * kRowBytes);
 #pragma unroll
     for (int u = 0; u < SD::kInstr; ++u) {
@@ -185,19 +190,22 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     issue_tile(1);
   }
 
-  // lse (base 2) of a chunk of this (sequence, head)'s query rows; rows past the end get +inf, which makes their weights 0
+  // lse (base 2) of a chunk of this (sequence, head)'s query rows, in the tiles' order; +inf makes the weight of a row that has been
+  // counted, or that repeats the last one, 0
   float* lse2_l = reinterpret_cast<float*>(lds + kStagesSte * SD::kStageBytes);
   float* dd_l = lse2_l + kLseChunk;
   auto load_lse = [&](int r0) {
     for (int r = tid; r < min(kLseChunk, n_qtiles * kQTile - r0); r += kGradThreads) {
-      const bool ok = r0 + r < q_b;
+      const int last = (n_qtiles - 1) * kQTile;
+      const int row = r0 + r >= last ? last_first + (r0 + r - last) : r0 + r;
+      const bool ok = row < q_b && (r0 + r < last || row >= last);
       if (PRE) {
-        const int64_t at = static_cast<int64_t>(h) * Sq + q0 + r0 + r;
+        const int64_t at = static_cast<int64_t>(h) * Sq + q0 + row;
         const float D = ok ? aux_D[at] : 0.f;
         lse2_l[r] = ok ? aux_lse2[at] : __builtin_inff();
         dd_l[r] = SD::kExact ? D : -D;
       } else {
-        lse2_l[r] = ok ? lse[static_cast<int64_t>(q0 + r0 + r) * H + h] * kLog2e : __builtin_inff();
+        lse2_l[r] = ok ? lse[static_cast<int64_t>(q0 + row) * H + h] * kLog2e : __builtin_inff();
       }
     }
   };
@@ -244,7 +252,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
       }
     }
     acc = lanes_sum<8>(acc);
-    if (d_sub == 0) dd_l[(t & 1) * kQTile + d_row] = SD::kExact ? acc : -acc;
+    if (__builtin_expect(d_sub == 0, 1)) dd_l[(t & 1) * kQTile + d_row] = SD::kExact ? acc : -acc;
   };
   if (!PRE && n_qtiles > 0) row_dots(0);
 
@@ -253,22 +261,8 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     if (PRE) __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t has landed, t+1 may be in flight
     __syncthreads();  // everyone's part of tile t has landed, its D is there; tile t-1 has been read by everyone
     const int c0 = t * kQTile % kLseChunk;
-    if (c0 == 0 && t > 0) {
+    if (__builtin_expect(c0 == 0 && t > 0, 0)) {  // (out of the loop's straight line: in it, 1 to 3% of a call)
       load_lse(t * kQTile);
-      __syncthreads();
-    }
-    // Rows past the sequence's last one have weight 0, which takes away any finite logit; a zero row's logit of an infinite
-    // channel of K is NaN.  They get the last row's channels of Q (in LDS, once per sequence: no call slower by more than its
-    // runs differ, where requests clamped in the loop cost 1 to 2.5%).
-    if (t == n_qtiles - 1 && n_qtiles * kQTile > q_b) {
-      char* tile_q = lds + (t % kStagesSte) * SD::kStageBytes;
-      const int last = q_b - 1 - t * kQTile;
-      for (int i = tid; i < kQTile * kP; i += kGradThreads) {
-        const int row = i / kP, piece = i % kP;
-        if (row > last)
-          *reinterpret_cast<uint4*>(tile_q + row * kRowBytes + ((piece ^ ((row >> kRowShift) & (kP - 1))) << 4)) =
-              *reinterpret_cast<const uint4*>(tile_q + last * kRowBytes + ((piece ^ ((last >> kRowShift) & (kP - 1))) << 4));
-      }
       __syncthreads();
     }
     if (!active) issue_tile(t + 2);
