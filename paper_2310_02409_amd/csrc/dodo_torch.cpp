@@ -86,24 +86,6 @@ size_t bytes_of(const at::Tensor& ws) { return ws.defined() ? static_cast<size_t
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 PyObject* wrap(const at::Tensor& t) { return THPVariable_Wrap(t); }
 
-// New tensors, made without the interpreter lock as torch's own functions make them: an allocation may wait for the device, for
-// another thread's or for an allocator that needs the interpreter.
-struct Unlocked {
-  PyThreadState* state = PyEval_SaveThread();
-  ~Unlocked() { PyEval_RestoreThread(state); }
-};
-at::Tensor new_empty(at::IntArrayRef sizes, const at::TensorOptions& options) {
-  Unlocked u;
-  return at::empty(sizes, options);
-}
-at::Tensor new_zeros(at::IntArrayRef sizes, const at::TensorOptions& options) {
-  Unlocked u;
-  return at::zeros(sizes, options);
-}
-at::Tensor new_like(const at::Tensor& t) {
-  Unlocked u;
-  return at::empty_like(t);
-}
 // an argument that is handed back is the caller's own object
 PyObject* same_or_new(PyObject* given, const at::Tensor& t) {
   if (given == Py_None) return wrap(t);
@@ -111,13 +93,21 @@ PyObject* same_or_new(PyObject* given, const at::Tensor& t) {
   return given;
 }
 
-// Runs `call` without the interpreter lock, as a call through ctypes does; raises the binding's error if it fails.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// Runs `call` -- the allocation of missing results, then the library call -- without the interpreter lock, as torch's own
+// functions and a call through ctypes do (an allocation may wait for the device, for another thread's or for an allocator that
+// needs the interpreter); raises the binding's error if it fails.
 template <class F>
 bool run(const char* where, F call) {
   int rc;
-  Py_BEGIN_ALLOW_THREADS;
-  rc = call();
-  Py_END_ALLOW_THREADS;
+  {
+    Unlocked u;
+    rc = call();
+  }
   if (rc == 0) return true;
   PyObject* r = PyObject_CallFunction(raise_error, "is", rc, where);
   Py_XDECREF(r);
@@ -146,11 +136,12 @@ PyObject* score(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(hidden.dim() == 2 && w.dim() == 1 && w.size(0) == hidden.size(1) && w.scalar_type() == hidden.scalar_type());
     const int code = dtype_code(hidden);
     const int64_t N = hidden.size(0);
-    if (!scores.defined()) scores = new_empty({N}, hidden.options().dtype(at::kFloat));
-    require(scores.scalar_type() == at::kFloat && scores.numel() == N);
+    require(!scores.defined() || (scores.scalar_type() == at::kFloat && scores.numel() == N));
     const int32_t d = int32(hidden.size(1));
-    void* s = stream();
-    if (!run("dodo_score", [&] { return L.score(ptr(hidden), ptr(w), bias, code, N, d, hidden.stride(0), fptr(scores), s); }))
+    if (!run("dodo_score", [&] {
+          if (!scores.defined()) scores = at::empty({N}, hidden.options().dtype(at::kFloat));
+          return L.score(ptr(hidden), ptr(w), bias, code, N, d, hidden.stride(0), fptr(scores), stream());
+        }))
       return nullptr;
     return same_or_new(a[3], scores);
   });
@@ -166,13 +157,12 @@ PyObject* select_topk(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(scores.scalar_type() == at::kFloat && cu_seqlens.numel() == cu_nuggets.numel() && flags >= 0 && flags <= 0x7fffffff);
     require(ws.defined() || max_n <= whole(a[9]));
     require(cu_seqlens.numel() >= 1 && total >= 0);
-    if (!idx.defined()) idx = new_empty({total}, cu_seqlens.options().device(scores.device()));
-    require(idx.scalar_type() == at::kInt && idx.numel() >= total);
+    require(!idx.defined() || (idx.scalar_type() == at::kInt && idx.numel() >= total));
     const int32_t B = int32(cu_seqlens.numel() - 1);
-    void* s = stream();
     if (!run("dodo_select_topk", [&] {
+          if (!idx.defined()) idx = at::empty({total}, cu_seqlens.options().device(scores.device()));
           return L.select_topk(fptr(scores), iptr(cu_seqlens), iptr(cu_nuggets), B, max_n, max_k, static_cast<uint32_t>(flags),
-                               iptr(idx), ptr(ws), bytes_of(ws), s);
+                               iptr(idx), ptr(ws), bytes_of(ws), stream());
         }))
       return nullptr;
     return same_or_new(a[7], idx);
@@ -190,14 +180,13 @@ PyObject* gather_nuggets(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const int64_t h_kv = K.size(1), d_h = K.size(2);
     const bool token = layout == DODO_LAYOUT_TOKEN_MAJOR;
     const int64_t shape[3] = {token ? total : h_kv, token ? h_kv : total, d_h};
-    if (!Kn.defined()) Kn = new_empty(shape, K.options());
-    if (!Vn.defined()) Vn = new_empty(shape, K.options());
-    require(Kn.sizes() == at::IntArrayRef(shape) && Vn.sizes() == at::IntArrayRef(shape));
+    require((!Kn.defined() || Kn.sizes() == at::IntArrayRef(shape)) && (!Vn.defined() || Vn.sizes() == at::IntArrayRef(shape)));
     const int32_t B = int32(cu_seqlens.numel() - 1), h = int32(h_kv), dh = int32(d_h);
-    void* s = stream();
     if (!run("dodo_gather_nuggets", [&] {
+          if (!Kn.defined()) Kn = at::empty(shape, K.options());
+          if (!Vn.defined()) Vn = at::empty(shape, K.options());
           return L.gather(ptr(K), ptr(V), code, iptr(idx), iptr(cu_seqlens), iptr(cu_nuggets), B, total, h, dh, K.stride(0), ptr(Kn),
-                          ptr(Vn), static_cast<int>(layout), s);
+                          ptr(Vn), static_cast<int>(layout), stream());
         }))
       return nullptr;
     PyObject* k = same_or_new(a[7], Kn);
@@ -220,6 +209,7 @@ struct AttentionArgs {
   int32_t H, d_h, B, max_q, max_k, max_local;
   int code;
   float scale;
+  bool want;
   at::Tensor O, lse, ws;
   PyObject *O_given, *lse_given;
 
@@ -235,19 +225,19 @@ struct AttentionArgs {
     max_local = int32(whole(ml));
     code = dtype_code(Q);
     scale = static_cast<float>(softmax_scale == Py_None ? 1.0 / std::sqrt(static_cast<double>(d_h)) : real(softmax_scale));
-    const bool want = truth(want_lse);
-    if (!O.defined()) O = new_like(Q);
-    if (!lse.defined() && want) lse = new_empty({Q.size(0), Q.size(1)}, Q.options().dtype(at::kFloat));
+    want = truth(want_lse);
   }
-  // (the rule of _attention_workspace)
-  void workspace(size_t need, bool grouped) {
+  // Missing results, and a workspace by the rule of _attention_workspace
+  void allocate(size_t need, bool grouped) {
+    if (!O.defined()) O = at::empty_like(Q);
+    if (!lse.defined() && want) lse = at::empty({Q.size(0), Q.size(1)}, Q.options().dtype(at::kFloat));
     const bool block = code == DODO_DTYPE_BF16 && max_q >= DODO_ATTENTION_BLOCK_MIN_Q;
     if (need == 0 || ws.defined() || (!grouped && !block && 2ll * B * H * max_q > 256)) return;
     if (block) {
-      ws = new_empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
+      ws = at::empty({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
       return;
     }
-    ws = new_zeros({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
+    ws = at::zeros({static_cast<int64_t>(need)}, Q.options().dtype(at::kByte));
   }
   PyObject* result() const {
     PyObject* o = same_or_new(O_given, O);
@@ -273,13 +263,12 @@ PyObject* nugget_attention(PyObject*, PyObject* const* args, Py_ssize_t n) {
     AttentionArgs p(a[0], a[5], a[8], a[9], a[10], a[11], a[13], a[14], a[15], a[16]);
     const int32_t H_kv = int32(Kl.size(1));
     const int64_t Kt = Kn.size(layout == DODO_LAYOUT_TOKEN_MAJOR ? 0 : 1);
-    p.workspace(L.attention_ws_grouped(p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.code),
-                p.code == DODO_DTYPE_BF16 && static_cast<int64_t>(p.H) * p.max_q >= 4ll * H_kv);
-    void* s = stream();
     if (!run("dodo_nugget_attention", [&] {
+          p.allocate(L.attention_ws_grouped(p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.code),
+                     p.code == DODO_DTYPE_BF16 && static_cast<int64_t>(p.H) * p.max_q >= 4ll * H_kv);
           return L.attention(ptr(p.Q), ptr(Kn), ptr(Vn), ptr(Kl), ptr(Vl), iptr(p.cu_q), iptr(cu_n), iptr(cu_l), p.B, p.H, H_kv, p.d_h,
                              p.max_q, p.max_k, p.max_local, Kt, p.scale, p.code, static_cast<int>(layout), ptr(p.O), fptr(p.lse),
-                             ptr(p.ws), bytes_of(p.ws), s);
+                             ptr(p.ws), bytes_of(p.ws), stream());
         }))
       return nullptr;
     return p.result();
@@ -294,12 +283,11 @@ PyObject* nugget_attention_indexed(PyObject*, PyObject* const* args, Py_ssize_t 
     const int32_t max_n = int32(whole(a[13]));
     AttentionArgs p(a[0], a[7], a[10], a[11], a[12], a[14], a[15], a[16], a[17], a[18]);
     const int32_t H_kv = int32(K.size(1));
-    p.workspace(L.attention_ws(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.code), false);
-    void* s = stream();
     if (!run("dodo_nugget_attention_indexed", [&] {
+          p.allocate(L.attention_ws(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.code), false);
           return L.attention_indexed(ptr(p.Q), ptr(K), ptr(V), iptr(idx), iptr(cu_s), ptr(Kl), ptr(Vl), iptr(p.cu_q), iptr(cu_n),
                                      iptr(cu_l), p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, max_n, K.stride(0), p.scale,
-                                     p.code, ptr(p.O), fptr(p.lse), ptr(p.ws), bytes_of(p.ws), s);
+                                     p.code, ptr(p.O), fptr(p.lse), ptr(p.ws), bytes_of(p.ws), stream());
         }))
       return nullptr;
     return p.result();
@@ -315,13 +303,12 @@ PyObject* nugget_attention_cached(PyObject*, PyObject* const* args, Py_ssize_t n
     AttentionArgs p(a[0], a[5], a[9], a[10], a[11], a[12], a[14], a[15], a[16], a[17]);
     const int32_t H_kv = int32(Kl.size(1));
     const int64_t Kt = Kn.size(layout == DODO_LAYOUT_TOKEN_MAJOR ? 0 : 1);
-    p.workspace(L.attention_ws_grouped(p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.code),
-                p.code == DODO_DTYPE_BF16 && static_cast<int64_t>(p.H) * p.max_q >= 4ll * H_kv);
-    void* s = stream();
     if (!run("dodo_nugget_attention_cached", [&] {
+          p.allocate(L.attention_ws_grouped(p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.code),
+                     p.code == DODO_DTYPE_BF16 && static_cast<int64_t>(p.H) * p.max_q >= 4ll * H_kv);
           return L.attention_cached(ptr(p.Q), ptr(Kn), ptr(Vn), ptr(Kl), ptr(Vl), iptr(p.cu_q), iptr(start), iptr(len), iptr(cu_l), p.B,
                                     p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, Kt, p.scale, p.code, static_cast<int>(layout),
-                                    ptr(p.O), fptr(p.lse), ptr(p.ws), bytes_of(p.ws), s);
+                                    ptr(p.O), fptr(p.lse), ptr(p.ws), bytes_of(p.ws), stream());
         }))
       return nullptr;
     return p.result();
@@ -339,10 +326,9 @@ PyObject* stream_append(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const int code = dtype_code(K_rows);
     const int32_t B = int32(K_rows.size(0)), h = int32(K_rows.size(1)), dh = int32(K_rows.size(2)), cap = int32(Kn.size(1));
     require(K_rows.stride(2) == 1 && K_rows.stride(1) == dh);
-    void* s = stream();
     if (!run("dodo_stream_append", [&] {
           return L.stream_append(fptr(scores), fptr(lam), ptr(K_rows), ptr(V_rows), code, B, h, dh, K_rows.stride(0), cap, iptr(counts),
-                                 iptr(dropped), ptr(Kn), ptr(Vn), s);
+                                 iptr(dropped), ptr(Kn), ptr(Vn), stream());
         }))
       return nullptr;
     Py_RETURN_TRUE;
@@ -361,15 +347,12 @@ PyObject* score_mlp(PyObject*, PyObject* const* args, Py_ssize_t n) {
     require(W1.size(1) == d && b1.size(0) == d_hid && w2.size(0) == d_hid && b1.scalar_type() == at::kFloat);
     require(W1.scalar_type() == hidden.scalar_type() && w2.scalar_type() == hidden.scalar_type());
     const int code = dtype_code(hidden);
-    if (!out.defined()) out = new_empty({N}, hidden.options().dtype(at::kFloat));
-    if (!ws.defined()) {
-      const size_t need = L.score_mlp_ws(code, N, d, d_hid);
-      if (need > 0) ws = new_empty({static_cast<int64_t>(need)}, hidden.options().dtype(at::kByte));
-    }
-    void* s = stream();
     if (!run("dodo_score_mlp", [&] {
+          if (!out.defined()) out = at::empty({N}, hidden.options().dtype(at::kFloat));
+          const size_t need = ws.defined() ? 0 : L.score_mlp_ws(code, N, d, d_hid);
+          if (need > 0) ws = at::empty({static_cast<int64_t>(need)}, hidden.options().dtype(at::kByte));
           return L.score_mlp(ptr(hidden), ptr(W1), fptr(b1), ptr(w2), b2, act, code, N, d, d_hid, hidden.stride(0), fptr(out), ptr(ws),
-                             bytes_of(ws), s);
+                             bytes_of(ws), stream());
         }))
       return nullptr;
     return same_or_new(a[6], out);
