@@ -272,3 +272,22 @@ def test_workspace_of_shared_keys_serves_a_decode_call():
         check_attention(O, want, torch.bfloat16)
         got = decode(ws)
         assert torch.equal(got[0], fresh[0]) and torch.equal(got[1], fresh[1])
+
+
+# What one (sequence, head) holds stays there: tiles that are not full leave nothing of an earlier tile, block or head in LDS (rows
+# past a tile's last one arrive as zeros).  NaN in all K and V of two of 256 pairs; every other row has the bits of a run without.
+@pytest.mark.parametrize("q,k", [(300, 70), (100, 70), (129, 3)])
+def test_nan_stays_in_its_head(q, k):
+    import paper_2310_02409_amd as D
+    B, H, d_h, m = 8, 32, 128, q + 5
+    _, t = make_attention_case(580 + q, [q] * B, [k] * B, [m] * B, H, H, d_h, torch.bfloat16, dev())
+    run = lambda: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], q, k, m, want_lse=True)
+    O, lse = run()
+    bad = torch.zeros(B * q, H, dtype=torch.bool, device=dev())
+    for b, h in ((2, 3), (5, 17)):
+        for n, rows in (("Kn", k), ("Vn", k), ("Kl", m), ("Vl", m)):
+            t[n][b * rows:(b + 1) * rows, h] = float("nan")
+        bad[b * q:(b + 1) * q, h] = True
+    O2, lse2 = run()
+    assert torch.equal(O2[~bad], O[~bad]) and torch.equal(lse2[~bad], lse[~bad])
+    assert torch.isnan(O2[bad]).all()
