@@ -85,7 +85,7 @@ __device__ __forceinline__ float load_elem(const void* p, int64_t i) {
 // Inline assembly, so the compiler does not order later LDS reads behind it: callers keep the vmcnt bookkeeping.
 // The compiler does not count wait states into it either: a scalar register that a vector instruction (v_readfirstlane)
 // wrote may be read by a memory instruction 5 wait states later, so m0's write and 4 idle ones stand before the load whatever
-// comes before.  (With the one that m0 needs, 55 loads of the build came 2 to 4 after the write.  The three more cost nothing
+// comes before.  (With the one that m0 needs, 55 loads of the library came 2 to 4 after the write.  The three more cost nothing
 // that can be measured, whether per load or once per descriptor: 2048 rows, 103 nuggets, 16 x 40 heads 843 against 844 us a
 // layer, 8 x 512 rows, 410 nuggets 134.0 against 134.3.)
 // STREAM: with the non-temporal hint, for data that no one reads again soon.

@@ -1,4 +1,4 @@
-"""Wait states in the device code of this build, read from its assembly (CPU only).
+"""Wait states in the device code of the built library, read from its assembly (CPU only).
 
 A vector instruction that writes a scalar register has to be 5 wait states ahead of a memory instruction that reads that
 register.  The compiler sees to it for its own loads but does not look into inline assembly, from which the direct loads to
