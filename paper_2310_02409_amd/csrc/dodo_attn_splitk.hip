@@ -16,6 +16,13 @@
 // order and the last split has the highest indices, so what it waits for is running or done; the wait is bounded
 // anyway), merges the partials in split order, writes the row and clears the flags.  No float atomics anywhere,
 // so results are run-to-run deterministic.
+//
+// A split call of one sequence is bound by latencies: of 8.0 us (667 rows, 32 heads, eight splits) 2.0 were the launch,
+// 2.5 the first rows, 0.8 their arithmetic, 0.9 the merge inside the workgroup and 1.8 that of the splits.  Lane swaps
+// instead of LDS permutes, one wavefront that merges, stores and signals without a barrier, and polls 64 instead of 1024
+// cycles apart: 7.35 us (2 x 667 rows 10.1 -> 9.6, 8 x 1057 rows of 64 channels, 16 heads 12.4 -> 11.3, 1 x 6500 22.4 -> 21.6).
+#include <type_traits>
+
 #include "dodo_attn.h"
 
 namespace dodo {
@@ -65,13 +72,31 @@ __device__ __forceinline__ float sum_over_row_lanes(float d) {
   return d;
 }
 
+// x of the lower and of the upper lane of the pair (lane, lane ^ OFF), the same in both.  Lanes 16 and 32 apart: the swap
+// instructions, which exchange one half of the first operand with the other half of the second.
+template <int OFF>
+__device__ __forceinline__ void lane_pair(float x, float& lower, float& upper) {
+  const uint32_t b = __float_as_uint(x);
+  if constexpr (OFF == 8) {
+    const float other = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(b), 0x128, 0xf, 0xf, false)));  // row_ror:8
+    const bool up = (threadIdx.x & 8) != 0;
+    lower = up ? other : x;
+    upper = up ? x : other;
+  } else {
+    static_assert(OFF == 16 || OFF == 32, "lanes 8, 16 or 32 apart");
+    const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(b, b, false, false) : __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    lower = __uint_as_float(r[0]);
+    upper = __uint_as_float(r[1]);
+  }
+}
+
 __device__ __forceinline__ float exp2_guard(float x) { return __builtin_amdgcn_exp2f(x); }  // exp2(-inf) = 0
 
 // INDEXED: Kn / Vn are the context's K / V ([N, H_kv, DH], nug_tok_stride between tokens) and nugget j of
 // sequence b is token cu_ctx[b] + nug_idx[cu_nuggets[b] + j] of it (no packed cache has been made).
 // GROUPED: the workgroup serves GH query heads of one KV head times QR query rows, more than one query vector in all
 // (else both are 1 and everything about them folds away).
-constexpr int kThreads = 256;  // (1024-thread workgroups were never faster: two more rounds of the merge, and a split less)
+constexpr int kThreads = 256;  // (512- and 1024-thread workgroups were never faster: more partials to merge)
 template <int DTYPE, int DH, bool INDEXED, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void splitk_attention_kernel(
     const void* __restrict__ Q, const void* __restrict__ Kn, const void* __restrict__ Vn,
@@ -295,23 +320,25 @@ __global__ __launch_bounds__(kThreads) void splitk_attention_kernel(
   // partial per wavefront and the loops below are short.  Several query vectors: one partial per lane group.
   constexpr int kParts = GROUPED ? kGroups : kThreads / kWave;
   if (!GROUPED) {
-#pragma unroll
-    for (int off = kLPR; off < kWave; off <<= 1) {
-      const bool upper = (threadIdx.x & off) != 0;
-      const float m_x = __shfl_xor(m, off, kWave), s_x = __shfl_xor(ssum, off, kWave);
-      const float m_a = upper ? m_x : m, m_b2 = upper ? m : m_x;
-      const float s_a = upper ? s_x : ssum, s_b2 = upper ? ssum : s_x;
+    auto merge_lanes = [&](auto off_tag) {
+      constexpr int OFF = decltype(off_tag)::value;
+      float m_a, m_b2, s_a, s_b2;
+      lane_pair<OFF>(m, m_a, m_b2);
+      lane_pair<OFF>(ssum, s_a, s_b2);
       const float mb = fmaxf(m_a, m_b2);
       const float w_a = (mb == kNegInf) ? 0.f : exp2_guard(m_a - mb), w_b = (mb == kNegInf) ? 0.f : exp2_guard(m_b2 - mb);
       ssum = fmaf(s_b2, w_b, s_a * w_a);
 #pragma unroll
       for (int e = 0; e < kEPL; ++e) {
-        const float o_x = __shfl_xor(o[e], off, kWave);
-        const float o_a = upper ? o_x : o[e], o_b = upper ? o[e] : o_x;
+        float o_a, o_b;
+        lane_pair<OFF>(o[e], o_a, o_b);
         o[e] = fmaf(o_b, w_b, o_a * w_a);
       }
       m = mb;
-    }
+    };
+    if (kLPR <= 8) merge_lanes(std::integral_constant<int, 8>{});
+    if (kLPR <= 16) merge_lanes(std::integral_constant<int, 16>{});
+    merge_lanes(std::integral_constant<int, 32>{});
   }
   const int part = GROUPED ? g : static_cast<int>(threadIdx.x) / kWave;
   if (GROUPED || (threadIdx.x & (kWave - 1)) < kLPR) {
@@ -323,37 +350,46 @@ __global__ __launch_bounds__(kThreads) void splitk_attention_kernel(
     for (int e = 0; e < kEPL; ++e) part_o[part][sub * kEPL + e] = o[e];
   }
   __syncthreads();
-  for (int hh = 0; hh < GV; ++hh) {  // one query vector of the workgroup after the other (uniform over the workgroup)
+  // A query vector's merge is the work of one wavefront, which needs no barrier for it: lane l takes channels l and l + 64
+  // (one, if the head has no more).
+  static_assert(DH == 64 || DH == 128, "one or two channels per lane");
+  constexpr int kCh = DH / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int hh = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); hh < GV; hh += kThreads / kWave) {
     const int i_out = i0 + (hh >> GH_L), h_out = head0 + (hh & (GH - 1));
     if (i_out >= q_b) continue;
     const int64_t out_row = static_cast<int64_t>(q0 + i_out) * H + h_out;
-    float Mg = kNegInf, Sg = 0.f, og = 0.f;  // this workgroup's merged partial of the head (threads < DH: channel threadIdx.x)
-    if (threadIdx.x < DH) {
-      const int c = threadIdx.x;
-      float M = kNegInf;
-      for (int gg = hh; gg < kParts; gg += GV) M = fmaxf(M, part_m[gg]);
-      float S = 0.f, oc = 0.f;
-      if (M != kNegInf) {
-        for (int gg = hh; gg < kParts; gg += GV) {
-          const float wgt = exp2_guard(part_m[gg] - M);
-          S = fmaf(part_s[gg], wgt, S);
-          oc = fmaf(part_o[gg][c], wgt, oc);
+    auto store_row = [&](const float (&val)[kCh], float lse_val) {
+#pragma unroll
+      for (int e = 0; e < kCh; ++e) {
+        const int64_t at = out_row * DH + lane + e * kWave;
+        if (DTYPE == DODO_DTYPE_F32) {
+          static_cast<float*>(O)[at] = val[e];
+        } else {
+          static_cast<uint16_t*>(O)[at] = static_cast<uint16_t>(f32_to_bf16_bits(val[e]));
         }
       }
-      Mg = M;
-      Sg = S;
-      og = oc;
-      if (nsplit == 1) {
-        const float val = (S > 0.f) ? oc / S : 0.f;
-        if (DTYPE == DODO_DTYPE_F32) {
-          static_cast<float*>(O)[out_row * DH + c] = val;
-        } else {
-          static_cast<uint16_t*>(O)[out_row * DH + c] = static_cast<uint16_t>(f32_to_bf16_bits(val));
-        }
-        if (lse != nullptr && c == 0) lse[out_row] = (S > 0.f) ? (M + __log2f(S)) * 0.6931471805599453f : kNegInf;
+      if (lse != nullptr && lane == 0) lse[out_row] = lse_val;
+    };
+    float Mg = kNegInf, Sg = 0.f, og[kCh];  // this workgroup's merged partial of the head
+#pragma unroll
+    for (int e = 0; e < kCh; ++e) og[e] = 0.f;
+    for (int gg = hh; gg < kParts; gg += GV) Mg = fmaxf(Mg, part_m[gg]);
+    if (Mg != kNegInf) {
+      for (int gg = hh; gg < kParts; gg += GV) {
+        const float wgt = exp2_guard(part_m[gg] - Mg);
+        Sg = fmaf(part_s[gg], wgt, Sg);
+#pragma unroll
+        for (int e = 0; e < kCh; ++e) og[e] = fmaf(part_o[gg][lane + e * kWave], wgt, og[e]);
       }
     }
-    if (nsplit == 1) continue;
+    if (nsplit == 1) {
+      float val[kCh];
+#pragma unroll
+      for (int e = 0; e < kCh; ++e) val[e] = (Sg > 0.f) ? og[e] / Sg : 0.f;
+      store_row(val, (Sg > 0.f) ? (Mg + __log2f(Sg)) * 0.6931471805599453f : kNegInf);
+      continue;
+    }
 
     // ---- several splits: the last one combines, in split order ----
     const int64_t slot0 = ((static_cast<int64_t>(b) * max_q + i_out) * H + h_out) * nsplit;
@@ -362,86 +398,90 @@ __global__ __launch_bounds__(kThreads) void splitk_attention_kernel(
       // loads that go to the level where all XCDs agree), so no cache has to be written back or
       // invalidated as a whole; the wait makes sure that the record has arrived there before the
       // flag is sent after it.
-      if (threadIdx.x < DH) {
-        float* rec = ws + (slot0 + split) * partial_floats<DH>();
-        if (threadIdx.x == 0) {
-          __hip_atomic_store(rec + 0, Mg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(rec + 1, Sg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __hip_atomic_store(rec + 2 + threadIdx.x, og, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's stores are acknowledged
-      }
-      __syncthreads();
-      if (threadIdx.x == 0)
+      float* rec = ws + (slot0 + split) * partial_floats<DH>();
+      if (lane < 2) __hip_atomic_store(rec + lane, lane == 0 ? Mg : Sg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int e = 0; e < kCh; ++e)
+        __hip_atomic_store(rec + 2 + lane + e * kWave, og[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the wavefront's stores are acknowledged
+      if (lane == 0)
         __hip_atomic_store(flags + slot0 + split, kPartialReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       continue;
     }
-    // one thread per flag, all at once: a device-scope load is a round trip past the XCD's L2, and the splits of
+    // one lane per flag, all at once: a device-scope load is a round trip past the XCD's L2, and the splits of
     // a row finish at about the same time, so polling the flags one after the other would cost a trip each
-    int ok = 1;
-    if (static_cast<int>(threadIdx.x) + 1 < nsplit) {
-      int polls = 0;
-      while (__hip_atomic_load(flags + slot0 + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kPartialReady) {
-        if (++polls > kMaxPolls) {
-          ok = 0;
+    bool complete = true;
+    for (int f0 = 0; f0 + 1 < nsplit; f0 += kWave) {
+      const int f = min(f0 + lane, nsplit - 2);
+      for (int polls = 0;; ++polls) {
+        const uint32_t flag = __hip_atomic_load(flags + slot0 + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__all(flag == kPartialReady)) break;
+        if (polls >= kMaxPolls) {
+          complete = false;
           break;
         }
-        __builtin_amdgcn_s_sleep(16);
+        __builtin_amdgcn_s_sleep(1);
       }
     }
-    const int all_there = __syncthreads_and(ok);
-    if (threadIdx.x < DH) {
-      const int c = threadIdx.x;
-      const float* rec0 = ws + slot0 * partial_floats<DH>();
-      // splits in batches of 8 with all loads of a batch issued before the first use; the own
-      // partial (the last split) comes last, so the order of the merge is the split order
-      constexpr int kBatch = 8;
-      float M = kNegInf, S = 0.f, oc = 0.f;
-      // a batch's records are summed before they join the sums so far (a shorter chain of rounded additions)
-      auto merge = [&](const float* m1, const float* s1, const float* o1, int n) {
-        float mb = M;
-        for (int u = 0; u < n; ++u) mb = fmaxf(mb, m1[u]);
-        if (mb == kNegInf) return;
-        float bs = 0.f, bo = 0.f;
-        for (int u = 0; u < n; ++u) {
-          const float wgt = exp2_guard(m1[u] - mb);
-          bs = fmaf(s1[u], wgt, bs);
-          bo = fmaf(o1[u], wgt, bo);
-        }
-        const float keep = exp2_guard(M - mb);
-        S = fmaf(S, keep, bs);
-        oc = fmaf(oc, keep, bo);
-        M = mb;
-      };
-      for (int s0 = 0; s0 + 1 < nsplit; s0 += kBatch) {
-        float mm[kBatch], sv[kBatch], ov[kBatch];
+    asm volatile("" ::: "memory");
+    const float* rec0 = ws + slot0 * partial_floats<DH>();
+    // splits in batches of 8 with all loads of a batch issued before the first use; the own
+    // partial (the last split) comes last, so the order of the merge is the split order
+    constexpr int kBatch = 8;
+    float M = kNegInf, S = 0.f, oc[kCh];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const float* r = rec0 + min(s0 + u, nsplit - 2) * partial_floats<DH>();
-          mm[u] = __hip_atomic_load(r + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          sv[u] = __hip_atomic_load(r + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ov[u] = __hip_atomic_load(r + 2 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    for (int e = 0; e < kCh; ++e) oc[e] = 0.f;
+    // a batch's records are summed before they join the sums so far (a shorter chain of rounded additions)
+    auto merge = [&](const float* m1, const float* s1, const float (*o1)[kCh], int n) {
+      float mb = M;
+      for (int u = 0; u < n; ++u) mb = fmaxf(mb, m1[u]);
+      if (mb == kNegInf) return;
+      float bs = 0.f, bo[kCh];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-          if (s0 + u + 1 >= nsplit) mm[u] = kNegInf;  // (past the last record of another split: weight 0)
-        merge(mm, sv, ov, kBatch);
+      for (int e = 0; e < kCh; ++e) bo[e] = 0.f;
+      for (int u = 0; u < n; ++u) {
+        const float wgt = exp2_guard(m1[u] - mb);
+        bs = fmaf(s1[u], wgt, bs);
+#pragma unroll
+        for (int e = 0; e < kCh; ++e) bo[e] = fmaf(o1[u][e], wgt, bo[e]);
       }
-      merge(&Mg, &Sg, &og, 1);
-      const bool complete = all_there != 0;
-      const float nan = __builtin_nanf("");
-      const float val = !complete ? nan : (S > 0.f) ? oc / S : 0.f;  // a partial never arrived: fail loudly
-      if (DTYPE == DODO_DTYPE_F32) {
-        static_cast<float*>(O)[out_row * DH + c] = val;
-      } else {
-        static_cast<uint16_t*>(O)[out_row * DH + c] = static_cast<uint16_t>(f32_to_bf16_bits(val));
+      const float keep = exp2_guard(M - mb);
+      S = fmaf(S, keep, bs);
+#pragma unroll
+      for (int e = 0; e < kCh; ++e) oc[e] = fmaf(oc[e], keep, bo[e]);
+      M = mb;
+    };
+    for (int s0 = 0; s0 + 1 < nsplit; s0 += kBatch) {
+      const int n_recs = min(kBatch, nsplit - 1 - s0);
+      // lane 2u has m of record u, lane 2u + 1 its s (lanes beyond: the last record's)
+      const int word = __float_as_int(__hip_atomic_load(rec0 + (s0 + min((lane & 15) >> 1, n_recs - 1)) * partial_floats<DH>() + (lane & 1),
+                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      float mm[kBatch], sv[kBatch], ov[kBatch][kCh];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int e = 0; e < kCh; ++e)
+          ov[u][e] = __hip_atomic_load(rec0 + (s0 + min(u, n_recs - 1)) * partial_floats<DH>() + 2 + lane + e * kWave, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        mm[u] = u < n_recs ? __int_as_float(__builtin_amdgcn_readlane(word, 2 * u)) : kNegInf;  // (past the last: weight 0)
+        sv[u] = __int_as_float(__builtin_amdgcn_readlane(word, 2 * u + 1));
       }
-      if (lse != nullptr && c == 0)
-        lse[out_row] = !complete ? nan : (S > 0.f) ? (M + __log2f(S)) * 0.6931471805599453f : kNegInf;
-      // the flags are left cleared for the next call on this workspace
-      for (int f = c; f + 1 < nsplit; f += DH)
-        __hip_atomic_store(flags + slot0 + f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      merge(mm, sv, ov, kBatch);
     }
+    float own[1][kCh];
+#pragma unroll
+    for (int e = 0; e < kCh; ++e) own[0][e] = og[e];
+    merge(&Mg, &Sg, own, 1);
+    // the flags are left cleared for the next call on this workspace
+    for (int f = lane; f + 1 < nsplit; f += kWave)
+      __hip_atomic_store(flags + slot0 + f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const float nan = __builtin_nanf("");
+    float val[kCh];
+#pragma unroll
+    for (int e = 0; e < kCh; ++e) val[e] = !complete ? nan : (S > 0.f) ? oc[e] / S : 0.f;  // a partial never arrived: fail loudly
+    store_row(val, !complete ? nan : (S > 0.f) ? (M + __log2f(S)) * 0.6931471805599453f : kNegInf);
   }
 }
 
@@ -500,10 +540,10 @@ int launch_t(const AttnParams& p, int nsplit) {
 }  // namespace
 
 namespace {
-// Most splits of a (query row, head).  The combining costs about 2 us, so nothing is split below 96 KiB of K rows
-// (350 rows of 32 heads, one sequence: 7.2 us unsplit, 7.4 in eight; 450 rows: 8.6 against 7.6; 667 rows: 10.5
-// against 8.0; 64-wide heads: level at twice as many rows), and a split keeps at least 12 KiB of them (48 rows of 128
-// channels in bf16, three quarters of what its wavefronts request in one go).
+// Most splits of a (query row, head).  The combining costs about 1.5 us (2 when this was measured), so nothing is split
+// below 96 KiB of K rows (350 rows of 32 heads, one sequence: 7.2 us unsplit, 7.4 in eight; 450 rows: 8.6 against 7.6; 667
+// rows: 10.5 against 8.0; 64-wide heads: level at twice as many rows), and a split keeps at least 12 KiB of them (48 rows of
+// 128 channels in bf16, three quarters of what its wavefronts request in one go).
 int64_t most_splits(int32_t d_h, int32_t max_k, int32_t max_local, int dtype) {
   const int64_t k_bytes = (static_cast<int64_t>(max_k) + max_local) * d_h * elem_bytes(dtype);
   if (k_bytes < 96 * 1024) return 1;
