@@ -134,12 +134,7 @@ struct TileLoader {
   // nothing and reads as zeros, so that neither the rows past a tile's last one nor a tile past the last need a test per
   // lane.  Every call enqueues the same number of loads.
   __device__ __forceinline__ void issue(const uint16_t* base, uint32_t range, const uint32_t (&off)[kPerWave], uint32_t lds_dst) const {
-    const uint64_t b = reinterpret_cast<uint64_t>(base);
-    u32x4_t buf;
-    buf.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b));
-    buf.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32) & 0xffffu);
-    buf.z = __builtin_amdgcn_readfirstlane(range);
-    buf.w = 0x00027000u;
+    const u32x4_t buf = buffer_of(base, range);
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) dma16_buffer(buf, off[u], __builtin_amdgcn_readfirstlane(lds_dst + lds_chunk0 + u * 1024));
   }

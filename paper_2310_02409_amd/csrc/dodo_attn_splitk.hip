@@ -72,24 +72,6 @@ __device__ __forceinline__ float sum_over_row_lanes(float d) {
   return d;
 }
 
-// x of the lower and of the upper lane of the pair (lane, lane ^ OFF), the same in both.  Lanes 16 and 32 apart: the swap
-// instructions, which exchange one half of the first operand with the other half of the second.
-template <int OFF>
-__device__ __forceinline__ void lane_pair(float x, float& lower, float& upper) {
-  const uint32_t b = __float_as_uint(x);
-  if constexpr (OFF == 8) {
-    const float other = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(b), 0x128, 0xf, 0xf, false)));  // row_ror:8
-    const bool up = (threadIdx.x & 8) != 0;
-    lower = up ? other : x;
-    upper = up ? x : other;
-  } else {
-    static_assert(OFF == 16 || OFF == 32, "lanes 8, 16 or 32 apart");
-    const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(b, b, false, false) : __builtin_amdgcn_permlane32_swap(b, b, false, false);
-    lower = __uint_as_float(r[0]);
-    upper = __uint_as_float(r[1]);
-  }
-}
-
 __device__ __forceinline__ float exp2_guard(float x) { return __builtin_amdgcn_exp2f(x); }  // exp2(-inf) = 0
 
 // INDEXED: Kn / Vn are the context's K / V ([N, H_kv, DH], nug_tok_stride between tokens) and nugget j of

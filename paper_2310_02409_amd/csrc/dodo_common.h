@@ -106,9 +106,25 @@ __device__ __forceinline__ void dma16_uniform(const void* base, uint32_t voff, u
 
 // The same through a buffer descriptor (in scalar registers): lanes whose offset lies outside of its range fetch nothing and
 // put zeros into LDS.
+template <bool STREAM = false>
 __device__ __forceinline__ void dma16_buffer(const u32x4_t& buf, uint32_t voff, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
-               : "memory", "m0");
+  if (STREAM) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen nt lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
+                 : "memory", "m0");
+  } else {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buf), "s"(lds_dst)
+                 : "memory", "m0");
+  }
+}
+// A descriptor of `range` bytes from `base` on (both uniform; made so explicitly).
+__device__ __forceinline__ u32x4_t buffer_of(const void* base, uint32_t range) {
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  u32x4_t buf;
+  buf.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b));
+  buf.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32) & 0xffffu);
+  buf.z = __builtin_amdgcn_readfirstlane(range);
+  buf.w = 0x00027000u;
+  return buf;
 }
 
 // Sum over groups of NL consecutive lanes (NL = 8 or 16: inside one row of 16 lanes), every lane getting its
@@ -135,6 +151,24 @@ __device__ __forceinline__ float wave_sum64(float x) {
   const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 32));
   const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(r, 48));
   return (r0 + r1) + (r2 + r3);
+}
+
+// x of the lower and of the upper lane of the pair (lane, lane ^ OFF), the same in both.  Lanes 16 and 32 apart: the swap
+// instructions, which exchange one half of the first operand with the other half of the second.
+template <int OFF>
+__device__ __forceinline__ void lane_pair(float x, float& lower, float& upper) {
+  const uint32_t b = __float_as_uint(x);
+  if constexpr (OFF == 8) {
+    const float other = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(b), 0x128, 0xf, 0xf, false)));  // row_ror:8
+    const bool up = (threadIdx.x & 8) != 0;
+    lower = up ? other : x;
+    upper = up ? x : other;
+  } else {
+    static_assert(OFF == 16 || OFF == 32, "lanes 8, 16 or 32 apart");
+    const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(b, b, false, false) : __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    lower = __uint_as_float(r[0]);
+    upper = __uint_as_float(r[1]);
+  }
 }
 
 // Division of a number below 2^31 by a divisor fixed on the host: one 32 x 32 -> 64 bit multiplication and a

@@ -208,3 +208,55 @@ def test_entry_point_that_allocates_nothing(D):
                                         t["cu_local"], max(q), max(k), max(m), scale, D.TOKEN_MAJOR, O, lse)
         check_attention(O, O_ref, BF)
         check_lse(lse, lse_ref, BF)
+
+
+# Tiles 16 (up to 16 query vectors per KV head) and 32 wide, at 4, 16, 17 and 32 vectors: nuggets and local rows at the edges of
+# the 32-key tiles and of the wavefronts' turns, and the weights' precision -- in two bf16 parts they leave O the error of its own
+# rounding (2^-9 relative: 2-norm 1.66e-3), where weights rounded to bf16 would show 2.1e-3 or more.
+@pytest.mark.parametrize("G,q", [(4, 1), (16, 1), (17, 1), (32, 1), (1, 4), (1, 15), (2, 8), (3, 10)])
+@pytest.mark.parametrize("d_h", [64, 128])
+def test_widths_of_the_tiles(D, G, q, d_h):
+    B, H_kv = 34, 8
+    edges = [0, 1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160, 255, 300]
+    k_lens = [edges[i % 14] for i in range(B)]
+    m_lens = [max(q, edges[(5 * i + 3) % 14]) for i in range(B)]
+    host, t = make_attention_case(800 + G, [q] * B, k_lens, m_lens, G * H_kv, H_kv, d_h, BF, dev())
+    scale = default_scale(d_h)
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], scale)
+    O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], q, max(k_lens),
+                                     max(m_lens), scale, want_lse=True)
+    check_attention(O, want, BF)
+    check_lse(lse, lse_want, BF)
+    err = O.float().cpu().double().numpy().reshape(want.shape) - want
+    assert np.linalg.norm(err) <= 1.9e-3 * np.linalg.norm(want)
+
+
+# An infinity in a visible row of V is the row's result, as with a weight in one piece; other rows and channels are not touched.
+def test_infinite_value_in_a_visible_row(D):
+    B, H, H_kv, d_h = 40, 32, 8, 128
+    host, t = make_attention_case(830, [1] * B, [90] * B, [40] * B, H, H_kv, d_h, BF, dev())
+    clean = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 1, 90, 40)[0]
+    t["Vn"][90 * 3 + 50, 2, 7] = float("inf")
+    t["Vl"][40 * 5 + 11, 0, 64] = float("-inf")
+    O = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 1, 90, 40)[0]
+    want = clean.clone()
+    want[3, 8:12, 7] = float("inf")
+    want[5, 0:4, 64] = float("-inf")
+    assert torch.equal(O, want)
+
+
+# A small batch with one query row each goes from the split-K kernel to this one where its vectors and rows are many; the line
+# lies at 128 Ki of their products.  Both sides have the same precision.
+@pytest.mark.parametrize("k", [200, 480, 500, 1500])
+def test_small_batches_on_either_side_of_the_line(D, k):
+    B, H, H_kv, d_h = 4, 64, 8, 128
+    k_lens, m_lens = [k - 7 * b for b in range(B)], [10 + b for b in range(B)]
+    host, t = make_attention_case(840, [1] * B, k_lens, m_lens, H, H_kv, d_h, BF, dev())
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], default_scale(d_h))
+    O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 1, max(k_lens),
+                                     max(m_lens), want_lse=True)
+    check_lse(lse, lse_want, BF)
+    err = O.float().cpu().double().numpy().reshape(want.shape) - want
+    assert np.linalg.norm(err) <= 1.9e-3 * np.linalg.norm(want)
