@@ -16,12 +16,14 @@ bool use_block_kernel(int dtype, int32_t d_h, int32_t max_q) {
 }  // namespace
 }  // namespace dodo
 
-extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k,
-                                                        int32_t max_local, int dtype) {
-  using namespace dodo;
+namespace dodo {
+namespace {
+
+// (H_kv = 0: not known)
+size_t workspace_bytes(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, int dtype) {
   if (B <= 0 || H <= 0 || d_h <= 0 || max_q <= 0 || max_k < 0 || max_local < 0) return 0;
   if (use_block_kernel(dtype, d_h, max_q)) {
-    const size_t block = block_workspace_bytes(B, H, d_h, max_q, max_k, max_local);
+    const size_t block = block_workspace_bytes(B, H, H_kv, d_h, max_q, max_k, max_local);
     if (block == 0) return 0;
     // it serves smaller calls too, and those of fewer rows than a query block split their keys over up to a record per
     // compute unit (the most (row, head) pairs that still do)
@@ -33,12 +35,21 @@ extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, in
   return splitk_most_records(B, H, d_h, max_q, max_k, max_local, dtype) * splitk_record_bytes(d_h);
 }
 
+}  // namespace
+}  // namespace dodo
+
+extern "C" size_t dodo_nugget_attention_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k,
+                                                        int32_t max_local, int dtype) {
+  return dodo::workspace_bytes(B, H, 0, d_h, max_q, max_k, max_local, dtype);
+}
+
 extern "C" size_t dodo_nugget_attention_workspace_bytes_grouped(int32_t B, int32_t H, int32_t H_kv, int32_t d_h,
                                                                 int32_t max_q, int32_t max_k, int32_t max_local,
                                                                 int dtype) {
   using namespace dodo;
-  const size_t plain = dodo_nugget_attention_workspace_bytes(B, H, d_h, max_q, max_k, max_local, dtype);
-  if (B <= 0 || H <= 0 || H_kv <= 0 || H % H_kv != 0 || max_q <= 0 || max_k < 0 || max_local < 0) return plain;
+  const bool known = H > 0 && H_kv > 0 && H % H_kv == 0;
+  const size_t plain = workspace_bytes(B, H, known ? H_kv : 0, d_h, max_q, max_k, max_local, dtype);
+  if (B <= 0 || !known || max_q <= 0 || max_k < 0 || max_local < 0) return plain;
   if (use_block_kernel(dtype, d_h, max_q) || dtype != DODO_DTYPE_BF16 || (d_h != 128 && d_h != 64)) return plain;
   if (group_launches(H, H_kv, max_q) == 0) return plain;  // too few query vectors share their K/V rows, or too many
   const size_t grouped = group_workspace_bytes(B, H, H_kv, d_h, max_q, max_k, max_local);

@@ -4,8 +4,10 @@
 // fp32 accumulation, d_h = 128 or 64 (a template parameter: the tile loops, LDS
 // layout and fragment counts follow from it).  Inputs must be finite.
 //
-// Work split: one workgroup owns NW*32 consecutive query rows of one (sequence,
-// head); each wavefront owns 32 of them.  Keys arrive in tiles of 64: first the
+// Work split: query heads of one K/V head see the same keys, so that the rows of G such
+// neighbours (G from 1 to H / H_kv, see plan_blocks) can go through the tiles together:
+// row f of the group is head f % G of query row f / G.  One workgroup owns NW*32
+// consecutive rows of one (sequence, group); each wavefront owns 32 of them.  Keys arrive in tiles of 64: first the
 // dense nugget tiles, then the local tiles up to the causal diagonal.  K and V
 // tiles go from global memory straight into LDS (16-byte direct loads issued as
 // inline assembly, so that the compiler does not order every later LDS read behind
@@ -36,6 +38,7 @@
 // bit selects, the row maximum taken in the first tile only: 2048 rows, 103 nuggets,
 // 16 x 40 heads 812 -> 772 us (931 -> 981 TFLOP/s); 1024 rows, 3277 nuggets, 2 x 32
 // heads 119 -> 113 us; 512 rows, 410 nuggets, 8 x 32 heads 75.5 -> 72.6 us.
+#include <algorithm>
 #include <type_traits>
 
 #include "dodo_attn.h"
@@ -248,19 +251,18 @@ struct BlockCfg {
 // (and, gather-free form, the first token of its context).  Read with scalar loads by load_seq_geom, for both query
 // blocks of a workgroup at the kernel's start, so that no block begins with a chain of dependent loads.
 struct SeqGeom {
-  int b, h, kvh;
+  int b, grp;
   int q0, q_b, k0, k_b, l0, m_b;
   int64_t ctx0;
 };
 template <bool IDX>
-__device__ __forceinline__ SeqGeom load_seq_geom(int bh, FastDiv div_H, int H, FastDiv div_G,
+__device__ __forceinline__ SeqGeom load_seq_geom(int bh, FastDiv div_groups, int n_groups,
                                                  const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_nuggets,
                                                  const int32_t* __restrict__ nug_len, const int32_t* __restrict__ cu_local,
                                                  const int32_t* __restrict__ loc_len, const int32_t* __restrict__ cu_ctx) {
   SeqGeom g;
-  g.b = static_cast<int>(fast_div(static_cast<uint32_t>(bh), div_H));
-  g.h = bh - g.b * H;
-  g.kvh = static_cast<int>(fast_div(static_cast<uint32_t>(g.h), div_G));
+  g.b = static_cast<int>(fast_div(static_cast<uint32_t>(bh), div_groups));
+  g.grp = bh - g.b * n_groups;
   const int32_t* k_end_p = nug_len != nullptr ? nug_len + g.b : cu_nuggets + g.b + 1;
   const int32_t* l_end_p = loc_len != nullptr ? loc_len + g.b : cu_local + g.b + 1;
   g.q0 = cu_q[g.b];
@@ -290,15 +292,16 @@ struct SplitArgs {
   int64_t first_row;  // the call's first query row
 };
 
-// One query block (kBM rows) of one (sequence, head); called by the whole workgroup.
+// One block (kBM rows) of one (sequence, group of G heads); called by the whole workgroup.
 // SPLIT (4 wavefronts): the workgroup takes an equal share of the key tiles and leaves its sums to
 // combine_splits_kernel.
 // IDX: Kn / Vn are the context's K / V and nugget j of sequence b is its token cu_ctx[b] + nug_idx[cu_nuggets[b] + j].
-template <int NW, bool IDX, int DH, bool SPLIT>
+// GROUPED: G_ heads go through the tiles together (else one).
+template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
 __device__ __forceinline__ void attend_query_block(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ nug_idx,
-    int H, int H_kv, const SeqGeom& geom, int qblk,
+    int H, int H_kv, int G_, FastDiv div_G, FastDiv div_kv, const SeqGeom& geom, int qblk,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse, const SplitArgs& sp) {
   static_assert(NW == 4 || !SPLIT, "only the 4-wavefront kernel shares the keys out");
@@ -314,27 +317,33 @@ __device__ __forceinline__ void attend_query_block(
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // stage s: K at 2s, V at 2s+1 (tiles of 16 KiB)
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
 
-  const int h = geom.h, kvh = geom.kvh;
+  const int G = GROUPED ? G_ : 1;
+  const int h0 = geom.grp * G, kvh = static_cast<int>(fast_div(static_cast<uint32_t>(geom.grp), div_kv));
   const int q0 = geom.q0, q_b = geom.q_b, k0 = geom.k0, k_b = geom.k_b, l0 = geom.l0, m_b = geom.m_b;
+  const int rows_b = q_b * G;
   const int i0 = qblk * kBM;
-  if (i0 >= q_b) return;  // uniform over the workgroup
+  if (i0 >= rows_b) return;  // uniform over the workgroup
+  // a row's query row inside the sequence, and its place among the call's (query row, head) pairs
+  auto query_of = [&](int f) -> int { return GROUPED ? static_cast<int>(fast_div(static_cast<uint32_t>(f), div_G)) : f; };
+  auto place_of = [&](int f, int i) -> int64_t { return static_cast<int64_t>(q0 + i) * H + h0 + (f - i * G); };
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = tid % kWave;
   const int j = lane & 31, g = lane >> 5;
-  const int w_i0 = i0 + wave * 32;  // first query row of this wavefront
+  const int w_i0 = i0 + wave * 32;  // first row of this wavefront
   // A wavefront past the sequence's last row only brings tiles: its matrix instructions would take the pipe and the LDS from the
   // others (8 x 530 rows, 200 nuggets, 32 heads 90.3 -> 80.0 us; 129 rows, 410 nuggets 28.7 -> 26.5; 16 x 32 rows 27.9 -> 25.9).
-  const bool has_rows = w_i0 < q_b;
+  const bool has_rows = w_i0 < rows_b;
   const int shift = m_b - q_b + 1;  // query row i sees local rows [0, i + shift)
-  const int my_i = w_i0 + j;        // this lane's query row inside the sequence
-  const bool row_ok = my_i < q_b;
+  const int my_f = w_i0 + j;        // this lane's row and query row
+  const int my_i = query_of(my_f);
+  const bool row_ok = my_f < rows_b;
   const int my_vis = row_ok ? max(0, min(m_b, my_i + shift)) : 0;
-  // local rows visible to the first / last query row of this wavefront and to the whole workgroup
-  const int w_lo = max(0, min(m_b, w_i0 + shift));
-  const int w_hi = max(0, min(m_b, min(w_i0 + 31, q_b - 1) + shift));
-  const int wg_vis = max(0, min(m_b, min(i0 + kBM, q_b) - 1 + shift));
+  // local rows visible to the first / last row of this wavefront and to the whole workgroup
+  const int w_lo = max(0, min(m_b, query_of(w_i0) + shift));
+  const int w_hi = max(0, min(m_b, query_of(min(w_i0 + 31, rows_b - 1)) + shift));
+  const int wg_vis = max(0, min(m_b, query_of(min(i0 + kBM, rows_b) - 1) + shift));
 
   const int n_nug_tiles = (k_b + kBN - 1) / kBN;
   const int n_loc_tiles = (wg_vis + kBN - 1) / kBN;
@@ -439,13 +448,27 @@ __device__ __forceinline__ void attend_query_block(
     TileLoader<NW, DH> q_loader;
     q_loader.init(wave, lane);
     uint32_t q_off[TileLoader<NW, DH>::kPerWave];
-    q_loader.template offsets<false>(static_cast<uint32_t>(H) * kRowBytes, q_off);
+    if (!GROUPED) q_loader.template offsets<false>(static_cast<uint32_t>(H) * kRowBytes, q_off);
 #pragma unroll
     for (int c = 0; c < kBM / kBN; ++c) {
-      const int rows = min(kBN, q_b - i0 - kBN * c);
-      q_loader.issue(Q + (static_cast<int64_t>(q0 + i0 + kBN * c) * H + h) * kDH,
-                     rows > 0 ? static_cast<uint32_t>(rows - 1) * static_cast<uint32_t>(H) * kRowBytes + kRowBytes : 0u, q_off,
-                     lds_base + (kQSlot0 + c) * kTileBytes);
+      const int f0 = i0 + kBN * c, first = query_of(f0);
+      const int rows = min(kBN, rows_b - f0);
+      uint32_t range = 0;
+      if (!GROUPED) {
+        if (rows > 0) range = static_cast<uint32_t>(rows - 1) * static_cast<uint32_t>(H) * kRowBytes + kRowBytes;
+      } else {  // (offsets from the first row's token and the group's first head: they grow with the row)
+        auto offset_of = [&](int f) -> uint32_t {
+          const int i = query_of(f);
+          return (static_cast<uint32_t>(i - first) * static_cast<uint32_t>(H) + static_cast<uint32_t>(f - i * G)) * kRowBytes;
+        };
+        if (rows > 0) range = offset_of(f0 + rows - 1) + kRowBytes;
+#pragma unroll
+        for (int u = 0; u < TileLoader<NW, DH>::kPerWave; ++u) {
+          const int row = q_loader.row0 + TileLoader<NW, DH>::kRowsPerInstr * u;
+          q_off[u] = offset_of(f0 + row) + q_loader.template piece_bytes<false>(row);
+        }
+      }
+      q_loader.issue(Q + (static_cast<int64_t>(q0 + first) * H + h0) * kDH, range, q_off, lds_base + (kQSlot0 + c) * kTileBytes);
     }
     if (NW == 8) {
       issue_tile(1);
@@ -454,7 +477,7 @@ __device__ __forceinline__ void attend_query_block(
       __builtin_amdgcn_s_waitcnt(0x0f70);
     }
     __syncthreads();
-    const int j_q = max(0, min(j, q_b - 1 - w_i0));
+    const int j_q = max(0, min(j, rows_b - 1 - w_i0));
     const char* qbuf = lds + kQSlot0 * kTileBytes + (wave * 32 + j_q) * kRowBytes;
 #pragma unroll
     for (int ds = 0; ds < kDH / 16; ++ds)
@@ -728,7 +751,7 @@ __device__ __forceinline__ void attend_query_block(
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
   if constexpr (SPLIT) {
     // (slots follow from max_q: rows of a sequence that is longer have none and are not written, rather than past the workspace)
-    const int64_t row_slot = static_cast<int64_t>(q0 - sp.first_row + my_i) * H + h;
+    const int64_t row_slot = place_of(my_f, my_i) - sp.first_row * H;
     if (row_ok && row_slot < sp.slots) {
       // A workspace may serve a call with flags next, and no flag may hold the ready value: neither does a record.
       auto word = [](float x) { return __float_as_uint(x) == kPartialReady ? __uint_as_float(kPartialReady + 1) : x; };
@@ -760,63 +783,69 @@ __device__ __forceinline__ void attend_query_block(
         *reinterpret_cast<uint2*>(obuf + j * kRowBytes + ((piece ^ ((j >> kRowShift) & (kP - 1))) << 4) + 8 * g) = out;
       }
     __builtin_amdgcn_wave_barrier();
-    const int n_rows = min(32, q_b - w_i0);  // valid rows of this wavefront (may be <= 0)
-    uint16_t* obase = O + (static_cast<int64_t>(q0 + w_i0) * H + h) * kDH;
+    const int n_rows = min(32, rows_b - w_i0);  // valid rows of this wavefront (may be <= 0)
 #pragma unroll
     for (int it = 0; it < kP / 2; ++it) {  // 64 / kP rows per iteration, 16 bytes per lane
       const int row = (64 / kP) * it + (lane >> HD::kPiecesLog2), piece = lane & (kP - 1);
       const uint4 val = *reinterpret_cast<const uint4*>(obuf + row * kRowBytes + ((piece ^ ((row >> kRowShift) & (kP - 1))) << 4));
-      if (row < n_rows) *reinterpret_cast<uint4*>(obase + static_cast<int64_t>(row) * H * kDH + piece * 8) = val;
+      const int f = w_i0 + row;
+      if (row < n_rows) *reinterpret_cast<uint4*>(O + place_of(f, query_of(f)) * kDH + piece * 8) = val;
     }
   }
   if (row_ok && lse != nullptr && g == 0) {
-    lse[static_cast<int64_t>(q0 + my_i) * H + h] =
+    lse[place_of(my_f, my_i)] =
         (l_tot > 0.f) ? (m_run + __log2f(l_tot)) * 0.6931471805599453f : kNegInf;
   }
 }
 
-// Workgroups are handed to the 8 XCDs round-robin, each XCD has an L2 of its own: the query blocks
-// of one (sequence, head) go to one XCD back to back (heaviest first), so that they start together
+// Workgroups are handed to the 8 XCDs round-robin, each XCD has an L2 of its own: the blocks
+// of one (sequence, group of heads) go to one XCD back to back (heaviest first), so that they start together
 // and share the K/V tiles in that L2.  With pair != 0 a workgroup takes two query blocks, one
 // after the other: a block i from the end and a block i from the start, so that under the causal
 // mask all workgroups carry the same load (new workgroups are handed out in order, and a compute
 // unit that finishes early is not refilled before the ones ahead of it in that order).
-template <int NW, bool IDX, int DH, bool SPLIT>
+template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
 __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kMinBlocks)) void block_attention_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_nuggets, const int32_t* __restrict__ nug_len,
     const int32_t* __restrict__ cu_local, const int32_t* __restrict__ loc_len, const int32_t* __restrict__ nug_idx,
     const int32_t* __restrict__ cu_ctx,
-    int B, int H, int H_kv, int n_qblocks, int pair, int heavy_last, int heads_xcd, FastDiv div_heads_xcd, FastDiv div_groups, FastDiv div_H, FastDiv div_G,
+    int B, int H, int H_kv, int G, int HG, int n_qblocks, int pair, int sorted, int heavy_last, int heads_xcd, FastDiv div_heads_xcd, FastDiv div_slots,
+    FastDiv div_pairs, FastDiv div_HG, FastDiv div_G, FastDiv div_kv,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse, float* __restrict__ part_o, float2* __restrict__ part_ml, int64_t slots) {
   // all arguments in one round of scalar loads (the compiler would fetch them a few at a time, before each first use)
   asm volatile("" ::"s"(Q), "s"(Kn), "s"(Vn), "s"(Kl), "s"(Vl), "s"(cu_q), "s"(cu_nuggets), "s"(nug_len), "s"(cu_local),
-               "s"(loc_len), "s"(nug_idx), "s"(cu_ctx), "s"(B), "s"(H), "s"(H_kv), "s"(n_qblocks), "s"(pair),
-               "s"(heavy_last), "s"(heads_xcd), "s"(div_heads_xcd.mul), "s"(div_heads_xcd.shift), "s"(div_groups.mul), "s"(div_groups.shift), "s"(div_H.mul), "s"(div_H.shift),
-               "s"(div_G.mul), "s"(div_G.shift), "s"(nug_tok_stride), "s"(nug_head_stride), "s"(scale_log2e), "s"(O),
-               "s"(lse));
-  const int n_groups = pair ? (n_qblocks + 1) >> 1 : n_qblocks;  // (div_groups divides by this)
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  // The i-th (sequence, head) pair of an XCD: heads_xcd consecutive heads of every sequence (ragged sequences weigh on all
-  // XCDs alike), starting at another head in each sequence, or every eighth pair (heads_xcd = 0).
+               "s"(loc_len), "s"(nug_idx), "s"(cu_ctx), "s"(B), "s"(H), "s"(H_kv), "s"(G), "s"(HG), "s"(n_qblocks), "s"(pair), "s"(sorted),
+               "s"(heavy_last), "s"(heads_xcd));
+  asm volatile("" ::"s"(div_heads_xcd.mul), "s"(div_heads_xcd.shift), "s"(div_slots.mul), "s"(div_slots.shift), "s"(div_pairs.mul),
+               "s"(div_pairs.shift), "s"(div_HG.mul), "s"(div_HG.shift), "s"(div_G.mul), "s"(div_G.shift), "s"(div_kv.mul),
+               "s"(div_kv.shift), "s"(nug_tok_stride), "s"(nug_head_stride), "s"(scale_log2e), "s"(O), "s"(lse));
+  const int n_slots = pair ? (n_qblocks + 1) >> 1 : n_qblocks, n_pairs = B * HG;  // (div_slots and div_pairs divide by these)
+  // The i-th (sequence, group) of an XCD: heads_xcd consecutive groups of every sequence (ragged sequences weigh on all
+  // XCDs alike), starting at another one in each sequence, or every eighth (heads_xcd = 0).
   auto pair_of = [&](int i, int x) -> int {
     if (heads_xcd == 0) return i * 8 + x;
     const int b = static_cast<int>(fast_div(static_cast<uint32_t>(i), div_heads_xcd));
-    return b * H + ((x + b) & 7) * heads_xcd + (i - b * heads_xcd);
+    return b * HG + ((x + b) & 7) * heads_xcd + (i - b * heads_xcd);
   };
-  const int j = static_cast<int>(fast_div(static_cast<uint32_t>(slot), div_groups));
+  // sorted: the heaviest block of every (sequence, group), then the next ones of all; else an XCD's (sequence, group)s one after
+  // the other
+  const int turn = sorted ? static_cast<int>(fast_div(blockIdx.x, div_pairs)) : 0;
+  const int place = static_cast<int>(blockIdx.x) - turn * n_pairs;
+  const int xcd = place & 7, slot = place >> 3;
+  const int j = sorted ? slot : static_cast<int>(fast_div(static_cast<uint32_t>(slot), div_slots));
   const int bh = pair_of(j, xcd);
-  const int heavy = n_qblocks - 1 - (slot - j * n_groups), light = n_qblocks - 1 - heavy;
-  if (bh >= B * H) return;
+  const int heavy = n_qblocks - 1 - (sorted ? turn : slot - j * n_slots), light = n_qblocks - 1 - heavy;
+  if (bh >= n_pairs) return;
   // Two neighbouring workgroups of an XCD (j even and odd) share two (sequence, head) pairs
   // crosswise: one takes the heavy block of the first pair and then the light block of the second,
   // the other the light block of the first and then the heavy block of the second.  Both carry the
   // same load, the two blocks that read the same K/V run at the same time and share it in L2, and
   // the bursts of first loads come from half of the compute units at a time.
   const int bh_other = pair_of(j ^ 1, xcd);
-  const bool cross = pair && light != heavy && bh_other < B * H;
+  const bool cross = pair && light != heavy && bh_other < n_pairs;
   int bh1 = bh, q1 = heavy, bh2 = bh, q2 = (pair && light != heavy) ? light : -1;
   if (cross) {
     if (j & 1) {
@@ -830,19 +859,19 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
   // heavy_last: the batch's entries grow in cost with their index (segments of a text see more and more nuggets);
   // workgroups are handed out in index order, so the entries are walked from the back to keep the tail light
   if (heavy_last) {
-    bh1 = B * H - 1 - bh1;
-    bh2 = B * H - 1 - bh2;
+    bh1 = n_pairs - 1 - bh1;
+    bh2 = n_pairs - 1 - bh2;
   }
   // both blocks' sequence data are requested here, before the first block's work
-  const SeqGeom g1 = load_seq_geom<IDX>(bh1, div_H, H, div_G, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
-  const SeqGeom g2 = load_seq_geom<IDX>(q2 >= 0 ? bh2 : bh1, div_H, H, div_G, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
+  const SeqGeom g1 = load_seq_geom<IDX>(bh1, div_HG, HG, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
+  const SeqGeom g2 = load_seq_geom<IDX>(q2 >= 0 ? bh2 : bh1, div_HG, HG, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
   SplitArgs sp{0, 1, nullptr, nullptr, 0, 0};
   if (SPLIT) sp = SplitArgs{static_cast<int>(blockIdx.y), static_cast<int>(gridDim.y), part_o, part_ml, slots, cu_q[0]};
-  attend_query_block<NW, IDX, DH, SPLIT>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g1, q1, nug_tok_stride, nug_head_stride,
+  attend_query_block<NW, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g1, q1, nug_tok_stride, nug_head_stride,
                                          scale_log2e, O, lse, sp);
   if (!SPLIT && q2 >= 0) {
     __syncthreads();  // the first block's use of LDS is over
-    attend_query_block<NW, IDX, DH, SPLIT>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, g2, q2, nug_tok_stride, nug_head_stride,
+    attend_query_block<NW, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g2, q2, nug_tok_stride, nug_head_stride,
                                            scale_log2e, O, lse, sp);
   }
 }
@@ -877,6 +906,96 @@ __global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(
   if (lse != nullptr && c == 0) lse[at] = sum > 0.f ? (M + __log2f(sum)) * 0.6931471805599453f : kNegInf;
 }
 
+inline size_t split_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int64_t n) {
+  return static_cast<size_t>(B) * max_q * H * n * (static_cast<size_t>(d_h) + 2) * sizeof(float);
+}
+
+// How a call's rows become workgroups.
+struct BlockPlan {
+  int32_t G = 1;        // query heads of a K/V head that go through the tiles together
+  int32_t waves = 4;    // wavefronts per workgroup: 4 (128 rows) or 8 (256)
+  int32_t nsplit = 1;   // workgroups that share the keys of a block (4 wavefronts)
+  bool pair = false;    // two blocks per workgroup, a heavy and a light one
+  bool sorted = false;  // all heavy blocks before the next ones
+};
+
+// The plan of least expected time, with at most max_splits shares of the keys.  Measured (ns): a 64-key tile 1350 in the
+// 4-wavefront kernel, 1.6 times that with two workgroups on a compute unit; in the 8-wavefront kernel 1200, 1600 where more than
+// half of the compute units run it, 2100 where hardly any two of them at work share their keys; heads of 64 channels two thirds
+// of that; a block's start and end 4000 and 6200.
+//
+// Heads together (G): where one head's blocks are more than the chip takes at once and leave lanes without a row or end far from
+// each other's causal limits.  One head / together: 64 heads over 8, 16 sequences of 34 rows over 460 nuggets 41.4 / 19.1 us, of 16
+// rows over 100 21.8 / 11.5; 8 of 336 rows, 143 nuggets 66.7 / 53.9; 32 heads over 8, 16 of 64 rows, 200 nuggets 19.8 / 17.0.  On a
+// chip that is not full a head per workgroup is faster (8 heads of 16 rows 9.5 / 10.1 us, of 64 rows 13.8 / 15.8).
+//
+// Two blocks per workgroup, heavy and light, or all heavy blocks first (sorted): pairs fill the last round badly where the blocks
+// of a group are odd in number or few; 8 sequences of 546 rows, 64 heads over 8 together 127.8 (pairs of one head's) / 92.1 us
+// (sorted), 32 over 8 65.6 / 51.4.  But blocks of one group, which read the same keys, are then seldom at work together: 1100
+// rows, 100 nuggets, 8 x 32 heads 146 (pairs) / 155 us (sorted).
+//
+// Keys shared by several workgroups: costs a launch and two passes over the partial results (one write, one read; 2 TB/s), so it
+// is for few rows and many keys.  64 rows, 3000 nuggets, 32 heads 71 -> 26 us; 3 x 23 rows, 2700 nuggets, 40 heads 67.5 -> 43 us;
+// 128 rows, 1500 nuggets, 64 heads over 8 42.5 -> 24 us; 2 x 21 rows, 332 nuggets, 32 heads 15.4 -> 13.6 us.  512 rows, 400
+// nuggets, 32 heads (17 MB of partial results for two splits) stay as they are: 23.7 us against 25.5.
+// The bounds decide, also where they promise more than there is: in the cached form max_k may be a capacity.  64 rows, 32 heads over
+// a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
+// 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
+BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, bool heavy_last,
+                      int64_t max_splits, bool eight_only = false) {
+  const int64_t cus = compute_units(), nug_tiles = (static_cast<int64_t>(max_k) + kBN - 1) / kBN;
+  const int64_t tiles = nug_tiles + (static_cast<int64_t>(max_local) + kBN - 1) / kBN;
+  const auto scaled = [&](int64_t ns) { return d_h == 128 ? ns : ns * 2 / 3; };
+  constexpr int64_t kStart4 = 4000, kStart8 = 6200;
+  BlockPlan best;
+  int64_t best_ns = -1;
+  const auto consider = [&](int64_t ns, int32_t G, int32_t waves, int64_t nsplit, bool pair, bool sorted) {
+    if (best_ns >= 0 && ns * 20 >= best_ns * 19) return;
+    best_ns = ns;
+    best = BlockPlan{G, waves, static_cast<int32_t>(nsplit), pair, sorted};
+  };
+  for (int32_t G = 1; G <= H / H_kv; ++G) {
+    if ((H / H_kv) % G != 0) continue;
+    const int64_t pairs = static_cast<int64_t>(B) * (H / G), rows = static_cast<int64_t>(max_q) * G;
+    const bool few = pairs % 8 != 0 && pairs < 64 && !heavy_last;  // (see launch_nw)
+    for (int32_t waves = 8; waves >= 4; waves -= 4) {
+      if (waves == 8 ? rows <= 128 : (rows > 128 && G == 1) || eight_only) continue;
+      const int64_t bm = 32 * waves, n = (rows + bm - 1) / bm, units = pairs * n, at_once = waves == 8 ? cus : 2 * cus;
+      const int64_t tile_ns = scaled(waves == 8 ? (2 * units <= cus ? 1200 : 1600) : units <= cus ? 1350 : 2160);
+      const auto block_ns = [&](int64_t blk) {  // the nuggets and what the block's last row sees of the local rows
+        const int64_t seen = max_local - max_q + (std::min((blk + 1) * bm, rows) + G - 1) / G;
+        return (nug_tiles + (std::max<int64_t>(0, seen) + kBN - 1) / kBN) * tile_ns + (waves == 8 ? kStart8 : kStart4);
+      };
+      const int64_t rounds = (units + at_once - 1) / at_once;
+      if (rounds <= 1) {
+        consider(block_ns(n - 1), G, waves, 1, false, false);
+        continue;
+      }
+      int64_t in_turn = 0, paired = -1;  // (blocks of one (sequence, group) run together in the latter only)
+      if (rounds <= 16 && !heavy_last) {
+        for (int64_t r = 0; r < rounds; ++r) in_turn += block_ns(n - 1 - r * at_once / pairs);
+      } else {
+        in_turn = rounds * (block_ns(0) + block_ns(n - 1)) / 2;
+      }
+      if (waves == 8 && 2 * pairs > cus) in_turn = in_turn * 21 / 16;
+      const int64_t wgs = (pairs + 7) / 8 * 8 * ((n + 1) / 2);
+      if (n >= 2 && wgs >= cus && !few) paired = (wgs + at_once - 1) / at_once * (block_ns(0) + block_ns(n - 1));
+      if (paired >= 0 && (heavy_last || rounds > 16 || paired * 20 <= in_turn * 21)) {
+        consider(paired, G, waves, 1, true, false);
+      } else {
+        consider(in_turn, G, waves, 1, false, n >= 2 && !heavy_last);
+      }
+    }
+    const int64_t units = pairs * ((rows + 127) / 128);
+    for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && units <= cus && s * units <= 2 * cus && 2 * s <= tiles; ++s) {
+      const int64_t tile_ns = scaled(s * units > cus ? 2160 : 1350);
+      const int64_t ns = (tiles + s - 1) / s * tile_ns + (max_q > 128 ? kStart8 : kStart4) + 5000 + static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000);
+      consider(ns, G, 4, s, false, false);
+    }
+  }
+  return best;
+}
+
 // Heads that an XCD gets of every sequence, next to each other (0: the pairs of sequence and head go to the XCDs in turn).
 // Heads are neighbours in a token's row of 256-byte pieces: with every eighth of them a tile's rows come from two of an
 // L2's sixteen channels, which the 8-wavefront kernel feels (8 sequences of 512 rows, 410 nuggets, 32 heads 72.7 -> 70.4 us;
@@ -884,24 +1003,26 @@ __global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(
 // 512 rows 66.7 -> 63.7 us, 128 rows 36.3 -> 33.1; 32 heads over 8, 64 rows 22.2 -> 19.3).  The 4-wavefront kernel, a few
 // tiles long, does better without where heads are not grouped (64 rows, 80 nuggets 11.05 against 11.2 us, 128 rows, 410
 // nuggets 26.45 against 26.8).
-int heads_per_xcd(const AttnParams& p, int waves) {
-  return p.H % 8 == 0 && (waves == 8 || p.H != p.H_kv) ? p.H / 8 : 0;
+int heads_per_xcd(const AttnParams& p, const BlockPlan& plan) {
+  const int HG = p.H / plan.G;
+  return HG % 8 == 0 && (plan.waves == 8 || HG != p.H_kv) ? HG / 8 : 0;
 }
 
 // nsplit > 1: the keys are shared by that many workgroups per query block, whose partial results the workspace holds.
-template <int NW, bool IDX, int DH, bool SPLIT = false>
-int launch_nw(const AttnParams& p, int nsplit = 1) {
+template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
+int launch_nw(const AttnParams& p, BlockPlan plan) {
   using Cfg = BlockCfg<NW, DH>;
   if (IDX && p.max_k > Cfg::kIdxCap) return DODO_ERR_UNSUPPORTED;
   constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0);
-  const int n_qblocks = (p.max_q + Cfg::kBM - 1) / Cfg::kBM;
-  // pairs of query blocks per workgroup, if that still leaves a workgroup for every compute unit
-  const int64_t bh8 = (static_cast<int64_t>(p.B) * p.H + 7) / 8 * 8;
-  const int pair = (!SPLIT && n_qblocks >= 2 && bh8 * ((n_qblocks + 1) / 2) >= compute_units()) ? 1 : 0;
-  const int64_t grid = bh8 * (pair ? (n_qblocks + 1) / 2 : n_qblocks);
-  if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
-  const int heads_xcd = heads_per_xcd(p, NW);
-  auto kern = block_attention_kernel<NW, IDX, DH, SPLIT>;
+  const int HG = p.H / plan.G, nsplit = plan.nsplit;
+  const int64_t pairs = static_cast<int64_t>(p.B) * HG, blocks = (static_cast<int64_t>(p.max_q) * plan.G + Cfg::kBM - 1) / Cfg::kBM;
+  // few (sequence, group)s that don't deal out evenly would leave XCDs idle: their blocks go to all of them in turn
+  if (pairs % 8 != 0 && pairs < 64 && !p.heavy_last) plan.sorted = true;
+  const int64_t n_slots = plan.pair ? (blocks + 1) / 2 : blocks;
+  const int64_t grid = (plan.sorted ? pairs : (pairs + 7) / 8 * 8) * n_slots;
+  if (pairs > 0x7fffffffLL || grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
+  const int n_qblocks = static_cast<int>(blocks), heads_xcd = heads_per_xcd(p, plan);
+  auto kern = block_attention_kernel<NW, IDX, DH, SPLIT, GROUPED>;
   const int64_t slots = SPLIT ? static_cast<int64_t>(p.B) * p.max_q * p.H : 0;
   float* part_o = SPLIT ? static_cast<float*>(p.ws) : nullptr;
   float2* part_ml = SPLIT ? reinterpret_cast<float2*>(part_o + slots * nsplit * DH) : nullptr;
@@ -909,13 +1030,14 @@ int launch_nw(const AttnParams& p, int nsplit = 1) {
     const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLds);
     if (rc != DODO_OK) return rc;
   }
+  const auto div = [](int64_t d) { return make_fast_div(static_cast<uint32_t>(d)); };
   hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid), SPLIT ? nsplit : 1), dim3(Cfg::kThreads), kLds, p.stream,
                      static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.Kn),
                      static_cast<const uint16_t*>(p.Vn), static_cast<const uint16_t*>(p.Kl),
                      static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, p.B, p.H, p.H_kv,
-                     n_qblocks, pair, p.heavy_last, heads_xcd, make_fast_div(static_cast<uint32_t>(heads_xcd > 0 ? heads_xcd : 1)), make_fast_div(static_cast<uint32_t>(pair ? (n_qblocks + 1) / 2 : n_qblocks)),
-                     make_fast_div(static_cast<uint32_t>(p.H)), make_fast_div(static_cast<uint32_t>(p.H / p.H_kv)),
-                     p.nug_tok_stride, p.nug_head_stride, p.scale_log2e, static_cast<uint16_t*>(p.O), p.lse, part_o, part_ml, slots);
+                     plan.G, HG, n_qblocks, plan.pair ? 1 : 0, plan.sorted ? 1 : 0, p.heavy_last, heads_xcd, div(heads_xcd > 0 ? heads_xcd : 1),
+                     div(n_slots), div(pairs), div(HG), div(plan.G), div(HG / p.H_kv), p.nug_tok_stride, p.nug_head_stride, p.scale_log2e,
+                     static_cast<uint16_t*>(p.O), p.lse, part_o, part_ml, slots);
   const int rc = launch_status();
   if (rc != DODO_OK || !SPLIT) return rc;
   constexpr int kRows = kCombineThreads / (DH / 4);
@@ -924,63 +1046,39 @@ int launch_nw(const AttnParams& p, int nsplit = 1) {
   return launch_status();
 }
 
-inline size_t split_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int64_t n) {
-  return static_cast<size_t>(B) * max_q * H * n * (static_cast<size_t>(d_h) + 2) * sizeof(float);
-}
-
-// How many workgroups share the keys of a query block of 128 rows (1: no sharing), where a workgroup per block would leave
-// most of the chip idle.  Sharing costs a launch and two passes over the partial results (one write, one read), so it is for
-// few rows and many keys; the count is the one with the least expected time.  Measured (ns): a 64-key tile 1350 in the
-// 4-wavefront kernel, 1.6 times that with two workgroups on a compute unit, 1200 in the 8-wavefront kernel (256 rows); heads
-// of 64 channels two thirds of that; 5000 for the second launch and the starts; the partial results at 2 TB/s, written and
-// read.  64 rows, 3000 nuggets, 32 heads 71 -> 26 us; 3 x 23 rows, 2700 nuggets, 40 heads 67.5 -> 43 us; 128 rows, 1500
-// nuggets, 64 heads over 8 42.5 -> 24 us; 2 x 21 rows, 332 nuggets, 32 heads 15.4 -> 13.6 us.  512 rows, 400 nuggets, 32 heads
-// (17 MB of partial results for two splits) stay as they are: 23.7 us against 25.5.
-// The bounds decide, also where they promise more than there is: in the cached form max_k may be a capacity.  64 rows, 32 heads over
-// a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
-// 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
-int split_count(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local) {
-  const int64_t cus = compute_units(), bh = static_cast<int64_t>(B) * H;
-  const int64_t units = bh * ((max_q + 127) / 128);
-  if (units > cus) return 1;
-  const int64_t tiles = (static_cast<int64_t>(max_k) + kBN - 1) / kBN + (static_cast<int64_t>(max_local) + kBN - 1) / kBN;
-  const int64_t tile_ns = d_h == 128 ? 1350 : 900, tile8_ns = d_h == 128 ? 1200 : 800;
-  int64_t best = tiles * (max_q > 128 ? tile8_ns : tile_ns);
-  int count = 1;
-  for (int64_t n = 2; n <= 16 && n * units <= 2 * cus && 2 * n <= tiles; ++n) {
-    const int64_t busy = n * units > cus ? tile_ns * 8 / 5 : tile_ns;
-    const int64_t t = (tiles + n - 1) / n * busy + 5000 + static_cast<int64_t>(split_bytes(B, H, d_h, max_q, n) / 2000);
-    if (t < best) {
-      best = t;
-      count = static_cast<int>(n);
-    }
-  }
-  return count;
-}
-
 template <int DH>
 int launch_dh(const AttnParams& p) {
   // the K/V row offsets inside one tile are kept in 32 bits
   if (p.nug_tok_stride * 2 * kBN > 0x7fffffffLL || static_cast<int64_t>(p.H_kv) * DH * 2 * kBN > 0x7fffffffLL ||
       static_cast<int64_t>(p.H) * DH * 2 * kBN > 0x7fffffffLL)
     return DODO_ERR_UNSUPPORTED;
-  int nsplit = p.ws != nullptr && aligned16(p.ws) ? split_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local) : 1;
-  while (nsplit > 1 && split_bytes(p.B, p.H, p.d_h, p.max_q, nsplit) > p.ws_bytes) --nsplit;
-  if (p.nug_idx != nullptr) {
+  int64_t max_splits = p.ws != nullptr && aligned16(p.ws) ? static_cast<int64_t>(p.ws_bytes / split_bytes(p.B, p.H, p.d_h, p.max_q, 1)) : 1;
+  const bool idx = p.nug_idx != nullptr;
+  if (idx) {
     // a token's byte offset from its sequence's first row is kept in 32 bits as well
     if (static_cast<int64_t>(p.max_n) * p.nug_tok_stride * 2 > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
-    if (nsplit > 1 && p.max_k <= BlockCfg<4, DH>::kIdxCap) return launch_nw<4, true, DH, true>(p, nsplit);
-    return p.max_q > 128 ? launch_nw<8, true, DH>(p) : launch_nw<4, true, DH>(p);
   }
-  if (nsplit > 1) return launch_nw<4, false, DH, true>(p, nsplit);
-  if (p.max_q > 128) return launch_nw<8, false, DH>(p);
-  return launch_nw<4, false, DH>(p);
+  // (only blocks of 256 rows have room for a longer list; up to 128 query rows it is refused)
+  const bool eight_only = idx && p.max_k > BlockCfg<4, DH>::kIdxCap;
+  if (eight_only && p.max_q <= 128) return DODO_ERR_UNSUPPORTED;
+  const BlockPlan plan = plan_blocks(p.B, p.H, p.H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.heavy_last != 0, max_splits, eight_only);
+  const auto launch = [&](auto grouped_tag) {
+    constexpr bool GROUPED = decltype(grouped_tag)::value;
+    if (plan.nsplit > 1) return idx ? launch_nw<4, true, DH, true, GROUPED>(p, plan) : launch_nw<4, false, DH, true, GROUPED>(p, plan);
+    if (plan.waves == 8) return idx ? launch_nw<8, true, DH, false, GROUPED>(p, plan) : launch_nw<8, false, DH, false, GROUPED>(p, plan);
+    return idx ? launch_nw<4, true, DH, false, GROUPED>(p, plan) : launch_nw<4, false, DH, false, GROUPED>(p, plan);
+  };
+  return plan.G > 1 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 }  // namespace
 
-size_t block_workspace_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local) {
-  const int n = split_count(B, H, d_h, max_q, max_k, max_local);
+size_t block_workspace_bytes(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local) {
+  // (never less than for as many K/V heads as query heads: smaller calls are served with it too)
+  int32_t n = 1;
+  for (int32_t h = H_kv > 0 ? H_kv : 1; h <= H; ++h)
+    if (h == H || h == H_kv || (H_kv <= 0 && H % h == 0))
+      n = std::max(n, plan_blocks(B, H, h, d_h, max_q, max_k, max_local, false, 16).nsplit);
   return n > 1 ? split_bytes(B, H, d_h, max_q, n) : 0;
 }
 

@@ -291,3 +291,29 @@ def test_nan_stays_in_its_head(q, k):
     O2, lse2 = run()
     assert torch.equal(O2[~bad], O[~bad]) and torch.equal(lse2[~bad], lse[~bad])
     assert torch.isnan(O2[bad]).all()
+
+
+# Grouped heads whose rows go through the tiles together: blocks of 128 and 256 rows, 2, 3, 4 and 8 heads (a block begins at any head
+# of a query row), rows left over, sequences of fewer rows than the bound, several blocks per sequence with the heavy ones first, and
+# keys shared by several workgroups; the same rows through an index list.
+@pytest.mark.parametrize("B,q,k,H,H_kv,d_h", [
+    (40, 16, 70, 16, 2, 128), (40, 17, 33, 16, 2, 128), (40, 21, 64, 16, 2, 64), (24, 43, 40, 24, 8, 128), (20, 33, 65, 32, 8, 64),
+    (70, 130, 20, 16, 8, 128), (12, 546, 30, 16, 2, 128), (5, 16, 2000, 64, 8, 128), (9, 40, 1500, 32, 8, 64),
+])
+def test_rows_of_grouped_heads_together(B, q, k, H, H_kv, d_h):
+    import paper_2310_02409_amd as D
+    q_lens = [max(1, q - (3 * b) % 11) for b in range(B)]
+    k_lens = [k - b % 5 for b in range(B)]
+    m_lens = [n + (7 * b) % 30 - (b % 3 == 2) * 9 for b, n in enumerate(q_lens)]
+    m_lens = [max(0, m) for m in m_lens]
+    host, t = make_attention_case(900 + q, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], scale)
+    a = (t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], max(q_lens), max(k_lens), max(m_lens))
+    O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], *a, scale, want_lse=True)
+    check_attention(O, want, torch.bfloat16)
+    check_lse(lse, lse_want, torch.bfloat16)
+    idx = torch.cat([torch.arange(n, dtype=torch.int32) for n in k_lens]).to(dev())
+    Oi, lse_i = D.dodo_nugget_attention_indexed(t["Q"], t["Kn"], t["Vn"], idx, t["cu_nuggets"], *a, max(k_lens), scale, want_lse=True)
+    assert torch.equal(O, Oi) and torch.equal(lse, lse_i)
