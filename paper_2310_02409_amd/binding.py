@@ -124,7 +124,9 @@ _native = _load_native()
 _native.bind(_raise_status, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
     lib.dodo_score, lib.dodo_select_topk, lib.dodo_gather_nuggets, lib.dodo_nugget_attention_workspace_bytes,
     lib.dodo_nugget_attention_workspace_bytes_grouped, lib.dodo_nugget_attention, lib.dodo_nugget_attention_indexed,
-    lib.dodo_nugget_attention_cached, lib.dodo_stream_append, lib.dodo_score_mlp_workspace_bytes, lib.dodo_score_mlp)))
+    lib.dodo_nugget_attention_cached, lib.dodo_stream_append, lib.dodo_score_mlp_workspace_bytes, lib.dodo_score_mlp,
+    lib.dodo_threshold_from_sample_workspace_bytes, lib.dodo_threshold_from_sample, lib.dodo_select_threshold, lib.dodo_segment_plan,
+    lib.dodo_nugget_attention_segments, lib.dodo_ste_score_grad_workspace_bytes, lib.dodo_ste_score_grad)))
 _BLOCK_MIN_Q = _native.ATTENTION_BLOCK_MIN_Q  # the header's
 _current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
@@ -428,6 +430,10 @@ def dodo_ste_score_grad(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.Tensor, dO:
                         layout: int = TOKEN_MAJOR, grad: Optional[torch.Tensor] = None, accumulate: bool = False,
                         ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Score gradient of the straight-through estimator (Eq. 17-18) for one layer; returns fp32 [Kt]."""
+    done = _native.ste_score_grad(Q, Kn, Vn, dO, O, lse, cu_q, cu_nuggets, max_q, max_k, softmax_scale, grad_scale, layout, grad,
+                                  accumulate, ws)
+    if done is not None:
+        return done
     _dev(Q, Kn, Vn, dO, O, lse, cu_q, cu_nuggets, grad, ws)
     Sq, H, d_h = Q.shape
     H_kv = Kn.shape[1] if layout == TOKEN_MAJOR else Kn.shape[0]
@@ -456,6 +462,9 @@ def dodo_segment_plan(nugget_idx: torch.Tensor, cu_seqlens: torch.Tensor, cu_nug
                       tau: int, capacity: int):
     """Entries of the segment form of the autoregressive objective (Sec. 2.4): returns the device int32 arrays
     (seg_cu_q [capacity+1], seg_nug_start, seg_nug_len, seg_loc_start, seg_loc_len [capacity], n_segments [1])."""
+    done = _native.segment_plan(nugget_idx, cu_seqlens, cu_nuggets, seg_len, tau, capacity)
+    if done is not None:
+        return done
     _dev(nugget_idx, cu_seqlens, cu_nuggets)
     B = cu_seqlens.numel() - 1
     mk = lambda n: torch.empty(n, dtype=torch.int32, device=cu_seqlens.device)
@@ -475,6 +484,10 @@ def dodo_nugget_attention_segments(Q: torch.Tensor, Kn: torch.Tensor, Vn: torch.
                                    ws: Optional[torch.Tensor] = None):
     """dodo_nugget_attention over (start, length) ranges of the nugget cache and of the texts' own K, V
     [N, H_kv, d_h], one entry per segment; returns (O, lse or None)."""
+    done = _native.nugget_attention_segments(Q, Kn, Vn, K, V, seg_cu_q, seg_nug_start, seg_nug_len, seg_loc_start, seg_loc_len, max_q,
+                                             max_k, max_local, softmax_scale, layout, O, lse, want_lse, ws)
+    if done is not None:
+        return done
     _dev(Q, Kn, Vn, K, V, seg_cu_q, seg_nug_start, seg_nug_len, seg_loc_start, seg_loc_len, O, lse, ws)
     Sq, H, d_h = Q.shape
     H_kv = K.shape[1]
@@ -539,6 +552,9 @@ def dodo_threshold_from_sample_workspace_bytes(n: int) -> int:
 def dodo_threshold_from_sample(sample: torch.Tensor, num: int, den: int, out: Optional[torch.Tensor] = None,
                                ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Threshold Lambda (device tensor with one fp32) from sampled scores: the (k+1)-th highest, k = nugget count."""
+    done = _native.threshold_from_sample(sample, num, den, out, ws, _ONE_WORKGROUP_TOKENS)
+    if done is not None:
+        return done
     _dev(sample, out, ws)
     assert sample.dtype == torch.float32 and sample.is_contiguous()
     if out is None:
@@ -554,6 +570,9 @@ def dodo_threshold_from_sample(sample: torch.Tensor, num: int, den: int, out: Op
 def dodo_select_threshold(scores: torch.Tensor, cu_seqlens: torch.Tensor, lam: torch.Tensor):
     """Threshold selection (Eq. 8): returns (counts [B], cu_nuggets [B+1], nugget_idx with room for all tokens),
     all on the device; the first cu_nuggets[B] entries of nugget_idx are the packed index lists."""
+    done = _native.select_threshold(scores, cu_seqlens, lam)
+    if done is not None:
+        return done
     _dev(scores, cu_seqlens, lam)
     assert scores.dtype == torch.float32 and lam.dtype == torch.float32
     B = cu_seqlens.numel() - 1

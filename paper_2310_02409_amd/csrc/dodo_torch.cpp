@@ -11,7 +11,9 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
 #include <cmath>
+#include <initializer_list>
 #include <limits>
 
 #include "dodo.h"
@@ -31,6 +33,13 @@ struct Entries {
   decltype(&dodo_stream_append) stream_append = nullptr;
   decltype(&dodo_score_mlp_workspace_bytes) score_mlp_ws = nullptr;
   decltype(&dodo_score_mlp) score_mlp = nullptr;
+  decltype(&dodo_threshold_from_sample_workspace_bytes) threshold_ws = nullptr;
+  decltype(&dodo_threshold_from_sample) threshold = nullptr;
+  decltype(&dodo_select_threshold) select_threshold = nullptr;
+  decltype(&dodo_segment_plan) segment_plan = nullptr;
+  decltype(&dodo_nugget_attention_segments) attention_segments = nullptr;
+  decltype(&dodo_ste_score_grad_workspace_bytes) ste_ws = nullptr;
+  decltype(&dodo_ste_score_grad) ste = nullptr;
 } L;
 PyObject* raise_error = nullptr;
 
@@ -315,6 +324,27 @@ PyObject* nugget_attention_cached(PyObject*, PyObject* const* args, Py_ssize_t n
   });
 }
 
+PyObject* nugget_attention_segments(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded(args, n, 19, [](PyObject* const* a) -> PyObject* {
+    const at::Tensor &Kn = tensor(a[1]), &Vn = tensor(a[2]), &K = tensor(a[3]), &V = tensor(a[4]), &nug_start = tensor(a[6]),
+                     &nug_len = tensor(a[7]), &loc_start = tensor(a[8]), &loc_len = tensor(a[9]);
+    const int64_t layout = whole(a[14]);
+    require(K.dim() >= 2 && Kn.dim() >= 2 && (layout == DODO_LAYOUT_TOKEN_MAJOR || layout == DODO_LAYOUT_HEAD_MAJOR));
+    AttentionArgs p(a[0], a[5], a[10], a[11], a[12], a[13], a[15], a[16], a[17], a[18]);
+    const int32_t H_kv = int32(K.size(1));
+    const int64_t Kt = Kn.size(layout == DODO_LAYOUT_TOKEN_MAJOR ? 0 : 1);
+    if (!run("dodo_nugget_attention_segments", [&] {
+          p.allocate(L.attention_ws_grouped(p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.code),
+                     p.code == DODO_DTYPE_BF16 && static_cast<int64_t>(p.H) * p.max_q >= 4ll * H_kv);
+          return L.attention_segments(ptr(p.Q), ptr(Kn), ptr(Vn), ptr(K), ptr(V), iptr(p.cu_q), iptr(nug_start), iptr(nug_len),
+                                      iptr(loc_start), iptr(loc_len), p.B, p.H, H_kv, p.d_h, p.max_q, p.max_k, p.max_local, Kt, p.scale,
+                                      p.code, static_cast<int>(layout), ptr(p.O), fptr(p.lse), ptr(p.ws), bytes_of(p.ws), stream());
+        }))
+      return nullptr;
+    return p.result();
+  });
+}
+
 // (True: done)
 PyObject* stream_append(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return guarded(args, n, 8, [](PyObject* const* a) -> PyObject* {
@@ -359,14 +389,122 @@ PyObject* score_mlp(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
+// a tuple of the tensors, in order
+PyObject* tuple_of(std::initializer_list<const at::Tensor*> tensors) {
+  PyObject* all = PyTuple_New(static_cast<Py_ssize_t>(tensors.size()));
+  if (all == nullptr) return nullptr;
+  Py_ssize_t i = 0;
+  for (const at::Tensor* t : tensors) {
+    PyObject* o = wrap(*t);
+    if (o == nullptr) {
+      Py_DECREF(all);
+      return nullptr;
+    }
+    PyTuple_SET_ITEM(all, i++, o);
+  }
+  return all;
+}
+
+// (one_workgroup: samples up to this length get no workspace of their own)
+PyObject* threshold_from_sample(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded(args, n, 6, [](PyObject* const* a) -> PyObject* {
+    const at::Tensor& sample = tensor(a[0]);
+    const int64_t num = whole(a[1]), den = whole(a[2]), one_workgroup = whole(a[5]);
+    at::Tensor out = optional_tensor(a[3]), ws = optional_tensor(a[4]);
+    require(sample.scalar_type() == at::kFloat);
+    const int64_t count = sample.numel();
+    if (!run("dodo_threshold_from_sample", [&] {
+          if (!out.defined()) out = at::empty({1}, sample.options());
+          const size_t need = ws.defined() || count <= one_workgroup ? 0 : L.threshold_ws(count);
+          if (need > 0) ws = at::empty({static_cast<int64_t>(need)}, sample.options().dtype(at::kByte));
+          return L.threshold(fptr(sample), count, num, den, fptr(out), ptr(ws), bytes_of(ws), stream());
+        }))
+      return nullptr;
+    return same_or_new(a[3], out);
+  });
+}
+
+PyObject* select_threshold(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded(args, n, 3, [](PyObject* const* a) -> PyObject* {
+    const at::Tensor &scores = tensor(a[0]), &cu_seqlens = tensor(a[1]), &lam = tensor(a[2]);
+    require(scores.scalar_type() == at::kFloat && lam.scalar_type() == at::kFloat && cu_seqlens.numel() >= 1);
+    const int32_t B = int32(cu_seqlens.numel() - 1);
+    at::Tensor counts, cu_nuggets, idx;
+    if (!run("dodo_select_threshold", [&] {
+          const auto ints = scores.options().dtype(at::kInt);
+          counts = at::empty({B}, ints);
+          cu_nuggets = at::empty({static_cast<int64_t>(B) + 1}, ints);
+          idx = at::empty({std::max<int64_t>(1, scores.numel())}, ints);
+          return L.select_threshold(fptr(scores), iptr(cu_seqlens), B, fptr(lam), iptr(counts), iptr(cu_nuggets), iptr(idx), stream());
+        }))
+      return nullptr;
+    return tuple_of({&counts, &cu_nuggets, &idx});
+  });
+}
+
+PyObject* segment_plan(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded(args, n, 6, [](PyObject* const* a) -> PyObject* {
+    const at::Tensor &idx = tensor(a[0]), &cu_seqlens = tensor(a[1]), &cu_nuggets = tensor(a[2]);
+    const int32_t seg_len = int32(whole(a[3])), tau = int32(whole(a[4])), capacity = int32(whole(a[5]));
+    require(cu_seqlens.numel() >= 1 && capacity >= 0);
+    const int32_t B = int32(cu_seqlens.numel() - 1);
+    at::Tensor cu_q, nug_start, nug_len, loc_start, loc_len, count;
+    if (!run("dodo_segment_plan", [&] {
+          const auto ints = cu_seqlens.options().dtype(at::kInt);
+          cu_q = at::empty({static_cast<int64_t>(capacity) + 1}, ints);
+          for (at::Tensor* t : {&nug_start, &nug_len, &loc_start, &loc_len}) *t = at::empty({capacity}, ints);
+          count = at::empty({1}, ints);
+          return L.segment_plan(iptr(idx), iptr(cu_seqlens), iptr(cu_nuggets), B, seg_len, tau, capacity, iptr(cu_q), iptr(nug_start),
+                                iptr(nug_len), iptr(loc_start), iptr(loc_len), iptr(count), stream());
+        }))
+      return nullptr;
+    return tuple_of({&cu_q, &nug_start, &nug_len, &loc_start, &loc_len, &count});
+  });
+}
+
+PyObject* ste_score_grad(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded(args, n, 16, [](PyObject* const* a) -> PyObject* {
+    const at::Tensor &Q = tensor(a[0]), &Kn = tensor(a[1]), &Vn = tensor(a[2]), &dO = tensor(a[3]), &O = tensor(a[4]), &lse = tensor(a[5]),
+                     &cu_q = tensor(a[6]), &cu_n = tensor(a[7]);
+    const int32_t max_q = int32(whole(a[8])), max_k = int32(whole(a[9]));
+    const int64_t layout = whole(a[12]);
+    at::Tensor grad = optional_tensor(a[13]), ws = optional_tensor(a[15]);
+    const bool accumulate = truth(a[14]);
+    require(Q.dim() == 3 && Kn.dim() >= 2 && cu_q.numel() >= 1 && Q.size(2) > 0);
+    require(layout == DODO_LAYOUT_TOKEN_MAJOR || layout == DODO_LAYOUT_HEAD_MAJOR);
+    const int64_t Sq = Q.size(0), rows[2] = {Sq, Q.size(1)};
+    const int64_t Kt = Kn.size(layout == DODO_LAYOUT_TOKEN_MAJOR ? 0 : 1);
+    const int32_t B = int32(cu_q.numel() - 1), H = int32(Q.size(1)), d_h = int32(Q.size(2));
+    const int32_t H_kv = int32(Kn.size(layout == DODO_LAYOUT_TOKEN_MAJOR ? 1 : 0));
+    const int code = dtype_code(Q);
+    for (const at::Tensor* t : {&dO, &O}) require(t->sizes() == Q.sizes() && t->scalar_type() == Q.scalar_type());
+    require(Kn.scalar_type() == Q.scalar_type() && Vn.scalar_type() == Q.scalar_type());
+    require(lse.scalar_type() == at::kFloat && lse.sizes() == at::IntArrayRef(rows) && (grad.defined() || !accumulate));
+    const double scale = a[10] == Py_None ? 1.0 / std::sqrt(static_cast<double>(d_h)) : real(a[10]);
+    const double grad_scale = a[11] == Py_None ? scale : real(a[11]);
+    if (!run("dodo_ste_score_grad", [&] {
+          if (!grad.defined()) grad = at::empty({Kt}, lse.options());
+          const size_t need = ws.defined() ? 0 : L.ste_ws(Sq, H, Kt);
+          if (need > 0) ws = at::empty({static_cast<int64_t>(need)}, lse.options().dtype(at::kByte));
+          return L.ste(ptr(Q), ptr(Kn), ptr(Vn), ptr(dO), ptr(O), fptr(lse), iptr(cu_q), iptr(cu_n), B, H, H_kv, d_h, max_q, max_k, Sq, Kt,
+                       static_cast<float>(scale), static_cast<float>(grad_scale), accumulate ? 1 : 0, code, static_cast<int>(layout),
+                       fptr(grad), ptr(ws), bytes_of(ws), stream());
+        }))
+      return nullptr;
+    return same_or_new(a[13], grad);
+  });
+}
+
+constexpr int kEntries = 18;
+
 // bind(raise, address, ...): the function that raises the binding's error and the entry points, in the order of Entries
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  void* p[11];
-  if (n != 12) {
-    PyErr_SetString(PyExc_TypeError, "bind takes a function and 11 addresses");
+  void* p[kEntries];
+  if (n != kEntries + 1) {
+    PyErr_SetString(PyExc_TypeError, "bind takes a function and the addresses of all entry points");
     return nullptr;
   }
-  for (int i = 0; i < 11; ++i) {
+  for (int i = 0; i < kEntries; ++i) {
     p[i] = PyLong_AsVoidPtr(a[i + 1]);
     if (p[i] == nullptr) {
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry point");
@@ -384,6 +522,13 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   L.stream_append = reinterpret_cast<decltype(L.stream_append)>(p[8]);
   L.score_mlp_ws = reinterpret_cast<decltype(L.score_mlp_ws)>(p[9]);
   L.score_mlp = reinterpret_cast<decltype(L.score_mlp)>(p[10]);
+  L.threshold_ws = reinterpret_cast<decltype(L.threshold_ws)>(p[11]);
+  L.threshold = reinterpret_cast<decltype(L.threshold)>(p[12]);
+  L.select_threshold = reinterpret_cast<decltype(L.select_threshold)>(p[13]);
+  L.segment_plan = reinterpret_cast<decltype(L.segment_plan)>(p[14]);
+  L.attention_segments = reinterpret_cast<decltype(L.attention_segments)>(p[15]);
+  L.ste_ws = reinterpret_cast<decltype(L.ste_ws)>(p[16]);
+  L.ste = reinterpret_cast<decltype(L.ste)>(p[17]);
   Py_INCREF(a[0]);
   Py_XDECREF(raise_error);
   raise_error = a[0];
@@ -393,7 +538,8 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
 #define DODO_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {DODO_METHOD(bind), DODO_METHOD(score), DODO_METHOD(select_topk), DODO_METHOD(gather_nuggets),
                          DODO_METHOD(nugget_attention), DODO_METHOD(nugget_attention_indexed), DODO_METHOD(nugget_attention_cached),
-                         DODO_METHOD(stream_append), DODO_METHOD(score_mlp), {nullptr, nullptr, 0, nullptr}};
+                         DODO_METHOD(nugget_attention_segments), DODO_METHOD(stream_append), DODO_METHOD(score_mlp), DODO_METHOD(threshold_from_sample),
+                         DODO_METHOD(select_threshold), DODO_METHOD(segment_plan), DODO_METHOD(ste_score_grad), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dodo_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -172,3 +172,67 @@ def test_calls_from_several_threads():
     for th in threads:
         th.join()
     assert not wrong
+
+
+# The calls of the autoregressive objective and of training, in the forms that programs use: the native call does them, with the
+# results of the one through ctypes, and what it declines the Python function refuses or takes as before.
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_training_calls_as_through_ctypes(dtype, monkeypatch):
+    t = _inputs("cuda", dtype)
+    names = ("threshold_from_sample", "select_threshold", "segment_plan", "nugget_attention_segments", "ste_score_grad")
+    real = B._native
+    done = []
+
+    def noting(name):
+        def call(*a):
+            r = getattr(real, name)(*a)
+            if r is not None:
+                done.append(name)
+            return r
+        return call
+
+    def calls():
+        out = {}
+        s = B.dodo_score(t["hidden"], t["w"])
+        lam = out["lambda"] = B.dodo_threshold_from_sample(s, 1, 10)
+        mine = torch.empty(1, device=s.device)
+        assert B.dodo_threshold_from_sample(s, 1, 10, out=mine) is mine and torch.equal(mine, lam)
+        counts, cu_k, idx = out["selection"] = B.dodo_select_threshold(s, t["cu_s"], lam)
+        total = int(cu_k[-1])
+        assert counts.shape == (2,) and cu_k.shape == (3,) and idx.shape == (300,)
+        out["selection"] = (counts, cu_k, idx[:total])
+        kn, vn = B.dodo_gather_nuggets(t["K"], t["V"], idx, t["cu_s"], cu_k, total)
+        plan = out["plan"] = B.dodo_segment_plan(idx, t["cu_s"], cu_k, 32, 7, 11)
+        q = t["K"].contiguous()
+        O = torch.empty_like(q)
+        got = out["segments"] = B.dodo_nugget_attention_segments(q, kn, vn, t["K"], t["V"], *plan[:5], 32, total, 39, 0.2, O=O, want_lse=True)
+        assert got[0] is O
+        a = (t["Kl"], t["Vl"], t["cu_q"], cu_k, t["cu_l"], 20, total, 35)
+        O, lse = B.dodo_nugget_attention(t["Q"], kn, vn, *a, want_lse=True)
+        b = (t["Q"], kn, vn, t["Q"], O, lse, t["cu_q"], cu_k, 20, total)
+        grad = out["grad"] = B.dodo_ste_score_grad(*b)
+        twice = grad.clone()
+        assert B.dodo_ste_score_grad(*b, grad=twice, accumulate=True) is twice
+        out["grad twice"] = twice
+        with pytest.raises((AssertionError, ValueError)):
+            B.dodo_ste_score_grad(*b, accumulate=True)
+        with pytest.raises((AssertionError, TypeError, ValueError)):
+            B.dodo_ste_score_grad(t["Q"], kn, vn, t["Q"], O, lse.double(), t["cu_q"], cu_k, 20, total)
+        with pytest.raises((AssertionError, ValueError)):
+            B.dodo_select_threshold(s.double(), t["cu_s"], lam)
+        with pytest.raises(B.DodoError):
+            B.dodo_threshold_from_sample(s, 0, 10)
+        return out
+
+    monkeypatch.setattr(B, "_native", types.SimpleNamespace(**{n: getattr(real, n) for n in dir(real) if not n.startswith("_")}))
+    for n in names:
+        monkeypatch.setattr(B._native, n, noting(n))
+    native = calls()
+    assert set(done) == set(names) and len(done) == 7
+    for n in names:
+        monkeypatch.setattr(B._native, n, lambda *a: None)
+    plain = calls()
+    for name in native:
+        for x, y in zip(_flat(native[name]), _flat(plain[name])):
+            assert x.dtype == y.dtype and torch.equal(x, y), name
