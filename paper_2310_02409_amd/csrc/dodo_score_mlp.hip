@@ -5,8 +5,9 @@
 // The paper does not name the activation; ReLU, GELU (erf form) and tanh are
 // offered.  2 N d d_hid flop: a dense contraction, so it runs on the matrix cores.
 //
-// Up to 64 tokens (bf16, d % 64 == 0, d_hid % 256 == 0): a kernel that streams W1
-// once over all compute units (score_mlp_few_kernel).
+// Up to 20 tokens (bf16, d % 64 == 0, d_hid % 256 == 0; up to 64 where d % 128 != 0):
+// a kernel that streams W1 once over all compute units (score_mlp_few_kernel).  Up to a
+// few hundred: tiles of 64 tokens, several steps in flight (score_mlp_some_kernel).
 //
 // MFMA kernel (the same shapes, more tokens): a workgroup of 8 wavefronts
 // owns 256 tokens and walks over 256-wide tiles of hidden units (or 4 wavefronts
@@ -317,15 +318,29 @@ __global__ __launch_bounds__((MlpTile<HB, TG, HG, KS>::kThreads), (MlpTile<HB, T
   }
 }
 
-// partial scores of the splits, added in split order, plus the output bias: the first n_big tokens have hs_big splits,
-// the others hs_small
-__global__ void score_mlp_combine_kernel(const float* __restrict__ partial, int hs_big, int64_t n_big, int hs_small, int64_t N,
-                                         float b2, float* __restrict__ scores) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= N) return;
+// partial scores of the splits, added in split order, plus the output bias: the first n_big tokens have hs_big splits, the next
+// n_small hs_small.  The n_some tokens after them have many splits: a wavefront per token, in the workgroups after thread_blocks,
+// every lane adding the splits of its own in order.
+constexpr int kCombineThreads = 256;
+__global__ __launch_bounds__(kCombineThreads) void score_mlp_combine_kernel(
+    const float* __restrict__ partial, int hs_big, int64_t n_big, int hs_small, int64_t n_small, int hs_some, int n_some,
+    int thread_blocks, float b2, float* __restrict__ scores) {
+  if (static_cast<int>(blockIdx.x) >= thread_blocks) {
+    const int t = (blockIdx.x - thread_blocks) * (kCombineThreads / kWave) + threadIdx.x / kWave;
+    if (t >= n_some) return;
+    const float* p0 = partial + hs_big * n_big + hs_small * n_small + t;
+    float s = 0.f;
+#pragma unroll 4
+    for (int p = lane_id(); p < hs_some; p += kWave) s += p0[static_cast<int64_t>(p) * n_some];
+    s = wave_sum64(s) + b2;
+    if (lane_id() == 0) scores[n_big + n_small + t] = (s == 0.f) ? 0.f : s;
+    return;
+  }
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * kCombineThreads + threadIdx.x;
+  if (t >= n_big + n_small) return;
   const bool big = t < n_big;
   const int splits = big ? hs_big : hs_small;
-  const int64_t stride = big ? n_big : N - n_big;
+  const int64_t stride = big ? n_big : n_small;
   const float* p0 = partial + (big ? t : hs_big * n_big + (t - n_big));
   float s = 0.f;
 #pragma unroll 8
@@ -346,6 +361,7 @@ __global__ void score_mlp_combine_kernel(const float* __restrict__ partial, int 
 // cost more than W1), against 84 us in the tile kernel, whose 16 workgroups walk over the channels one 64-wide step
 // after the other; d = d_hid = 5120: 17 and 31 against 190 us.
 constexpr int kFewTokens = 64;    // most tokens: four blocks of 16 (beyond, a workgroup re-reads too much of X from L2)
+constexpr int kFewBest = 20;      // beyond, tiles of 64 tokens are faster where they fit
 constexpr int kFewWaves = 8;
 constexpr int kFewRun = 64;       // channels per run
 
@@ -468,6 +484,143 @@ __global__ __launch_bounds__(kWave) void score_mlp_combine_few_kernel(const floa
   if (threadIdx.x == 0) scores[t] = (s == 0.f) ? 0.f : s;
 }
 
+// ---- some tokens: tiles of 64 tokens and 32 HB hidden units, so that a few hundred tokens fill the chip ----
+// Bound by what a compute unit takes from L2 (a step of 128 channels is 24 KiB at HB = 1, 32 KiB at HB = 2, against 128 or 256
+// cycles of matrix instructions), so the tile is as large as still gives every compute unit work, and kStages steps are in flight.
+// The tile kernel above gives 128 tokens to 32 of 256 compute units at d_hid = 4096 and has one step in flight.
+// Wavefronts: 2 groups of 32 tokens times 2 halves of a step's channels (HB = 1) or 2 blocks of 32 hidden units (HB = 2).
+constexpr int kSomeTok = 64, kSomeChannels = 128, kSomeRowBytes = kSomeChannels * 2;
+template <int HB, int STAGES>
+struct SomeTile {
+  static constexpr int kHid = 32 * HB;
+  static constexpr int kXBytes = kSomeTok * kSomeRowBytes;
+  static constexpr int kStageBytes = kXBytes + kHid * kSomeRowBytes;
+  static constexpr int kLds = STAGES * kStageBytes;
+  static constexpr int kXLoads = 4, kWLoads = 2 * HB, kLoads = kXLoads + kWLoads;  // per wavefront and step, 4 rows each
+  static constexpr int kParts = HB == 1 ? 4 : 8;                                    // 16-channel parts of a step per wavefront
+};
+template <int HB, int STAGES>
+__global__ __launch_bounds__(256, 2) void score_mlp_some_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W1, const float* __restrict__ b1,
+    const uint16_t* __restrict__ w2, int act, int N, int d, int splits, int64_t row_stride, float* __restrict__ partial) {
+  using Tile = SomeTile<HB, STAGES>;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (64 token rows | 32 HB rows of W1)
+  const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid % kWave, j32 = lane & 31, g = lane >> 5;
+  const int tg = wave & 1, part_of = wave >> 1;  // token group; half of the channels or hidden block
+  const int split = static_cast<int>(blockIdx.x % splits);  // (the token tiles of a split on one XCD, where 8 divides their number)
+  const int tok0 = static_cast<int>(blockIdx.x / splits) * kSomeTok, h0 = split * Tile::kHid;
+  const int n_steps = d / kSomeChannels;
+
+  // loader: an instruction brings 4 rows; piece p (16 bytes) of row r sits at position p ^ (r & 15)
+  uint32_t x_off[Tile::kXLoads], w_off[Tile::kWLoads];
+  const int l_row = lane >> 4, l_pos = lane & 15;
+#pragma unroll
+  for (int u = 0; u < Tile::kXLoads; ++u) {
+    const int r = 4 * (Tile::kXLoads * wave + u) + l_row;
+    const int tok = min(tok0 + r, N - 1) - tok0;  // rows past the end re-read the last token; nothing of them is stored
+    x_off[u] = static_cast<uint32_t>(tok) * static_cast<uint32_t>(row_stride * 2) + ((l_pos ^ (r & 15)) << 4);
+  }
+#pragma unroll
+  for (int u = 0; u < Tile::kWLoads; ++u) {
+    const int r = 4 * (Tile::kWLoads * wave + u) + l_row;
+    w_off[u] = static_cast<uint32_t>(r) * static_cast<uint32_t>(d) * 2u + ((l_pos ^ (r & 15)) << 4);
+  }
+  const uint16_t* x_base = X + static_cast<int64_t>(tok0) * row_stride;
+  const uint16_t* w_base = W1 + static_cast<int64_t>(h0) * d;
+  auto issue = [&](int step) {  // (past the last step nothing is fetched)
+    const uint32_t range = step < n_steps ? 0x7fffffffu : 0u;
+    const int c0 = step < n_steps ? step * kSomeChannels : 0;
+    const u32x4_t xb = buffer_of(x_base + c0, range), wb = buffer_of(w_base + c0, range);
+    const uint32_t stage = lds_base + (step % STAGES) * Tile::kStageBytes;
+#pragma unroll
+    for (int u = 0; u < Tile::kXLoads; ++u)
+      dma16_buffer(xb, x_off[u], __builtin_amdgcn_readfirstlane(stage + (Tile::kXLoads * wave + u) * 1024));
+#pragma unroll
+    for (int u = 0; u < Tile::kWLoads; ++u)
+      dma16_buffer(wb, w_off[u], __builtin_amdgcn_readfirstlane(stage + Tile::kXBytes + (Tile::kWLoads * wave + u) * 1024));
+  };
+  // Four sums, each of every fourth part, added up every 1024 channels: short chains of rounded additions (against 64 bits, 2-norm,
+  // d = 4096: one sum 4e-7, this way 1.3e-7 to 1.6e-7, the kernel for few tokens 1.7e-7 to 2e-7, the tile kernel 3e-7), and no
+  // matrix instruction waits for the one before.
+  constexpr int kFold = 1024 / kSomeChannels;
+  floatx16 acc, acc4[4];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    acc[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc4[i][v] = 0.f;
+  }
+  auto fold = [&]() {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      acc[v] += (acc4[0][v] + acc4[1][v]) + (acc4[2][v] + acc4[3][v]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc4[i][v] = 0.f;
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < STAGES - 1; ++t) issue(t);
+  const int x_row = (32 * tg + j32) * kSomeRowBytes;
+  const int w_row = Tile::kXBytes + ((HB == 2 ? 32 * part_of : 0) + j32) * kSomeRowBytes;
+  const int first_part = HB == 2 ? 0 : Tile::kParts * part_of;
+  constexpr int kYounger = (STAGES - 2) * Tile::kLoads;
+  static_assert(kYounger < 64, "vmcnt has six bits");
+  for (int step = 0; step < n_steps; ++step) {
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (kYounger & 15) | (kYounger >> 4 << 14));  // this wavefront's part of the step has landed
+    __syncthreads();  // everyone's has, and everyone has read the step before
+    issue(step + STAGES - 1);
+    const char* stg = lds + (step % STAGES) * Tile::kStageBytes;
+    bf16x8 xf[Tile::kParts], wf[Tile::kParts];
+#pragma unroll
+    for (int p = 0; p < Tile::kParts; ++p) {
+      const int at = ((2 * (first_part + p) + g) ^ (j32 & 15)) << 4;
+      xf[p] = *reinterpret_cast<const bf16x8*>(stg + x_row + at);
+      wf[p] = *reinterpret_cast<const bf16x8*>(stg + w_row + at);
+    }
+#pragma unroll
+    for (int p = 0; p < Tile::kParts; ++p)
+      acc4[p & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[p], xf[p], acc4[p & 3], 0, 0, 0);
+    if (step % kFold == kFold - 1) fold();
+  }
+  fold();
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();  // (the stages become a reduction buffer)
+  float* red = reinterpret_cast<float*>(lds);
+  if (HB == 1) {  // the halves of the channels, added before the activation
+    if (part_of == 1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[(tg * 16 + v) * kWave + lane] = acc[v];
+    }
+    __syncthreads();
+    if (part_of == 1) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] += red[(tg * 16 + v) * kWave + lane];
+  }
+  // accumulator v is hidden unit 8 (v / 4) + 4 g + v % 4 of the block, for this lane's token
+  float s = 0.f;
+  const int hb = h0 + (HB == 2 ? 32 * part_of : 0) + 4 * g;
+#pragma unroll
+  for (int vq = 0; vq < 4; ++vq) {
+    const float4 bb = *reinterpret_cast<const float4*>(b1 + hb + 8 * vq);
+    const uint2 ww = *reinterpret_cast<const uint2*>(w2 + hb + 8 * vq);
+    const float wv[4] = {bf16_lo(ww.x), bf16_hi(ww.x), bf16_lo(ww.y), bf16_hi(ww.y)}, bv[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(wv[e], activation(acc[4 * vq + e] + bv[e], act), s);
+  }
+  s += __shfl_xor(s, 32, kWave);
+  if (HB == 2) {
+    if (part_of == 1 && g == 0) red[32 * tg + j32] = s;
+    __syncthreads();
+    if (part_of == 1) return;
+    s += red[32 * tg + j32];
+  }
+  const int tok = tok0 + 32 * tg + j32;
+  if (g == 0 && tok < N) partial[static_cast<int64_t>(split) * N + tok] = s;
+}
+
 // ---- plain kernel: `kTok` token rows in LDS, one hidden unit per wavefront at a time
 constexpr int kPlainThreads = 256;
 template <int DTYPE>
@@ -543,18 +696,47 @@ size_t hidden_splits_most_bytes(int64_t N, int32_t d_hid) {
 // round of those would take longer than two workgroups per unit (1500 tokens 69.6 against 58.5 us).
 // d = d_hid = 4096, big tiles with four splits at least -> now: 128 tokens 85 -> 36 us, 2048 104 -> 70 us, 4096 the
 // same 116 us, 25123 (with their selection) 853 -> 716 us; 5120: 512 tokens 111 -> 44 us.
+//
+// Up to a few hundred tokens -- all there are, or what whole rounds of the other tiles leave -- take tiles of 64 tokens instead, in one
+// round, of 32 hidden units where that is at most one tile per compute unit, of 64 beyond.  d = d_hid = 4096, before -> now: 64 tokens
+// 25.2 -> 17.0 us, 128 35.8 -> 17.5, 256 36.3 -> 22.5, 512 36.8 -> 27.5, 2322 109 -> 95 (whole rounds before them); 5120: 128 tokens
+// 44.1 -> 26.5, 256 44.3 -> 31.5; 8192: 64 tokens 52.8 -> 37, 128 80 -> 42; 1024: 64 to 2048 tokens 11.2 to 16.2 -> 8.2 to 11.8.
+// (32 units with two tiles per compute unit: 256 tokens 24.4 us; more than a round of either: 547 tokens 46 us against 36.)
 struct MlpPlan {
   int64_t n_big;
   int hs_big;
   int64_t n_small;
   int hs_small;
   bool halves;  // small tiles: two groups of wavefronts share the channels
-  bool direct() const { return n_small == 0 && hs_big == 1; }  // the only split writes the scores itself
+  int n_some;
+  int hs_some;
+  bool direct() const { return n_small == 0 && n_some == 0 && hs_big == 1; }  // the only split writes the scores itself
   size_t bytes() const {
-    return direct() ? 0 : (static_cast<size_t>(hs_big) * n_big + static_cast<size_t>(hs_small) * n_small) * sizeof(float);
+    return direct() ? 0 : (static_cast<size_t>(hs_big) * n_big + static_cast<size_t>(hs_small) * n_small +
+                           static_cast<size_t>(hs_some) * n_some) * sizeof(float);
   }
 };
 constexpr int kBigRound = 100, kSmallHalves = 32, kSmallOne = 45, kSmallTwo = 60;
+// Tiles of 64 tokens: 1 (32 hidden units, two workgroups per compute unit), 2 (64, one) or 3 (64, two); 0: more than one round of them.
+constexpr int kSomeCost[4] = {0, 12, 16, 20};
+int some_tiles(int64_t n, int32_t d, int32_t d_hid) {
+  const int64_t cus = compute_units(), tiles = (n + kSomeTok - 1) / kSomeTok;
+  if (n <= 0 || d % kSomeChannels != 0 || tiles > 2 * cus) return 0;
+  if (tiles * (d_hid / 32) <= cus) return 1;
+  return tiles * (d_hid / 64) <= cus ? 2 : tiles * (d_hid / 64) <= 2 * cus ? 3 : 0;
+}
+int some_splits(int64_t n, int32_t d, int32_t d_hid) { return d_hid / (some_tiles(n, d, d_hid) == 1 ? 32 : 64); }
+size_t some_bytes(int64_t n, int32_t d, int32_t d_hid) {
+  return some_tiles(n, d, d_hid) == 0 ? 0 : static_cast<size_t>(some_splits(n, d, d_hid)) * n * sizeof(float);
+}
+// the most that these tiles take for any number of tokens up to N
+size_t some_most_bytes(int64_t N, int32_t d, int32_t d_hid) {
+  const int64_t cus = compute_units();
+  size_t most = 0;
+  for (const int64_t tiles : {cus / (d_hid / 32), cus / (d_hid / 64), 2 * cus / (d_hid / 64)})
+    most = std::max(most, some_bytes(std::min(N, tiles * kSomeTok), d, d_hid));
+  return most;
+}
 MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid) {
   const int cus = compute_units(), cus_xcd = cus >= 8 ? cus / 8 : 1;
   const int tiles = d_hid / MlpBig::kHid, small_tiles = d_hid / MlpSmall::kHid;
@@ -568,18 +750,30 @@ MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid) {
   };
   // (beyond 32 groups the rounds repeat: 32 groups are as many whole rounds as there are hidden tiles)
   const int64_t groups_all = (N + 8 * MlpBig::kTok - 1) / (8 * MlpBig::kTok);
-  int64_t best_groups = 0, best = -1;
+  int64_t best_groups = 0, best = -1, best_some = 0;
+  const int64_t small_round = 2 * cus / small_tiles * MlpSmall::kTok;  // tokens of one (0: more than one round for any)
   for (int64_t t = groups_all; t >= 0 && t > groups_all - 33; --t) {
-    const int64_t n_big = t * 8 * MlpBig::kTok < N ? t * 8 * MlpBig::kTok : N;
-    const int64_t cost = (t * tiles + cus_xcd - 1) / cus_xcd * kBigRound + small_cost(N - n_big);
-    if (best < 0 || cost < best) {
+    const int64_t n_big = t * 8 * MlpBig::kTok < N ? t * 8 * MlpBig::kTok : N, rest = N - n_big;
+    const int64_t rounds = (t * tiles + cus_xcd - 1) / cus_xcd * kBigRound;
+    const auto consider = [&](int64_t n_some) {
+      // (a launch of their own after another one's tail: 8 us, 7 hundredths of a round at d = 4096; at d = 1024 25123 tokens with
+      // their last 547 this way 84 us, without 71.5)
+      const int64_t more = n_some > 0 && n_some < N ? 30000 / d : 0;
+      const int64_t cost = rounds + small_cost(rest - n_some) + kSomeCost[some_tiles(n_some, d, d_hid)] + more;
+      if (best >= 0 && cost >= best) return;
       best = cost;
       best_groups = t;
-    }
+      best_some = n_some;
+    };
+    consider(0);
+    if (some_tiles(rest, d, d_hid) > 0) consider(rest);
+    if (small_round > 0 && rest > small_round && some_tiles(rest % small_round, d, d_hid) > 0) consider(rest % small_round);
   }
   MlpPlan p;
   p.n_big = best_groups * 8 * MlpBig::kTok < N ? best_groups * 8 * MlpBig::kTok : N;
-  p.n_small = N - p.n_big;
+  p.n_some = static_cast<int>(best_some);
+  p.hs_some = best_some > 0 ? some_splits(best_some, d, d_hid) : 0;
+  p.n_small = N - p.n_big - best_some;
   p.hs_small = small_tiles;
   p.halves = in_halves(p.n_small);
   // as many tiles per workgroup as leave the number of rounds alone (fewer starts and partial scores)
@@ -606,6 +800,17 @@ int launch_mfma(Kernel kern, const uint16_t* X, const uint16_t* W1, const float*
   return launch_status();
 }
 
+template <int HB, int STAGES>
+int launch_some(const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* w2, int act, int n, int d, int splits,
+                int64_t row_stride, float* out, hipStream_t s) {
+  const int lds = SomeTile<HB, STAGES>::kLds;
+  const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(score_mlp_some_kernel<HB, STAGES>), lds);
+  if (rc != DODO_OK) return rc;
+  hipLaunchKernelGGL((score_mlp_some_kernel<HB, STAGES>), dim3((n + kSomeTok - 1) / kSomeTok * splits), dim3(256), lds, s, X, W1, b1, w2,
+                     act, n, d, splits, row_stride, out);
+  return launch_status();
+}
+
 }  // namespace
 }  // namespace dodo
 
@@ -617,7 +822,7 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   const size_t few = static_cast<size_t>(few_splits(d_hid)) * (N < kFewTokens ? N : kFewTokens) * sizeof(float);
   const size_t least = hidden_splits_most_bytes(N, d_hid);
   const size_t plan = N <= kFewTokens ? 0 : plan_mlp(N, d, d_hid).bytes();
-  return std::max(plan, std::max(few, least));
+  return std::max({plan, few, least, some_most_bytes(N, d, d_hid)});
 }
 
 extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b1, const void* w2, float b2, int act,
@@ -633,7 +838,8 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
   if (mfma_path(dtype, N, d, d_hid, row_stride, hidden, W1, b1, w2)) {
     float* partial = static_cast<float*>(ws);
     const size_t room = ws != nullptr ? ws_bytes : 0;
-    if (N <= kFewTokens && room >= static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float)) {
+    const bool some = N > kFewBest && some_tiles(N, d, d_hid) > 0 && room >= some_bytes(N, d, d_hid);  // (then that is the plan)
+    if (N <= kFewTokens && !some && room >= static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float)) {
       const int splits = few_splits(d_hid), hid = few_hid(d_hid), n = static_cast<int>(N);
       const uint32_t x_bytes = static_cast<uint32_t>(((N - 1) * row_stride + d) * 2);
 #define DODO_LAUNCH_FEW(NB, RT)                                                                                          \
@@ -653,7 +859,7 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
     }
     MlpPlan p = plan_mlp(N, d, d_hid);
     if (room < p.bytes()) {
-      p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0, false};
+      p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0, false, 0, 0};
       if (room < p.bytes()) return DODO_ERR_WORKSPACE_TOO_SMALL;
     }
     const uint16_t* x = static_cast<const uint16_t*>(hidden);
@@ -672,8 +878,19 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
                                   d, d_hid, row_stride, p.hs_small, 1, partial + p.hs_big * p.n_big, s);
       if (rc != DODO_OK) return rc;
     }
-    hipLaunchKernelGGL(score_mlp_combine_kernel, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s, partial, p.hs_big,
-                       p.n_big, p.hs_small, N, b2, scores);
+    if (p.n_some > 0) {
+      const uint16_t* xs = x + (p.n_big + p.n_small) * row_stride;
+      float* out = partial + p.hs_big * p.n_big + p.hs_small * p.n_small;
+      const int form = some_tiles(p.n_some, d, d_hid);
+      const int rc = form == 1   ? launch_some<1, 3>(xs, w, b1, wo, act, p.n_some, d, p.hs_some, row_stride, out, s)
+                     : form == 2 ? launch_some<2, 4>(xs, w, b1, wo, act, p.n_some, d, p.hs_some, row_stride, out, s)
+                                 : launch_some<2, 2>(xs, w, b1, wo, act, p.n_some, d, p.hs_some, row_stride, out, s);
+      if (rc != DODO_OK) return rc;
+    }
+    const int64_t thread_blocks = (p.n_big + p.n_small + kCombineThreads - 1) / kCombineThreads;
+    const int64_t blocks = thread_blocks + (p.n_some + kCombineThreads / kWave - 1) / (kCombineThreads / kWave);
+    hipLaunchKernelGGL(score_mlp_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kCombineThreads), 0, s, partial, p.hs_big,
+                       p.n_big, p.hs_small, p.n_small, p.hs_some, p.n_some, static_cast<int>(thread_blocks), b2, scores);
     return launch_status();
   }
   // plain kernel: as many token rows per workgroup as fit in 128 KiB of LDS (at most 8)

@@ -172,3 +172,33 @@ def test_channels_shared_by_two_groups_that_are_not_finite(D, N, d, dh):
     assert np.isnan(got[nan]).all()
     rest = np.setdiff1d(np.arange(N), nan)
     _check(got[rest], oracle.score_mlp(W.to_numpy(x[rest]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 2))
+
+
+# Tiles of 64 tokens: 32 hidden units per tile (a tile per compute unit at most), 64 with one and with two tiles per unit; tokens around
+# a tile's end, fewer steps than there are stages, one more than are folded, and an even number; what whole rounds of other tiles leave.
+@pytest.mark.parametrize("N,d,dh", [(17, 128, 256), (63, 1152, 512), (64, 128, 8192), (65, 256, 4096), (129, 384, 4096), (256, 2048, 1024),
+                                    (300, 512, 4096), (512, 128, 4096), (577, 1152, 2048), (2100, 4096, 512), (9000, 1152, 4096)])
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_tiles_of_64_tokens(D, N, d, dh, act):
+    x, W1, b1, w2 = _case(1020 + N, N, d, dh, torch.bfloat16)
+    rows = np.unique(np.r_[0:min(N, 20), 60:min(N, 70), max(0, N - 70):N])
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, act)
+    padded = torch.full((N, d + 8), float("nan"), dtype=torch.bfloat16)
+    padded[:, :d] = x
+    t = [v.to(dev()) for v in (padded, W1, b1, w2)]
+    ws = torch.full((D.dodo_score_mlp_workspace_bytes(D.BF16, N, d, dh) + 64,), 255, dtype=torch.uint8, device=dev())
+    got = D.dodo_score_mlp(t[0][:, :d], *t[1:], 0.25, act, ws=ws[:-64]).cpu().numpy()
+    _check(got[rows], want)
+    assert torch.all(ws[-64:] == 255)
+
+
+@pytest.mark.parametrize("N,d,dh", [(40, 256, 4096), (150, 256, 4096), (300, 128, 4096)])
+def test_tiles_of_64_tokens_that_are_not_finite(D, N, d, dh):
+    x, W1, b1, w2 = _case(1040 + N, N, d, dh, torch.bfloat16)
+    x[N // 2, 9], x[3, d - 5], x[N - 1, d // 2] = float("-inf"), float("inf"), float("inf")
+    nan = [1, 30, N - 2]
+    x[1, 0], x[30, d // 2 - 1], x[N - 2, d - 1] = float("nan"), float("nan"), float("nan")
+    got = D.dodo_score_mlp(*[v.to(dev()) for v in (x, W1, b1, w2)], act=D.TANH).cpu().numpy()
+    assert np.isnan(got[nan]).all()
+    rest = np.setdiff1d(np.arange(N), nan)
+    _check(got[rest], oracle.score_mlp(W.to_numpy(x[rest]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 2))
