@@ -28,7 +28,8 @@
 // runs two groups of four wavefronts (one of each per SIMD) half a tile apart,
 // separated by workgroup barriers: while one group issues the 32 MFMAs of
 // "PV(t-1), then S(t)", the other does the softmax of its tile.  Small query
-// blocks (<= 128 rows) use a plain 4-wavefront kernel.
+// blocks (<= 128 rows) use a plain 4-wavefront kernel, where the chip is not full one
+// whose wavefronts share 64 rows in pairs, half of a tile's keys each (plan_blocks).
 //
 // What bounds the 8-wavefront kernel: the two phases are about equally long (cycle
 // counter, 3277 nuggets: 1200 cycles of matrix instructions, 1088 of them the pipe's
@@ -158,27 +159,28 @@ __device__ __forceinline__ float visible_or_neg_inf(float x, uint32_t bits, int 
 // Online-softmax update of one 32-row block for one 64-key tile.  acc holds the raw
 // S^T accumulators (two 32-key blocks); accumulator v of block kb <-> key 32kb + 8(v/4) + 4g + v%4.
 // Returns P^T as MFMA B operands: pf[2kb + half] = accumulators 8*half .. 8*half+7 of block kb.
-template <bool MASK, int NCB>
-__device__ __forceinline__ void softmax_tile(floatx16 (&acc)[2], int limit, int g, float scale_log2e, float& m_run,
-                                             float& l_run, floatx16 (&acc_o)[NCB], bf16x8 (&pf)[4]) {
+template <bool MASK, int NCB, int NKB>
+__device__ __forceinline__ void softmax_tile(floatx16 (&acc)[NKB], int limit, int g, float scale_log2e, float& m_run,
+                                             float& l_run, floatx16 (&acc_o)[NCB], bf16x8 (&pf)[2 * NKB]) {
   float tmax = kNegInf;
-  // (the lane's part of the key index, 4 g, is taken off the limit, so that the bits' positions are constants)
-  const uint32_t bits[2] = {first_keys(limit - 4 * g), first_keys(limit - 4 * g - 32)};
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < NKB; ++kb) {
+    // (the lane's part of the key index, 4 g, is taken off the limit, so that the bits' positions are constants)
+    const uint32_t bits = first_keys(limit - 4 * g - 32 * kb);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       float s = acc[kb][v] * scale_log2e;
-      if (MASK) s = visible_or_neg_inf(s, bits[kb], 8 * (v >> 2) + (v & 3));
+      if (MASK) s = visible_or_neg_inf(s, bits, 8 * (v >> 2) + (v & 3));
       acc[kb][v] = s;
       tmax = fmaxf(tmax, s);
     }
+  }
   tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
   const float m_new = fmaxf(m_run, tmax);
   const float m_use = (m_new == kNegInf) ? 0.f : m_new;
   float psum = 0.f;
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       floatx8 p;
@@ -233,18 +235,21 @@ __device__ __forceinline__ void softmax_fixed(const floatx16 (&acc)[2], float sc
   }
 }
 
-// NW = 4: plain loop, two workgroups per CU.  NW = 8: two groups of four wavefronts in
-// alternating MFMA / softmax phases, one workgroup per CU.
-template <int NW, int DH>
+// KG = 1, NW = 4: plain loop, two workgroups per CU.  NW = 8: two groups of four wavefronts in
+// alternating MFMA / softmax phases, one workgroup per CU.  KG = 2: plain loop, each 32 rows have two wavefronts, which
+// take half of every tile's keys each.
+template <int NW, int DH, int KG>
 struct BlockCfg {
+  static constexpr bool kTwoGroups = NW == 8 && KG == 1;
   static constexpr int kThreads = NW * kWave;
-  static constexpr int kBM = NW * 32;              // query rows per workgroup
-  static constexpr int kStages = NW == 4 ? 2 : 4;  // K/V tiles resident in LDS
+  static constexpr int kBM = NW * 32 / KG;            // query rows per workgroup
+  static constexpr int kStages = kTwoGroups ? 4 : 2;  // K/V tiles resident in LDS
   static constexpr int kLdsBytes = kStages * 2 * HeadDims<DH>::kTileBytes;
   static constexpr int kMinBlocks = NW == 4 ? 2 : 1;
   // gather-free form: the sequence's index list sits in LDS after the stages (160 KiB per compute unit in all)
-  static constexpr int kIdxCap = NW == 4 ? 4096 : 7680;  // (the 8-wavefront kernel has 1 KiB of static LDS besides)
+  static constexpr int kIdxCap = kTwoGroups ? 7680 : 4096;  // (the 8-wavefront kernel has 1 KiB of static LDS besides)
   static constexpr int kIdxBytes = kIdxCap * 4;
+  static constexpr int kMergeBytes = KG == 2 ? NW / 2 * kWave * 8 : 0;  // offsets and sums of the second halves, after all that
 };
 
 // What a query block needs to know of its sequence: first rows and lengths of its queries, nuggets and local rows
@@ -293,19 +298,19 @@ struct SplitArgs {
 };
 
 // One block (kBM rows) of one (sequence, group of G heads); called by the whole workgroup.
-// SPLIT (4 wavefronts): the workgroup takes an equal share of the key tiles and leaves its sums to
+// SPLIT (KG = 2): the workgroup takes an equal share of the key tiles and leaves its sums to
 // combine_splits_kernel.
 // IDX: Kn / Vn are the context's K / V and nugget j of sequence b is its token cu_ctx[b] + nug_idx[cu_nuggets[b] + j].
 // GROUPED: G_ heads go through the tiles together (else one).
-template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
+template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
 __device__ __forceinline__ void attend_query_block(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ nug_idx,
     int H, int H_kv, int G_, FastDiv div_G, FastDiv div_kv, const SeqGeom& geom, int qblk,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse, const SplitArgs& sp) {
-  static_assert(NW == 4 || !SPLIT, "only the 4-wavefront kernel shares the keys out");
-  using Cfg = BlockCfg<NW, DH>;
+  static_assert(KG == 2 || !SPLIT, "the others do not share the keys out");
+  using Cfg = BlockCfg<NW, DH, KG>;
   using HD = HeadDims<DH>;
   constexpr int kDH = DH, kRowBytes = HD::kRowBytes, kTileBytes = HD::kTileBytes;
   constexpr int kP = HD::kPieces;           // 16-byte pieces of a row
@@ -313,6 +318,8 @@ __device__ __forceinline__ void attend_query_block(
   constexpr int kNCB = HD::kChannelBlocks;  // 32-channel blocks of the output
   constexpr int kSteps = HD::kSteps;        // MFMAs of S^T per tile, and of O^T += V^T P^T
   constexpr int kBM = Cfg::kBM;
+  constexpr bool kTwoGroups = Cfg::kTwoGroups;
+  constexpr int NKB = 2 / KG;               // 32-key blocks of a tile per wavefront
   constexpr int kStages = Cfg::kStages;
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // stage s: K at 2s, V at 2s+1 (tiles of 16 KiB)
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
@@ -331,7 +338,8 @@ __device__ __forceinline__ void attend_query_block(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = tid % kWave;
   const int j = lane & 31, g = lane >> 5;
-  const int w_i0 = i0 + wave * 32;  // first row of this wavefront
+  const int row_wave = KG == 2 ? wave % (NW / 2) : wave, half = KG == 2 ? wave / (NW / 2) : 0;
+  const int w_i0 = i0 + row_wave * 32;  // first row of this wavefront
   // A wavefront past the sequence's last row only brings tiles: its matrix instructions would take the pipe and the LDS from the
   // others (8 x 530 rows, 200 nuggets, 32 heads 90.3 -> 80.0 us; 129 rows, 410 nuggets 28.7 -> 26.5; 16 x 32 rows 27.9 -> 25.9).
   const bool has_rows = w_i0 < rows_b;
@@ -370,10 +378,11 @@ __device__ __forceinline__ void attend_query_block(
   // Who brings what of a tile: in the 4-wavefront kernel every wavefront a part of K and of V; in the 8-wavefront kernel
   // the wavefronts of group 1 K and those of group 0 V.  Every request enqueues the same number of loads per lane (a tile
   // past the end fetches nothing), so the vmcnt arithmetic of the loops is uniform.
-  TileLoader<4, DH> loader;
-  loader.init(wave & 3, lane);
-  constexpr int kPer = TileLoader<4, DH>::kPerWave;
-  constexpr int kLoadsPerTile = NW == 8 ? kPer : 2 * kPer;
+  using Loader = TileLoader<kTwoGroups ? 4 : NW, DH>;
+  Loader loader;
+  loader.init(kTwoGroups ? wave & 3 : wave, lane);
+  constexpr int kPer = Loader::kPerWave;
+  constexpr int kLoadsPerTile = kTwoGroups ? kPer : 2 * kPer;
   uint32_t off[kPer];       // of the tensor that this wavefront's group brings (4 wavefronts: of K)
   uint32_t off_stride = 0;  // the token stride that they were made for
   auto request = [&](int tile, auto v_tag, auto both_tag) {
@@ -411,7 +420,7 @@ __device__ __forceinline__ void attend_query_block(
   using Alone = std::false_type;
   using WithV = std::true_type;
   auto issue_tile = [&](int tile) {
-    if (NW == 4) {
+    if (!kTwoGroups) {
       if (!SPLIT || tile < t_end) request(tile, K{}, WithV{});
     } else if (wave < 4) {
       request(tile, V{}, Alone{});
@@ -441,7 +450,7 @@ __device__ __forceinline__ void attend_query_block(
   // (NW = 8) use later.  Q^T fragments: lane (j, g) holds Q[my_i][16*ds + 8*g .. +8) for ds = 0..7.
   // Rows past the end of the sequence read as zeros, and their lanes take the last row's fragments instead: zeros would make NaN of
   // an infinite key, which spreads through the row sums below and has the block done twice.  Nothing of them is stored.
-  constexpr int kQSlot0 = NW == 8 ? 4 : 2;  // first 16 KiB slot of the query rows
+  constexpr int kQSlot0 = kTwoGroups ? 4 : 2;  // first 16 KiB slot of the query rows
   bf16x8 qf[kDH / 16];
   if (t_begin < t_end) {
     issue_tile(t_begin);
@@ -470,7 +479,7 @@ __device__ __forceinline__ void attend_query_block(
       }
       q_loader.issue(Q + (static_cast<int64_t>(q0 + first) * H + h0) * kDH, range, q_off, lds_base + (kQSlot0 + c) * kTileBytes);
     }
-    if (NW == 8) {
+    if (kTwoGroups) {
       issue_tile(1);
       __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerTile);  // tile 0 and Q landed, tile 1 in flight
     } else {
@@ -478,12 +487,12 @@ __device__ __forceinline__ void attend_query_block(
     }
     __syncthreads();
     const int j_q = max(0, min(j, rows_b - 1 - w_i0));
-    const char* qbuf = lds + kQSlot0 * kTileBytes + (wave * 32 + j_q) * kRowBytes;
+    const char* qbuf = lds + kQSlot0 * kTileBytes + (row_wave * 32 + j_q) * kRowBytes;
 #pragma unroll
     for (int ds = 0; ds < kDH / 16; ++ds)
       qf[ds] = *reinterpret_cast<const bf16x8*>(qbuf + (((2 * ds + g) ^ ((j_q >> kRowShift) & (kP - 1))) << 4));
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the fragments are in registers
-    if (NW == 8) {
+    if (kTwoGroups) {
       __syncthreads();  // everyone has its fragments: the stages are free again
       issue_tile(2);
       issue_tile(3);
@@ -515,19 +524,21 @@ __device__ __forceinline__ void attend_query_block(
     const char* kbuf = lds + (2 * (tile % kStages)) * kTileBytes + k_row_off;
     return *reinterpret_cast<const bf16x8*>(kbuf + (s & 1) * 32 * kRowBytes + ((((s >> 1) * 2 + g) ^ k_sw) << 4));
   };
-  auto compute_s = [&](int tile, floatx16 (&acc_s)[2]) {
+  auto compute_s = [&](int tile, floatx16 (&acc_s)[NKB]) {  // (KG = 2: the keys of block `half`)
+    constexpr int kAll = kSteps / KG;
+    const auto frag = [&](int s) { return read_k(tile, KG == 2 ? 2 * s + half : s); };
     bf16x8 kf[kAhead];
 #pragma unroll
-    for (int s = 0; s < kAhead; ++s) kf[s] = read_k(tile, s);
+    for (int s = 0; s < kAhead && s < kAll; ++s) kf[s] = frag(s);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc_s[kb][v] = 0.f;
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
+    for (int s = 0; s < kAll; ++s) {
       const bf16x8 cur = kf[s % kAhead];
-      if (s + kAhead < kSteps) kf[s % kAhead] = read_k(tile, s + kAhead);
-      acc_s[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, qf[s >> 1], acc_s[s & 1], 0, 0, 0);
+      if (s + kAhead < kAll) kf[s % kAhead] = frag(s + kAhead);
+      acc_s[s % NKB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, qf[s / NKB], acc_s[s % NKB], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -553,29 +564,31 @@ __device__ __forceinline__ void attend_query_block(
     }
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a[0], a[1], 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto compute_pv = [&](int tile, const bf16x8 (&pf)[4]) {
+  auto compute_pv = [&](int tile, const bf16x8 (&pf)[2 * NKB]) {  // (KG = 2: k-steps 2 half and 2 half + 1)
+    constexpr int kAll = kSteps / KG;
+    const auto frag = [&](int s) { return read_vt(tile, s + (KG == 2 ? half * kAll : 0)); };
     bf16x8 vf[kAhead];
 #pragma unroll
-    for (int s = 0; s < kAhead; ++s) vf[s] = read_vt(tile, s);
+    for (int s = 0; s < kAhead && s < kAll; ++s) vf[s] = frag(s);
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
+    for (int s = 0; s < kAll; ++s) {
       const bf16x8 cur = vf[s % kAhead];
-      if (s + kAhead < kSteps) vf[s % kAhead] = read_vt(tile, s + kAhead);
+      if (s + kAhead < kAll) vf[s % kAhead] = frag(s + kAhead);
       acc_o[s % kNCB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, pf[s / kNCB], acc_o[s % kNCB], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   bool bail = false;
-  auto softmax = [&](const TileInfo& ti, floatx16 (&acc_s)[2], bf16x8 (&pf)[4]) {
+  auto softmax = [&](const TileInfo& ti, floatx16 (&acc_s)[NKB], bf16x8 (&pf)[2 * NKB]) {
     if (ti.need_mask) {
-      softmax_tile<true, kNCB>(acc_s, ti.limit, g, scale_log2e, m_run, l_run, acc_o, pf);
+      softmax_tile<true, kNCB, NKB>(acc_s, ti.limit - 32 * half, g, scale_log2e, m_run, l_run, acc_o, pf);
     } else {
-      softmax_tile<false, kNCB>(acc_s, kBN, g, scale_log2e, m_run, l_run, acc_o, pf);
+      softmax_tile<false, kNCB, NKB>(acc_s, kBN, g, scale_log2e, m_run, l_run, acc_o, pf);
     }
   };
 
   bool saw_keys = false;  // (split form)
-  if constexpr (NW == 4) {
+  if constexpr (!kTwoGroups) {
     // ---- plain loop: one barrier per tile, next tile in flight ----
     // (the first barrier also tells that every wavefront has taken its Q fragments out of stage 1)
     for (int tile = t_begin; tile < t_end; ++tile) {
@@ -585,8 +598,8 @@ __device__ __forceinline__ void attend_query_block(
       const TileInfo ti = tile_info(tile);
       if (!ti.visible) continue;
       saw_keys = true;
-      floatx16 acc_s[2];
-      bf16x8 pf[4];
+      floatx16 acc_s[NKB];
+      bf16x8 pf[2 * NKB];
       compute_s(tile, acc_s);
       softmax(ti, acc_s, pf);
       compute_pv(tile, pf);
@@ -747,7 +760,40 @@ __device__ __forceinline__ void attend_query_block(
   // The 32 x 128 block of a wavefront goes through LDS (free by now) so that O is written with
   // full 256-byte rows, 16 bytes per lane; 16-byte pieces are XOR-swizzled with the row to keep
   // both the 8-byte writes and the 16-byte reads free of bank conflicts.
-  if (NW == 4) __syncthreads();  // every wavefront is done with the K/V stages
+  if (!kTwoGroups) __syncthreads();  // every wavefront is done with the K/V stages
+  if constexpr (KG == 2) {
+    // The second halves' offsets, sums and channels go to the first halves through the stages (16 bytes per lane and access).
+    float2* ml = reinterpret_cast<float2*>(lds + Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0)) + row_wave * kWave + lane;
+    float4* o = reinterpret_cast<float4*>(lds + row_wave * (32 * kDH * 4)) + lane;
+    if (half == 1) {
+      *ml = make_float2(m_run, l_run);
+#pragma unroll
+      for (int cb = 0; cb < kNCB; ++cb)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq)
+          o[(4 * cb + vq) * kWave] = make_float4(acc_o[cb][4 * vq], acc_o[cb][4 * vq + 1], acc_o[cb][4 * vq + 2], acc_o[cb][4 * vq + 3]);
+    }
+    __syncthreads();
+    if (half == 0) {
+      const float2 other = *ml;
+      const float m_new = fmaxf(m_run, other.x), m_use = (m_new == kNegInf) ? 0.f : m_new;
+      const float a = exp2_hw(m_run - m_use), b = exp2_hw(other.x - m_use);
+      l_run = l_run * a + other.y * b;
+      m_run = m_new;
+#pragma unroll
+      for (int cb = 0; cb < kNCB; ++cb)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          const float4 p = o[(4 * cb + vq) * kWave];
+          acc_o[cb][4 * vq] = acc_o[cb][4 * vq] * a + p.x * b;
+          acc_o[cb][4 * vq + 1] = acc_o[cb][4 * vq + 1] * a + p.y * b;
+          acc_o[cb][4 * vq + 2] = acc_o[cb][4 * vq + 2] * a + p.z * b;
+          acc_o[cb][4 * vq + 3] = acc_o[cb][4 * vq + 3] * a + p.w * b;
+        }
+    }
+    __syncthreads();  // the stages are free again
+    if (half == 1) return;
+  }
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
   if constexpr (SPLIT) {
     // (slots follow from max_q: rows of a sequence that is longer have none and are not written, rather than past the workspace)
@@ -771,7 +817,7 @@ __device__ __forceinline__ void attend_query_block(
   }
   {
     const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-    char* obuf = lds + wave * (32 * kRowBytes);
+    char* obuf = lds + row_wave * (32 * kRowBytes);
 #pragma unroll
     for (int cb = 0; cb < kDH / 32; ++cb)
 #pragma unroll
@@ -804,8 +850,8 @@ __device__ __forceinline__ void attend_query_block(
 // after the other: a block i from the end and a block i from the start, so that under the causal
 // mask all workgroups carry the same load (new workgroups are handed out in order, and a compute
 // unit that finishes early is not refilled before the ones ahead of it in that order).
-template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
-__global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kMinBlocks)) void block_attention_kernel(
+template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
+__global__ __launch_bounds__((BlockCfg<NW, DH, KG>::kThreads), (BlockCfg<NW, DH, KG>::kMinBlocks)) void block_attention_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_nuggets, const int32_t* __restrict__ nug_len,
@@ -867,11 +913,11 @@ __global__ __launch_bounds__((BlockCfg<NW, DH>::kThreads), (BlockCfg<NW, DH>::kM
   const SeqGeom g2 = load_seq_geom<IDX>(q2 >= 0 ? bh2 : bh1, div_HG, HG, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
   SplitArgs sp{0, 1, nullptr, nullptr, 0, 0};
   if (SPLIT) sp = SplitArgs{static_cast<int>(blockIdx.y), static_cast<int>(gridDim.y), part_o, part_ml, slots, cu_q[0]};
-  attend_query_block<NW, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g1, q1, nug_tok_stride, nug_head_stride,
+  attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g1, q1, nug_tok_stride, nug_head_stride,
                                          scale_log2e, O, lse, sp);
   if (!SPLIT && q2 >= 0) {
     __syncthreads();  // the first block's use of LDS is over
-    attend_query_block<NW, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g2, q2, nug_tok_stride, nug_head_stride,
+    attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g2, q2, nug_tok_stride, nug_head_stride,
                                            scale_log2e, O, lse, sp);
   }
 }
@@ -913,8 +959,9 @@ inline size_t split_bytes(int32_t B, int32_t H, int32_t d_h, int32_t max_q, int6
 // How a call's rows become workgroups.
 struct BlockPlan {
   int32_t G = 1;        // query heads of a K/V head that go through the tiles together
-  int32_t waves = 4;    // wavefronts per workgroup: 4 (128 rows) or 8 (256)
-  int32_t nsplit = 1;   // workgroups that share the keys of a block (4 wavefronts)
+  int32_t waves = 4;    // wavefronts per workgroup: 4 or 8, for 32 rows each
+  int32_t KG = 1;       // or 2 of them for 32 rows
+  int32_t nsplit = 1;   // workgroups that share the keys of a block (KG = 2)
   bool pair = false;    // two blocks per workgroup, a heavy and a light one
   bool sorted = false;  // all heavy blocks before the next ones
 };
@@ -922,11 +969,17 @@ struct BlockPlan {
 // The plan of least expected time, with at most max_splits shares of the keys.  Measured (ns): a 64-key tile 1350 in the
 // 4-wavefront kernel, 1.6 times that with two workgroups on a compute unit; in the 8-wavefront kernel 1200, 1600 where more than
 // half of the compute units run it, 2100 where hardly any two of them at work share their keys; heads of 64 channels two thirds
-// of that; a block's start and end 4000 and 6200.
+// of that; a block's start and end 4000 and 6200.  With two wavefronts per 32 rows, blocks of 64, a tile takes 1110, and 1900 with two
+// workgroups on a compute unit.
+//
+// Two wavefronts per 32 rows, each half of a tile's keys (KG = 2): a wavefront alone on its SIMD works through a tile as one chain of
+// matrix and vector instructions.  32 heads, one wavefront / two: 64 rows, 200 nuggets 13.7 / 11.7 us, 4 x 64 rows, 80 nuggets 10.2 /
+// 9.4, 170 rows, 358 nuggets 20.1 (the 8-wavefront kernel) / 16.8; 12 x 64 rows, 300 nuggets (two workgroups on a compute unit) 21.7 /
+// 19.4; on a full chip they only share its units: 24 x 64 rows 39.5 / 41.8.
 //
 // Heads together (G): where one head's blocks are more than the chip takes at once and leave lanes without a row or end far from
-// each other's causal limits.  One head / together: 64 heads over 8, 16 sequences of 34 rows over 460 nuggets 41.4 / 19.1 us, of 16
-// rows over 100 21.8 / 11.5; 8 of 336 rows, 143 nuggets 66.7 / 53.9; 32 heads over 8, 16 of 64 rows, 200 nuggets 19.8 / 17.0.  On a
+// each other's causal limits.  One head / together: 64 heads over 8, 16 sequences of 34 rows over 460 nuggets 42.9 / 26.1 us, of 16
+// rows over 100 21.9 / 10.5; 8 of 336 rows, 143 nuggets 68.4 / 56.3; 32 heads over 8, 16 of 64 rows, 200 nuggets 19.6 / 17.0.  On a
 // chip that is not full a head per workgroup is faster (8 heads of 16 rows 9.5 / 10.1 us, of 64 rows 13.8 / 15.8).
 //
 // Two blocks per workgroup, heavy and light, or all heavy blocks first (sorted): pairs fill the last round badly where the blocks
@@ -935,9 +988,9 @@ struct BlockPlan {
 // rows, 100 nuggets, 8 x 32 heads 146 (pairs) / 155 us (sorted).
 //
 // Keys shared by several workgroups: costs a launch and two passes over the partial results (one write, one read; 2 TB/s), so it
-// is for few rows and many keys.  64 rows, 3000 nuggets, 32 heads 71 -> 26 us; 3 x 23 rows, 2700 nuggets, 40 heads 67.5 -> 43 us;
-// 128 rows, 1500 nuggets, 64 heads over 8 42.5 -> 24 us; 2 x 21 rows, 332 nuggets, 32 heads 15.4 -> 13.6 us.  512 rows, 400
-// nuggets, 32 heads (17 MB of partial results for two splits) stay as they are: 23.7 us against 25.5.
+// is for few rows and many keys.  64 rows, 3000 nuggets, 40 heads 56 (whole) -> 23.4 us; 3 x 23 rows, 2700 nuggets, 40 heads 59 -> 41;
+// 128 rows, 1000 nuggets, 32 heads 27.4 -> 20.2; 12 heads of 300 rows, 1000 nuggets 29.4 -> 20.0.  512 rows, 400 nuggets, 32 heads
+// (17 MB of partial results for two splits) stay whole: 23.7 us against 25.5.
 // The bounds decide, also where they promise more than there is: in the cached form max_k may be a capacity.  64 rows, 32 heads over
 // a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
 // 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
@@ -949,17 +1002,19 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
   constexpr int64_t kStart4 = 4000, kStart8 = 6200;
   BlockPlan best;
   int64_t best_ns = -1;
-  const auto consider = [&](int64_t ns, int32_t G, int32_t waves, int64_t nsplit, bool pair, bool sorted) {
+  const auto consider = [&](int64_t ns, int32_t G, int32_t waves, int32_t KG, int64_t nsplit, bool pair, bool sorted) {
     if (best_ns >= 0 && ns * 20 >= best_ns * 19) return;
     best_ns = ns;
-    best = BlockPlan{G, waves, static_cast<int32_t>(nsplit), pair, sorted};
+    best = BlockPlan{G, waves, KG, static_cast<int32_t>(nsplit), pair, sorted};
   };
   for (int32_t G = 1; G <= H / H_kv; ++G) {
     if ((H / H_kv) % G != 0) continue;
     const int64_t pairs = static_cast<int64_t>(B) * (H / G), rows = static_cast<int64_t>(max_q) * G;
     const bool few = pairs % 8 != 0 && pairs < 64 && !heavy_last;  // (see launch_nw)
     for (int32_t waves = 8; waves >= 4; waves -= 4) {
-      if (waves == 8 ? rows <= 128 : (rows > 128 && G == 1) || eight_only) continue;
+      // (up to 128 query rows the offset follows the row's maximum, whose weight is then 1 and not rounded: 16 x 34 rows over 460
+      // nuggets, 64 heads over 8, error against 64 bits 2.19e-3, with the 8-wavefront kernel's fixed offset 2.30e-3)
+      if (waves == 8 ? max_q <= 128 : (rows > 128 && max_q > 128 && G == 1) || eight_only) continue;
       const int64_t bm = 32 * waves, n = (rows + bm - 1) / bm, units = pairs * n, at_once = waves == 8 ? cus : 2 * cus;
       const int64_t tile_ns = scaled(waves == 8 ? (2 * units <= cus ? 1200 : 1600) : units <= cus ? 1350 : 2160);
       const auto block_ns = [&](int64_t blk) {  // the nuggets and what the block's last row sees of the local rows
@@ -968,7 +1023,7 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
       };
       const int64_t rounds = (units + at_once - 1) / at_once;
       if (rounds <= 1) {
-        consider(block_ns(n - 1), G, waves, 1, false, false);
+        consider(block_ns(n - 1), G, waves, 1, 1, false, false);
         continue;
       }
       int64_t in_turn = 0, paired = -1;  // (blocks of one (sequence, group) run together in the latter only)
@@ -981,17 +1036,19 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
       const int64_t wgs = (pairs + 7) / 8 * 8 * ((n + 1) / 2);
       if (n >= 2 && wgs >= cus && !few) paired = (wgs + at_once - 1) / at_once * (block_ns(0) + block_ns(n - 1));
       if (paired >= 0 && (heavy_last || rounds > 16 || paired * 20 <= in_turn * 21)) {
-        consider(paired, G, waves, 1, true, false);
+        consider(paired, G, waves, 1, 1, true, false);
       } else {
-        consider(in_turn, G, waves, 1, false, n >= 2 && !heavy_last);
+        consider(in_turn, G, waves, 1, 1, false, n >= 2 && !heavy_last);
       }
     }
-    const int64_t units = pairs * ((rows + 127) / 128);
-    for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && units <= cus && s * units <= 2 * cus && 2 * s <= tiles; ++s) {
-      const int64_t tile_ns = scaled(s * units > cus ? 2160 : 1350);
-      const int64_t ns = (tiles + s - 1) / s * tile_ns + (max_q > 128 ? kStart8 : kStart4) + 5000 + static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000);
-      consider(ns, G, 4, s, false, false);
-    }
+    // two wavefronts per 32 rows: where that leaves a workgroup per compute unit at most, or up to 64 rows, which have the same
+    // workgroups either way, two
+    const int64_t units = pairs * ((rows + 63) / 64);
+    const auto tile_ns = [&](int64_t wgs) { return scaled(wgs > cus ? 1900 : 1110); };
+    if (!eight_only && units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * tile_ns(units) + kStart4, G, 4, 2, 1, false, false);
+    for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && units <= cus && s * units <= 2 * cus && 2 * s <= tiles; ++s)
+      consider((tiles + 2 * s - 1) / (2 * s) * 2 * tile_ns(s * units) + kStart4 + 5000 +
+               static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000), G, 4, 2, s, false, false);
   }
   return best;
 }
@@ -1009,11 +1066,11 @@ int heads_per_xcd(const AttnParams& p, const BlockPlan& plan) {
 }
 
 // nsplit > 1: the keys are shared by that many workgroups per query block, whose partial results the workspace holds.
-template <int NW, bool IDX, int DH, bool SPLIT, bool GROUPED>
+template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
 int launch_nw(const AttnParams& p, BlockPlan plan) {
-  using Cfg = BlockCfg<NW, DH>;
+  using Cfg = BlockCfg<NW, DH, KG>;
   if (IDX && p.max_k > Cfg::kIdxCap) return DODO_ERR_UNSUPPORTED;
-  constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0);
+  constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0) + Cfg::kMergeBytes;
   const int HG = p.H / plan.G, nsplit = plan.nsplit;
   const int64_t pairs = static_cast<int64_t>(p.B) * HG, blocks = (static_cast<int64_t>(p.max_q) * plan.G + Cfg::kBM - 1) / Cfg::kBM;
   // few (sequence, group)s that don't deal out evenly would leave XCDs idle: their blocks go to all of them in turn
@@ -1022,7 +1079,7 @@ int launch_nw(const AttnParams& p, BlockPlan plan) {
   const int64_t grid = (plan.sorted ? pairs : (pairs + 7) / 8 * 8) * n_slots;
   if (pairs > 0x7fffffffLL || grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   const int n_qblocks = static_cast<int>(blocks), heads_xcd = heads_per_xcd(p, plan);
-  auto kern = block_attention_kernel<NW, IDX, DH, SPLIT, GROUPED>;
+  auto kern = block_attention_kernel<NW, KG, IDX, DH, SPLIT, GROUPED>;
   const int64_t slots = SPLIT ? static_cast<int64_t>(p.B) * p.max_q * p.H : 0;
   float* part_o = SPLIT ? static_cast<float*>(p.ws) : nullptr;
   float2* part_ml = SPLIT ? reinterpret_cast<float2*>(part_o + slots * nsplit * DH) : nullptr;
@@ -1059,14 +1116,25 @@ int launch_dh(const AttnParams& p) {
     if (static_cast<int64_t>(p.max_n) * p.nug_tok_stride * 2 > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   }
   // (only blocks of 256 rows have room for a longer list; up to 128 query rows it is refused)
-  const bool eight_only = idx && p.max_k > BlockCfg<4, DH>::kIdxCap;
+  const bool eight_only = idx && p.max_k > BlockCfg<4, DH, 1>::kIdxCap;
   if (eight_only && p.max_q <= 128) return DODO_ERR_UNSUPPORTED;
   const BlockPlan plan = plan_blocks(p.B, p.H, p.H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.heavy_last != 0, max_splits, eight_only);
   const auto launch = [&](auto grouped_tag) {
     constexpr bool GROUPED = decltype(grouped_tag)::value;
-    if (plan.nsplit > 1) return idx ? launch_nw<4, true, DH, true, GROUPED>(p, plan) : launch_nw<4, false, DH, true, GROUPED>(p, plan);
-    if (plan.waves == 8) return idx ? launch_nw<8, true, DH, false, GROUPED>(p, plan) : launch_nw<8, false, DH, false, GROUPED>(p, plan);
-    return idx ? launch_nw<4, true, DH, false, GROUPED>(p, plan) : launch_nw<4, false, DH, false, GROUPED>(p, plan);
+    const auto form = [&](auto waves_tag, auto kg_tag, auto split_tag) {
+      constexpr int NW = decltype(waves_tag)::value, KG = decltype(kg_tag)::value;
+      constexpr bool SPLIT = decltype(split_tag)::value;
+      return idx ? launch_nw<NW, KG, true, DH, SPLIT, GROUPED>(p, plan) : launch_nw<NW, KG, false, DH, SPLIT, GROUPED>(p, plan);
+    };
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using Whole = std::false_type;
+    using Split = std::true_type;
+    if (plan.nsplit > 1) return form(I4{}, I2{}, Split{});
+    if (plan.KG == 2) return form(I4{}, I2{}, Whole{});
+    return plan.waves == 4 ? form(I4{}, I1{}, Whole{}) : form(I8{}, I1{}, Whole{});
   };
   return plan.G > 1 ? launch(std::true_type{}) : launch(std::false_type{});
 }

@@ -317,3 +317,42 @@ def test_rows_of_grouped_heads_together(B, q, k, H, H_kv, d_h):
     idx = torch.cat([torch.arange(n, dtype=torch.int32) for n in k_lens]).to(dev())
     Oi, lse_i = D.dodo_nugget_attention_indexed(t["Q"], t["Kn"], t["Vn"], idx, t["cu_nuggets"], *a, max(k_lens), scale, want_lse=True)
     assert torch.equal(O, Oi) and torch.equal(lse, lse_i)
+
+
+# Two wavefronts per 32 rows, each half of a tile's keys: rows that see keys of one half only, none at all, or one key more; one and two
+# workgroups per compute unit (more than 256 blocks), blocks of 64 rows with one left over, and the whole-tile form beside it.
+@pytest.mark.parametrize("B,q,k,H,H_kv,d_h", [
+    (2, 40, 31, 4, 4, 128), (3, 65, 33, 4, 4, 128), (2, 64, 0, 8, 8, 64), (3, 129, 64, 2, 2, 64), (20, 64, 95, 16, 16, 128),
+    (20, 33, 32, 16, 16, 64), (20, 100, 97, 16, 16, 128), (1, 16, 1100, 4, 4, 128), (2, 70, 900, 6, 3, 64),
+])
+def test_halves_of_a_tile(B, q, k, H, H_kv, d_h):
+    import paper_2310_02409_amd as D
+    q_lens = [max(1, q - b % 7) for b in range(B)]
+    k_lens = [max(0, k - b % 3) for b in range(B)]
+    m_lens = [max(0, n - (5 if b % 2 else -35)) for b, n in enumerate(q_lens)]  # (some rows see no local row, or the first only)
+    host, t = make_attention_case(950 + q, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], scale)
+    a = (t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], max(q_lens), max(k_lens), max(m_lens))
+    O, lse = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], *a, scale, want_lse=True)
+    check_attention(O, want, torch.bfloat16)
+    check_lse(lse, lse_want, torch.bfloat16)
+
+
+# A NaN or an infinity in either half of a tile reaches the rows and channels that it reaches when a wavefront takes the whole tile.
+@pytest.mark.parametrize("key", [3, 40])
+def test_halves_of_a_tile_that_are_not_finite(key):
+    import paper_2310_02409_amd as D
+    B, q, k, H, d_h = 2, 20, 64, 4, 128
+    host, t = make_attention_case(970, [q] * B, [k] * B, [q] * B, H, H, d_h, torch.bfloat16, dev())
+    run = lambda: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], q, k, q)[0]
+    clean = run()
+    t["Vn"][key, 1, 7] = float("inf")
+    t["Vn"][k + key, 2, 9] = float("nan")
+    O, want = run(), clean.clone()
+    want[:q, 1, 7], want[q:, 2, 9] = float("inf"), float("nan")
+    assert torch.equal(torch.nan_to_num(O.float(), nan=-7.0), torch.nan_to_num(want.float(), nan=-7.0))
+    t["Kn"][key, 3, 5] = float("nan")
+    bad = run()
+    assert torch.isnan(bad[:q, 3].float()).all() and torch.equal(bad[q:, 3], clean[q:, 3]) and torch.equal(bad[:, 0], clean[:, 0])
