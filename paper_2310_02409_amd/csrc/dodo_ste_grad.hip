@@ -11,7 +11,7 @@
 //
 // Two contractions (Q K^T and dO V^T) restricted to the nugget columns:
 // 4 k q d_h flop per (sequence, head).  bf16 with d_h = 128 or 64 runs on the
-// matrix cores: each of a workgroup's 4 wavefronts owns 64 nuggets of one
+// matrix cores: each of a workgroup's 4 wavefronts owns 64 (or 32) nuggets of one
 // (sequence, head), whose K and V fragments stay in its registers; the workgroup
 // walks over the sequence's query rows in tiles of 32 (Q, dO and O rows stream into
 // a 3-stage LDS ring by 16-byte direct loads, two tiles ahead, shared by the 4
@@ -32,6 +32,8 @@
 // 1024 rows: 130 us (136 us).  Heads of 64, 4 x 250 nuggets, 300 rows, 16 heads:
 // 17.3 us, 2249 us in the plain kernel.  Error against 64 bits (2-norm), 512 rows,
 // 410 / 3277 nuggets: 2.9e-7 / 4.1e-7 (were 4.2e-7 / 4.7e-7).
+#include <type_traits>
+
 #include "dodo_common.h"
 
 namespace dodo {
@@ -43,8 +45,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kGradWaves = 4;
 constexpr int kGradThreads = kGradWaves * kWave;
-constexpr int kWaveNug = 64;                       // nuggets per wavefront
-constexpr int kNugTile = kGradWaves * kWaveNug;    // nuggets per workgroup
+constexpr int nuggets_per_workgroup(int blocks) { return kGradWaves * 32 * blocks; }  // (blocks of 32 per wavefront)
 constexpr int kQTile = 32;                         // query rows per step
 constexpr int kStagesSte = 3;
 constexpr int kLseChunk = 1024;                    // query rows whose lse sits in LDS at a time
@@ -112,13 +113,14 @@ __global__ __launch_bounds__(256) void ste_rowdot_kernel(const void* __restrict_
   }
 }
 
-template <int DH, bool PRE>
+template <int DH, bool PRE, int NB>
 __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ dO, const uint16_t* __restrict__ O, const float* __restrict__ lse,
     const float* __restrict__ aux_lse2, const float* __restrict__ aux_D, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_nuggets, int B, int H, int H_kv, int n_nug_tiles, int64_t Sq, int64_t Kt, int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, float* __restrict__ partial) {
   using SD = SteDims<DH, PRE>;
+  constexpr int kWaveNug = 32 * NB, kNugTile = nuggets_per_workgroup(NB);
   constexpr int kRowBytes = SD::kRowBytes, kP = SD::kPieces, kRowShift = SD::kRowShift, kTileBytes = SD::kTileBytes;
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // stages of (Q | dO | O tile), then lse2 of a chunk, D or -D of two tiles or of the chunk
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = tid % kWave;
   const int n = lane & 31, g = lane >> 5;
-  const int nug0 = tile * kNugTile + wave * kWaveNug;  // this wavefront's 64 nuggets
+  const int nug0 = tile * kNugTile + wave * kWaveNug;  // this wavefront's first nugget
   const bool active = nug0 < k_b;                      // (the others only help to load and with D)
 
   // loader: a stage is 32 query rows of Q, dO and O; wavefront w brings rows 8w .. 8w+7 of each, whole rows; the 16-byte
@@ -211,11 +213,11 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   };
   load_lse(0);
 
-  // K and V fragments of the two 32-nugget blocks (B operands: lane (n, g) holds channels 16 ks + 8 g .. + 8 of
+  // K and V fragments of the 32-nugget blocks (B operands: lane (n, g) holds channels 16 ks + 8 g .. + 8 of
   // nugget row n); rows past the sequence's last nugget re-read it, their sums are not stored
-  bf16x8 kf[2][DH / 16], vf[2][DH / 16];
+  bf16x8 kf[NB][DH / 16], vf[NB][DH / 16];
 #pragma unroll
-  for (int blk = 0; blk < 2; ++blk) {
+  for (int blk = 0; blk < NB; ++blk) {
     const int r = min(nug0 + 32 * blk + n, k_b - 1);
     const int64_t off = static_cast<int64_t>(k0 + r) * nug_tok_stride + static_cast<int64_t>(kvh) * nug_head_stride + 8 * g;
 #pragma unroll
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   // a wait written in assembly: with only that, it waited for them inside the loop, down to vmcnt(0) at the last matrix
   // instruction of every tile, that is for the tile that had just been requested.)
 #pragma unroll
-  for (int blk = 0; blk < 2; ++blk)
+  for (int blk = 0; blk < NB; ++blk)
 #pragma unroll
     for (int ks = 0; ks < DH / 16; ++ks) asm volatile("" : "+v"(kf[blk][ks]), "+v"(vf[blk][ks]));
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): tiles 0 and 1 too
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   };
   if (!PRE && n_qtiles > 0) row_dots(0);
 
-  float ds[2] = {0.f, 0.f}, lost[2] = {0.f, 0.f};  // sum, and what its additions rounded away
+  float ds[NB] = {}, lost[NB] = {};  // sum, and what its additions rounded away
   for (int t = 0; t < n_qtiles; ++t) {
     if (PRE) __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // this wavefront's part of tile t has landed, t+1 may be in flight
     __syncthreads();  // everyone's part of tile t has landed, its D is there; tile t-1 has been read by everyone
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     if (!active) issue_tile(t + 2);
     const float* dd_t = dd_l + (PRE ? c0 : (t & 1) * kQTile);
     const char* stg = lds + (t % kStagesSte) * SD::kStageBytes;
-    floatx16 acc_s[2], acc_p[2];
+    floatx16 acc_s[NB], acc_p[NB];
     if (active) {
       // S starts from 0, dP from -D or from 0 (SteDims::kExact)
       floatx16 first;
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
         }
       }
 #pragma unroll
-      for (int blk = 0; blk < 2; ++blk) {
+      for (int blk = 0; blk < NB; ++blk) {
         acc_p[blk] = first;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc_s[blk][v] = 0.f;
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
         if (ks + 2 < DH / 16) read_frags(ks + 2);
         if (ks == DH / 32) issue_tile(t + 2);
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
+        for (int blk = 0; blk < NB; ++blk) {
           acc_s[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[blk][ks], acc_s[blk], 0, 0, 0);
           acc_p[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, vf[blk][ks], acc_p[blk], 0, 0, 0);
         }
@@ -321,7 +323,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
     if (!active) continue;
     // accumulator v of a block is query row 8 (v / 4) + 4 g + v % 4 of the tile, for this lane's nugget; a tile's rows are
     // summed before they join the others (shorter chains of rounded additions)
-    float part[2] = {0.f, 0.f};
+    float part[NB] = {};
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) {
       const float4 l2 = *reinterpret_cast<const float4*>(lse2_l + c0 + 8 * vq + 4 * g);
@@ -332,7 +334,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
         ddv[0] = dd.x; ddv[1] = dd.y; ddv[2] = dd.z; ddv[3] = dd.w;
       }
 #pragma unroll
-      for (int blk = 0; blk < 2; ++blk)
+      for (int blk = 0; blk < NB; ++blk)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float p = __builtin_amdgcn_exp2f(acc_s[blk][4 * vq + e] * scale_log2e - l2v[e]);
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
         }
     }
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
+    for (int blk = 0; blk < NB; ++blk) {
       if (SD::kExact) {
         const float add = part[blk] - lost[blk], sum = ds[blk] + add;
         lost[blk] = (sum - ds[blk]) - add;
@@ -355,7 +357,7 @@ __global__ __launch_bounds__(kGradThreads, 2) void ste_grad_mfma_kernel(
   // the two halves of a nugget's query rows sit in lanes n and n + 32
   if (active) {
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
+    for (int blk = 0; blk < NB; ++blk) {
       const float both = ds[blk] + __shfl_xor(ds[blk], 32, kWave);
       const int i = nug0 + 32 * blk + n;
       if (g == 0 && i < k_b) partial[static_cast<int64_t>(h) * Kt + k0 + i] = both;
@@ -483,8 +485,15 @@ extern "C" int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn
   };
   int rc;
   if (mfma) {
-    const int n_nug_tiles = (max_k + kNugTile - 1) / kNugTile;
     const int64_t bh8 = (static_cast<int64_t>(B) * H + 7) / 8 * 8;
+    // One block of 32 nuggets per wavefront instead of two (the same bits) where two would leave wavefronts or compute units without
+    // any: a row tile's chain is half as long then.  32 heads of 128, two / one: 7 x 980 rows, 82 nuggets 49.1 / 39.0 us, 512 rows, 410
+    // nuggets 28.2 / 22.1, 1000 rows, 800 nuggets 44.1 / 33.9, 4 x 400 rows, 128 nuggets 24.2 / 20.2.  With more workgroups than compute
+    // units every one of which reads the rows and forms D again: 5 x 800 rows, 250 nuggets 40.6 / 46.2, 4 x 300 rows, 400 nuggets 22.9 /
+    // 24.4; heads of 64, 8 x 300 rows, 400 nuggets, 16 heads 17.5 / 16.3.
+    const int narrow = (max_k + nuggets_per_workgroup(1) - 1) / nuggets_per_workgroup(1);
+    const bool one_block = narrow == 1 || bh8 * narrow <= (d_h == 64 ? 2 : 1) * compute_units();
+    const int n_nug_tiles = one_block ? narrow : (max_k + nuggets_per_workgroup(2) - 1) / nuggets_per_workgroup(2);
     const int64_t grid = bh8 * n_nug_tiles;
     if (grid > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
     // D in the kernel costs about 0.3 us for every query tile that a compute unit's workgroups walk over, a kernel of
@@ -508,9 +517,13 @@ extern "C" int dodo_ste_score_grad(const void* Q, const void* Kn, const void* Vn
                          Sq, Kt, tok_stride, head_stride, scale_log2e, partial);
       return DODO_OK;
     };
-    rc = pre          ? launch(ste_grad_mfma_kernel<128, true>, SteDims<128, true>::kLds)
-         : d_h == 128 ? launch(ste_grad_mfma_kernel<128, false>, SteDims<128, false>::kLds)
-                      : launch(ste_grad_mfma_kernel<64, false>, SteDims<64, false>::kLds);
+    const auto launch_blocks = [&](auto blocks_tag) {
+      constexpr int NB = decltype(blocks_tag)::value;
+      return pre          ? launch(ste_grad_mfma_kernel<128, true, NB>, SteDims<128, true>::kLds)
+             : d_h == 128 ? launch(ste_grad_mfma_kernel<128, false, NB>, SteDims<128, false>::kLds)
+                          : launch(ste_grad_mfma_kernel<64, false, NB>, SteDims<64, false>::kLds);
+    };
+    rc = one_block ? launch_blocks(std::integral_constant<int, 1>{}) : launch_blocks(std::integral_constant<int, 2>{});
     if (rc != DODO_OK) return rc;
   } else {
     if (H > 65535) return DODO_ERR_UNSUPPORTED;

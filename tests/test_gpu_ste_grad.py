@@ -152,3 +152,19 @@ def test_ruled_out_nugget(D, q, H, d_h):
                                  oracle.cu_from_lengths([k - 1]), cu[2], scale, scale)
     assert got[41] == 0
     _check(got[rest], want, torch.bfloat16)
+
+
+# One block of 32 nuggets per wavefront (up to 128 nuggets, or few workgroups) and two: nuggets around a block's and a workgroup's end,
+# rows around a row tile's, D formed in the kernel and before it (many nugget tiles).
+@pytest.mark.parametrize("q_lens,k_lens,H,H_kv,d_h", [
+    ([31, 64, 33], [31, 33, 32], 4, 4, 128), ([65, 1, 40], [127, 128, 1], 4, 2, 64), ([50, 32], [129, 257], 2, 2, 128),
+    ([40 - b for b in range(20)], [max(0, 130 - 7 * b) for b in range(20)], 8, 4, 128), ([33] * 20, [130 - 6 * b for b in range(20)], 32, 32, 64),
+    ([200], [8320], 4, 4, 128),
+])
+def test_blocks_of_nuggets_per_wavefront(D, q_lens, k_lens, H, H_kv, d_h):
+    m_lens = [q + 5 for q in q_lens]
+    t, cu = _case(760 + len(q_lens), q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16)
+    scale = d_h ** -0.5
+    want = oracle.ste_score_grad(*(W.to_numpy(t[k]) for k in ("Q", "Kn", "Vn", "Kl", "Vl", "dO")), *cu, scale, 1.0)
+    got = _gpu(D, t, cu, q_lens, k_lens, m_lens, scale, 1.0)
+    _check(got, want, torch.bfloat16)
