@@ -249,7 +249,9 @@ struct BlockCfg {
   // gather-free form: the sequence's index list sits in LDS after the stages (160 KiB per compute unit in all)
   static constexpr int kIdxCap = kTwoGroups ? 7680 : 4096;  // (the 8-wavefront kernel has 1 KiB of static LDS besides)
   static constexpr int kIdxBytes = kIdxCap * 4;
-  static constexpr int kMergeBytes = KG == 2 ? NW / 2 * kWave * 8 : 0;  // offsets and sums of the second halves, after all that
+  // KG = 2: the second halves' channels, offsets and sums meet the first halves' in the stages
+  static constexpr int kMergeO = NW / 2 * 32 * DH * 4;
+  static_assert(KG == 1 || kMergeO + NW / 2 * kWave * 8 <= kLdsBytes, "the merge of the halves fits into the stages");
 };
 
 // What a query block needs to know of its sequence: first rows and lengths of its queries, nuggets and local rows
@@ -763,7 +765,9 @@ __device__ __forceinline__ void attend_query_block(
   if (!kTwoGroups) __syncthreads();  // every wavefront is done with the K/V stages
   if constexpr (KG == 2) {
     // The second halves' offsets, sums and channels go to the first halves through the stages (16 bytes per lane and access).
-    float2* ml = reinterpret_cast<float2*>(lds + Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0)) + row_wave * kWave + lane;
+    // (Behind the stages their offsets and sums would take the index list's workgroups the second place on a compute unit: 12 x 64
+    // rows, 300 nuggets, 32 heads through the list 30.4 us there, 21.9 here; 9 x 64 rows, 100 nuggets 20.2 / 13.9.)
+    float2* ml = reinterpret_cast<float2*>(lds + Cfg::kMergeO) + row_wave * kWave + lane;
     float4* o = reinterpret_cast<float4*>(lds + row_wave * (32 * kDH * 4)) + lane;
     if (half == 1) {
       *ml = make_float2(m_run, l_run);
@@ -1070,7 +1074,8 @@ template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
 int launch_nw(const AttnParams& p, BlockPlan plan) {
   using Cfg = BlockCfg<NW, DH, KG>;
   if (IDX && p.max_k > Cfg::kIdxCap) return DODO_ERR_UNSUPPORTED;
-  constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0) + Cfg::kMergeBytes;
+  constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0);
+  static_assert(Cfg::kMinBlocks * kLds <= 160 * 1024, "a compute unit has LDS for the workgroups that plan_blocks puts there");
   const int HG = p.H / plan.G, nsplit = plan.nsplit;
   const int64_t pairs = static_cast<int64_t>(p.B) * HG, blocks = (static_cast<int64_t>(p.max_q) * plan.G + Cfg::kBM - 1) / Cfg::kBM;
   // few (sequence, group)s that don't deal out evenly would leave XCDs idle: their blocks go to all of them in turn

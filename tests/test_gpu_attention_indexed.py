@@ -76,6 +76,15 @@ def test_block_kernel_bf16(D, n_lens, k_lens, q_lens, m_lens, H, H_kv):
     _check(D, 505, n_lens, k_lens, q_lens, m_lens, H, H_kv, 64, torch.bfloat16)
 
 
+# Blocks of 64 rows whose wavefronts take half of a tile's keys each, more of them than compute units: two workgroups share a unit's LDS,
+# the stages, index lists and merges of both.
+@pytest.mark.parametrize("q,k,d_h", [(64, 150, 128), (33, 65, 128), (64, 200, 64)])
+def test_halves_of_a_tile_through_the_index_list(D, q, k, d_h):
+    B, H = 20, 16
+    k_lens, q_lens = [k - b % 5 for b in range(B)], [q - b % 3 for b in range(B)]
+    _check(D, 506, [3 * k] * B, k_lens, q_lens, [n + 20 - b % 40 for b, n in enumerate(q_lens)], H, H, d_h, torch.bfloat16)
+
+
 def test_block_kernel_padded_token_stride_and_long_index_list(D):
     _check(D, 503, [20000], [4000], [256], [256], 2, 1, 128, torch.bfloat16, pad_heads=1)
 
