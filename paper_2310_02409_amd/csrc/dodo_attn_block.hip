@@ -300,7 +300,7 @@ struct SplitArgs {
 };
 
 // One block (kBM rows) of one (sequence, group of G heads); called by the whole workgroup.
-// SPLIT (KG = 2): the workgroup takes an equal share of the key tiles and leaves its sums to
+// SPLIT (4 wavefronts): the workgroup takes an equal share of the key tiles and leaves its sums to
 // combine_splits_kernel.
 // IDX: Kn / Vn are the context's K / V and nugget j of sequence b is its token cu_ctx[b] + nug_idx[cu_nuggets[b] + j].
 // GROUPED: G_ heads go through the tiles together (else one).
@@ -311,7 +311,7 @@ __device__ __forceinline__ void attend_query_block(
     int H, int H_kv, int G_, FastDiv div_G, FastDiv div_kv, const SeqGeom& geom, int qblk,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse, const SplitArgs& sp) {
-  static_assert(KG == 2 || !SPLIT, "the others do not share the keys out");
+  static_assert(NW == 4 || !SPLIT, "the 8-wavefront kernel does not share the keys out");
   using Cfg = BlockCfg<NW, DH, KG>;
   using HD = HeadDims<DH>;
   constexpr int kDH = DH, kRowBytes = HD::kRowBytes, kTileBytes = HD::kTileBytes;
@@ -965,7 +965,7 @@ struct BlockPlan {
   int32_t G = 1;        // query heads of a K/V head that go through the tiles together
   int32_t waves = 4;    // wavefronts per workgroup: 4 or 8, for 32 rows each
   int32_t KG = 1;       // or 2 of them for 32 rows
-  int32_t nsplit = 1;   // workgroups that share the keys of a block (KG = 2)
+  int32_t nsplit = 1;   // workgroups that share the keys of a block (4 wavefronts)
   bool pair = false;    // two blocks per workgroup, a heavy and a light one
   bool sorted = false;  // all heavy blocks before the next ones
 };
@@ -991,10 +991,13 @@ struct BlockPlan {
 // (sorted), 32 over 8 65.6 / 51.4.  But blocks of one group, which read the same keys, are then seldom at work together: 1100
 // rows, 100 nuggets, 8 x 32 heads 146 (pairs) / 155 us (sorted).
 //
-// Keys shared by several workgroups: costs a launch and two passes over the partial results (one write, one read; 2 TB/s), so it
-// is for few rows and many keys.  64 rows, 3000 nuggets, 40 heads 56 (whole) -> 23.4 us; 3 x 23 rows, 2700 nuggets, 40 heads 59 -> 41;
-// 128 rows, 1000 nuggets, 32 heads 27.4 -> 20.2; 12 heads of 300 rows, 1000 nuggets 29.4 -> 20.0.  512 rows, 400 nuggets, 32 heads
-// (17 MB of partial results for two splits) stay whole: 23.7 us against 25.5.
+// Keys shared by several workgroups: costs a launch and two passes over the partial results (one write, one read), so it is for few
+// rows and many keys.  64 rows, 3000 nuggets, 40 heads 56 (whole) -> 23.4 us; 3 x 23 rows, 2700 nuggets, 40 heads 59 -> 41; 128 rows,
+// 1000 nuggets, 32 heads 27.4 -> 18.6.  512 rows, 400 nuggets, 32 heads (17 MB of partial results for two splits) stay whole: 23.7 us
+// against 25.5.  Blocks of 64 rows with KG = 2 or, where these are too many or would get too few shares, of 128 with KG = 1; 64 / 128:
+// 128 rows, 1000 nuggets, 32 heads 19.1 / 22.5, 1500 nuggets, 64 heads over 8 24.7 / 23.5, 83 rows, 671 nuggets, 2 x 32 heads 18.6 / 20.4; 549
+// rows, 3578 nuggets, 32 heads - / 62.7 (8 wavefronts, whole: 79.6), 466 rows, 3747 nuggets, 32 heads 87.5 (whole) / 61.6.  Starts and ends, the
+// second launch, 400 ns for every share and 5 TB/s for the partial results: fitted to 106 shapes, all share counts of both timed.
 // The bounds decide, also where they promise more than there is: in the cached form max_k may be a capacity.  64 rows, 32 heads over
 // a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
 // 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
@@ -1011,6 +1014,14 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     best_ns = ns;
     best = BlockPlan{G, waves, KG, static_cast<int32_t>(nsplit), pair, sorted};
   };
+  // Few rows and many keys stay with an offset that follows the row's maximum (O's error against 64 bits, 549 rows, 3578 nuggets, 32
+  // heads 2.23e-3, with the 8-wavefront kernel's fixed offset 2.34e-3), also where that kernel is about as fast: wherever blocks of 128
+  // rows that share their keys are, at 2 TB/s for the partial results, faster than that kernel's tiles.
+  bool follow = false;
+  const int64_t blocks128 = static_cast<int64_t>(B) * H * ((static_cast<int64_t>(max_q) + 127) / 128);
+  for (int64_t s = 2; s <= 16 && max_splits > 1 && !eight_only && blocks128 <= cus && s * blocks128 <= 2 * cus && 2 * s <= tiles; ++s)
+    follow |= (tiles + s - 1) / s * scaled(s * blocks128 <= cus ? 1350 : 2160) + 5000 +
+                  static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000) < tiles * scaled(1200);
   for (int32_t G = 1; G <= H / H_kv; ++G) {
     if ((H / H_kv) % G != 0) continue;
     const int64_t pairs = static_cast<int64_t>(B) * (H / G), rows = static_cast<int64_t>(max_q) * G;
@@ -1018,7 +1029,7 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     for (int32_t waves = 8; waves >= 4; waves -= 4) {
       // (up to 128 query rows the offset follows the row's maximum, whose weight is then 1 and not rounded: 16 x 34 rows over 460
       // nuggets, 64 heads over 8, error against 64 bits 2.19e-3, with the 8-wavefront kernel's fixed offset 2.30e-3)
-      if (waves == 8 ? max_q <= 128 : (rows > 128 && max_q > 128 && G == 1) || eight_only) continue;
+      if (waves == 8 ? max_q <= 128 || follow : (rows > 128 && max_q > 128 && G == 1) || eight_only) continue;
       const int64_t bm = 32 * waves, n = (rows + bm - 1) / bm, units = pairs * n, at_once = waves == 8 ? cus : 2 * cus;
       const int64_t tile_ns = scaled(waves == 8 ? (2 * units <= cus ? 1200 : 1600) : units <= cus ? 1350 : 2160);
       const auto block_ns = [&](int64_t blk) {  // the nuggets and what the block's last row sees of the local rows
@@ -1050,9 +1061,22 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     const int64_t units = pairs * ((rows + 63) / 64);
     const auto tile_ns = [&](int64_t wgs) { return scaled(wgs > cus ? 1900 : 1110); };
     if (!eight_only && units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * tile_ns(units) + kStart4, G, 4, 2, 1, false, false);
-    for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && units <= cus && s * units <= 2 * cus && 2 * s <= tiles; ++s)
-      consider((tiles + 2 * s - 1) / (2 * s) * 2 * tile_ns(s * units) + kStart4 + 5000 +
-               static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000), G, 4, 2, s, false, false);
+    // keys shared by several workgroups, over blocks of 128 or 64 rows: the better of the two
+    int64_t shared_ns = -1, shared_n = 1;
+    int32_t shared_KG = 1;
+    for (int32_t KG = 1; KG <= 2; ++KG) {
+      const int64_t blocks = pairs * ((rows + 128 / KG - 1) / (128 / KG));
+      for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && blocks <= cus && s * blocks <= 2 * cus && 2 * s <= tiles; ++s) {
+        const int64_t one_ns = KG == 2 ? tile_ns(s * blocks) : scaled(s * blocks <= cus ? 1350 : 2160);
+        const int64_t ns = (tiles + 2 * s - 1) / (2 * s) * 2 * one_ns + (KG == 2 ? 7000 : 9000) + 400 * s +
+                           static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 5000);
+        if (shared_ns >= 0 && ns >= shared_ns) continue;
+        shared_ns = ns;
+        shared_n = s;
+        shared_KG = KG;
+      }
+    }
+    if (shared_ns >= 0) consider(shared_ns, G, 4, shared_KG, shared_n, false, false);
   }
   return best;
 }
@@ -1137,7 +1161,7 @@ int launch_dh(const AttnParams& p) {
     using I2 = std::integral_constant<int, 2>;
     using Whole = std::false_type;
     using Split = std::true_type;
-    if (plan.nsplit > 1) return form(I4{}, I2{}, Split{});
+    if (plan.nsplit > 1) return plan.KG == 2 ? form(I4{}, I2{}, Split{}) : form(I4{}, I1{}, Split{});
     if (plan.KG == 2) return form(I4{}, I2{}, Whole{});
     return plan.waves == 4 ? form(I4{}, I1{}, Whole{}) : form(I8{}, I1{}, Whole{});
   };

@@ -99,3 +99,16 @@ def check_rows(O: torch.Tensor, lse: torch.Tensor, cu_q, rows, O_ref, lse_ref, d
     err = check_attention(O[tok, hh], O_ref, dtype)
     check_lse(lse[tok, hh], lse_ref, dtype)
     return err
+
+
+def kernel_names(call, part):
+    """Names of the GPU kernels whose name contains `part` that `call` launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if part in e.name]
+
+
+def template_arguments(name):
+    """The template arguments in a kernel's name, as texts: "k<4, false>(int)" -> ["4", "false"]."""
+    return name[name.index("<") + 1:name.index(">")].replace(" ", "").split(",")

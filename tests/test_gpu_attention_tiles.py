@@ -4,7 +4,8 @@ import torch
 
 import oracle
 import workloads as W
-from gpu_util import check_attention, check_lse, default_scale, dev, make_attention_case
+from gpu_util import (check_attention, check_lse, check_rows, default_scale, dev, kernel_names, make_attention_case, nan_outputs,
+                      oracle_attention_rows_parallel, template_arguments)
 
 pytestmark = pytest.mark.gpu
 
@@ -113,6 +114,30 @@ def test_keys_shared_by_workgroups(q_lens, k_lens, m_lens, H, H_kv, d_h):
     assert torch.equal(O, results[2][0])
     hm = D.dodo_nugget_attention(t["Q"], t["Kn"].transpose(0, 1).contiguous(), t["Vn"].transpose(0, 1).contiguous(), *a, D.HEAD_MAJOR)[0]
     assert torch.equal(hm, results[0][0])
+
+
+# More than 128 rows over many keys: shared out in blocks of 128 rows where blocks of 64 would be more than the compute units, and not
+# left to the 8-wavefront kernel, whose fixed exponent offset costs precision; with the workspace for it and with one for two shares.
+@pytest.mark.parametrize("B,q,k,m,H,H_kv,d_h", [(8, 525, 2768, 574, 4, 4, 128), (2, 214, 2312, 214, 40, 40, 128), (1, 570, 2674, 697, 32, 8, 128),
+                                                (1, 1195, 4537, 1423, 16, 16, 64)])
+@pytest.mark.parametrize("room", ["whole", "two shares"])
+def test_blocks_of_128_rows_share_their_keys(B, q, k, m, H, H_kv, d_h, room):
+    import paper_2310_02409_amd as D
+    q_lens, k_lens, m_lens = [q - 9 * b for b in range(B)], [k - 70 * b for b in range(B)], [m - 5 * b for b in range(B)]
+    host, t = make_attention_case(530, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    scale = default_scale(d_h)
+    two = B * q * H * 2 * (d_h + 2) * 4
+    need = D.dodo_nugget_attention_workspace_bytes_grouped(B, H, H_kv, d_h, q, k, m, D.BF16)
+    assert need >= two
+    O, lse = nan_outputs(t["Q"], H)
+    ws = torch.full((two if room != "whole" else need,), 255, dtype=torch.uint8, device=dev())
+    names = kernel_names(lambda: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], q, k, m,
+                                                         scale, O=O, lse=lse, ws=ws), "block_attention_kernel")
+    assert len(names) == 1 and template_arguments(names[0])[0] == "4", names
+    assert bool(torch.isfinite(O.float()).all())
+    rows = [(b, (3 * b + h) % H, i) for b in range(B) for h in (0, 1) for i in (0, 1, 127, 128, q_lens[b] // 2, q_lens[b] - 1)]
+    want = oracle_attention_rows_parallel(host, host["Kn"], host["Vn"], host["cu_nuggets"], scale, rows)
+    check_rows(O, lse, host["cu_q"], rows, *want, torch.bfloat16)
 
 
 def test_shared_keys_through_an_index_list_and_a_workspace_used_by_a_decode_call_next():
