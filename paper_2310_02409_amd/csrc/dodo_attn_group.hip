@@ -661,24 +661,25 @@ int64_t most_splits(const AttnParams& p) { return p.d_h == 128 ? GroupDims<128, 
 // Units run their workgroups side by side and at the same pace, so while some have a workgroup more than the others they go on
 // alone with it: 264 workgroups take as long as 512 (33 sequences over 8 KV heads, 1897 rows, whole / in two / three / four:
 // 63.5 / 57.8 / 54.0 / 53.4 us; 667 rows 28.0 / 28.6 / 27.1 / 27.4, where 24 sequences take 16.9 whole and 20.8 in two).
-// Merging costs 5 us (up to five splits; 7 beyond): 8 sequences, 1897 rows 27.9 whole, 20.9 / 20.1 / 18.7 in 2 / 3 / 4, 24.1 in 8;
-// 667 rows 10.6 whole, 11.1 in two; 2 sequences, 1897 rows 19.8 / 15.5 / 14.5 / 12.7 in 1 / 2 / 3 / 4, 13.4 in 8.
-int64_t wanted_splits(const AttnParams& p) {
+// Merging costs 5 us (up to five splits; beyond, 6 and 0.3 for every one over four): 8 sequences, 1897 rows 27.9 whole, 20.9 / 20.1 /
+// 18.7 in 2 / 3 / 4, 24.1 in 8; 667 rows 10.6 whole, 11.1 in two; 2 sequences, 1897 rows 19.8 / 15.5 / 14.5 / 12.7 in 1 / 2 / 3 / 4, 13.4
+// in 8, 14.3 in 13.
+struct Wanted {
+  int64_t splits, ns;  // and the time
+};
+Wanted wanted(const AttnParams& p) {
   const int64_t pairs = static_cast<int64_t>(p.B) * p.H_kv, cus = compute_units();
   const int64_t tiles = (static_cast<int64_t>(p.max_k) + kKeys - 1) / kKeys + (static_cast<int64_t>(p.max_local) + kKeys - 1) / kKeys;
   const int64_t most = most_splits(p);
   const int64_t alone_ns = p.d_h == 128 ? 440 : 220, shared_ns = p.d_h == 128 ? 660 : 330;
-  int64_t count = 1, best = 0;
+  Wanted best{1, 0};
   for (int64_t n = 1; n <= most && (n == 1 || (4 * n <= tiles && n * pairs <= 8 * cus)); ++n) {
     const int64_t rounds = (n * pairs + cus - 1) / cus, rest = n * pairs - (rounds - 1) * cus;  // `rest` units have one more
     const int64_t last_ns = std::max(alone_ns, shared_ns * rest / cus);
-    const int64_t t = (tiles + n - 1) / n * ((rounds - 1) * shared_ns + last_ns) + (n == 1 ? 0 : n <= 5 ? 5000 : 7000);
-    if (n == 1 || t < best) {
-      best = t;
-      count = n;
-    }
+    const int64_t t = (tiles + n - 1) / n * ((rounds - 1) * shared_ns + last_ns) + (n == 1 ? 0 : n <= 5 ? 5000 : 6000 + 300 * (n - 4));
+    if (n == 1 || t < best.ns) best = Wanted{n, t};
   }
-  return count;
+  return best;
 }
 
 // Splits that the caller's workspace has records for (none if it is not 8-byte aligned: records are read in 8-byte words).
@@ -700,7 +701,7 @@ int64_t routing_splits(const AttnParams& p, int64_t fit) {
   const int64_t rows = static_cast<int64_t>(p.max_k) + p.max_local, wanted = ((pairs >= cus ? 2 * cus : cus) + pairs - 1) / pairs;
   return std::max<int64_t>(1, std::min({wanted, rows / (8 * kKeys), most_splits(p), fit}));
 }
-int group_split_count(const AttnParams& p) { return static_cast<int>(std::max<int64_t>(1, std::min(wanted_splits(p), splits_that_fit(p)))); }
+int group_split_count(const AttnParams& p) { return static_cast<int>(std::max<int64_t>(1, std::min(wanted(p).splits, splits_that_fit(p)))); }
 
 }  // namespace
 
@@ -708,7 +709,7 @@ size_t group_workspace_bytes(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, in
                              int32_t max_local) {
   AttnParams p{};
   p.B = B; p.H = H; p.H_kv = H_kv; p.d_h = d_h; p.max_q = max_q; p.max_k = max_k; p.max_local = max_local;
-  const int64_t n = std::max(wanted_splits(p), routing_splits(p, most_splits(p)));
+  const int64_t n = std::max(wanted(p).splits, routing_splits(p, most_splits(p)));
   return n <= 1 ? 0 : static_cast<size_t>(B) * max_q * H * static_cast<size_t>(n) * (d_h + 3) * sizeof(float);
 }
 
@@ -734,14 +735,20 @@ bool group_attention_applies(const AttnParams& p) {
   const int64_t fit = splits_that_fit(p);
   if (static_cast<int64_t>(p.B) * p.H_kv * routing_splits(p, fit) * 2 >= compute_units()) return true;
   // ... or, where the narrow tiles hold all vectors and the workspace every wanted split, enough vectors times rows for the
-  // split-K kernel, which works on each of them, to be the slower one.  64 heads over 8, split-K / this kernel: 4 x 357 rows
-  // (91 thousand) 7.1 / 7.7 us, 2 x 667 (85) 9.8 / 9.9, 4 x 667 (171) 10.3 / 10.5, 6 x 357 (137) 10.4 / 7.9, 8 x 357 (183) 10.7 / 8.2, 2 x 1897
-  // (243) 14.8 / 14.2; 32 over 8: 2 x 1897 (121) 11.4 / 12.8, 12 x 357 (137) 11.5 / 8.4.
+  // split-K kernel, which works on each of them, to be the slower one.  It takes 4.5 us and 7.3 ns (5.3 for heads of 64 channels) for
+  // each row of a workgroup's share and each workgroup that a compute unit gets, and 2 more where the shares are merged; this kernel 1.5 beyond
+  // the time above, or 2.3 with several splits.  64 heads over 8, split-K / this kernel: 4 x 357 rows 7.1 / 7.7 us, 4 x 579 9.3 / 9.4,
+  // 4 x 667 9.3 / 10.1, 2 x 1099 11.3 / 10.0, 5 x 454 11.5 / 8.5, 6 x 357 9.8 / 6.6, 13 x 204 11.4 / 5.8; 40 over 8, 2 x 1887 12.0 / 13.7; 32 over 8, 7 x
+  // 687 10.4 / 10.9; 32 over 4, 9 x 627 15.6 / 9.8, heads of 64 2 x 3168 11.1 / 13.5, 5 x 1242 9.5 / 8.8.  (Below 128 Ki of vectors times rows little is won.)
   // (One query row per sequence only: rows that a vector does not see are not read there.)
   const int64_t vectors = static_cast<int64_t>(p.H) * p.max_q, rows = static_cast<int64_t>(p.max_k) + p.max_local;
-  if (p.max_q > 1 || vectors > 16 * static_cast<int64_t>(p.H_kv) || std::max<int64_t>(1, fit) < wanted_splits(p) || vectors * p.B * rows < 128 * 1024) return false;
+  const Wanted here = wanted(p);
+  if (p.max_q > 1 || vectors > 16 * static_cast<int64_t>(p.H_kv) || std::max<int64_t>(1, fit) < here.splits || vectors * p.B * rows < 128 * 1024) return false;
+  const int64_t shares = splitk_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.dtype), cus = compute_units();
+  const int64_t splitk_ns = 4500 + (rows + shares - 1) / shares * (p.d_h == 128 ? 73 : 53) / 10 * ((vectors * p.B * shares + cus - 1) / cus) + (shares > 1 ? 2000 : 0);
+  if (here.ns + (here.splits > 1 ? 2300 : 1500) > splitk_ns) return false;
   // (a call that the split-K kernel refuses for want of a workspace is refused whichever kernel would take it)
-  const int64_t records = vectors * p.B * splitk_count(p.B, p.H, p.d_h, p.max_q, p.max_k, p.max_local, p.dtype);
+  const int64_t records = vectors * p.B * shares;
   return records == vectors * p.B || rows < 512 || p.ws_flags != nullptr ||
          (p.ws != nullptr && p.ws_bytes >= static_cast<size_t>(records) * splitk_record_bytes(p.d_h));
 }

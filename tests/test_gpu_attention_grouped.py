@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import workloads as W
-from gpu_util import check_attention, check_lse, default_scale, dev, make_attention_case, nan_outputs
+from gpu_util import check_attention, check_lse, default_scale, dev, kernel_names, make_attention_case, nan_outputs
 
 pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
@@ -246,8 +246,8 @@ def test_infinite_value_in_a_visible_row(D):
     assert torch.equal(O, want)
 
 
-# A small batch with one query row each goes from the split-K kernel to this one where its vectors and rows are many; the line
-# lies at 128 Ki of their products.  Both sides have the same precision.
+# A small batch with one query row each goes from the split-K kernel to this one where its vectors and rows are many (128 Ki of their
+# products) and this one is the faster.  Both sides have the same precision.
 @pytest.mark.parametrize("k", [200, 480, 500, 1500])
 def test_small_batches_on_either_side_of_the_line(D, k):
     B, H, H_kv, d_h = 4, 64, 8, 128
@@ -260,3 +260,23 @@ def test_small_batches_on_either_side_of_the_line(D, k):
     check_lse(lse, lse_want, BF)
     err = O.float().cpu().double().numpy().reshape(want.shape) - want
     assert np.linalg.norm(err) <= 1.9e-3 * np.linalg.norm(want)
+
+
+# Which kernel takes a small batch with one query row each: this one where the split-K kernel's workgroups are more than the compute units
+# or its shares long, that one where its workgroups come out even or this one would merge many splits.
+@pytest.mark.parametrize("B,rows,H,H_kv,d_h,kernel", [
+    (4, 357, 64, 8, 128, "splitk"), (6, 357, 64, 8, 128, "group"), (4, 667, 64, 8, 128, "splitk"), (5, 454, 64, 8, 128, "group"),
+    (2, 1887, 40, 8, 128, "splitk"), (2, 1099, 64, 8, 128, "group"), (7, 687, 32, 8, 128, "splitk"), (2, 3168, 32, 4, 64, "splitk"),
+    (9, 1508, 16, 2, 64, "group"),
+])
+def test_kernel_of_a_small_batch(D, B, rows, H, H_kv, d_h, kernel):
+    k, m = rows - 20, 20
+    host, t = make_attention_case(850, [1] * B, [k] * B, [m] * B, H, H_kv, d_h, BF, dev())
+    out = []
+    names = kernel_names(lambda: out.extend(D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"],
+                                                                    1, k, m, want_lse=True)), "attention_kernel")
+    assert len(names) == 1 and kernel + "_attention_kernel" in names[0], names
+    want, lse_want = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                                      host["cu_local"], default_scale(d_h))
+    check_attention(out[0], want, BF)
+    check_lse(out[1], lse_want, BF)
