@@ -116,21 +116,22 @@ __device__ __forceinline__ float vector_sum(float x) {
 
 // Online-softmax update for one 32-key tile.  acc holds the raw S^T accumulators: register v <-> key 8 (v / 4) + 4 g + v % 4
 // (NV = 32, g = lane / 32) or 16 (v / 4) + 4 g + v % 4 (NV = 16, g = lane / 16).  MASK: keys at or beyond `limit` are masked.
-// Returns P^T as the MFMA B operands (NV = 32: k-step t covers keys 16t .. 16t+15) in two parts: the weights' upper 8 bits of
-// mantissa, and what they lack, in bf16 again.  With both they count with 16 bits, and O's error is that of its own rounding to
-// bf16, as in the split-K kernel, which keeps them in single precision (2-norm against 64 bits 1.65e-3; 2.1e-3 to 2.3e-3 with
-// weights rounded to bf16); the matrix pipe, which is idle three quarters of the time here, does twice the work for V (64
-// sequences of 667 rows, 64 heads over 8: 32.4 -> 33.3 us).  Neither part of a weight is negative, nor zero unless the weight is:
-// with an infinity in V their products are that infinity.
+// Returns P^T as the MFMA B operands (NV = 32: k-step t covers keys 16t .. 16t+15) in PARTS parts: the weights' upper 8 bits of
+// mantissa, and what they lack, in bf16 again.  With two they count with 16 bits, and O's error is that of its own rounding to
+// bf16 (2-norm against 64 bits 1.66e-3; 2.1e-3 to 2.3e-3 with weights rounded to bf16); the matrix pipe, which is idle three
+// quarters of the time here, does twice the work for V (64 sequences of 667 rows, 64 heads over 8: 32.4 -> 33.3 us).  With three they
+// are whole, as in the split-K kernel: calls that come here only to be faster than there have these (with two, one value of O in 250
+// rounded to another neighbour than the 64-bit result does, with three one in 6000, as there; 6 sequences of 357 rows, 64 heads over 8
+// 6.6 -> 6.7 us, 14 of 457 9.2 -> 9.6).  No part of a weight is negative, nor zero unless the weight is: with an
+// infinity in V their products are that infinity.
 // The exponent offset m_run of a vector is moved (and its sum and output accumulators rescaled) only when the tile's
 // maximum exceeds it by more than kSlack: the result does not depend on the offset, the weights stay below
 // 2^kSlack, and after the first tiles of a vector the output accumulators are hardly ever touched again (the rescale is
 // a wavefront-uniform branch: taken if any vector of the wavefront moves).
 constexpr float kSlack = 8.f;
-template <bool MASK, int NV, int CB, int REGS>
+template <bool MASK, int NV, int CB, int REGS, int PARTS>
 __device__ __forceinline__ void softmax_tile32(float (&acc)[REGS], int limit, int g, float scale_log2e, float& m_run,
-                                               float& l_run, typename Mfma<NV>::Acc (&acc_o)[CB], bf16x8 (&pf)[REGS / 8],
-                                               bf16x8 (&pf_low)[REGS / 8]) {
+                                               float& l_run, typename Mfma<NV>::Acc (&acc_o)[CB], bf16x8 (&pf)[PARTS][REGS / 8]) {
   float tmax = kNegInf;
 #pragma unroll
   for (int v = 0; v < REGS; ++v) {
@@ -159,26 +160,34 @@ __device__ __forceinline__ void softmax_tile32(float (&acc)[REGS], int limit, in
 #pragma unroll
   for (int half = 0; half < REGS / 8; ++half) {
     floatx8 low;
-    uint32_t high[4];
+    uint32_t high[PARTS - 1][4];
 #pragma unroll
     for (int v = 0; v < 8; v += 2) {
       const float p0 = exp2_hw(acc[8 * half + v] - m_use), p1 = exp2_hw(acc[8 * half + v + 1] - m_use);
       psum += p0;
       psum += p1;
-      const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-      high[v / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);  // the upper halves: rounded towards zero
-      low[v] = __builtin_amdgcn_fmed3f(p0 - __uint_as_float(b0 & 0xffff0000u), 1e-30f, p0);
-      low[v + 1] = __builtin_amdgcn_fmed3f(p1 - __uint_as_float(b1 & 0xffff0000u), 1e-30f, p1);
+      float r0 = p0, r1 = p1;
+#pragma unroll
+      for (int part = 0; part < PARTS - 1; ++part) {
+        const uint32_t b0 = __float_as_uint(r0), b1 = __float_as_uint(r1);
+        high[part][v / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);  // the upper halves: rounded towards zero
+        r0 = __builtin_amdgcn_fmed3f(r0 - __uint_as_float(b0 & 0xffff0000u), 1e-30f, p0);
+        r1 = __builtin_amdgcn_fmed3f(r1 - __uint_as_float(b1 & 0xffff0000u), 1e-30f, p1);
+      }
+      low[v] = r0;
+      low[v + 1] = r1;
     }
-    pf[half] = __builtin_bit_cast(bf16x8, make_uint4(high[0], high[1], high[2], high[3]));
-    pf_low[half] = __builtin_convertvector(low, bf16x8);  // hardware round-to-nearest-even pack
+#pragma unroll
+    for (int part = 0; part < PARTS - 1; ++part)
+      pf[part][half] = __builtin_bit_cast(bf16x8, make_uint4(high[part][0], high[part][1], high[part][2], high[part][3]));
+    pf[PARTS - 1][half] = __builtin_convertvector(low, bf16x8);  // hardware round-to-nearest-even pack
   }
   l_run += psum;
 }
 
-// NWV wavefronts per workgroup; STREAM: K/V rows with the non-temporal hint; NV: width of the MFMA tiles.  Grid: (KV head,
-// sequence, split).
-template <int DH, int NWV, bool STREAM, int NV>
+// NWV wavefronts per workgroup; STREAM: K/V rows with the non-temporal hint; NV: width of the MFMA tiles; PARTS: of a weight.
+// Grid: (KV head, sequence, split).
+template <int DH, int NWV, bool STREAM, int NV, int PARTS>
 __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
@@ -381,20 +390,18 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
     float sv[kRegs];
 #pragma unroll
     for (int v = 0; v < kRegs; ++v) sv[v] = acc_s[v / Mfma<NV>::kRegs][v % Mfma<NV>::kRegs];
-    bf16x8 pf[kRegs / 8], pf_low[kRegs / 8];
+    bf16x8 pf[PARTS][kRegs / 8];
     if (__all(limit >= kKeys)) {
-      softmax_tile32<false, NV>(sv, limit, g, scale_log2e, m_run, l_run, acc_o, pf, pf_low);
+      softmax_tile32<false, NV>(sv, limit, g, scale_log2e, m_run, l_run, acc_o, pf);
     } else {
-      softmax_tile32<true, NV>(sv, limit, g, scale_log2e, m_run, l_run, acc_o, pf, pf_low);
+      softmax_tile32<true, NV>(sv, limit, g, scale_log2e, m_run, l_run, acc_o, pf);
     }
 #pragma unroll
-    for (int t = 0; t < GD::kPvSteps; ++t)
+    for (int part = 0; part < PARTS; ++part)
 #pragma unroll
-      for (int cb = 0; cb < kCB; ++cb) acc_o[cb] = Mfma<NV>::mul(vt[t][cb], pf[t], acc_o[cb]);
+      for (int t = 0; t < GD::kPvSteps; ++t)
 #pragma unroll
-    for (int t = 0; t < GD::kPvSteps; ++t)
-#pragma unroll
-      for (int cb = 0; cb < kCB; ++cb) acc_o[cb] = Mfma<NV>::mul(vt[t][cb], pf_low[t], acc_o[cb]);
+        for (int cb = 0; cb < kCB; ++cb) acc_o[cb] = Mfma<NV>::mul(vt[t][cb], pf[part][t], acc_o[cb]);
   }
 
   // ---- the wavefronts' partials meet in LDS: [vector][channel] floats, then m and l per vector ----
@@ -611,10 +618,10 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
   }
 }
 
-template <int DH, int NWV, bool STREAM, int NV>
+template <int DH, int NWV, bool STREAM, int NV, int PARTS>
 int launch_nwv(const AttnParams& p, int row0, int rows_per, int nsplit, uint32_t* flags) {
   constexpr int kLds = NWV * GroupDims<DH, NV>::kWaveLds + GroupDims<DH, NV>::kQBytes;
-  const auto kernel = &group_attention_kernel<DH, NWV, STREAM, NV>;
+  const auto kernel = &group_attention_kernel<DH, NWV, STREAM, NV, PARTS>;
   const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), kLds);
   if (rc != DODO_OK) return rc;
   const int G = p.H / p.H_kv;
@@ -629,12 +636,12 @@ int launch_nwv(const AttnParams& p, int row0, int rows_per, int nsplit, uint32_t
   return launch_status();
 }
 
-template <int DH, int NV>
+template <int DH, int NV, int PARTS>
 int launch_dh(const AttnParams& p, bool two, bool stream, int row0, int rows_per, int nsplit, uint32_t* flags) {
   if (stream) {
-    return two ? launch_nwv<DH, 2, true, NV>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, true, NV>(p, row0, rows_per, nsplit, flags);
+    return two ? launch_nwv<DH, 2, true, NV, PARTS>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, true, NV, PARTS>(p, row0, rows_per, nsplit, flags);
   }
-  return two ? launch_nwv<DH, 2, false, NV>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, false, NV>(p, row0, rows_per, nsplit, flags);
+  return two ? launch_nwv<DH, 2, false, NV, PARTS>(p, row0, rows_per, nsplit, flags) : launch_nwv<DH, 4, false, NV, PARTS>(p, row0, rows_per, nsplit, flags);
 }
 
 // Whether the K/V rows are requested with the non-temporal hint: where the call reads them once and they are more than a quarter
@@ -701,6 +708,10 @@ int64_t routing_splits(const AttnParams& p, int64_t fit) {
   const int64_t rows = static_cast<int64_t>(p.max_k) + p.max_local, wanted = ((pairs >= cus ? 2 * cus : cus) + pairs - 1) / pairs;
   return std::max<int64_t>(1, std::min({wanted, rows / (8 * kKeys), most_splits(p), fit}));
 }
+// Whether that is one for every other compute unit at least.
+bool fills_units(const AttnParams& p, int64_t fit) {
+  return static_cast<int64_t>(p.B) * p.H_kv * routing_splits(p, fit) * 2 >= compute_units();
+}
 int group_split_count(const AttnParams& p) { return static_cast<int>(std::max<int64_t>(1, std::min(wanted(p).splits, splits_that_fit(p)))); }
 
 }  // namespace
@@ -733,7 +744,7 @@ bool group_attention_applies(const AttnParams& p) {
     return false;
   // a workgroup for every other compute unit ...
   const int64_t fit = splits_that_fit(p);
-  if (static_cast<int64_t>(p.B) * p.H_kv * routing_splits(p, fit) * 2 >= compute_units()) return true;
+  if (fills_units(p, fit)) return true;
   // ... or, where the narrow tiles hold all vectors and the workspace every wanted split, enough vectors times rows for the
   // split-K kernel, which works on each of them, to be the slower one.  It takes 4.5 us and 7.3 ns (5.3 for heads of 64 channels) for
   // each row of a workgroup's share and each workgroup that a compute unit gets, and 2 more where the shares are merged; this kernel 1.5 beyond
@@ -769,13 +780,17 @@ int launch_group_attention(const AttnParams& p) {
   const bool two = wgs > cus && (nsplit > 1 || !narrow_all || 2 * wgs < 5 * cus);
   const int rows_per = kMaxVectors / (p.H / p.H_kv);
   const bool stream = streams_rows(p, rows_per);
+  const bool whole = !fills_units(p, splits_that_fit(p));  // weights in three parts: a call that the split-K kernel could take
   for (int row0 = 0; row0 < p.max_q; row0 += rows_per) {  // (records and flags of different rows are apart)
     // the narrow tiles where their 16 columns hold the launch's vectors: half of the matrix work, and half of the registers
     const bool narrow = std::min(rows_per, p.max_q - row0) * (p.H / p.H_kv) <= 16;
-    const int rc = p.d_h == 128 ? (narrow ? launch_dh<128, 16>(p, two, stream, row0, rows_per, nsplit, flags)
-                                          : launch_dh<128, 32>(p, two, stream, row0, rows_per, nsplit, flags))
-                                : (narrow ? launch_dh<64, 16>(p, two, stream, row0, rows_per, nsplit, flags)
-                                          : launch_dh<64, 32>(p, two, stream, row0, rows_per, nsplit, flags));
+    const auto launch = [&](auto dh_tag) {
+      constexpr int DH = decltype(dh_tag)::value;
+      return !narrow ? launch_dh<DH, 32, 2>(p, two, stream, row0, rows_per, nsplit, flags)
+             : whole ? launch_dh<DH, 16, 3>(p, two, stream, row0, rows_per, nsplit, flags)
+                     : launch_dh<DH, 16, 2>(p, two, stream, row0, rows_per, nsplit, flags);
+    };
+    const int rc = p.d_h == 128 ? launch(std::integral_constant<int, 128>{}) : launch(std::integral_constant<int, 64>{});
     if (rc != DODO_OK) return rc;
   }
   return DODO_OK;

@@ -280,3 +280,34 @@ def test_kernel_of_a_small_batch(D, B, rows, H, H_kv, d_h, kernel):
                                       host["cu_local"], default_scale(d_h))
     check_attention(out[0], want, BF)
     check_lse(out[1], lse_want, BF)
+
+
+# Small batches that come here from the split-K kernel keep weights of 24 bits.  O is then off by a few 1e-7 of itself before it is rounded
+# to bf16, whose neighbours are 2^-8 to 2^-7 apart: about one value in 5000 rounds to another neighbour than the 64-bit result (1.2e-4 to
+# 3.3e-4 in the split-K kernel too); with weights of 16 bits, off by up to 2^-17, it is one in 250.
+@pytest.mark.parametrize("B,k,m,H,H_kv,d_h", [(6, 300, 57, 64, 8, 128), (13, 200, 40, 64, 8, 128), (2, 1000, 99, 64, 8, 128), (9, 1450, 50, 16, 2, 64),
+                                              (10, 500, 5, 32, 4, 64)])
+def test_weights_of_a_small_batch_are_whole(D, B, k, m, H, H_kv, d_h):
+    host, t = make_attention_case(860, [1] * B, [k] * B, [m] * B, H, H_kv, d_h, BF, dev())
+    want, _ = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
+                               host["cu_local"], default_scale(d_h))
+    O = D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 1, k, m)[0]
+    check_attention(O, want, BF)
+    other = (O.cpu() != torch.from_numpy(want).to(BF).reshape(O.shape)).double().mean().item()
+    assert other <= 1e-3, other
+
+
+# An infinity in V with weights in three parts, one of them far below the others.
+def test_infinite_value_in_a_visible_row_of_a_small_batch(D):
+    B, k, m, H, H_kv, d_h = 6, 300, 57, 64, 8, 128
+    host, t = make_attention_case(861, [1] * B, [k] * B, [m] * B, H, H_kv, d_h, BF, dev())
+    t["Kn"][k * 3 + 50, 2] = -8 * t["Q"][3, 2 * 8]  # a logit far below the rest, for the first of the heads
+    run = lambda: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"], 1, k, m)[0]
+    want = run()
+    t["Vn"][k * 3 + 50, 2, 7] = float("inf")
+    t["Vl"][m * 5 + 11, 0, 64] = float("-inf")
+    O = run()
+    want[3, 17:24, 7] = float("inf")
+    want[5, 0:8, 64] = float("-inf")
+    O[3, 16, 7] = want[3, 16, 7]  # (its weight may have underflowed to zero: 0 x inf)
+    assert torch.equal(O, want)
