@@ -717,7 +717,7 @@ struct MlpPlan {
   }
 };
 constexpr int kBigRound = 100, kSmallHalves = 32, kSmallOne = 45, kSmallTwo = 60;
-// Tiles of 64 tokens: 1 (32 hidden units, two workgroups per compute unit), 2 (64, one) or 3 (64, two); 0: more than one round of them.
+// Tiles of 64 tokens: 1 (32 hidden units, at most one workgroup per compute unit), 2 (64, one) or 3 (64, two); 0: more than one round of them.
 constexpr int kSomeCost[4] = {0, 12, 16, 20};
 int some_tiles(int64_t n, int32_t d, int32_t d_hid) {
   const int64_t cus = compute_units(), tiles = (n + kSomeTok - 1) / kSomeTok;
@@ -737,7 +737,8 @@ size_t some_most_bytes(int64_t N, int32_t d, int32_t d_hid) {
     most = std::max(most, some_bytes(std::min(N, tiles * kSomeTok), d, d_hid));
   return most;
 }
-MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid) {
+// (some: with tiles of 64 tokens)
+MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid, bool some = true) {
   const int cus = compute_units(), cus_xcd = cus >= 8 ? cus / 8 : 1;
   const int tiles = d_hid / MlpBig::kHid, small_tiles = d_hid / MlpSmall::kHid;
   auto small_units = [&](int64_t n) -> int64_t { return (n + MlpSmall::kTok - 1) / MlpSmall::kTok * small_tiles; };
@@ -766,6 +767,7 @@ MlpPlan plan_mlp(int64_t N, int32_t d, int32_t d_hid) {
       best_some = n_some;
     };
     consider(0);
+    if (!some) continue;
     if (some_tiles(rest, d, d_hid) > 0) consider(rest);
     if (small_round > 0 && rest > small_round && some_tiles(rest % small_round, d, d_hid) > 0) consider(rest % small_round);
   }
@@ -821,7 +823,7 @@ extern "C" size_t dodo_score_mlp_workspace_bytes(int dtype, int64_t N, int32_t d
   // room for this N, and for every smaller one as well: a caller may keep the buffer
   const size_t few = static_cast<size_t>(few_splits(d_hid)) * (N < kFewTokens ? N : kFewTokens) * sizeof(float);
   const size_t least = hidden_splits_most_bytes(N, d_hid);
-  const size_t plan = N <= kFewTokens ? 0 : plan_mlp(N, d, d_hid).bytes();
+  const size_t plan = N <= kFewTokens ? 0 : std::max(plan_mlp(N, d, d_hid).bytes(), plan_mlp(N, d, d_hid, false).bytes());
   return std::max({plan, few, least, some_most_bytes(N, d, d_hid)});
 }
 
@@ -858,6 +860,9 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
       return launch_status();
     }
     MlpPlan p = plan_mlp(N, d, d_hid);
+    // a buffer that was sized for another number of tokens may hold the plan without tiles of 64 tokens though not this one (d = 4096,
+    // 6348 tokens in the buffer of 6793 228 us in the last form, 224 so; d = 2048, 6165 in that of 6987 127 / 123), or neither
+    if (room < p.bytes()) p = plan_mlp(N, d, d_hid, false);
     if (room < p.bytes()) {
       p = MlpPlan{N, hidden_splits(N, d_hid), 0, 0, false, 0, 0};
       if (room < p.bytes()) return DODO_ERR_WORKSPACE_TOO_SMALL;

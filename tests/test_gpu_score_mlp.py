@@ -100,6 +100,20 @@ def test_workspace_kept_for_fewer_tokens(D, most):
             _check(got[rows], oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 0))
 
 
+# a buffer sized for more tokens may be too small for the plan with tiles of 64 tokens: the plan without them is next (big tiles in eight
+# splits, which fill whole rounds), and not big tiles in as many splits as there are hidden tiles
+@pytest.mark.parametrize("most,N", [(6987, 6165), (8054, 6226)])
+def test_workspace_too_small_for_tiles_of_64_tokens(D, most, N):
+    d, dh = 2048, 4096
+    x, W1, b1, w2 = _case(992, N, d, dh, torch.bfloat16)
+    t = [v.to(dev()) for v in (x, W1, b1, w2)]
+    ws = torch.full((D.dodo_score_mlp_workspace_bytes(D.BF16, most, d, dh),), 255, dtype=torch.uint8, device=dev())
+    got = D.dodo_score_mlp(*t, ws=ws).cpu().numpy()
+    rows = np.unique(np.r_[0:20, 4090:4100, N - 20:N])
+    _check(got[rows], oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 0))
+    assert not torch.all(ws[7 * N * 4:8 * N * 4] == 255) and torch.all(ws[8 * N * 4:] == 255)
+
+
 @pytest.mark.parametrize("N,dh", [(1, 256), (16, 256), (40, 5120), (70, 256)])
 def test_infinite_channel_saturates(D, N, dh):
     # tanh of an infinite hidden unit is 1 or -1: the score stays finite, also where a workgroup's share of the hidden units
