@@ -5,7 +5,7 @@
 // The paper does not name the activation; ReLU, GELU (erf form) and tanh are
 // offered.  2 N d d_hid flop: a dense contraction, so it runs on the matrix cores.
 //
-// Up to 20 tokens (bf16, d % 64 == 0, d_hid % 256 == 0; up to 64 where d % 128 != 0):
+// Up to 20 or 28 tokens (bf16, d % 64 == 0, d_hid % 256 == 0; up to 64 where d % 128 != 0):
 // a kernel that streams W1 once over all compute units (score_mlp_few_kernel).  Up to a
 // few hundred: tiles of 64 tokens, several steps in flight (score_mlp_some_kernel).
 //
@@ -361,7 +361,6 @@ __global__ __launch_bounds__(kCombineThreads) void score_mlp_combine_kernel(
 // cost more than W1), against 84 us in the tile kernel, whose 16 workgroups walk over the channels one 64-wide step
 // after the other; d = d_hid = 5120: 17 and 31 against 190 us.
 constexpr int kFewTokens = 64;    // most tokens: four blocks of 16 (beyond, a workgroup re-reads too much of X from L2)
-constexpr int kFewBest = 20;      // beyond, tiles of 64 tokens are faster where they fit
 constexpr int kFewWaves = 8;
 constexpr int kFewRun = 64;       // channels per run
 
@@ -729,6 +728,10 @@ int some_splits(int64_t n, int32_t d, int32_t d_hid) { return d_hid / (some_tile
 size_t some_bytes(int64_t n, int32_t d, int32_t d_hid) {
   return some_tiles(n, d, d_hid) == 0 ? 0 : static_cast<size_t>(some_splits(n, d, d_hid)) * n * sizeof(float);
 }
+// Most tokens for which the kernel for few tokens is the faster one where both fit: 28 where these tiles leave half of the compute units
+// idle with 2048 channels of W1 or more to bring (d = d_hid = 2048, 21 / 28 tokens: 10.6 / 11.2 us there, 11.3 in tiles; 4096: 15.6 /
+// 17.0, 17.3), else 20 (1024, 24 tokens 8.7 against 8.5; 5120, 21 tokens 20.9 against 20.6; 8192 38.4 against 35.9).
+int few_best(int32_t d, int32_t d_hid) { return d >= 2048 && d_hid / 32 * 2 <= compute_units() ? 28 : 20; }
 // the most that these tiles take for any number of tokens up to N
 size_t some_most_bytes(int64_t N, int32_t d, int32_t d_hid) {
   const int64_t cus = compute_units();
@@ -840,7 +843,7 @@ extern "C" int dodo_score_mlp(const void* hidden, const void* W1, const float* b
   if (mfma_path(dtype, N, d, d_hid, row_stride, hidden, W1, b1, w2)) {
     float* partial = static_cast<float*>(ws);
     const size_t room = ws != nullptr ? ws_bytes : 0;
-    const bool some = N > kFewBest && some_tiles(N, d, d_hid) > 0 && room >= some_bytes(N, d, d_hid);  // (then that is the plan)
+    const bool some = N > few_best(d, d_hid) && some_tiles(N, d, d_hid) > 0 && room >= some_bytes(N, d, d_hid);  // (then that is the plan)
     if (N <= kFewTokens && !some && room >= static_cast<size_t>(few_splits(d_hid)) * N * sizeof(float)) {
       const int splits = few_splits(d_hid), hid = few_hid(d_hid), n = static_cast<int>(N);
       const uint32_t x_bytes = static_cast<uint32_t>(((N - 1) * row_stride + d) * 2);

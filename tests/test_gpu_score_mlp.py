@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import workloads as W
-from gpu_util import dev
+from gpu_util import dev, kernel_names, template_arguments
 
 pytestmark = pytest.mark.gpu
 
@@ -56,6 +56,20 @@ def test_few_tokens(D, N, d, dh):
     padded[:, :d] = x
     got = D.dodo_score_mlp(padded.to(dev())[:, :d], W1.to(dev()), b1.to(dev()), w2.to(dev()), 0.25, 1).cpu().numpy()
     _check(got, want)
+
+
+# The kernel for few tokens and tiles of 64 tokens on either side of the line between them: 28 tokens where the tiles are at most half as many as
+# the compute units and W1 has 2048 channels or more, 20 elsewhere.
+@pytest.mark.parametrize("d,dh,line", [(2048, 2048, 28), (4096, 4096, 28), (1024, 1024, 20), (2048, 4352, 20)])
+def test_line_between_few_tokens_and_tiles_of_64(D, d, dh, line):
+    x, W1, b1, w2 = _case(975, line + 1, d, dh, torch.bfloat16)
+    t = [v.to(dev()) for v in (x, W1, b1, w2)]
+    want = oracle.score_mlp(W.to_numpy(x), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, 1)
+    for N, kernel in ((line, "score_mlp_few_kernel"), (line + 1, "score_mlp_some_kernel")):
+        out = []
+        names = kernel_names(lambda: out.append(D.dodo_score_mlp(t[0][:N], *t[1:], 0.25, 1)), "score_mlp_")
+        assert any(kernel in n for n in names), names
+        _check(out[0].cpu().numpy(), want[:N])
 
 
 # small tiles alone (edges of 128 tokens), whole rounds of big tiles followed by small ones, big tiles alone
