@@ -246,9 +246,12 @@ struct BlockCfg {
   static constexpr int kStages = kTwoGroups ? 4 : 2;  // K/V tiles resident in LDS
   static constexpr int kLdsBytes = kStages * 2 * HeadDims<DH>::kTileBytes;
   static constexpr int kMinBlocks = NW == 4 ? 2 : 1;
-  // gather-free form: the sequence's index list sits in LDS after the stages (160 KiB per compute unit in all)
-  static constexpr int kIdxCap = kTwoGroups ? 7680 : 4096;  // (the 8-wavefront kernel has 1 KiB of static LDS besides)
-  static constexpr int kIdxBytes = kIdxCap * 4;
+  // gather-free form: the sequence's index list sits in LDS after the stages (160 KiB per compute unit in all; the 8-wavefront
+  // kernel has 1 KiB of static LDS besides).  Up to kShortIdx entries leave two workgroups of 4 wavefronts room on a compute unit.
+  static constexpr int kIdxCap = 7680, kShortIdx = 4096;
+  static int idx_entries(int32_t max_k) { return kMinBlocks == 2 && max_k <= kShortIdx ? kShortIdx : kIdxCap; }
+  static_assert(kMinBlocks * (kLdsBytes + (kMinBlocks == 2 ? kShortIdx : kIdxCap) * 4) <= 160 * 1024 && kLdsBytes + kIdxCap * 4 <= 159 * 1024,
+                "a compute unit has LDS for the workgroups that plan_blocks puts there");
   // KG = 2: the second halves' channels, offsets and sums meet the first halves' in the stages
   static constexpr int kMergeO = NW / 2 * 32 * DH * 4;
   static_assert(KG == 1 || kMergeO + NW / 2 * kWave * 8 <= kLdsBytes, "the merge of the halves fits into the stages");
@@ -307,7 +310,7 @@ struct SplitArgs {
 template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
 __device__ __forceinline__ void attend_query_block(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
-    const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ nug_idx,
+    const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ nug_idx, int idx_cap,
     int H, int H_kv, int G_, FastDiv div_G, FastDiv div_kv, const SeqGeom& geom, int qblk,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
     float* __restrict__ lse, const SplitArgs& sp) {
@@ -370,7 +373,7 @@ __device__ __forceinline__ void attend_query_block(
   if (IDX) {
     // (a previous query block of this workgroup is past its last tile request: the caller's barrier)
     int32_t* dst = reinterpret_cast<int32_t*>(lds + Cfg::kLdsBytes);
-    for (int t = threadIdx.x; t < min(k_b, Cfg::kIdxCap); t += Cfg::kThreads) dst[t] = nug_idx[k0 + t];
+    for (int t = threadIdx.x; t < min(k_b, idx_cap); t += Cfg::kThreads) dst[t] = nug_idx[k0 + t];
     __syncthreads();
   }
   const int64_t loc_stride = static_cast<int64_t>(H_kv) * kDH;
@@ -860,7 +863,7 @@ __global__ __launch_bounds__((BlockCfg<NW, DH, KG>::kThreads), (BlockCfg<NW, DH,
     const uint16_t* __restrict__ Kl, const uint16_t* __restrict__ Vl, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_nuggets, const int32_t* __restrict__ nug_len,
     const int32_t* __restrict__ cu_local, const int32_t* __restrict__ loc_len, const int32_t* __restrict__ nug_idx,
-    const int32_t* __restrict__ cu_ctx,
+    const int32_t* __restrict__ cu_ctx, int idx_cap,
     int B, int H, int H_kv, int G, int HG, int n_qblocks, int pair, int sorted, int heavy_last, int heads_xcd, FastDiv div_heads_xcd, FastDiv div_slots,
     FastDiv div_pairs, FastDiv div_HG, FastDiv div_G, FastDiv div_kv,
     int64_t nug_tok_stride, int64_t nug_head_stride, float scale_log2e, uint16_t* __restrict__ O,
@@ -917,11 +920,11 @@ __global__ __launch_bounds__((BlockCfg<NW, DH, KG>::kThreads), (BlockCfg<NW, DH,
   const SeqGeom g2 = load_seq_geom<IDX>(q2 >= 0 ? bh2 : bh1, div_HG, HG, cu_q, cu_nuggets, nug_len, cu_local, loc_len, cu_ctx);
   SplitArgs sp{0, 1, nullptr, nullptr, 0, 0};
   if (SPLIT) sp = SplitArgs{static_cast<int>(blockIdx.y), static_cast<int>(gridDim.y), part_o, part_ml, slots, cu_q[0]};
-  attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g1, q1, nug_tok_stride, nug_head_stride,
+  attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, idx_cap, H, H_kv, G, div_G, div_kv, g1, q1, nug_tok_stride, nug_head_stride,
                                          scale_log2e, O, lse, sp);
   if (!SPLIT && q2 >= 0) {
     __syncthreads();  // the first block's use of LDS is over
-    attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, H, H_kv, G, div_G, div_kv, g2, q2, nug_tok_stride, nug_head_stride,
+    attend_query_block<NW, KG, IDX, DH, SPLIT, GROUPED>(Q, Kn, Vn, Kl, Vl, nug_idx, idx_cap, H, H_kv, G, div_G, div_kv, g2, q2, nug_tok_stride, nug_head_stride,
                                            scale_log2e, O, lse, sp);
   }
 }
@@ -1002,7 +1005,7 @@ struct BlockPlan {
 // a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
 // 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
 BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local, bool heavy_last,
-                      int64_t max_splits, bool eight_only = false) {
+                      int64_t max_splits) {
   const int64_t cus = compute_units(), nug_tiles = (static_cast<int64_t>(max_k) + kBN - 1) / kBN;
   const int64_t tiles = nug_tiles + (static_cast<int64_t>(max_local) + kBN - 1) / kBN;
   const auto scaled = [&](int64_t ns) { return d_h == 128 ? ns : ns * 2 / 3; };
@@ -1019,7 +1022,7 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
   // rows that share their keys are, at 2 TB/s for the partial results, faster than that kernel's tiles.
   bool follow = false;
   const int64_t blocks128 = static_cast<int64_t>(B) * H * ((static_cast<int64_t>(max_q) + 127) / 128);
-  for (int64_t s = 2; s <= 16 && max_splits > 1 && !eight_only && blocks128 <= cus && s * blocks128 <= 2 * cus && 2 * s <= tiles; ++s)
+  for (int64_t s = 2; s <= 16 && max_splits > 1 && blocks128 <= cus && s * blocks128 <= 2 * cus && 2 * s <= tiles; ++s)
     follow |= (tiles + s - 1) / s * scaled(s * blocks128 <= cus ? 1350 : 2160) + 5000 +
                   static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 2000) < tiles * scaled(1200);
   for (int32_t G = 1; G <= H / H_kv; ++G) {
@@ -1029,7 +1032,7 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     for (int32_t waves = 8; waves >= 4; waves -= 4) {
       // (up to 128 query rows the offset follows the row's maximum, whose weight is then 1 and not rounded: 16 x 34 rows over 460
       // nuggets, 64 heads over 8, error against 64 bits 2.19e-3, with the 8-wavefront kernel's fixed offset 2.30e-3)
-      if (waves == 8 ? max_q <= 128 || follow : (rows > 128 && max_q > 128 && G == 1) || eight_only) continue;
+      if (waves == 8 ? max_q <= 128 || follow : (rows > 128 && max_q > 128 && G == 1)) continue;
       const int64_t bm = 32 * waves, n = (rows + bm - 1) / bm, units = pairs * n, at_once = waves == 8 ? cus : 2 * cus;
       const int64_t tile_ns = scaled(waves == 8 ? (2 * units <= cus ? 1200 : 1600) : units <= cus ? 1350 : 2160);
       const auto block_ns = [&](int64_t blk) {  // the nuggets and what the block's last row sees of the local rows
@@ -1060,13 +1063,13 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     // workgroups either way, two
     const int64_t units = pairs * ((rows + 63) / 64);
     const auto tile_ns = [&](int64_t wgs) { return scaled(wgs > cus ? 1900 : 1110); };
-    if (!eight_only && units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * tile_ns(units) + kStart4, G, 4, 2, 1, false, false);
+    if (units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * tile_ns(units) + kStart4, G, 4, 2, 1, false, false);
     // keys shared by several workgroups, over blocks of 128 or 64 rows: the better of the two
     int64_t shared_ns = -1, shared_n = 1;
     int32_t shared_KG = 1;
     for (int32_t KG = 1; KG <= 2; ++KG) {
       const int64_t blocks = pairs * ((rows + 128 / KG - 1) / (128 / KG));
-      for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && !eight_only && blocks <= cus && s * blocks <= 2 * cus && 2 * s <= tiles; ++s) {
+      for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && blocks <= cus && s * blocks <= 2 * cus && 2 * s <= tiles; ++s) {
         const int64_t one_ns = KG == 2 ? tile_ns(s * blocks) : scaled(s * blocks <= cus ? 1350 : 2160);
         const int64_t ns = (tiles + 2 * s - 1) / (2 * s) * 2 * one_ns + (KG == 2 ? 7000 : 9000) + 400 * s +
                            static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 5000);
@@ -1098,8 +1101,7 @@ template <int NW, int KG, bool IDX, int DH, bool SPLIT, bool GROUPED>
 int launch_nw(const AttnParams& p, BlockPlan plan) {
   using Cfg = BlockCfg<NW, DH, KG>;
   if (IDX && p.max_k > Cfg::kIdxCap) return DODO_ERR_UNSUPPORTED;
-  constexpr int kLds = Cfg::kLdsBytes + (IDX ? Cfg::kIdxBytes : 0);
-  static_assert(Cfg::kMinBlocks * kLds <= 160 * 1024, "a compute unit has LDS for the workgroups that plan_blocks puts there");
+  const int idx_cap = IDX ? Cfg::idx_entries(p.max_k) : 0, lds_bytes = Cfg::kLdsBytes + idx_cap * 4;
   const int HG = p.H / plan.G, nsplit = plan.nsplit;
   const int64_t pairs = static_cast<int64_t>(p.B) * HG, blocks = (static_cast<int64_t>(p.max_q) * plan.G + Cfg::kBM - 1) / Cfg::kBM;
   // few (sequence, group)s that don't deal out evenly would leave XCDs idle: their blocks go to all of them in turn
@@ -1112,15 +1114,15 @@ int launch_nw(const AttnParams& p, BlockPlan plan) {
   const int64_t slots = SPLIT ? static_cast<int64_t>(p.B) * p.max_q * p.H : 0;
   float* part_o = SPLIT ? static_cast<float*>(p.ws) : nullptr;
   float2* part_ml = SPLIT ? reinterpret_cast<float2*>(part_o + slots * nsplit * DH) : nullptr;
-  if (kLds > 64 * 1024) {
-    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLds);
+  if (lds_bytes > 64 * 1024) {
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes);
     if (rc != DODO_OK) return rc;
   }
   const auto div = [](int64_t d) { return make_fast_div(static_cast<uint32_t>(d)); };
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid), SPLIT ? nsplit : 1), dim3(Cfg::kThreads), kLds, p.stream,
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid), SPLIT ? nsplit : 1), dim3(Cfg::kThreads), lds_bytes, p.stream,
                      static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.Kn),
                      static_cast<const uint16_t*>(p.Vn), static_cast<const uint16_t*>(p.Kl),
-                     static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, p.B, p.H, p.H_kv,
+                     static_cast<const uint16_t*>(p.Vl), p.cu_q, p.cu_nuggets, p.nug_len, p.cu_local, p.loc_len, p.nug_idx, p.cu_ctx, idx_cap, p.B, p.H, p.H_kv,
                      plan.G, HG, n_qblocks, plan.pair ? 1 : 0, plan.sorted ? 1 : 0, p.heavy_last, heads_xcd, div(heads_xcd > 0 ? heads_xcd : 1),
                      div(n_slots), div(pairs), div(HG), div(plan.G), div(HG / p.H_kv), p.nug_tok_stride, p.nug_head_stride, p.scale_log2e,
                      static_cast<uint16_t*>(p.O), p.lse, part_o, part_ml, slots);
@@ -1144,10 +1146,9 @@ int launch_dh(const AttnParams& p) {
     // a token's byte offset from its sequence's first row is kept in 32 bits as well
     if (static_cast<int64_t>(p.max_n) * p.nug_tok_stride * 2 > 0x7fffffffLL) return DODO_ERR_UNSUPPORTED;
   }
-  // (only blocks of 256 rows have room for a longer list; up to 128 query rows it is refused)
-  const bool eight_only = idx && p.max_k > BlockCfg<4, DH, 1>::kIdxCap;
-  if (eight_only && p.max_q <= 128) return DODO_ERR_UNSUPPORTED;
-  const BlockPlan plan = plan_blocks(p.B, p.H, p.H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.heavy_last != 0, max_splits, eight_only);
+  // (up to 128 query rows a longer list is refused; beyond, the plan is that of the packed form, and so are the bits)
+  if (idx && p.max_k > BlockCfg<4, DH, 1>::kShortIdx && p.max_q <= 128) return DODO_ERR_UNSUPPORTED;
+  const BlockPlan plan = plan_blocks(p.B, p.H, p.H_kv, p.d_h, p.max_q, p.max_k, p.max_local, p.heavy_last != 0, max_splits);
   const auto launch = [&](auto grouped_tag) {
     constexpr bool GROUPED = decltype(grouped_tag)::value;
     const auto form = [&](auto waves_tag, auto kg_tag, auto split_tag) {

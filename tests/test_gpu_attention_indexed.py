@@ -89,10 +89,34 @@ def test_block_kernel_padded_token_stride_and_long_index_list(D):
     _check(D, 503, [20000], [4000], [256], [256], 2, 1, 128, torch.bfloat16, pad_heads=1)
 
 
+# Lists of more entries than two workgroups of a compute unit have room for: the plan, and with it the bits, of the packed form, whether
+# the keys are shared out, halves of tiles, whole tiles of grouped heads, or the 8-wavefront kernel's
+@pytest.mark.parametrize("B,q,k,H,H_kv,d_h,room", [(1, 160, 4500, 2, 2, 128, True), (1, 160, 4500, 2, 2, 128, False), (1, 200, 7680, 4, 4, 64, True),
+                                                   (11, 160, 4200, 32, 8, 128, False), (2, 300, 4097, 32, 32, 128, False)])
+def test_long_index_lists_have_the_packed_plan(D, B, q, k, H, H_kv, d_h, room):
+    g = torch.Generator().manual_seed(k + q)
+    r = lambda *s: torch.randn(s, generator=g).to(torch.bfloat16).to(dev())
+    n, m, cu = k + 300, q + 40, lambda v: W.cumulative([v] * B, dev())
+    K, V, Q, Kl, Vl = r(B * n, H_kv, d_h), r(B * n, H_kv, d_h), r(B * q, H, d_h), r(B * m, H_kv, d_h), r(B * m, H_kv, d_h)
+    idx = torch.cat([torch.randperm(n, generator=g)[:k].sort().values for _ in range(B)]).int().to(dev())
+    Kn, Vn = D.dodo_gather_nuggets(K, V, idx, cu(n), cu(k), B * k)
+    size = D.dodo_nugget_attention_workspace_bytes(B, H, d_h, q, k, m, D.BF16) if room else 16
+    ws = torch.zeros(size, dtype=torch.uint8, device=dev())
+    a = (Kl, Vl, cu(q), cu(k), cu(m), q, k, m)
+    O, lse = D.dodo_nugget_attention(Q, Kn, Vn, *a, want_lse=True, ws=ws)
+    Oi, lse_i = D.dodo_nugget_attention_indexed(Q, K, V, idx, cu(n), *a, n, want_lse=True, ws=ws)
+    assert bool(torch.isfinite(O.float()).all()) and torch.equal(O, Oi) and torch.equal(lse, lse_i)
+
+
 def test_limits_are_reported(D):
     # more nuggets in a sequence than the query-block kernel keeps in LDS: refused, not wrong
     host, d = _case(504, [9000], [7681], [256], [256], 1, 1, 128, torch.bfloat16)
     with pytest.raises(D.DodoError) as e:
         D.dodo_nugget_attention_indexed(d["Q"], d["K"], d["V"], d["idx"], d["cu_s"], d["Kl"], d["Vl"], d["cu_q"],
                                         d["cu_k"], d["cu_l"], 256, 7681, 256, 9000)
+    assert e.value.status == -2
+    host, d = _case(504, [9000], [4097], [128], [128], 1, 1, 128, torch.bfloat16)  # (up to 128 query rows)
+    with pytest.raises(D.DodoError) as e:
+        D.dodo_nugget_attention_indexed(d["Q"], d["K"], d["V"], d["idx"], d["cu_s"], d["Kl"], d["Vl"], d["cu_q"],
+                                        d["cu_k"], d["cu_l"], 128, 4097, 128, 9000)
     assert e.value.status == -2
