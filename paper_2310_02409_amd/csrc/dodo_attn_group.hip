@@ -293,7 +293,8 @@ __global__ __launch_bounds__(NWV * kWave) void group_attention_kernel(
   // Every wavefront enqueues the same number of loads.
   constexpr int kQInstr = (GD::kQBytes / 1024 + NWV - 1) / NWV;
   {
-    const u32x4_t qbuf = buffer_of(Q + (static_cast<int64_t>(q0 + row0) * H + kvh * G) * kDH, 0x7fffffffu);
+    // (offsets below 32 rows of the K/V heads' bytes, which group_attention_applies holds below 2^32)
+    const u32x4_t qbuf = buffer_of(Q + (static_cast<int64_t>(q0 + row0) * H + kvh * G) * kDH, 0xffffffffu);
 #pragma unroll
     for (int u = 0; u < kQInstr; ++u) {
       const int chunk = min(wave * kQInstr + u, GD::kQBytes / 1024 - 1);

@@ -311,3 +311,21 @@ def test_infinite_value_in_a_visible_row_of_a_small_batch(D):
     want[5, 0:8, 64] = float("-inf")
     O[3, 16, 7] = want[3, 16, 7]  # (its weight may have underflowed to zero: 0 x inf)
     assert torch.equal(O, want)
+
+
+# Query rows further than 2^31 bytes from the launch's first one (the heads of a row take 157 MB): the last one has its own result.
+def test_query_rows_far_apart(D):
+    q, G, H_kv, d_h = 15, 2, 307200, 128
+    g = torch.Generator(device=dev()).manual_seed(5)
+    r = lambda n, h: torch.randn((n, h, d_h), generator=g, dtype=BF, device=dev())
+    Q, Kl, Vl = r(q, G * H_kv), r(q, H_kv), r(q, H_kv)
+    cu = W.cumulative([q], dev())
+    none = torch.empty((0, H_kv, d_h), dtype=BF, device=dev())
+    O = D.dodo_nugget_attention(Q, none, none, Kl, Vl, cu, W.cumulative([0], dev()), cu, q, 0, q, ws=torch.zeros(16, dtype=torch.uint8, device=dev()))[0]
+    for h0 in (0, H_kv - 500):
+        K, V = Kl[:, h0:h0 + 500].float(), Vl[:, h0:h0 + 500].float()
+        last = Q[q - 1].view(H_kv, G, d_h)[h0:h0 + 500].float()
+        P = torch.softmax((K.unsqueeze(2) * last).sum(-1) * default_scale(d_h), 0)  # [key, K/V head, head of the group]
+        want = (P.unsqueeze(-1) * V.unsqueeze(2)).sum(0)
+        got = O[q - 1].view(H_kv, G, d_h)[h0:h0 + 500].float()
+        assert (got - want).abs().max().item() <= 2e-2
