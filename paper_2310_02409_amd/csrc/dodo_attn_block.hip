@@ -221,9 +221,11 @@ __device__ __forceinline__ float tile_max(const floatx16 (&acc)[2]) {
 }
 // Softmax with a fixed exponent offset per row (used by the two-group kernel): the offset m_off is the row maximum of
 // the first tile -- every row that sees anything sees keys of it -- and is never moved afterwards, so the output
-// accumulators are not rescaled: O = sum(p v) / sum(p) does not depend on the offset.  An overflow of the fixed offset
-// shows up as a non-finite row sum at the end, in which case the caller redoes the rows with softmax_tile, as it does where
-// every logit of a row's first tile is -inf, which leaves the row no offset.  Needs scale_log2e > 0.
+// accumulators are not rescaled: O = sum(p v) / sum(p) does not depend on the offset.  Logits far above the fixed offset
+// show up as a row sum beyond kMostSum (or one that is not finite) at the end, in which case the caller redoes the rows with
+// softmax_tile, as it does where every logit of a row's first tile is -inf, which leaves the row no offset.  The sum stays finite
+// for a while after sum(p v) has overflowed; below kMostSum that takes values of V beyond 2^63.  Needs scale_log2e > 0.
+constexpr float kMostSum = 0x1p64f;
 __device__ __forceinline__ void softmax_fixed(const floatx16 (&acc)[2], float scale_log2e, float m_off, bf16x8 (&pf)[4]) {
   const float neg = (m_off == kNegInf) ? 0.f : -m_off;
 #pragma unroll
@@ -730,12 +732,12 @@ __device__ __forceinline__ void attend_query_block(
       const float sum_lo = __shfl(acc_l[0], lane & 15, kWave), sum_hi = __shfl(acc_l[1], lane & 15, kWave);
       const float l_row = (j & 16) ? sum_hi : sum_lo;
       l_run = (g == 0) ? l_row : 0.f;
-      bail = !(l_row - l_row == 0.f) ||  // +inf or NaN: some logit overflowed the row's fixed offset
+      bail = !(l_row <= kMostSum) ||  // or NaN: some logit is too far above the row's fixed offset
              (m_run == kNegInf && row_ok && (k_b > 0 || my_vis > 0));  // no offset, though the row sees keys
     } else {
       bail = n_tiles > 0;
     }
-    // Rare: some logit overflowed its row's fixed offset, or a row has none (or the scale is not positive).  Redo the
+    // Rare: some logit is too far above its row's fixed offset, or a row has none (or the scale is not positive).  Redo the
     // workgroup's rows with the exact running-maximum softmax, one tile at a time.
     __builtin_amdgcn_s_waitcnt(0x0f70);
     if (__syncthreads_or(bail)) {

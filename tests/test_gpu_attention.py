@@ -266,12 +266,12 @@ def test_attention_is_deterministic(D):
 
 @pytest.mark.parametrize("scale", [8.0, -0.09, 0.0])
 def test_block_attention_exact_fallback_paths(D, scale):
-    # 8-wavefront kernel: a huge scale spreads the logits far beyond the fixed per-row exponent offset
-    # (rows fall back to the running-maximum loop); non-positive scales take that loop from the start
+    # more than 128 rows, few heads (shared keys of halves of tiles): a huge scale spreads the logits, non-positive scales
+    # order them the other way (the 8-wavefront kernel, which has a loop of its own for these, in test_gpu_attention_tiles.py)
     _full_check(D, 415, [300, 130], [200, 64], [364, 130], 2, 2, 128, torch.bfloat16, scale=scale)
     # 4-wavefront kernel (short query block) with the same scales
     _full_check(D, 416, [100], [70], [120], 2, 1, 128, torch.bfloat16, scale=scale)
-    # 64-wide heads, both kernels
+    # 64-wide heads, both
     _full_check(D, 418, [300, 130], [200, 64], [364, 130], 2, 2, 64, torch.bfloat16, scale=scale)
     _full_check(D, 419, [100], [70], [120], 2, 1, 64, torch.bfloat16, scale=scale)
 

@@ -196,8 +196,8 @@ def test_shared_keys_that_are_not_finite(tensor, value, d_h):
         assert (lse[ok] - got[0][1][ok]).abs().max() <= 2e-2
 
 
-# The two-group kernel takes a row's exponent offset from its first tile: a first tile whose logits are all -inf (nuggets that a
-# caller rules out so) leaves it none.  The rest decides, also where it lies far from zero.
+# A first tile whose logits are all -inf (nuggets that a caller rules out so): the rest decides, also where it lies far from zero.  (Few
+# heads, which halves of tiles take; the 8-wavefront kernel, whose offsets come from the first tile, further down.)
 @pytest.mark.parametrize("far", [0.0, -300.0, 300.0])
 def test_first_tile_without_a_finite_logit(far):
     import paper_2310_02409_amd as D
@@ -219,7 +219,7 @@ def test_first_tile_without_a_finite_logit(far):
 
 
 # Rows past the sequence's last one in a query block (they read as zeros, so that a ruled-out nugget's logits are NaN there) have
-# no say in the others' results: the same bits as in a block that is full.
+# no say in the others' results: the same bits as in a block that is full.  (Few heads; the 8-wavefront kernel further down.)
 def test_rows_past_the_last_do_not_count():
     import paper_2310_02409_amd as D
     q, k, H, d_h = 160, 300, 2, 128
@@ -381,3 +381,82 @@ def test_halves_of_a_tile_that_are_not_finite(key):
     t["Kn"][key, 3, 5] = float("nan")
     bad = run()
     assert torch.isnan(bad[:q, 3].float()).all() and torch.equal(bad[q:, 3], clean[q:, 3]) and torch.equal(bad[:, 0], clean[:, 0])
+
+
+# ---- the 8-wavefront kernel, by its name: it takes calls whose blocks of 64 rows are more than the compute units ----
+def _eight(host, t, q_lens, k_lens, m_lens, scale, rows, grouped=False):
+    """The call's (O, lse), checked against the oracle at `rows`, and that the 8-wavefront kernel made them."""
+    import paper_2310_02409_amd as D
+    O, lse = nan_outputs(t["Q"], t["Q"].shape[1])
+    names = kernel_names(lambda: D.dodo_nugget_attention(t["Q"], t["Kn"], t["Vn"], t["Kl"], t["Vl"], t["cu_q"], t["cu_nuggets"], t["cu_local"],
+                                                         max(q_lens), max(k_lens), max(m_lens), scale, O=O, lse=lse), "block_attention_kernel")
+    assert len(names) == 1, names
+    args = template_arguments(names[0])
+    assert args[:2] == ["8", "1"] and args[-1] == ("true" if grouped else "false"), names
+    assert bool(torch.isfinite(O.float()).all())
+    want = oracle_attention_rows_parallel(host, host["Kn"], host["Vn"], host["cu_nuggets"], scale, rows)
+    check_rows(O, lse, host["cu_q"], rows, *want, torch.bfloat16)
+    return O, lse
+
+
+# A huge scale spreads the logits far beyond the fixed exponent offset of a row, so that the block is done again with the running maximum;
+# scales that are not positive take that loop from the start.  Blocks of 256 rows and the rest of them, sequences without nuggets.
+@pytest.mark.parametrize("q_lens,H,H_kv,d_h", [([300, 160, 257], 32, 32, 128), ([300, 160, 257], 32, 32, 64), ([336, 300, 129, 330, 336, 257, 312, 336], 64, 8, 128)])
+@pytest.mark.parametrize("scale", [8.0, -0.09, 0.0])
+def test_eight_wavefronts_without_a_fixed_offset(q_lens, H, H_kv, d_h, scale):
+    B = len(q_lens)
+    k_lens, m_lens = [(60, 0, 30)[b % 3] for b in range(B)], [q + (64, 0, 11)[b % 3] for b, q in enumerate(q_lens)]
+    host, t = make_attention_case(1100, q_lens, k_lens, m_lens, H, H_kv, d_h, torch.bfloat16, dev())
+    rows = [(b, (5 * b + 3 * i) % H, i) for b, q in enumerate(q_lens) for i in [*range(0, q, 17), 255, 256, q - 1] if i < q]
+    _eight(host, t, q_lens, k_lens, m_lens, scale, rows, grouped=H != H_kv)
+
+
+# The row's exponent offset comes from its first tile: one whose logits are all -inf leaves it none, and the block is done again.
+@pytest.mark.parametrize("d_h", [64, 128])
+@pytest.mark.parametrize("far", [0.0, -300.0, 300.0])
+def test_eight_wavefronts_with_a_first_tile_without_a_finite_logit(far, d_h):
+    q_lens, k_lens, m_lens, H = [160, 300, 150], [100, 65, 70], [160, 290, 170], 32
+    host, t = make_attention_case(1110, q_lens, k_lens, m_lens, H, H, d_h, torch.bfloat16, "cpu")
+    scale = default_scale(d_h)
+    t["Q"][..., 0], t["Q"][..., 1] = 1.0, 16.0
+    for x in (t["Kn"], t["Kl"]):
+        x[..., 0], x[..., 1] = 0.0, far / (16.0 * scale)
+    for b, first in enumerate((0, 100, 165)):
+        if b != 1:  # (sequence 1 keeps its offsets)
+            t["Kn"][first:first + 64, :, 0] = float("-inf")
+    host = {n: W.to_numpy(v) for n, v in t.items()}
+    rows = [(b, (5 * b + 3 * i) % H, i) for b, q in enumerate(q_lens) for i in [*range(0, q, 11), q - 1]]
+    _eight(host, {n: v.to(dev()) for n, v in t.items()}, q_lens, k_lens, m_lens, scale, rows)
+
+
+# One key far above a row's fixed offset: its weight 2^e times values of 3 overflows (e = 127) before the row sum does (e = 128), and either has
+# the block done again; below 2^64 it is not.
+@pytest.mark.parametrize("e", [60, 100, 126, 127, 128])
+def test_eight_wavefronts_with_a_key_far_above_the_offset(e):
+    B, q, k, H, d_h = 3, 160, 130, 32, 128
+    host, t = make_attention_case(1115, [q] * B, [k] * B, [0] * B, H, H, d_h, torch.bfloat16, "cpu")
+    scale = default_scale(d_h)
+    t["Q"][..., 0] = 16.0
+    t["Kn"][..., 0] = 0.0
+    t["Kn"][[70, k + 129, 2 * k + 64], :, 0] = e / (16.0 * scale * 1.4426950408889634)
+    t["Vn"][[70, k + 129, 2 * k + 64]] = 3.0
+    host = {n: W.to_numpy(v) for n, v in t.items()}
+    rows = [(b, (5 * b + 3 * i) % H, i) for b in range(B) for i in range(0, q, 9)]
+    _eight(host, {n: v.to(dev()) for n, v in t.items()}, [q] * B, [k] * B, [0] * B, scale, rows)
+
+
+# Spare rows of a block have no say in the others' results: a ruled-out nugget, whose logit a row of zeros would make NaN, leaves the rest its
+# bits, and the block its fixed offsets.
+@pytest.mark.parametrize("d_h", [64, 128])
+def test_eight_wavefronts_rows_past_the_last_do_not_count(d_h):
+    B, q, k, H = 3, 160, 300, 32
+    host, t = make_attention_case(1120, [q] * B, [k] * B, [0] * B, H, H, d_h, torch.bfloat16, dev())
+    t["Q"][..., 0] = 1.0
+    t["Kn"][[7, k + 70, 2 * k + 299], :, 0] = float("-inf")
+    got = []
+    for n in (160, 150):
+        part = dict(t, Q=t["Q"].view(B, q, H, d_h)[:, :n].reshape(B * n, H, d_h).contiguous(), cu_q=W.cumulative([n] * B, dev()))
+        rows = [(b, (5 * b + 3 * i) % H, i) for b in range(B) for i in [*range(0, n, 17), n - 1]]
+        got.append(_eight({x: W.to_numpy(v) for x, v in part.items()}, part, [n] * B, [k] * B, [0] * B, default_scale(d_h), rows))
+    whole = [x.view(B, q, *x.shape[1:])[:, :150].reshape(B * 150, *x.shape[1:]) for x in got[0]]
+    assert torch.equal(whole[0], got[1][0]) and torch.equal(whole[1], got[1][1])
