@@ -276,23 +276,29 @@ def test_block_attention_exact_fallback_paths(D, scale):
     _full_check(D, 419, [100], [70], [120], 2, 1, 64, torch.bfloat16, scale=scale)
 
 
-# Merges of partial results at the edges of their batches: 2, 8, 9 and 28 splits of one query vector per workgroup, 2, 3, 5
-# and 14 for grouped heads (the workspace may hold more); twice on one workspace, so that the first call has left its flags cleared.
+# Merges of partial results at the edges of their batches: 2, 8, 9 and 28 splits of one query vector per workgroup (as many as there are
+# compute units for); 2, 3, 5, 10, 17 and 18 for grouped heads, which the workspace holds them to (as many are wanted, or more).  Every split
+# but the last leaves a record there, which tells their number.  Twice on one workspace, so that the first call has left its flags cleared.
 @pytest.mark.parametrize("B,H,H_kv,d_h,k,dtype,splits", [
     (4, 32, 32, 128, 500, torch.bfloat16, 2), (1, 32, 32, 128, 500, torch.bfloat16, 8), (1, 28, 28, 64, 1800, torch.float32, 9),
     (1, 9, 9, 128, 1400, torch.bfloat16, 28), (16, 64, 8, 128, 1640, torch.bfloat16, 2), (8, 64, 8, 128, 1640, torch.bfloat16, 3),
-    (4, 64, 8, 128, 1640, torch.bfloat16, 5), (2, 64, 8, 128, 4400, torch.bfloat16, 14)])
+    (4, 64, 8, 128, 1640, torch.bfloat16, 5), (2, 64, 8, 128, 4400, torch.bfloat16, 10), (1, 64, 8, 128, 7400, torch.bfloat16, 17),
+    (1, 64, 8, 128, 11000, torch.bfloat16, 18)])
 def test_merge_of_splits(D, B, H, H_kv, d_h, k, dtype, splits):
     k_b, m_b = [k - 3 * b for b in range(B)], [70 + b for b in range(B)]
     host, d = make_attention_case(460, [1] * B, k_b, m_b, H, H_kv, d_h, dtype, dev())
     scale = default_scale(d_h)
     need = D.dodo_nugget_attention_workspace_bytes_grouped(B, H, H_kv, d_h, 1, max(k_b), max(m_b), D.F32 if dtype == torch.float32 else D.BF16)
-    assert need // (B * H * (d_h + 3) * 4) >= splits
+    assert need >= splits * B * H * (d_h + 3) * 4
+    if H != H_kv:
+        need = splits * B * H * (d_h + 3) * 4
     O_ref, lse_ref = oracle.attention(host["Q"], host["Kn"], host["Vn"], host["Kl"], host["Vl"], host["cu_q"], host["cu_nuggets"],
                                       host["cu_local"], scale)
     ws = torch.zeros(need, dtype=torch.uint8, device=dev())
     got = [D.dodo_nugget_attention(d["Q"], d["Kn"], d["Vn"], d["Kl"], d["Vl"], d["cu_q"], d["cu_nuggets"], d["cu_local"], 1, max(k_b), max(m_b),
                                    scale, want_lse=True, ws=ws) for _ in range(2)]
+    records = (ws.view(torch.int32) != 0).sum().item() / (B * H * (d_h + 2))  # (a word or two of them may be zero)
+    assert splits - 1.01 < records <= splits - 1, records
     for O, lse in got:
         check_attention(O, O_ref, dtype)
         check_lse(lse, lse_ref, dtype)

@@ -175,8 +175,8 @@ def test_llama7b_shape_sampled_tokens(D):
     _check(got[rows].cpu().numpy(), want)
 
 
-# small tiles whose channels two groups of wavefronts share: one, two and an odd number of steps each, the most tiles that
-# take this form and one more, and an odd number of steps in all, which does not
+# channels shared by two groups of wavefronts, in small tiles (1024 tokens the most of them, 1025 too many) and, up to a few hundred
+# tokens, in tiles of 64: one, two and an odd number of steps each
 @pytest.mark.parametrize("N,d,dh", [(65, 128, 256), (129, 256, 512), (128, 384, 256), (1024, 128, 4096), (1025, 128, 4096),
                                     (130, 192, 512), (200, 1024, 512)])
 @pytest.mark.parametrize("act", [0, 2])
@@ -188,7 +188,7 @@ def test_channels_shared_by_two_groups(D, N, d, dh, act):
     _check(got[rows], want)
 
 
-# Infinite and NaN channels in either group's half: tanh of an infinite hidden unit is 1 or -1, a NaN channel makes its token's score
+# Infinite and NaN channels in either half of the channels (tiles of 64 tokens; small tiles below): tanh of an infinite hidden unit is 1 or -1, a NaN channel makes its token's score
 # NaN and no other one's.
 @pytest.mark.parametrize("N,d,dh", [(65, 128, 256), (130, 128, 512), (200, 384, 256)])
 def test_channels_shared_by_two_groups_that_are_not_finite(D, N, d, dh):
@@ -203,7 +203,8 @@ def test_channels_shared_by_two_groups_that_are_not_finite(D, N, d, dh):
 
 
 # Tiles of 64 tokens: 32 hidden units per tile (a tile per compute unit at most), 64 with one and with two tiles per unit; tokens around
-# a tile's end, fewer steps than there are stages, one more than are folded, and an even number; what whole rounds of other tiles leave.
+# a tile's end, fewer steps than there are stages, one more than are folded, and an even number; beside them a call of few tokens and one of
+# big and small tiles.  (What whole rounds of other tiles leave: further down.)
 @pytest.mark.parametrize("N,d,dh", [(17, 128, 256), (63, 1152, 512), (64, 128, 8192), (65, 256, 4096), (129, 384, 4096), (256, 2048, 1024),
                                     (300, 512, 4096), (512, 128, 4096), (577, 1152, 2048), (2100, 4096, 512), (9000, 1152, 4096)])
 @pytest.mark.parametrize("act", [0, 1, 2])
@@ -230,3 +231,44 @@ def test_tiles_of_64_tokens_that_are_not_finite(D, N, d, dh):
     assert np.isnan(got[nan]).all()
     rest = np.setdiff1d(np.arange(N), nan)
     _check(got[rest], oracle.score_mlp(W.to_numpy(x[rest]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.0, 2))
+
+
+# Small tiles whose channels two groups of wavefronts share, by the kernel's name: one, three, two, five and one (odd) steps each, tokens at a
+# tile's edges; then with NaN and infinite channels in either group's half.
+@pytest.mark.parametrize("N,d,dh", [(808, 128, 4096), (1010, 384, 4096), (700, 256, 4096), (1024, 640, 4096), (600, 128, 5120)])
+@pytest.mark.parametrize("finite", [True, False])
+def test_small_tiles_in_two_groups(D, N, d, dh, finite):
+    x, W1, b1, w2 = _case(1060 + N, N, d, dh, torch.bfloat16)
+    nan = [] if finite else [1, 140, N - 2]
+    if not finite:
+        x[N // 2, 9], x[3, d - 5], x[N - 1, d // 2] = float("-inf"), float("inf"), float("inf")
+        x[1, 0], x[140, d // 2 - 1], x[N - 2, d - 1] = float("nan"), float("nan"), float("nan")
+    rows = np.setdiff1d(np.r_[0:8, 124:150, 250:260, N // 2, N - 30:N], nan)
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, 2)
+    t, out = [v.to(dev()) for v in (x, W1, b1, w2)], []
+    names = [n for n in kernel_names(lambda: out.append(D.dodo_score_mlp(*t, 0.25, D.TANH)), "score_mlp_") if "combine" not in n]
+    assert len(names) == 1 and "score_mlp_mfma_kernel" in names[0] and template_arguments(names[0])[3] == "2", names
+    got = out[0].cpu().numpy()
+    _check(got[rows], want)
+    assert np.isnan(got[nan]).all() and np.isfinite(np.delete(got, nan)).all()
+
+
+# Several kinds of tiles in one call: whole rounds of big or of small tiles and, for what they leave, tiles of 64 tokens, whose partial
+# scores have a region and a part of the last kernel of their own; tokens on both sides of the boundary, rows further apart than d.
+@pytest.mark.parametrize("N,first,d,dh", [(2322, 2048, 4096, 4096), (2100, 2048, 1920, 4096), (4121, 4096, 2048, 4096), (4121, 4096, 2048, 2048),
+                                          (6165, 6144, 2048, 4096)])
+@pytest.mark.parametrize("act", [0, 2])
+def test_tiles_of_64_tokens_after_whole_rounds(D, N, first, d, dh, act):
+    x, W1, b1, w2 = _case(1070 + N, N, d, dh, torch.bfloat16)
+    rows = np.unique(np.r_[0:4, 4094:min(N, 4098), first - 12:first + 20, first + 60:min(N, first + 68), N - 6:N] % N)
+    want = oracle.score_mlp(W.to_numpy(x[rows]), W.to_numpy(W1), b1.numpy(), W.to_numpy(w2), 0.25, act)
+    padded = torch.full((N, d + 8), float("nan"), dtype=torch.bfloat16)
+    padded[:, :d] = x
+    t = [v.to(dev()) for v in (padded, W1, b1, w2)]
+    ws = torch.full((D.dodo_score_mlp_workspace_bytes(D.BF16, N, d, dh) + 64,), 255, dtype=torch.uint8, device=dev())
+    out = torch.full((N + 16,), float("nan"), device=dev())
+    names = kernel_names(lambda: D.dodo_score_mlp(t[0][:, :d], *t[1:], 0.25, act, out=out[:N], ws=ws[:-64]), "score_mlp_")
+    assert any("some_kernel" in n for n in names) and any("mfma_kernel" in n for n in names), names
+    got = out.cpu().numpy()
+    _check(got[rows], want)
+    assert np.isfinite(got[:N]).all() and np.isnan(got[N:]).all() and torch.all(ws[-64:] == 255)
