@@ -979,7 +979,7 @@ struct BlockPlan {
 // 4-wavefront kernel, 1.6 times that with two workgroups on a compute unit; in the 8-wavefront kernel 1200, 1600 where more than
 // half of the compute units run it, 2100 where hardly any two of them at work share their keys; heads of 64 channels two thirds
 // of that; a block's start and end 4000 and 6200.  With two wavefronts per 32 rows, blocks of 64, a tile takes 1110, and 1900 with two
-// workgroups on a compute unit.
+// workgroups on a compute unit (shares of keys 1800, heads of 64 channels 950).
 //
 // Two wavefronts per 32 rows, each half of a tile's keys (KG = 2): a wavefront alone on its SIMD works through a tile as one chain of
 // matrix and vector instructions.  32 heads, one wavefront / two: 64 rows, 200 nuggets 13.7 / 11.7 us, 4 x 64 rows, 80 nuggets 10.2 /
@@ -1002,7 +1002,7 @@ struct BlockPlan {
 // against 25.5.  Blocks of 64 rows with KG = 2 or, where these are too many or would get too few shares, of 128 with KG = 1; 64 / 128:
 // 128 rows, 1000 nuggets, 32 heads 19.1 / 22.5, 1500 nuggets, 64 heads over 8 24.7 / 23.5, 83 rows, 671 nuggets, 2 x 32 heads 18.6 / 20.4; 549
 // rows, 3578 nuggets, 32 heads - / 62.7 (8 wavefronts, whole: 79.6), 466 rows, 3747 nuggets, 32 heads 87.5 (whole) / 61.6.  Starts and ends, the
-// second launch, 400 ns for every share and 5 TB/s for the partial results: fitted to 106 shapes, all share counts of both timed.
+// second launch, 400 ns for every share and 4 TB/s for the partial results: fitted to 206 shapes, all share counts of both timed.
 // The bounds decide, also where they promise more than there is: in the cached form max_k may be a capacity.  64 rows, 32 heads over
 // a cache of 8192 rows, whole / shared: empty 6.8 / 12.5 us, 1% full 9.7 / 13.2, 5% 16.4 / 15.6, 10% 24.4 / 18.5, full 179 / 41;
 // 4 sequences over 4096 rows each: 1% 8.6 / 15.5, 10% 17.6 / 19.5, 25% 29.6 / 27.0, full 96 / 58.
@@ -1064,17 +1064,17 @@ BlockPlan plan_blocks(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t m
     // two wavefronts per 32 rows: where that leaves a workgroup per compute unit at most, or up to 64 rows, which have the same
     // workgroups either way, two
     const int64_t units = pairs * ((rows + 63) / 64);
-    const auto tile_ns = [&](int64_t wgs) { return scaled(wgs > cus ? 1900 : 1110); };
-    if (units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * tile_ns(units) + kStart4, G, 4, 2, 1, false, false);
+    if (units <= (rows <= 64 ? 2 : 1) * cus) consider(tiles * scaled(units > cus ? 1900 : 1110) + kStart4, G, 4, 2, 1, false, false);
     // keys shared by several workgroups, over blocks of 128 or 64 rows: the better of the two
     int64_t shared_ns = -1, shared_n = 1;
     int32_t shared_KG = 1;
     for (int32_t KG = 1; KG <= 2; ++KG) {
       const int64_t blocks = pairs * ((rows + 128 / KG - 1) / (128 / KG));
       for (int64_t s = 2; s <= std::min<int64_t>(16, max_splits) && blocks <= cus && s * blocks <= 2 * cus && 2 * s <= tiles; ++s) {
-        const int64_t one_ns = KG == 2 ? tile_ns(s * blocks) : scaled(s * blocks <= cus ? 1350 : 2160);
-        const int64_t ns = (tiles + 2 * s - 1) / (2 * s) * 2 * one_ns + (KG == 2 ? 7000 : 9000) + 400 * s +
-                           static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 5000);
+        const bool two = s * blocks > cus;  // workgroups on a compute unit
+        const int64_t one_ns = KG == 1 ? scaled(two ? 2160 : 1350) : two ? (d_h == 128 ? 1800 : 950) : scaled(1110);
+        const int64_t ns = (tiles + 2 * s - 1) / (2 * s) * 2 * one_ns + (KG == 2 ? 7300 : 9000) + 400 * s +
+                           static_cast<int64_t>(split_bytes(B, H, d_h, max_q, s) / 4000);
         if (shared_ns >= 0 && ns >= shared_ns) continue;
         shared_ns = ns;
         shared_n = s;
