@@ -51,7 +51,7 @@ int group_launches(int32_t H, int32_t H_kv, int32_t max_q);  // 0: not for these
 size_t group_workspace_bytes(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k,
                              int32_t max_local);
 int launch_group_attention(const AttnParams& p);
-// bf16, d_h in {64,128}: MFMA kernel over blocks of 128 or 256 query vectors of a K/V head.  Few of them and many keys: the keys are shared out as
+// bf16, d_h in {64,128}: MFMA kernel over blocks of 64, 128 or 256 query vectors of a K/V head.  Few of them and many keys: the keys are shared out as
 // far as the caller's workspace has room for partial results; block_workspace_bytes is what that would like (0: no split;
 // H_kv = 0: enough for any number of K/V heads).
 size_t block_workspace_bytes(int32_t B, int32_t H, int32_t H_kv, int32_t d_h, int32_t max_q, int32_t max_k, int32_t max_local);

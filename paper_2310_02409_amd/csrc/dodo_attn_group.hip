@@ -10,7 +10,7 @@
 // keys and wavefront:
 //   S^T = K Q^T     8 x v_mfma_f32_32x32x16_bf16, A = K rows (LDS), B = Q^T (registers): lane <-> query vector
 //   online softmax in base 2 on the accumulators (row statistics are lane-local, one exchange with lane^32)
-//   O^T += V^T P^T  16 MFMAs, A = V^T through the transposing LDS read, B = P^T straight from the accumulators, in two parts
+//   O^T += V^T P^T  16 MFMAs, A = V^T through the transposing LDS read, B = P^T straight from the accumulators, in two parts (or three)
 // Up to 16 vectors take v_mfma_f32_16x16x32_bf16 instead: half of the matrix work, exponentials and registers.
 // (the LDS swizzles and the k-slot <-> key permutation are those of the query-block kernel).  The wavefronts'
 // partial (m, l, O) meet in LDS and are merged in wavefront order; with several splits the workgroup writes a

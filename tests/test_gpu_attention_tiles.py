@@ -320,10 +320,11 @@ def test_nan_stays_in_its_head(q, k):
 
 # Grouped heads whose rows go through the tiles together: blocks of 128 and 256 rows, 2, 3, 4 and 8 heads (a block begins at any head
 # of a query row), rows left over, sequences of fewer rows than the bound, several blocks per sequence with the heavy ones first, and
-# keys shared by several workgroups; the same rows through an index list.
+# keys shared by several workgroups in blocks of 64 and of 128 rows; the same rows through an index list.
 @pytest.mark.parametrize("B,q,k,H,H_kv,d_h", [
     (40, 16, 70, 16, 2, 128), (40, 17, 33, 16, 2, 128), (40, 21, 64, 16, 2, 64), (24, 43, 40, 24, 8, 128), (20, 33, 65, 32, 8, 64),
     (70, 130, 20, 16, 8, 128), (12, 546, 30, 16, 2, 128), (5, 16, 2000, 64, 8, 128), (9, 40, 1500, 32, 8, 64),
+    (6, 33, 1960, 16, 4, 128), (6, 71, 905, 16, 4, 128), (3, 91, 1081, 16, 4, 128), (2, 139, 560, 16, 2, 128),
 ])
 def test_rows_of_grouped_heads_together(B, q, k, H, H_kv, d_h):
     import paper_2310_02409_amd as D
