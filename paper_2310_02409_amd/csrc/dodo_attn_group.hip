@@ -750,8 +750,8 @@ bool group_attention_applies(const AttnParams& p) {
   // split-K kernel, which works on each of them, to be the slower one.  It takes 4.5 us and 7.3 ns (5.3 for heads of 64 channels) for
   // each row of a workgroup's share and each workgroup that a compute unit gets, and 2 more where the shares are merged; this kernel 1.5 beyond
   // the time above, or 2.3 with several splits.  64 heads over 8, split-K / this kernel: 4 x 357 rows 7.1 / 7.7 us, 4 x 579 9.3 / 9.4,
-  // 4 x 667 9.3 / 10.1, 2 x 1099 11.3 / 10.0, 5 x 454 11.5 / 8.5, 6 x 357 9.8 / 6.6, 13 x 204 11.4 / 5.8; 40 over 8, 2 x 1887 12.0 / 13.7; 32 over 8, 7 x
-  // 687 10.4 / 10.9; 32 over 4, 9 x 627 15.6 / 9.8, heads of 64 2 x 3168 11.1 / 13.5, 5 x 1242 9.5 / 8.8.  (Below 128 Ki of vectors times rows little is won.)
+  // 4 x 667 9.3 / 10.1, 2 x 1099 11.2 / 10.1, 5 x 454 11.5 / 8.5, 6 x 357 9.8 / 6.7, 13 x 204 11.4 / 6.0; 40 over 8, 2 x 1887 12.0 / 13.7; 32 over 8, 7 x
+  // 687 10.4 / 10.9; 32 over 4, 9 x 627 15.7 / 9.8, heads of 64 2 x 3168 11.1 / 13.5, 5 x 1242 9.6 / 8.9.  (Below 128 Ki of vectors times rows little is won.)
   // (One query row per sequence only: rows that a vector does not see are not read there.)
   const int64_t vectors = static_cast<int64_t>(p.H) * p.max_q, rows = static_cast<int64_t>(p.max_k) + p.max_local;
   const Wanted here = wanted(p);
